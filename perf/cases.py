@@ -1,0 +1,202 @@
+"""Performance cases: what a training program has this library do, through its Python entry points.
+
+A case is one pass of one rank's shard: an optimizer step (reduce R gradient slices, unscale, Adam or LAMB, emit fp16
+weights, raise the overflow flag) or the model-parallel epilogue.  Sizes and value ranges come from the benchmark
+configurations (`workloads.config`), the sliced lists and the epilogue shapes of the benchmark's sweeps, or are generic.
+
+`listed()` gives the fixed cases, `draw(rng)` another one of the same ranges, `prepare` the device state a program holds
+before the call, `run` one pass, `work` the bytes and operations the pass cannot do without, `tolerance` how far another
+correct implementation may be off.
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+from paper_2105_05720_amd import binding as cc
+from paper_2105_05720_amd import workloads as W
+from paper_2105_05720_amd.shard import Shard
+
+ADAM, LAMB, LAMB_PHASES, ADAM_STATIC, EPILOGUE = "adam", "lamb", "lamb_phases", "adam_static", "epilogue"
+MOST_BYTES = 44e9          # the largest listed case (lamb_8b) is the upper end of the drawn range
+
+
+def step_case(op, list_, R, *, slices=1, numel=0, grad="f16", guard=False, l2=False, average=False, loss_scale=1.0, name=""):
+    """An optimizer step.  list_: "flat" (one tensor of `numel`), or a parameter list of the benchmark with every tensor
+    cut into `slices`, one slice per tensor kept.  guard: state in place, per-element guard; otherwise ping-pong state."""
+    c = {"op": op, "list": list_, "slices": slices, "numel": numel, "R": R, "grad": grad, "guard": guard, "l2": l2,
+         "average": average, "loss_scale": float(loss_scale)}
+    return dict(name=name, **c) if name else c
+
+
+def epilogue_case(numel, first, hidden, R, p, *, name=""):
+    c = {"op": EPILOGUE, "numel": numel, "first": first, "hidden": hidden, "R": R, "p": p}
+    return dict(name=name, **c) if name else c
+
+
+def listed():
+    full = 8 * 1024 * 3072
+    return [
+        # One odd-sized small tensor that a framework steps by itself (a head or an adapter): nothing but latency.
+        step_case(ADAM, "flat", 4, numel=4099, name="adam_tiny"),
+        # The call for programs that may not allocate, on a ragged tensor: no plan, descriptor in the arguments.
+        step_case(ADAM_STATIC, "flat", 2, numel=100003, name="adam_static_100k"),
+        # Benchmark configuration 1: one flat tensor of 2^20 elements, four ranks.
+        step_case(ADAM, "flat", 4, numel=1 << 20, name="adam_flat_1Mi"),
+        # One of 64 ranks' share of the BERT-Large list: 398 scattered tensors, most of them a handful of elements.
+        step_case(ADAM, "bert", 8, slices=64, name="adam_bert_1of64"),
+        # fp32 slices with the rarer options together: L2 decay, averaging, in place with the per-element guard.
+        step_case(ADAM, "flat", 4, numel=12345679, grad="f32", guard=True, l2=True, average=True, loss_scale=128,
+                  name="adam_f32_guard_12M"),
+        # Benchmark configuration 2, the headline: the whole BERT-Large list, eight ranks.
+        step_case(ADAM, "bert", 8, name="adam_bert"),
+        # One odd-sized small tensor under LAMB: latency and the number of launches.
+        step_case(LAMB, "flat", 8, numel=10007, name="lamb_tiny"),
+        # One of eight ranks' slices of the BERT-Large list, in two calls: between them a program adds the ranks' norms.
+        step_case(LAMB_PHASES, "bert", 8, slices=8, name="lamb_phases_bert_1of8"),
+        # Benchmark configuration 3: LAMB on the whole BERT-Large list.
+        step_case(LAMB, "bert", 8, name="lamb_bert"),
+        # Benchmark configuration 5, the largest: one rank's eighth of an 8.3B transformer, 73 tensors of 14 M elements.
+        step_case(LAMB, "megatron", 8, name="lamb_8b"),
+        # One rank's eighth of the [8, 1024, 3072] epilogue: its slice starts inside the tensor.
+        epilogue_case(full // 8, full // 8 * 3, 3072, 8, 0.1, name="epilogue_1of8"),
+        # The whole [8, 1024, 3072] tensor on one rank.
+        epilogue_case(full, 0, 3072, 8, 0.1, name="epilogue_whole"),
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    while True:
+        kind = rng.choice((ADAM, ADAM, LAMB, LAMB, LAMB_PHASES, ADAM_STATIC, EPILOGUE))
+        if kind == EPILOGUE:
+            hidden = rng.choice((1024, 1600, 3072, 4096))
+            c = epilogue_case(max(8, _log_uniform(rng, 1 << 13, 1 << 26) // 8 * 8), rng.randrange(1 << 20) * 8, hidden,
+                              rng.choice((1, 2, 4, 8, 16)), rng.choice((0.0, 0.1, 0.3)))
+        elif kind == ADAM_STATIC:
+            c = step_case(kind, "flat", rng.choice((1, 2, 4, 8, 16)), numel=_log_uniform(rng, 1 << 10, 1 << 26),
+                          l2=rng.random() < 0.3, average=rng.random() < 0.3, loss_scale=rng.choice((1, 1024)))
+        else:
+            opts = dict(grad="f32" if rng.random() < 0.25 else "f16", average=rng.random() < 0.3,
+                        loss_scale=rng.choice((1, 128, 1024)))
+            if kind == ADAM:
+                opts.update(guard=rng.random() < 0.3, l2=rng.random() < 0.3)
+            R = rng.choice((1, 2, 4, 8, 8, 16))
+            if rng.random() < 0.5:
+                c = step_case(kind, "flat", R, numel=_log_uniform(rng, 1 << 10, 1 << 28), **opts)
+            else:
+                list_ = rng.choice(("bert", "bert", "gpt2", "megatron"))
+                c = step_case(kind, list_, R, slices=_log_uniform(rng, 1 if list_ == "bert" else 4, 512), **opts)
+        if work(c)["bytes"] <= MOST_BYTES:
+            return c
+
+
+LISTS = {"bert": W.bert_large_list, "gpt2": W.gpt2_xl_list, "megatron": W.megatron_8p3b_shard_list}
+
+
+def _params(case):
+    """[(numel, kind)] of the shard's tensors."""
+    if case["list"] == "flat":
+        return [(case["numel"], "matrix")]
+    return [(-(-s.numel // case["slices"]), s.kind) for s in LISTS[case["list"]]()]
+
+
+def _numel(case):
+    return sum(n for n, _ in _params(case)) if case["op"] != EPILOGUE else case["numel"]
+
+
+def _fill(x, std, gen):
+    """N(0, std) in fp32, rounded to x's type, in pieces so that the fp32 draw stays small."""
+    for piece in x.split(1 << 28):
+        if piece.dtype == torch.float32:
+            piece.normal_(0.0, std, generator=gen)
+        else:
+            piece.copy_(torch.empty(piece.numel(), dtype=torch.float32, device=x.device).normal_(0.0, std, generator=gen))
+
+
+def _prepare_epilogue(case, gen):
+    n = case["numel"]
+    half = lambda k, std: torch.empty(k, device="cuda").normal_(0.0, std, generator=gen).half()
+    return {"case": case, "partials": [half(n, 0.3) for _ in range(case["R"])], "bias": half(case["hidden"], 0.1),
+            "residual": half(n, 1.0), "out": torch.empty(n, dtype=torch.float16, device="cuda"), "seed": 2021}
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    if case["op"] == EPILOGUE:
+        return _prepare_epilogue(case, gen)
+    params, R, scale = _params(case), case["R"], case["loss_scale"]
+    std = 1e-3                                   # of one slice's unscaled gradients, as in configurations 2 to 5
+    shard = Shard([n for n, _ in params], [0.01 if kind == "matrix" else 0.0 for _, kind in params], R,
+                  in_place=case["guard"], unfused=False,
+                  grad_dtype=torch.float16 if case["grad"] == "f16" else torch.float32)
+    # A thousand steps into training: weights near their initial spread, moments of the size the gradients give.
+    _fill(shard.w[0], 0.02, gen)
+    for k, (_, kind) in enumerate(params):
+        if kind != "matrix":
+            shard.w_of(k).add_(1.0 if kind == "ln_gamma" else 0.0)
+    reduced = std * math.sqrt(R) / (R if case["average"] else 1)
+    _fill(shard.m[0], 0.3 * reduced, gen)
+    shard.v[0].uniform_(0.2, 1.8, generator=gen).mul_(reduced * reduced)
+    shard.w16[0].copy_(shard.w[0])
+    for g in shard.grads:
+        _fill(g, std * scale, gen)
+    state = {"case": case, "shard": shard, "t": 1000,
+             "hyper": dict(lr=1e-4, loss_scale=scale, grad_average=int(case["average"]), adam_mode=0 if case["l2"] else 1,
+                           skip_mode=1 if case["guard"] else 0)}
+    if case["op"] == ADAM_STATIC:
+        n = params[0][0]
+        state["tensors"] = [cc.Tensor(numel=n, w_in=shard.w[a], m_in=shard.m[a], v_in=shard.v[a], w_out=shard.w[b],
+                                      m_out=shard.m[b], v_out=shard.v[b], w16_out=shard.w16[b], grad=shard.grads,
+                                      weight_decay=shard.wds[0]) for a, b in ((0, 1), (1, 0))]
+    return state
+
+
+def run(state):
+    """One pass: the step of training iteration t, and the new state adopted (the flag is read later, with the loss)."""
+    case = state["case"]
+    if case["op"] == EPILOGUE:
+        cc.cc_fused_epilogue(state["partials"], state["bias"], state["residual"], state["out"], case["first"], case["hidden"],
+                             case["p"], state["seed"])
+        return state["out"]
+    shard = state["shard"]
+    state["t"] += 1
+    hp = cc.Hyper(step=state["t"], **state["hyper"])
+    if case["op"] == ADAM:
+        shard.run(cc.cc_fused_adam_step, hp)
+    elif case["op"] == ADAM_STATIC:
+        cc.cc_fused_adam_step_static(state["tensors"][shard.cur], case["R"], hp, shard.flag)
+    elif case["op"] == LAMB:
+        shard.run(cc.cc_fused_lamb_step, hp)
+    else:
+        shard.run(cc.cc_fused_lamb_phase1, hp)
+        shard.run(cc.cc_fused_lamb_phase2, hp)
+    shard.commit()
+    return {"w": shard.w[shard.cur], "m": shard.m[shard.cur], "v": shard.v[shard.cur], "w16": shard.w16[shard.cur],
+            "flag": shard.flag}
+
+
+def work(case):
+    n, R = _numel(case), case["R"]
+    if case["op"] == EPILOGUE:
+        # R partial outputs, residual and bias in, out once, all fp16; a sum, the bias, the scale and the residual
+        return {"bytes": n * (2 * R + 4) + 2 * case["hidden"], "flops": n * (R + 3)}
+    # the slices and w, m, v in; w, m, v and the fp16 weights out, each once (LAMB as well: its second look at the state
+    # is not a thing the path cannot do without).  R - 1 adds and about 16 more operations per element.
+    slice_bytes = 2 if case["grad"] == "f16" else 4
+    lamb = case["op"] in (LAMB, LAMB_PHASES)
+    return {"bytes": n * (slice_bytes * R + 26) + 4, "flops": n * (R + (22 if lamb else 15))}
+
+
+def tolerance(case):
+    """Four times what was measured against the same pass in 64 bits (fp32 state and fp16 results rounded once): the step's
+    w, m, v are 2.6e-8 off in the 2-norm and its fp16 weights 2e-7, because a few elements in 10^7 take the neighbouring
+    fp16 value (at most 2^-10 of the value, hence "max"); the epilogue, all fp16, is 1.2e-5 off."""
+    if case["op"] == EPILOGUE:
+        return {"rel": 5e-5, "max": 4e-3}
+    return {"rel": 8e-7, "max": 4e-3}
