@@ -5,8 +5,8 @@ weights, raise the overflow flag) or the model-parallel epilogue.  Sizes and val
 configurations (`workloads.config`), the sliced lists and the epilogue shapes of the benchmark's sweeps, or are generic.
 
 `listed()` gives the fixed cases, `draw(rng)` another one of the same ranges, `prepare` the device state a program holds
-before the call, `run` one pass, `work` the bytes and operations the pass cannot do without, `tolerance` how far another
-correct implementation may be off.
+before the call, `run` one pass, `exact` what that pass gives in 64 bits, `work` the bytes and operations the pass cannot
+do without, `tolerance` how far another correct implementation may be off.
 """
 from __future__ import annotations
 
@@ -179,6 +179,72 @@ def run(state):
     shard.commit()
     return {"w": shard.w[shard.cur], "m": shard.m[shard.cur], "v": shard.v[shard.cur], "w16": shard.w16[shard.cur],
             "flag": shard.flag}
+
+
+def _f32(x):
+    """The value the library receives: its interface takes fp32 scalars."""
+    return float(torch.tensor(x, dtype=torch.float32))
+
+
+def _dropout_keeps(n, first, p, seed):
+    """Philox4x32-10 of the global element index: counter = index / 4, word index % 4; kept iff word >= floor(p 2^32)."""
+    mask = 0xFFFFFFFF
+
+    def mul(a, b):                                          # 32 x 32 bits -> high and low word, in int64 without overflow
+        t = a * (b & 0xFFFF)
+        u = a * (b >> 16) + (t >> 16)
+        return u >> 16, ((u & 0xFFFF) << 16) | (t & 0xFFFF)
+
+    block = torch.arange(first // 4, (first + n + 3) // 4, device="cuda")
+    c = [block & mask, block >> 32, torch.zeros_like(block), torch.zeros_like(block)]
+    k0, k1 = seed & mask, seed >> 32
+    for _ in range(10):
+        hi0, lo0 = mul(0xD2511F53, c[0])
+        hi1, lo1 = mul(0xCD9E8D57, c[2])
+        c = [hi1 ^ c[1] ^ k0, lo1, hi0 ^ c[3] ^ k1, lo0]
+        k0, k1 = (k0 + 0x9E3779B9) & mask, (k1 + 0xBB67AE85) & mask
+    words = torch.stack(c, 1).reshape(-1)[first % 4:first % 4 + n]
+    return words >= math.floor(p * 2.0 ** 32)
+
+
+def _exact_epilogue(state):
+    case, p = state["case"], _f32(state["case"]["p"])
+    n, hidden = case["numel"], case["hidden"]
+    x = sum(q.double() for q in state["partials"])
+    x += state["bias"].double()[(case["first"] + torch.arange(n, device="cuda")) % hidden]
+    x = torch.where(_dropout_keeps(n, case["first"], p, state["seed"]), x / (1.0 - p), 0.0)
+    return x + state["residual"].double()
+
+
+def exact(case, seed):
+    """The pass of `run` on these inputs in 64 bits, tensor by tensor; what lies between the tensors is not written."""
+    state = prepare(case, seed)
+    if case["op"] == EPILOGUE:
+        return _exact_epilogue(state)
+    shard, hyper, t = state["shard"], state["hyper"], state["t"] + 1
+    defaults = cc.Hyper()
+    lr, scale = _f32(hyper["lr"]), _f32(hyper["loss_scale"])
+    b1, b2, eps = _f32(defaults.beta1), _f32(defaults.beta2), _f32(defaults.eps)
+    arenas = {"w": shard.w, "m": shard.m, "v": shard.v, "w16": shard.w16}
+    out = {k: (a[0].double() if shard.in_place else torch.zeros_like(a[0], dtype=torch.float64)) for k, a in arenas.items()}
+    for k in range(len(shard.numels)):
+        wd = _f32(shard.wds[k])
+        w, m, v = shard.w_of(k).double(), shard.m_of(k).double(), shard.v_of(k).double()
+        g = sum(shard.grad_of(r, k).double() for r in range(case["R"])) / (scale * (case["R"] if case["average"] else 1))
+        if case["l2"]:
+            g = g + wd * w
+        m = b1 * m + (1.0 - b1) * g
+        v = b2 * v + (1.0 - b2) * g * g
+        u = m / (1.0 - b1 ** t) / (torch.sqrt(v / (1.0 - b2 ** t)) + eps)
+        if not case["l2"]:
+            u = u + wd * w
+        if case["op"] in (LAMB, LAMB_PHASES):
+            nw, nu = w.norm(), u.norm()
+            u = u * torch.where((nw > 0) & (nu > 0), nw / nu, 1.0)
+        w = w - lr * u
+        for x, a in ((w, "w"), (m, "m"), (v, "v"), (w, "w16")):
+            shard.view(out[a], k).copy_(x)
+    return dict(out, flag=None)
 
 
 def work(case):
