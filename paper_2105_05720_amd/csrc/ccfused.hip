@@ -790,13 +790,23 @@ int check_epilogue(const cc_epilogue *e, EpilogueArgs *a)
 }
 
 constexpr int kEpilogueBlock = 512;             // the unfused pipeline's kernels (64, 128 and 256 threads are 2-8 % slower)
-// The fused kernel spends about half as long on the mask generator's integer arithmetic as on its memory traffic, and
-// overlaps the two best as single-wave workgroups that come and go independently: 78.0 us against 86.0 us with 512
-// threads on the [8, 1024, 3072] tensor (256 threads: 78.5 us; 128: 81.8 us).  Two groups of 8 elements per lane where
-// the call is bound by HBM, one where it stays in the Infinity Cache (its 1/8 slices: 10.0 and 20.9 us against 10.4
-// and 22.3 us with two).
-constexpr int kEpilogueFusedBlock = 64;
-constexpr uint64_t kEpilogueCachedBytes = 200ull << 20;
+// How the fused kernel's single-wave workgroups are laid over the device, by the bytes of the call (2R + 4 per element).
+// Figures: R = 8, three sets of buffers used in turn; before these rules the kernel took the pieces in grid order with
+// non-temporal accesses, two groups per lane from 200 MiB on.  The stores are always written through (sc1): 78.6 against
+// 83.8 us on the [8, 1024, 3072] tensor (480 MiB), and never slower.
+//   * from 16 MiB on the XCDs take runs of pieces (piece_in_runs): 4.9 against 5.3 us at 20 MiB, 11.6 against 12.9 at
+//     60 MiB, 27.1 against 29.2 at 160 MiB; below, one or two rounds of the grid are all there is (3.0 without, 3.3 with
+//     them at 10 MiB).
+//   * below 80 MiB plain loads: the partial outputs were written just before and are still in the 256 MB Infinity Cache
+//     (10.9 against 11.6 us at 60 MiB; with evicted caches 13.7 against 12.2, and 24.7 against 21.2 us at 120 MiB).
+//   * from 384 MiB on, with R >= 4, ten waves per compute unit (the launch asks for LDS that nobody uses) and the pieces
+//     in grid order: the addresses in flight are then a narrow window that moves through the ten streams, which DRAM
+//     rewards more than runs: 75.9 against 78.6 us at 480 MiB (runs: 77.2), 201 against 213 us at 1280 MiB (runs: 217),
+//     R = 16 at 2304 MiB 375 against 400 us.  With fewer slices ten waves have too little in flight (R = 2, 512 MiB: 98
+//     against 85 us; runs: 83 us).
+constexpr uint64_t kEpilogueRunsMinBytes = 16ull << 20, kEpilogueCachedBytes = 80ull << 20, kEpilogueNarrowMinBytes = 384ull << 20;
+constexpr int32_t kEpilogueNarrowMinR = 4;
+constexpr unsigned kEpilogueNarrowLds = 16384;   // bytes per workgroup: 160 KiB hold ten
 
 int epilogue_grid(uint64_t numel, uint32_t chunk, unsigned *grid)
 {
@@ -814,17 +824,20 @@ int cc_fused_epilogue(const cc_epilogue *e, void *stream)
     int rc = check_epilogue(e, &a);
     if (rc) return rc;
     if (e->numel == 0) return CC_OK;
-    const int groups = e->numel * (2u * (uint64_t)e->R + 4u) < kEpilogueCachedBytes ? 1 : 2;
+    const uint64_t bytes = e->numel * (2u * (uint64_t)e->R + 4u);
+    const bool narrow = bytes >= kEpilogueNarrowMinBytes && e->R >= kEpilogueNarrowMinR;
+    a.runs = bytes >= kEpilogueRunsMinBytes && !narrow;
+    const unsigned lds = narrow ? kEpilogueNarrowLds : 0u;
     unsigned grid;
-    if ((rc = epilogue_grid(e->numel, (uint32_t)(kEpilogueFusedBlock * 8 * groups), &grid))) return rc;
+    if ((rc = epilogue_grid(e->numel, kEpiloguePiece, &grid))) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if (groups == 2) switch (e->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, kEpilogueFusedBlock, 2>), dim3(grid), dim3(kEpilogueFusedBlock), 0, st, a); break;
+    if (bytes < kEpilogueCachedBytes) switch (e->R) {
+#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, Resident>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, a); break;
         FOR_EACH_R(CASE)
 #undef CASE
     }
     else switch (e->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, kEpilogueFusedBlock, 1>), dim3(grid), dim3(kEpilogueFusedBlock), 0, st, a); break;
+#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, WriteThrough>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, a); break;
         FOR_EACH_R(CASE)
 #undef CASE
     }

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "ccfused.h"
+#include "piece_order.hpp"
 
 namespace ccf {
 
@@ -1395,6 +1396,7 @@ struct EpilogueArgs {
     const uint16_t *residual;
     uint16_t *out;
     float *sum;               // unfused pipeline only: fp32 reduced partial outputs
+    uint32_t runs;            // fused kernel: take the pieces in runs per XCD (piece_in_runs)
 };
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
@@ -1421,8 +1423,15 @@ __device__ __forceinline__ float epilogue_value(float x_sum, float bias, float r
     return (keep ? x * scale : 0.0f) + residual;
 }
 
-__device__ __forceinline__ f16x8 ld_f16x8(gcbytes b, uint32_t off) { return __builtin_nontemporal_load((const CCF_GLOBAL f16x8 *)(b + off)); }
-__device__ __forceinline__ void st_f16x8(gbytes b, uint32_t off, f16x8 x) { __builtin_nontemporal_store(x, (CCF_GLOBAL f16x8 *)(b + off)); }
+template <class Mem> __device__ __forceinline__ f16x8 ld_f16x8(gcbytes b, uint32_t off)
+{
+    if (Mem::kLoadNonTemporal) return __builtin_nontemporal_load((const CCF_GLOBAL f16x8 *)(b + off));
+    return *(const CCF_GLOBAL f16x8 *)(b + off);
+}
+template <class Mem> __device__ __forceinline__ void st_f16x8(gbytes b, uint32_t off, f16x8 x)
+{
+    st_f32x4<Mem>(b, off, __builtin_bit_cast(f32x4, x));
+}
 
 // Common part of the fused kernel and of the unfused pipeline's pointwise kernel: mask, bias column, output.
 struct EpilogueTail {
@@ -1457,7 +1466,7 @@ struct EpilogueTail {
     }
 };
 
-template <int R>
+template <int R, class Mem>
 struct FusedEpilogueOp {
     static constexpr uint32_t kPack = 8;
     gcbytes part[R];
@@ -1472,8 +1481,8 @@ struct FusedEpilogueOp {
     __device__ __forceinline__ void load(Regs &x, uint32_t e) const
     {
 #pragma unroll
-        for (int r = 0; r < R; ++r) x.p[r] = ld_f16x8(part[r], e * 2);
-        x.r = ld_f16x8(t.res, e * 2);
+        for (int r = 0; r < R; ++r) x.p[r] = ld_f16x8<Mem>(part[r], e * 2);
+        x.r = ld_f16x8<Mem>(t.res, e * 2);
         x.b = *(const CCF_GLOBAL f16x8 *)(t.bias + t.column(e) * 2);     // 8 columns never wrap: H and e are multiples of 8
         x.e = e;
     }
@@ -1495,7 +1504,7 @@ struct FusedEpilogueOp {
         }
         x.r = o;
     }
-    __device__ __forceinline__ void store(const Regs &x, uint32_t e) const { st_f16x8(t.out, e * 2, x.r); }
+    __device__ __forceinline__ void store(const Regs &x, uint32_t e) const { st_f16x8<Mem>(t.out, e * 2, x.r); }
     __device__ __forceinline__ void single(uint32_t j)
     {
         float sum = ld_f16(part[0], j * 2);
@@ -1505,15 +1514,21 @@ struct FusedEpilogueOp {
     }
 };
 
-template <int R, int BLOCK, int GROUPS>
-__global__ __launch_bounds__(BLOCK) void fused_epilogue_kernel(EpilogueArgs a)
+// Bound by reading HBM (2R + 2 of its 2R + 4 bytes per element); the mask generator's integer arithmetic hides behind
+// that (the kernel without it takes as long).  Single-wave workgroups of one group per lane come and go independently
+// and are the fastest shape at every R and size (two groups per lane: 0-9 % slower, 256 and 512 threads 1-5 %); what
+// they gain beyond that comes from the addresses in flight, see cc_fused_epilogue.
+constexpr int kEpilogueFusedBlock = 64;
+constexpr uint32_t kEpiloguePiece = kEpilogueFusedBlock * 8;
+template <int R, class Mem>
+__global__ __launch_bounds__(kEpilogueFusedBlock) void fused_epilogue_kernel(EpilogueArgs a)
 {
-    constexpr uint32_t kChunk = BLOCK * 8 * GROUPS;
-    const uint64_t base = (uint64_t)blockIdx.x * kChunk;
+    const uint32_t piece = a.runs ? piece_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint64_t base = (uint64_t)piece * kEpiloguePiece;
     const uint64_t rem = a.numel - base;
-    FusedEpilogueOp<R> op;
+    FusedEpilogueOp<R, Mem> op;
     op.init(a, base);
-    stream_chunk<BLOCK, FusedEpilogueOp<R>, GROUPS>(op, rem < kChunk ? (uint32_t)rem : kChunk);
+    stream_chunk<kEpilogueFusedBlock, FusedEpilogueOp<R, Mem>, 1>(op, rem < kEpiloguePiece ? (uint32_t)rem : kEpiloguePiece);
 }
 
 // Unfused pipeline: reduce the R partial outputs into an fp32 buffer (a lane owns 4 elements, so that the fp32

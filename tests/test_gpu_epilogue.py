@@ -79,6 +79,22 @@ def test_fused_equals_unfused_epilogue_bit_for_bit(n):
     check(to_np_bits(b), partials, bias, residual, 960, 0.1, 11)
 
 
+@pytest.mark.parametrize("R,n", [
+    (8, (16 << 20) // 20 - 5), (8, 512 * 2048 + 512 * 511 + 8),      # around 16 MiB: grid order, and runs with all but one piece of a round left over
+    (8, (80 << 20) // 20 - 3), (16, 512 * 512 * 12 + 1),             # around 80 MiB: plain loads below, non-temporal from there on; a last piece of one element
+    (4, (384 << 20) // 12 + 3), (3, (384 << 20) // 10 + 7),          # from 384 MiB: few waves with four slices and more, runs with fewer
+])
+def test_every_launch_shape_equals_unfused_bit_for_bit(R, n):
+    partials, bias, residual = make(n, R, 96, 5)
+    a = torch.zeros(n, dtype=torch.float16, device="cuda")
+    b = torch.zeros(n, dtype=torch.float16, device="cuda")
+    scratch = torch.empty(n + 8, dtype=torch.float32, device="cuda")
+    cc.cc_fused_epilogue(partials, bias, residual, a, 960, 96, 0.1, 11)
+    cc.cc_unfused_epilogue(partials, bias, residual, b, scratch, 960, 96, 0.1, 11)
+    torch.cuda.synchronize()
+    assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
 def test_mask_does_not_depend_on_slicing():
     n, H, p, seed = 8192 * 5, 128, 0.3, 21
     partials, bias, residual = make(n, 4, H, 6)
