@@ -124,13 +124,20 @@ void resolve_schedule(cc_plan *p)
     else if (p->schedule == CC_SCHEDULE_PER_CHUNK) p->ordered = false;
     else p->ordered = L.chunks >= kOrderedMinChunksPerCu * (int64_t)p->cus && !(p->grad_f32 && p->R > kOrderedMaxF32Slices);
     if (L.chunk_elems != kDefaultChunkElems || L.chunks == 0) p->ordered = false;
-    if (p->cache_policy != CC_CACHE_AUTO) p->mem = p->mem_lamb = p->cache_policy;
+    const uint64_t footprint = p->numel * ((p->grad_f32 ? 4u : 2u) * (uint64_t)p->R + 12u + 14u);
+    if (p->cache_policy != CC_CACHE_AUTO) p->mem = p->mem_lamb = p->mem_lamb2 = p->mem_unfused = p->cache_policy;
     else {
-        const uint64_t footprint = p->numel * ((p->grad_f32 ? 4u : 2u) * (uint64_t)p->R + 12u + 14u);
-        p->mem = auto_cache_policy(footprint, p->numel * kAdamStoreBytes);
-        p->mem_lamb = auto_cache_policy(footprint, p->numel * kLambStoreBytes);
+        const uint64_t stored = p->numel * kAdamStoreBytes;
+        p->mem = auto_cache_policy(footprint, stored, p->single < 0);
+        p->mem_unfused = auto_cache_policy(footprint, stored, false);
+        if (footprint < kResidentMaxBytes) p->mem_lamb = p->mem_lamb2 = p->mem;
+        else {
+            p->mem_lamb = CC_CACHE_WRITE_THROUGH;
+            p->mem_lamb2 = stored < kLambThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
+        }
     }
-    if (L.block != kSmallBlock || p->ordered) p->mem = p->mem_lamb = CC_CACHE_STREAMING;
+    p->spread = footprint >= kResidentMaxBytes && L.block == kSmallBlock && !p->ordered;
+    if (L.block != kSmallBlock || p->ordered) p->mem = p->mem_lamb = p->mem_lamb2 = p->mem_unfused = CC_CACHE_STREAMING;
 }
 
 void free_layout(Layout &L)
@@ -548,6 +555,7 @@ int check_hparams(const cc_hparams *hp, const void *flag, Opt opt, int32_t R, bo
 int check_step(const cc_plan *p, const cc_hparams *hp, const void *flag, Opt opt, StepScalars *s)
 {
     if (!p) return fail(CC_ERR_NULL, "plan is NULL");
+    s->runs = p->spread ? 1u : 0u;
     return check_hparams(hp, flag, opt, p->R, p->in_place, p->lay().chunk_elems, s);
 }
 
@@ -653,6 +661,7 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
                     return fail(CC_ERR_ALIAS, "two of the tensor's buffers overlap and one of them is an output");
     }
     StepScalars s;
+    s.runs = 0;
     int rc = check_hparams(hp, flag, Opt::Adam, R, in_place, kSmallChunkElems, &s);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
@@ -669,7 +678,7 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
     d.wd = t->weight_decay;
     const unsigned grid = (unsigned)((t->numel + (uint64_t)kSmallChunkElems - 1) / (uint64_t)kSmallChunkElems);
     const int mode = (hp->skip_mode == 1 ? kModeGuard : 0) | (hp->adam_mode == 0 ? kModeL2 : 0);
-    const int32_t mem = auto_cache_policy(t->numel * (2u * (uint64_t)R + 26u), t->numel * kAdamStoreBytes);   // the plans' AUTO rule
+    const int32_t mem = auto_cache_policy(t->numel * (2u * (uint64_t)R + 26u), t->numel * kAdamStoreBytes, false);   // the plans' AUTO rule
     launch_fused_adam_flat_f16(d, R, grid, mem, s, fs, flag, st, mode);
     return launched("fused_adam_flat_kernel");
 }

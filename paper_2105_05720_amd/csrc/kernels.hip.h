@@ -70,6 +70,7 @@ struct StepScalars {
     float rc1, rc2;           // 1 / (1 - beta^t)
     float eps, lr;
     uint32_t chunk_elems;
+    uint32_t runs;            // one workgroup per chunk: take the chunks in runs per XCD (piece_in_runs)
 };
 
 enum : int { kModeGuard = 1, kModeL2 = 2 };
@@ -221,15 +222,16 @@ __device__ __forceinline__ Where locate_at(const DevTensor *__restrict__ tensors
 // its data is after one trip to memory instead of two dependent ones (entry, then descriptor): 2-4 % of a launch-bound
 // step (same machine, with / without: 4.70 / 4.90 us on 398 tensors in 571 chunks, 9.60 / 9.90 us on 10 tensors in
 // 1280 chunks).
-__device__ __forceinline__ Where locate(const DevTensor *__restrict__ tensors, const Chunk *__restrict__ chunks,
-                                        uint32_t chunk_elems)
+constexpr uint32_t kChunkRunLog2 = 5;
+__device__ __forceinline__ Where locate(const DevTensor *__restrict__ tensors, const Chunk *__restrict__ chunks, const StepScalars &s)
 {
-    if (chunks != nullptr) return locate_at(tensors, chunks, blockIdx.x, chunk_elems);
+    const uint32_t entry = s.runs ? piece_in_runs<kChunkRunLog2>(blockIdx.x, gridDim.x) : blockIdx.x;
+    if (chunks != nullptr) return locate_at(tensors, chunks, entry, s.chunk_elems);
     Where wh;
-    wh.t = tensors + blockIdx.x;
+    wh.t = tensors + entry;
     wh.tensor = wh.t->tensor;
     wh.index = wh.t->chunk_index;
-    finish_where(wh, chunk_elems);
+    finish_where(wh, s.chunk_elems);
     return wh;
 }
 
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(BLOCK) void fused_adam_kernel(const DevTensor *__re
 {
     FlagCount<BLOCK> fc;
     fc.arrive(fs);
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
     op.init(wh.t, wh.base, s);
     sweep_and_publish<BLOCK, GROUPS>(op, wh.len, fc, fs, flag);
@@ -802,7 +804,7 @@ __global__ __launch_bounds__(BLOCK) void adam_from_sum_kernel(const DevTensor *_
                                                               const int32_t *__restrict__ flag)
 {
     if (!(MODE & kModeGuard) && *flag != 0) return;
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     AdamOp<typename std::conditional<SUM16, GradSumHalf<Mem>, GradSum<Mem>>::type, MODE, false> op;
     op.init(wh.t, wh.base, s);
     stream_chunk<BLOCK>(op, wh.len);
@@ -940,7 +942,7 @@ __device__ __forceinline__ void lamb_phase1_body(const DevTensor *__restrict__ t
 {
     FlagCount<BLOCK> fc;
     if (RAISE) fc.arrive(fs);
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     LambPhase1Op<Grad> op;
     op.init(wh.t, wh.base, s);
     op.partials = partials;
@@ -1136,7 +1138,7 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_kernel(const DevTensor *__r
                                                             const int32_t *__restrict__ flag)
 {
     if (*flag != 0) return;              // whole-step skip: w and w16 stay as they were
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     const double sw = sums[2 * (uint64_t)wh.tensor], su = sums[2 * (uint64_t)wh.tensor + 1];
     const float ratio = (sw > 0.0 && su > 0.0) ? (float)(__builtin_sqrt(sw) / __builtin_sqrt(su)) : 1.0f;
     LambPhase2Op<EMIT16, Mem> op;
@@ -1155,7 +1157,7 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
                                                                        double *__restrict__ sums,
                                                                        const int32_t *__restrict__ flag)
 {
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     double sw, su;
     tensor_sums<BLOCK>(partials + 2 * (uint64_t)wh.t->first_chunk, wh.t->num_chunks, sw, su);
     if (wh.index == 0 && threadIdx.x == 0) {
@@ -1228,7 +1230,7 @@ __global__ __launch_bounds__(BLOCK) void reduce_kernel(const DevTensor *__restri
 {
     FlagCount<BLOCK> fc;
     fc.arrive(fs);
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     ReduceOp<R, GF32, Mem> op;
     op.init(wh.t, wh.base);
     stream_chunk<BLOCK>(op, wh.len);
@@ -1302,7 +1304,7 @@ __global__ __launch_bounds__(BLOCK) void reduce_half_kernel(const DevTensor *__r
 {
     FlagCount<BLOCK> fc;
     fc.arrive(fs);
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     ReduceHalfOp<R, Mem> op;
     op.init(wh.t, wh.base);
     stream_chunk<BLOCK>(op, wh.len);
@@ -1351,7 +1353,7 @@ __global__ __launch_bounds__(BLOCK) void cast_kernel(const DevTensor *__restrict
                                                      const int32_t *__restrict__ flag, int guarded)
 {
     if (guarded && *flag != 0) return;
-    const Where wh = locate(tensors, chunks, s.chunk_elems);
+    const Where wh = locate(tensors, chunks, s);
     CastOp<Mem> op;
     op.init(wh.t, wh.base);
     stream_chunk<BLOCK>(op, wh.len);

@@ -53,7 +53,7 @@ int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipS
         return launched("lamb_phase2_ordered_kernel");
     }
     const dim3 grid((unsigned)L.chunks);
-    if (emit16) BY_BLOCK_MEM(p, p->mem_lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
+    if (emit16) BY_BLOCK_MEM(p, p->mem_lamb2, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
     else BY_BLOCK_MEM(p, p->mem_lamb, hipLaunchKernelGGL((lamb_phase2_kernel<false, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
     return launched("lamb_phase2_kernel");
 }
@@ -62,7 +62,7 @@ int lamb_phase2_with_norms(cc_plan *p, const StepScalars &s, const int32_t *flag
 {
     const Layout &L = p->lay();
     const dim3 grid((unsigned)L.chunks);
-    BY_BLOCK_MEM(p, p->mem_lamb, hipLaunchKernelGGL((lamb_phase2_with_norms_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials, p->d_sums, flag));
+    BY_BLOCK_MEM(p, p->mem_lamb2, hipLaunchKernelGGL((lamb_phase2_with_norms_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials, p->d_sums, flag));
     return launched("lamb_phase2_with_norms_kernel");
 }
 

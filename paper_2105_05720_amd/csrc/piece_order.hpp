@@ -13,16 +13,17 @@ namespace ccf {
 
 // Which piece workgroup `b` of a grid of `grid` takes when every XCD is to own runs of consecutive pieces.  The hardware
 // deals workgroups to the eight XCDs in turn, so taking piece b scatters neighbouring pieces over all of them; here the
-// workgroups of one XCD take 64 consecutive ones (64 KiB of an fp16 array in the epilogue's pieces of 512 elements), the
-// next XCD the run behind it.  A round of eight runs covers the same pieces either way, and what is left of the grid
+// workgroups of one XCD take 2^RUN_LOG2 consecutive ones (64 KiB of an fp16 array: 64 of the epilogue's pieces of 512
+// elements, 32 of the optimizer kernels' small chunks of 1024), the next XCD the run behind it.  A round of eight runs covers the same pieces either way, and what is left of the grid
 // behind the last full round is taken in order, so every piece is taken exactly once.  Pays once the grid is a few rounds
 // deep; on one or two rounds it only costs the imbalance.
-constexpr uint32_t kRunLog2 = 6, kRoundLog2 = kRunLog2 + 3;
+template <uint32_t RUN_LOG2 = 6>
 CCF_ANYWHERE uint32_t piece_in_runs(uint32_t b, uint32_t grid)
 {
+    constexpr uint32_t kRoundLog2 = RUN_LOG2 + 3;
     const uint32_t round = b >> kRoundLog2, in = b & ((1u << kRoundLog2) - 1u);
     if (round >= grid >> kRoundLog2) return b;
-    return (round << kRoundLog2) + ((in & 7u) << kRunLog2) + (in >> 3);
+    return (round << kRoundLog2) + ((in & 7u) << RUN_LOG2) + (in >> 3);
 }
 
 }  // namespace ccf

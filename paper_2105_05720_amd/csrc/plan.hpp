@@ -28,17 +28,36 @@ constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per c
 // (88 MB), 27.6 against 29.6 at 2^22 (176 MB), but 68.1 against 60.2 at 2^23 (352 MB).  Below 2^17 elements the
 // non-temporal accesses are the faster ones by 1-6 % (LAMB at 2^14: 7.7 against 8.0 us), hence the lower bound.
 constexpr uint64_t kResidentMinBytes = 4ull << 20, kResidentMaxBytes = 200ull << 20;
-// ... and from there on non-temporal loads with write-through stores while one kernel stores less than this (see
-// WriteThrough): what a launch writes then about fits the Infinity Cache.  Fused Adam (14 B stored per element) at
-// R = 8: 141 against 147 us at 20 Mi elements, 160 against 157 us at 22 Mi; fused LAMB (8 B in its first sweep, 6 B in
-// its second): 318 against 338 us at 36 Mi elements, 373 against 368 us at 40 Mi.
+// ... and from there on non-temporal loads with write-through stores while one Adam launch stores less than this (see
+// WriteThrough): what it writes then about fits the Infinity Cache.  One tensor at R = 8: 141 against 147 us at 20 Mi
+// elements, 160 against 157 us at 22 Mi.
 constexpr uint64_t kWriteThroughMaxStoreBytes = 288ull << 20;
-constexpr uint32_t kAdamStoreBytes = 14, kLambStoreBytes = 8;      // per element: w', m', v', w16 / m', v'
-inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored)
+// A list of tensors goes back to non-temporal stores earlier, once the step's buffers exceed this.  BERT-Large list cut
+// into slices, three shards in turn, written through / non-temporal, us: 35.9 / 39.6 at 5.3 M elements (R = 8: 231 MB),
+// but 67.7 / 61.6 at 8.4 M (370 MB), 88.1 / 80.3 at 11.2 M, 151 / 145 at 21 M; R = 16 at 11.2 M (673 MB) 120.7 / 111.4;
+// eight fp32 slices at 8.4 M (504 MB) 92.2 / 83.7.
+constexpr uint64_t kListWriteThroughMaxBytes = 300ull << 20;
+constexpr uint64_t kAdamStoreBytes = 14;                           // per element: w', m', v', w16
+inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored, bool list)
 {
     if (footprint < kResidentMinBytes) return CC_CACHE_STREAMING;
-    return footprint < kResidentMaxBytes ? CC_CACHE_RESIDENT : stored < kWriteThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
+    if (footprint < kResidentMaxBytes) return CC_CACHE_RESIDENT;
+    return (list ? footprint < kListWriteThroughMaxBytes : stored < kWriteThroughMaxStoreBytes) ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
 }
+// LAMB's two sweeps want different stores once the shard has outgrown the Infinity Cache: written through in the first,
+// whose m' and v' the second reads again, and in the second, whose output nobody reads before the next step,
+// non-temporal from this many stored bytes per step on.  BERT-Large list in slices, R = 8, us with write-through in both /
+// write-through and non-temporal: 51.1 / 53.7 at 5.3 M elements, 100.7 / 102.7 at 11.2 M, but 127.9 / 124.3 at 14 M,
+// 194 / 180 at 21 M, 379 / 357 at 42 M (non-temporal in both: 372).
+constexpr uint64_t kLambThroughMaxStoreBytes = 176ull << 20;
+
+// Small chunks of a shard that does not fit the Infinity Cache (step's buffers of kResidentMaxBytes and more) are bound
+// by HBM, and what the addresses in flight look like decides: every XCD takes runs of 32 chunks (piece_in_runs), and the
+// fused Adam kernel asks for LDS that nobody uses, so that six of its 128-thread workgroups fit a compute unit instead of
+// up to sixteen.  Together, us before / runs only / runs and six workgroups: 36.6 / 36.1 / 35.9 at 5.3 M elements, 82.0 /
+// 81.1 / 80.3 at 11.2 M, 389.2 / 385.7 / 382.9 at 56 M.  LAMB's first sweep adds up its chunk behind a barrier and cannot
+// spare the waves (42 M elements: 357 us for both phases, 382 us with ten waves per compute unit).
+constexpr unsigned kSpreadLds = 24000;
 
 
 // Records the message for cc_last_error() on this thread and returns the code.
@@ -82,7 +101,10 @@ struct cc_plan {
     int32_t schedule = CC_SCHEDULE_AUTO;    // what the caller asked for
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
     int32_t mem = CC_CACHE_STREAMING;       // the policy in use (other than STREAMING: small-chunk layouts only)
-    int32_t mem_lamb = CC_CACHE_STREAMING;  // ... by LAMB's sweeps, which store fewer bytes per element
+    int32_t mem_lamb = CC_CACHE_STREAMING;  // ... by LAMB's first sweep
+    int32_t mem_lamb2 = CC_CACHE_STREAMING; // ... and by its second
+    int32_t mem_unfused = CC_CACHE_STREAMING; // by the unfused pipelines, which read again what they stored
+    bool spread = false;                    // small chunks of a shard bound by HBM (see kSpreadLds)
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
     int32_t cus = 0;                        // compute units of the device the plan was created on
     int32_t single = -1;                    // index of the only tensor with elements, or -1 if there are several (or none)

@@ -186,6 +186,23 @@ def test_mid_size_shard_under_the_automatic_cache_policy(fn, ofn, log2n, R, poli
     sh.destroy()
 
 
+@pytest.mark.parametrize("fn,ofn,numels,R,why", [
+    (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 3584 - 7, 3, 9], 16, "just over 200 MiB: written through, 14 rounds of runs and two workgroups behind them"),
+    (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 5000 + 1, 17, 1024 * 503], 16, "over 300 MiB: a list goes back to non-temporal stores"),
+    (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 7900 + 5, 11], 1, "176 MiB stored per step, just below: both sweeps write through"),
+    (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 7907 + 5, 11], 1, "and just over: the second sweep stores non-temporally"),
+])
+def test_chunks_in_runs(fn, ofn, numels, R, why):
+    """Shards that do not fit the Infinity Cache: each XCD takes runs of 32 chunks and what is left behind the last full
+    round goes in table order.  Every element against the oracle."""
+    sh = Shard(numels, wds_for(numels), R, align_elems=8, unfused=False)
+    assert cc.cc_plan_layout(sh.plans[0])[:2] == (1024, 128)
+    seeded_state(sh, 12)
+    ost = OracleState(sh, range(len(numels)))
+    run_steps(sh, ost, fn, ofn, [hyper_pair(step=3)], why, lambda i: seeded_grads(sh, 120 + i, 1e-3), expect_flags=[0])
+    sh.destroy()
+
+
 @pytest.mark.parametrize("fn,ofn", [(cc.cc_fused_adam_step, oracle.adam_step), (cc.cc_fused_lamb_step, oracle.lamb_step),
                                     (cc.cc_unfused_adam_step, oracle.adam_step)])
 def test_both_forms_of_the_chunk_table(fn, ofn):

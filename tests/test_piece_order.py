@@ -21,6 +21,10 @@ int main()
             const uint32_t p = ccf::piece_in_runs(b, g);
             if (p >= g || taken[p]++) { printf("grid %u: workgroup %u takes %u\n", g, b, p); return 1; }
         }
+        for (uint32_t b = 0; b < g; ++b) {                       // runs of 32
+            const uint32_t p = ccf::piece_in_runs<5>(b, g);
+            if (p >= g || taken[p]++ != 1) { printf("grid %u, runs of 32: workgroup %u takes %u\n", g, b, p); return 1; }
+        }
     }
     for (uint32_t x = 0; x < 8; ++x)                             // one XCD's workgroups b = x, x + 8, ... of the second round
         for (uint32_t k = 0; k < 64; ++k)
