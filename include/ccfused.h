@@ -157,7 +157,9 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  * Chunk size of the step calls: one of the sizes the plan was prepared for (see cc_plan_create), or 0 for the size
  * rule.  Adam results do not depend on it; LAMB's norms are summed chunk by chunk, so they move in the last bits.
  * cc_plan_layout reports what the plan will use (each pointer may be NULL): chunk size, threads per workgroup,
- * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).
+ * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).  (One tensor in chunks below 4096
+ * elements whose step's buffers total 200 MiB and more is the exception: there the fused Adam step runs single-wave
+ * workgroups of 256 elements.)
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);

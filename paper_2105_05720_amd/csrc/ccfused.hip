@@ -124,7 +124,7 @@ void resolve_schedule(cc_plan *p)
     else if (p->schedule == CC_SCHEDULE_PER_CHUNK) p->ordered = false;
     else p->ordered = L.chunks >= kOrderedMinChunksPerCu * (int64_t)p->cus && !(p->grad_f32 && p->R > kOrderedMaxF32Slices);
     if (L.chunk_elems != kDefaultChunkElems || L.chunks == 0) p->ordered = false;
-    const uint64_t footprint = p->numel * ((p->grad_f32 ? 4u : 2u) * (uint64_t)p->R + 12u + 14u);
+    const uint64_t footprint = step_footprint(p->numel, p->R, p->grad_f32);
     if (p->cache_policy != CC_CACHE_AUTO) p->mem = p->mem_lamb = p->mem_lamb2 = p->mem_unfused = p->cache_policy;
     else {
         const uint64_t stored = p->numel * kAdamStoreBytes;
@@ -678,7 +678,7 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
     d.wd = t->weight_decay;
     const unsigned grid = (unsigned)((t->numel + (uint64_t)kSmallChunkElems - 1) / (uint64_t)kSmallChunkElems);
     const int mode = (hp->skip_mode == 1 ? kModeGuard : 0) | (hp->adam_mode == 0 ? kModeL2 : 0);
-    const int32_t mem = auto_cache_policy(t->numel * (2u * (uint64_t)R + 26u), t->numel * kAdamStoreBytes, false);   // the plans' AUTO rule
+    const int32_t mem = auto_cache_policy(step_footprint(t->numel, R, false), t->numel * kAdamStoreBytes, false);   // the plans' AUTO rule
     launch_fused_adam_flat_f16(d, R, grid, mem, s, fs, flag, st, mode);
     return launched("fused_adam_flat_kernel");
 }

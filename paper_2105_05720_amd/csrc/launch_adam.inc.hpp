@@ -9,6 +9,21 @@ namespace ccf {
 
 namespace {
 
+// One tensor that does not fit the Infinity Cache, in single-wave pieces (see kFlatPiece).
+template <int MODE, bool GF32, class MEM>
+void launch_flat_pieces(const DevTensor &t, int R, StepScalars s, FlagScratch *fs, int32_t *flag, hipStream_t st)
+{
+    constexpr uint32_t kSliceBytes = GF32 ? 4 : 2;
+    const dim3 grid((unsigned)((t.numel + kFlatPiece - 1) / kFlatPiece)), block(kFlatBlock);
+    const unsigned lds = flat_lds(step_footprint(t.numel, R, GF32), kSliceBytes * (uint32_t)R);
+    s.chunk_elems = kFlatPiece;
+    switch (R) {
+#define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, kFlatBlock, GF32, 1, MEM>), grid, block, lds, st, t, s, fs, flag); break;
+        FOR_EACH_R(CASE)
+#undef CASE
+    }
+}
+
 template <int MODE, int BLK, bool GF32, class MEM>
 void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
@@ -25,6 +40,8 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
     const dim3 grid((unsigned)L.chunks), block(BLK);
     if (p->single >= 0) {                  // one tensor: no table, descriptor in the kernel arguments
         const DevTensor &t = L.host_tensors[(size_t)p->single];
+        if constexpr (!std::is_same<MEM, Resident>::value)
+            if (p->spread && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
         switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, 0, st, t, s, p->d_flag_scratch, flag); break;
             FOR_EACH_R(CASE)

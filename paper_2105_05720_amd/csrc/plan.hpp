@@ -37,6 +37,7 @@ constexpr uint64_t kWriteThroughMaxStoreBytes = 288ull << 20;
 // but 67.7 / 61.6 at 8.4 M (370 MB), 88.1 / 80.3 at 11.2 M, 151 / 145 at 21 M; R = 16 at 11.2 M (673 MB) 120.7 / 111.4;
 // eight fp32 slices at 8.4 M (504 MB) 92.2 / 83.7.
 constexpr uint64_t kListWriteThroughMaxBytes = 300ull << 20;
+inline uint64_t step_footprint(uint64_t numel, int R, bool grad_f32) { return numel * ((grad_f32 ? 4u : 2u) * (uint64_t)R + 12u + 14u); }
 constexpr uint64_t kAdamStoreBytes = 14;                           // per element: w', m', v', w16
 inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored, bool list)
 {
@@ -58,6 +59,24 @@ constexpr uint64_t kLambThroughMaxStoreBytes = 176ull << 20;
 // 81.1 / 80.3 at 11.2 M, 389.2 / 385.7 / 382.9 at 56 M.  LAMB's first sweep adds up its chunk behind a barrier and cannot
 // spare the waves (42 M elements: 357 us for both phases, 382 us with ten waves per compute unit).
 constexpr unsigned kSpreadLds = 24000;
+
+// One tensor that does not fit the Infinity Cache and stays below the ordered schedule: single-wave workgroups of one
+// group per lane, in grid order, and so few of them per compute unit (LDS that nobody uses again) that the addresses in
+// flight are a narrow window that moves through all streams.  Without a table a workgroup starts its loads at once, so a
+// small one costs nothing.  How few depends on what a wave has in flight, 4 (bytes of a slice element x R + 12) per lane:
+// the reservation that measured best was 10000 bytes at R = 1, 11600 at 2, 13312 at 4, 16000 at 8 and for four fp32
+// slices; short launches want more waves (5 M elements, R = 8: 32.3 us with 10000, 33.7 with 16000).  us, 128-thread
+// workgroups per 1024 elements / this: R = 8 33.1 / 32.3 at 5 M elements, 60.4 / 57.3 at 8.4 M, 172 / 165 at 25 M, 419 /
+// 393 at 60 M; R = 1 139 / 133 at 30 M; R = 2 80.8 / 75.4 at 16 M; R = 16 101 / 97 at 10 M, 377 / 378 at 40 M; four fp32
+// slices in place 90.8 / 82.5 at 12.3 M, 283 / 255 at 40 M.
+constexpr int kFlatBlock = 64;
+constexpr uint32_t kFlatPiece = kFlatBlock * 4;
+constexpr uint64_t kFlatShortBytes = 300ull << 20, kFlatMaxElems = 1ull << 33;      // 2^31 threads: a launch has less than 2^32
+inline unsigned flat_lds(uint64_t footprint, uint32_t slice_bytes)        // slice_bytes: of all slices, per element
+{
+    const unsigned lds = 4400u + 400u * (slice_bytes + 12u);
+    return footprint < kFlatShortBytes ? 10000u : lds < 16000u ? lds : 16000u;
+}
 
 
 // Records the message for cc_last_error() on this thread and returns the code.

@@ -203,6 +203,33 @@ def test_chunks_in_runs(fn, ofn, numels, R, why):
     sh.destroy()
 
 
+@pytest.mark.parametrize("n,R,grad_dtype,policy", [
+    (3615780 + 256, 16, torch.float16, cc.CC_CACHE_AUTO),              # just over 200 MiB of buffers: written through, the short-launch shape
+    (5423671 + 255, 16, torch.float16, cc.CC_CACHE_AUTO),              # just over 300 MiB, a piece that is one element short of full
+    (1024 * 7000 + 1, 1, torch.float32, cc.CC_CACHE_STREAMING),        # fp32 slices, non-temporal stores, a last piece of one element
+])
+def test_one_tensor_in_single_wave_pieces(n, R, grad_dtype, policy):
+    """One tensor beyond the Infinity Cache runs in 64-thread workgroups of 256 elements; its bits are those of the
+    512-thread workgroups on the same plan, under both overflow modes' arithmetic (guard in place, whole-step skip)."""
+    for in_place in (False, True):
+        sh = Shard([n], [0.01], R, align_elems=8, unfused=False, grad_dtype=grad_dtype, cache_policy=policy, in_place=in_place)
+        assert cc.cc_plan_layout(sh.plans[0])[0] == 1024
+        outs = []
+        for chunk in (0, 4096):
+            cc.cc_plan_set_chunk_elems(sh.plans[0], chunk)
+            seeded_state(sh, 6)
+            seeded_grads(sh, 60, 1e-3)
+            sh.grads[0][n - 1] = float("inf")
+            sh.run(cc.cc_fused_adam_step, cc.Hyper(step=5, skip_mode=1 if in_place else 0))
+            torch.cuda.synchronize()
+            assert int(sh.flag.item()) == 1
+            i = sh.out_index
+            outs.append([x[i].clone() for x in (sh.w, sh.m, sh.v, sh.w16)])
+        for a, b in zip(*outs):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        sh.destroy()
+
+
 @pytest.mark.parametrize("fn,ofn", [(cc.cc_fused_adam_step, oracle.adam_step), (cc.cc_fused_lamb_step, oracle.lamb_step),
                                     (cc.cc_unfused_adam_step, oracle.adam_step)])
 def test_both_forms_of_the_chunk_table(fn, ofn):
