@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2105_05720_amd import binding as cc
 from paper_2105_05720_amd import workloads as W
@@ -35,6 +36,25 @@ def test_struct_layout_matches_header():
     assert C.sizeof(cc.cc_tensor) == 8 + 7 * 8 + 16 * 8 + 8      # numel, 7 pointers, 16 gradient pointers, float + pad
     assert cc.cc_tensor.weight_decay.offset == 192
     assert C.sizeof(cc.cc_hparams) == 36
+
+
+@pytest.mark.parametrize("odd", [None, "address", "none", "wide", "numpy"])
+def test_packed_arguments_are_the_ctypes_structures(odd):
+    """The step calls pack their arguments into bytes: the same bytes as the ctypes structures, whatever the values."""
+    x = [torch.zeros(8) for _ in range(9)]
+    buf = {None: x[0], "address": 0x7f0000001230, "none": None, "wide": x[0], "numpy": x[0]}[odd]
+    t = cc.Tensor(numel=(1 << 64) + 5 if odd == "wide" else 1 << 40, w_in=buf, m_in=x[1], v_in=x[2], w_out=x[3], m_out=x[4], v_out=x[5],
+                  w16_out=x[6], grad=(x + x + [buf])[:19], weight_decay=1e39 if odd == "wide" else 0.01)
+    assert cc._tensor_bytes(t) == bytes(cc._c_tensor(t))
+    hp = cc.Hyper(lr=1e39 if odd == "wide" else 0.1, step=np.int64(7) if odd == "numpy" else (1 << 31) if odd == "wide" else 3, loss_scale=1024)
+    assert cc._hp_bytes(hp) == bytes(hp.to_c()) == cc._hp_bytes(hp.to_c())
+    e = (x[:3] + [buf] * 15, x[4], x[5], x[6], -1 if odd == "wide" else 1 << 40, 3072, 0.1, 2 ** 64 - 1, 1000)
+    assert cc._epilogue_bytes(*e) == bytes(cc._epilogue(*e))
+    for bad in ("a", 1.5, None):                                   # what the structures refuse stays refused
+        with pytest.raises(TypeError):
+            cc._hp_bytes(cc.Hyper(step=bad))
+        with pytest.raises(TypeError):
+            cc._tensor_bytes(cc.Tensor(**{**vars(t), "numel": bad}))
 
 
 def brute_table(numels, ce):
