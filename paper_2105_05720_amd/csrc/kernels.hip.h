@@ -376,6 +376,15 @@ struct FlagCount {
 //   void single(uint32_t j);                       one element, scalar accesses (ragged end of a tensor)
 // A sweep is two groups BLOCK*kPack elements apart.  A full sweep issues the loads of both groups, then computes
 // and stores; the ragged end of a chunk (only a tensor's last chunk has one) falls back group by group.
+// The last len % kPack elements of a chunk: one lane each, so that they cost one trip to memory together (one lane going
+// through three of them cost three).
+template <class Op>
+__device__ __forceinline__ void ragged_end(Op &op, uint32_t len)
+{
+    constexpr uint32_t kMask = Op::kPack - 1;
+    if (threadIdx.x < (len & kMask)) op.single((len & ~kMask) + threadIdx.x);
+}
+
 template <int BLOCK, class Op, int GROUPS = 2>
 __device__ __forceinline__ void stream_chunk(Op &op, uint32_t len)
 {
@@ -395,45 +404,81 @@ __device__ __forceinline__ void stream_chunk(Op &op, uint32_t len)
             op.store(x[g], s0 + g * kGroup + lane_e);
         }
     }
-    for (uint32_t e = s0 + lane_e; e < len; e += kGroup) {
-        if (e + kLanePack <= len) {
-            typename Op::Regs a;
-            op.load(a, e);
-            op.compute(a);
-            op.store(a, e);
-        } else {
-            for (uint32_t j = e; j < len; ++j) op.single(j);
-        }
+    for (uint32_t e = s0 + lane_e; e + kLanePack <= len; e += kGroup) {
+        typename Op::Regs a;
+        op.load(a, e);
+        op.compute(a);
+        op.store(a, e);
     }
+    ragged_end(op, len);
 }
 
-// One workgroup per chunk, for an Op that raises the flag.  `fc` has arrived already (first act of the kernel).  When
-// the chunk is exactly one sweep (the launch shapes the plans use), the stages of the count are placed where their
-// results are free: the slot level behind the issue of the loads, the top level behind the sums, the reports behind
-// the stores.  The waves of a workgroup never wait for each other here.
+// A chunk of at most one sweep (the launch shapes the plans use), in the same steps whether it is full or not: a lane
+// past the end loads the chunk's last whole pack once more, so that all loads are issued together and without branches,
+// and stores nothing.  (Every tensor ends in a short chunk and most tensors of a list are one; group by group they cost a
+// trip to memory per group, with the flag's three behind them.)  Needs at least one whole pack.
+template <int BLOCK, int GROUPS, class Op>
+struct Sweep {
+    static constexpr uint32_t kGroup = BLOCK * Op::kPack;
+    typename Op::Regs x[GROUPS];
+    __device__ __forceinline__ static uint32_t first(int g) { return g * kGroup + threadIdx.x * Op::kPack; }
+    __device__ __forceinline__ static bool mine(int g, uint32_t len) { return first(g) + Op::kPack <= len; }
+    __device__ __forceinline__ void load(const Op &op, uint32_t len)
+    {
+        const uint32_t last = (len & ~(Op::kPack - 1u)) - Op::kPack;
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) op.load(x[g], first(g) < last ? first(g) : last);
+    }
+    __device__ __forceinline__ void update_and_store(Op &op, uint32_t len)
+    {
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g)
+            if (mine(g, len)) { op.update(x[g]); op.store(x[g], first(g)); }
+        ragged_end(op, len);
+    }
+};
+
+// One workgroup per chunk, for an Op that raises the flag.  `fc` has arrived already (first act of the kernel).  The
+// stages of the count are placed where their results are free: the slot level behind the issue of the loads, the top
+// level behind the sums, the reports behind the stores.  The waves of a workgroup never wait for each other here.
 template <int BLOCK, int GROUPS, class Op>
 __device__ __forceinline__ void sweep_and_publish(Op &op, uint32_t len, FlagCount<BLOCK> &fc, FlagScratch *fs, int32_t *flag)
 {
-    constexpr uint32_t kGroup = BLOCK * Op::kPack;
-    if (len == GROUPS * kGroup) {
-        const uint32_t lane_e = threadIdx.x * Op::kPack;
-        typename Op::Regs x[GROUPS];
-#pragma unroll
-        for (int g = 0; g < GROUPS; ++g) op.load(x[g], g * kGroup + lane_e);
+    typedef Sweep<BLOCK, GROUPS, Op> S;
+    if (len >= Op::kPack && len <= GROUPS * S::kGroup) {
+        S sw;
+        sw.load(op, len);
         __builtin_amdgcn_sched_barrier(0);
         fc.slot_level(fs);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < GROUPS; ++g) op.reduce(x[g]);
+        for (int g = 0; g < GROUPS; ++g) op.reduce(sw.x[g]);
         fc.top_level(fs, flag);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int g = 0; g < GROUPS; ++g) { op.update(x[g]); op.store(x[g], g * kGroup + lane_e); }
+        sw.update_and_store(op, len);
         __builtin_amdgcn_sched_barrier(0);
         fc.finish(op.bad, fs, flag);
     } else {
         stream_chunk<BLOCK, Op, GROUPS>(op, len);
         fc.settle(op.bad, fs, flag);
+    }
+}
+
+// One workgroup per chunk, for an Op whose loads need nothing that the rest of the kernel waits for: they are issued
+// first, then ready() finds out what the arithmetic needs, or returns false to leave without a store.
+template <int BLOCK, int GROUPS, class Op, class Ready>
+__device__ __forceinline__ void sweep_when_ready(Op &op, uint32_t len, Ready ready)
+{
+    typedef Sweep<BLOCK, GROUPS, Op> S;
+    if (len >= Op::kPack && len <= GROUPS * S::kGroup) {
+        S sw;
+        sw.load(op, len);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!ready()) return;
+        sw.update_and_store(op, len);
+    } else {
+        if (!ready()) return;
+        stream_chunk<BLOCK, Op, GROUPS>(op, len);
     }
 }
 
@@ -1095,14 +1140,20 @@ struct LambPhase2Op {
     float wd, step;
     struct Regs { float w[4], m[4], v[4]; };
 
-    __device__ __forceinline__ void init(const DevTensor *t, uint64_t base, const StepScalars &sc, float ratio)
+    // Everything but the ratio: the loads need none.
+    __device__ __forceinline__ void init(const DevTensor *t, uint64_t base, const StepScalars &sc)
     {
         w_in = chunk_base((const void *)t->w_in, base * 4);
         m_new = chunk_base((const void *)t->m_out, base * 4); v_new = chunk_base((const void *)t->v_out, base * 4);
         w_out = chunk_base((void *)t->w_out, base * 4); w16 = chunk_base((void *)t->w16, base * 2);
         s = sc;
         wd = t->wd;
-        step = sc.lr * ratio;
+    }
+    // ... formed from the tensor's sums of w^2 and u^2.
+    __device__ __forceinline__ void scale(double sw, double su)
+    {
+        const float ratio = (sw > 0.0 && su > 0.0) ? (float)(__builtin_sqrt(sw) / __builtin_sqrt(su)) : 1.0f;
+        step = s.lr * ratio;
     }
     __device__ __forceinline__ void load(Regs &x, uint32_t e) const
     {
@@ -1112,11 +1163,12 @@ struct LambPhase2Op {
     {
         return __builtin_fmaf(-step, direction<0>(w, wd, m, v, s), w);
     }
-    __device__ __forceinline__ void compute(Regs &x)
+    __device__ __forceinline__ void update(Regs &x) const
     {
 #pragma unroll
         for (int k = 0; k < 4; ++k) x.w[k] = one(x.w[k], x.m[k], x.v[k]);
     }
+    __device__ __forceinline__ void compute(Regs &x) const { update(x); }
     __device__ __forceinline__ void store(const Regs &x, uint32_t e) const
     {
         st_f32x4<Mem>(w_out, e * 4, x.w);
@@ -1137,13 +1189,14 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_kernel(const DevTensor *__r
                                                             const double *__restrict__ sums,
                                                             const int32_t *__restrict__ flag)
 {
-    if (*flag != 0) return;              // whole-step skip: w and w16 stay as they were
     const Where wh = locate(tensors, chunks, s);
-    const double sw = sums[2 * (uint64_t)wh.tensor], su = sums[2 * (uint64_t)wh.tensor + 1];
-    const float ratio = (sw > 0.0 && su > 0.0) ? (float)(__builtin_sqrt(sw) / __builtin_sqrt(su)) : 1.0f;
     LambPhase2Op<EMIT16, Mem> op;
-    op.init(wh.t, wh.base, s, ratio);
-    stream_chunk<BLOCK>(op, wh.len);
+    op.init(wh.t, wh.base, s);
+    sweep_when_ready<BLOCK, 2>(op, wh.len, [&] {
+        if (*flag != 0) return false;    // whole-step skip: w and w16 stay as they were
+        op.scale(sums[2 * (uint64_t)wh.tensor], sums[2 * (uint64_t)wh.tensor + 1]);
+        return true;
+    });
 }
 
 // Phase 2 of a plan whose tensors have few chunks each, with the second level folded in: every workgroup adds up the
@@ -1158,17 +1211,20 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
                                                                        const int32_t *__restrict__ flag)
 {
     const Where wh = locate(tensors, chunks, s);
-    double sw, su;
-    tensor_sums<BLOCK>(partials + 2 * (uint64_t)wh.t->first_chunk, wh.t->num_chunks, sw, su);
-    if (wh.index == 0 && threadIdx.x == 0) {
-        sums[2 * (uint64_t)wh.tensor] = sw;
-        sums[2 * (uint64_t)wh.tensor + 1] = su;
-    }
-    if (*flag != 0) return;              // whole-step skip: w and w16 stay as they were
-    const float ratio = (sw > 0.0 && su > 0.0) ? (float)(__builtin_sqrt(sw) / __builtin_sqrt(su)) : 1.0f;
     LambPhase2Op<EMIT16, Mem> op;
-    op.init(wh.t, wh.base, s, ratio);
-    stream_chunk<BLOCK>(op, wh.len);
+    op.init(wh.t, wh.base, s);
+    sweep_when_ready<BLOCK, 2>(op, wh.len, [&] {
+        const int32_t overflowed = *flag;
+        double sw, su;
+        tensor_sums<BLOCK>(partials + 2 * (uint64_t)wh.t->first_chunk, wh.t->num_chunks, sw, su);
+        if (wh.index == 0 && threadIdx.x == 0) {
+            sums[2 * (uint64_t)wh.tensor] = sw;
+            sums[2 * (uint64_t)wh.tensor + 1] = su;
+        }
+        if (overflowed != 0) return false;       // whole-step skip: w and w16 stay as they were
+        op.scale(sw, su);
+        return true;
+    });
 }
 
 template <bool EMIT16, int BLOCK>
@@ -1183,9 +1239,8 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_ordered_kernel(const DevTen
     Op a, b;
     auto bind = [&](Op &op, uint32_t entry) {
         const Where wh = locate_at(tensors, chunks, entry, s.chunk_elems);
-        const double sw = sums[2 * (uint64_t)wh.tensor], su = sums[2 * (uint64_t)wh.tensor + 1];
-        const float ratio = (sw > 0.0 && su > 0.0) ? (float)(__builtin_sqrt(sw) / __builtin_sqrt(su)) : 1.0f;
-        op.init(wh.t, wh.base, s, ratio);
+        op.init(wh.t, wh.base, s);
+        op.scale(sums[2 * (uint64_t)wh.tensor], sums[2 * (uint64_t)wh.tensor + 1]);
         return wh;
     };
     ordered_stream<BLOCK, 2>(a, b, bind, nfull, nchunks, span, q);

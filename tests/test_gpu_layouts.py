@@ -203,6 +203,14 @@ def test_chunks_in_runs(fn, ofn, numels, R, why):
     sh.destroy()
 
 
+@pytest.mark.parametrize("fn,ofn", [(cc.cc_fused_adam_step, oracle.adam_step), (cc.cc_fused_lamb_step, oracle.lamb_step)])
+@pytest.mark.parametrize("numels", [[1, 2, 3, 4, 5, 7, 8, 511, 512, 513, 515, 516, 1023, 1024, 1025, 1026, 1028, 2047], [1], [3], [6], [1022]])
+def test_short_chunks(fn, ofn, numels):
+    """Chunks shorter than a sweep: no whole pack of four, lanes and whole groups past the end, one to three elements
+    behind the last pack; as a list and as one tensor, every element against the oracle."""
+    run_shape(fn, ofn, 1024, cc.CC_CACHE_STREAMING, numels=numels, steps=2)
+
+
 @pytest.mark.parametrize("n,R,grad_dtype,policy", [
     (3615780 + 256, 16, torch.float16, cc.CC_CACHE_AUTO),              # just over 200 MiB of buffers: written through, the short-launch shape
     (5423671 + 255, 16, torch.float16, cc.CC_CACHE_AUTO),              # just over 300 MiB, a piece that is one element short of full
