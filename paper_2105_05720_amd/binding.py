@@ -309,7 +309,8 @@ def cc_plan_info(plan: Plan):
 # one go (native sizes and alignment, as in cc_hparams, cc_tensor and cc_epilogue) instead of filling ctypes structures
 # field by field: 0.3 against 0.8 us for the hyper-parameters, 1.3 against 2.5 us for a tensor with two slices, and 0.2 us
 # less in the call itself.  What does not pack (an integer address, a value out of its field's range, a wrong type) goes
-# through the ctypes structures, whose conversions and errors are the definition.
+# through the ctypes structures, whose conversions and errors are the definition; so does a hyper-parameter object that is
+# not exactly a Hyper, because its to_c() is what counts.
 _PACK_HP = struct.Struct("5f4i").pack
 _PACK_TENSOR = struct.Struct("Q7Q16Qf4x").pack
 _PACK_EPILOGUE = struct.Struct("QQIi16QQQQf4xQ").pack
@@ -317,6 +318,8 @@ _NO_PTRS = (0,) * CC_MAX_R
 
 
 def _hp_bytes(hp) -> bytes:
+    if type(hp) is not Hyper:                 # a cc_hparams, or something that says with to_c() what it stands for
+        return bytes(_hp(hp))
     try:
         return _PACK_HP(hp.lr, hp.beta1, hp.beta2, hp.eps, hp.loss_scale, hp.step, hp.grad_average, hp.adam_mode, hp.skip_mode)
     except (struct.error, OverflowError, TypeError):

@@ -57,6 +57,27 @@ def test_packed_arguments_are_the_ctypes_structures(odd):
             cc._tensor_bytes(cc.Tensor(**{**vars(t), "numel": bad}))
 
 
+def test_hyper_parameters_of_another_class_go_through_to_c():
+    """The step calls take a cc_hparams or anything with to_c(), and it is to_c() that counts: an object that has nothing
+    else, and a subclass of Hyper that overrides it.  Attributes alone are not accepted."""
+    class Scheduled(cc.Hyper):
+        def to_c(self):
+            return cc.Hyper(lr=2 * self.lr, step=self.step).to_c()
+
+    class OnlyToC:
+        def to_c(self):
+            return cc.Hyper(lr=0.2, step=5).to_c()
+
+    class Attributes:
+        lr, beta1, beta2, eps, loss_scale, step, grad_average, adam_mode, skip_mode = 0.2, 0.9, 0.999, 1e-6, 1.0, 5, 0, 1, 0
+
+    want = bytes(cc.Hyper(lr=0.2, step=5).to_c())
+    for hp in (Scheduled(lr=0.1, step=5), OnlyToC(), cc.Hyper(lr=0.2, step=5).to_c(), cc.Hyper(lr=0.2, step=5)):
+        assert cc._hp_bytes(hp) == want
+    with pytest.raises(AttributeError):
+        cc._hp_bytes(Attributes())
+
+
 def brute_table(numels, ce):
     out = []
     for t, n in enumerate(numels):
