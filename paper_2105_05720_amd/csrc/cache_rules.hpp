@@ -1,0 +1,64 @@
+// Which cache policy each kernel family of a plan uses.  No HIP in here: the host can run it as well.
+#pragma once
+
+#include <stdint.h>
+
+#include "ccfused.h"
+
+namespace ccf {
+
+// AUTO cache policy: plain loads and write-through stores instead of non-temporal accesses while the step's buffers (R
+// gradient slices, both copies of w, m, v and of the fp16 weights) total between these bounds, i.e. fit the 256 MB
+// Infinity Cache.  Size sweep at R = 8, us per step: 6.2 against 7.9 at 2^20 elements (44 MB), 14.9 against 15.8 at 2^21
+// (88 MB), 27.6 against 29.6 at 2^22 (176 MB), but 68.1 against 60.2 at 2^23 (352 MB).  Below 2^17 elements the
+// non-temporal accesses are the faster ones by 1-6 % (LAMB at 2^14: 7.7 against 8.0 us), hence the lower bound.
+constexpr uint64_t kResidentMinBytes = 4ull << 20, kResidentMaxBytes = 200ull << 20;
+// ... and from there on non-temporal loads with write-through stores while one Adam launch stores less than this (see
+// WriteThrough): what it writes then about fits the Infinity Cache.  One tensor at R = 8: 141 against 147 us at 20 Mi
+// elements, 160 against 157 us at 22 Mi.
+constexpr uint64_t kWriteThroughMaxStoreBytes = 288ull << 20;
+// A list of tensors goes back to non-temporal stores earlier, once the step's buffers exceed this.  BERT-Large list cut
+// into slices, three shards in turn, written through / non-temporal, us: 35.9 / 39.6 at 5.3 M elements (R = 8: 231 MB),
+// but 67.7 / 61.6 at 8.4 M (370 MB), 88.1 / 80.3 at 11.2 M, 151 / 145 at 21 M; R = 16 at 11.2 M (673 MB) 120.7 / 111.4;
+// eight fp32 slices at 8.4 M (504 MB) 92.2 / 83.7.
+constexpr uint64_t kListWriteThroughMaxBytes = 300ull << 20;
+inline uint64_t step_footprint(uint64_t numel, int R, bool grad_f32) { return numel * ((grad_f32 ? 4u : 2u) * (uint64_t)R + 12u + 14u); }
+constexpr uint64_t kAdamStoreBytes = 14, kLambStoreBytes = 8;      // per element: w', m', v', w16 / m', v' (LAMB's first sweep)
+inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored, bool list)
+{
+    if (footprint < kResidentMinBytes) return CC_CACHE_STREAMING;
+    if (footprint < kResidentMaxBytes) return CC_CACHE_RESIDENT;
+    return (list ? footprint < kListWriteThroughMaxBytes : stored < kWriteThroughMaxStoreBytes) ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
+}
+// LAMB's two sweeps want different stores once the shard has outgrown the Infinity Cache: written through in the first,
+// whose m' and v' the second reads again, and in the second, whose output nobody reads before the next step,
+// non-temporal from this many stored bytes per step on.  BERT-Large list in slices, R = 8, us with write-through in both /
+// write-through and non-temporal: 51.1 / 53.7 at 5.3 M elements, 100.7 / 102.7 at 11.2 M, but 127.9 / 124.3 at 14 M,
+// 194 / 180 at 21 M, 379 / 357 at 42 M (non-temporal in both: 372).
+constexpr uint64_t kLambThroughMaxStoreBytes = 176ull << 20;
+
+// What a plan's small-chunk kernels use, by kernel family (cc_cache_policy values).
+struct CachePolicies {
+    int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step; what cc_plan_layout reports
+    int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep
+    int32_t lamb2 = CC_CACHE_STREAMING;         // ... and its second
+    int32_t unfused = CC_CACHE_STREAMING;       // the unfused pipelines: reduce, Adam from the sum, cast
+    int32_t unfused_lamb = CC_CACHE_STREAMING;  // ... and LAMB's two sweeps in them, by the bytes that its first one stores
+};
+inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool grad_f32, bool list)
+{
+    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked, asked, asked};
+    const uint64_t footprint = step_footprint(numel, R, grad_f32), stored = numel * kAdamStoreBytes;
+    CachePolicies c;
+    c.adam = auto_cache_policy(footprint, stored, list);
+    c.unfused = auto_cache_policy(footprint, stored, false);
+    c.unfused_lamb = auto_cache_policy(footprint, numel * kLambStoreBytes, false);
+    if (footprint < kResidentMaxBytes) c.lamb1 = c.lamb2 = c.adam;
+    else {
+        c.lamb1 = CC_CACHE_WRITE_THROUGH;
+        c.lamb2 = stored < kLambThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
+    }
+    return c;
+}
+
+}  // namespace ccf

@@ -124,20 +124,9 @@ void resolve_schedule(cc_plan *p)
     else if (p->schedule == CC_SCHEDULE_PER_CHUNK) p->ordered = false;
     else p->ordered = L.chunks >= kOrderedMinChunksPerCu * (int64_t)p->cus && !(p->grad_f32 && p->R > kOrderedMaxF32Slices);
     if (L.chunk_elems != kDefaultChunkElems || L.chunks == 0) p->ordered = false;
-    const uint64_t footprint = step_footprint(p->numel, p->R, p->grad_f32);
-    if (p->cache_policy != CC_CACHE_AUTO) p->mem = p->mem_lamb = p->mem_lamb2 = p->mem_unfused = p->cache_policy;
-    else {
-        const uint64_t stored = p->numel * kAdamStoreBytes;
-        p->mem = auto_cache_policy(footprint, stored, p->single < 0);
-        p->mem_unfused = auto_cache_policy(footprint, stored, false);
-        if (footprint < kResidentMaxBytes) p->mem_lamb = p->mem_lamb2 = p->mem;
-        else {
-            p->mem_lamb = CC_CACHE_WRITE_THROUGH;
-            p->mem_lamb2 = stored < kLambThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
-        }
-    }
-    p->spread = footprint >= kResidentMaxBytes && L.block == kSmallBlock && !p->ordered;
-    if (L.block != kSmallBlock || p->ordered) p->mem = p->mem_lamb = p->mem_lamb2 = p->mem_unfused = CC_CACHE_STREAMING;
+    const bool small = L.block == kSmallBlock && !p->ordered;
+    p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, p->single < 0) : CachePolicies{};
+    p->spread = small && step_footprint(p->numel, p->R, p->grad_f32) >= kResidentMaxBytes;
 }
 
 void free_layout(Layout &L)
@@ -420,7 +409,7 @@ int cc_plan_layout(const cc_plan *p, int32_t *chunk_elems, int32_t *block_thread
     if (!p) return fail(CC_ERR_NULL, "cc_plan_layout: plan is NULL");
     if (chunk_elems) *chunk_elems = p->lay().chunk_elems;
     if (block_threads) *block_threads = p->lay().block;
-    if (cache_policy) *cache_policy = p->mem;
+    if (cache_policy) *cache_policy = p->mem.adam;
     return CC_OK;
 }
 

@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <vector>
 
+#include "cache_rules.hpp"
 #include "ccfused.h"
 #include "kernels.hip.h"
 
@@ -22,35 +23,6 @@ constexpr int kBigBlock = 512, kSmallBlock = 128;
 constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-chunk layout keeps a descriptor per chunk (224 B each)
 constexpr int kOrderedMaxF32Slices = 8;           // fp32 slices: the ordered schedule wins up to 8 (config-2 list: 3.18 against 3.41 ms), at 16 two chunks spill
 constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per compute unit a plan keeps one workgroup per chunk
-// AUTO cache policy: plain loads and write-through stores instead of non-temporal accesses while the step's buffers (R
-// gradient slices, both copies of w, m, v and of the fp16 weights) total between these bounds, i.e. fit the 256 MB
-// Infinity Cache.  Size sweep at R = 8, us per step: 6.2 against 7.9 at 2^20 elements (44 MB), 14.9 against 15.8 at 2^21
-// (88 MB), 27.6 against 29.6 at 2^22 (176 MB), but 68.1 against 60.2 at 2^23 (352 MB).  Below 2^17 elements the
-// non-temporal accesses are the faster ones by 1-6 % (LAMB at 2^14: 7.7 against 8.0 us), hence the lower bound.
-constexpr uint64_t kResidentMinBytes = 4ull << 20, kResidentMaxBytes = 200ull << 20;
-// ... and from there on non-temporal loads with write-through stores while one Adam launch stores less than this (see
-// WriteThrough): what it writes then about fits the Infinity Cache.  One tensor at R = 8: 141 against 147 us at 20 Mi
-// elements, 160 against 157 us at 22 Mi.
-constexpr uint64_t kWriteThroughMaxStoreBytes = 288ull << 20;
-// A list of tensors goes back to non-temporal stores earlier, once the step's buffers exceed this.  BERT-Large list cut
-// into slices, three shards in turn, written through / non-temporal, us: 35.9 / 39.6 at 5.3 M elements (R = 8: 231 MB),
-// but 67.7 / 61.6 at 8.4 M (370 MB), 88.1 / 80.3 at 11.2 M, 151 / 145 at 21 M; R = 16 at 11.2 M (673 MB) 120.7 / 111.4;
-// eight fp32 slices at 8.4 M (504 MB) 92.2 / 83.7.
-constexpr uint64_t kListWriteThroughMaxBytes = 300ull << 20;
-inline uint64_t step_footprint(uint64_t numel, int R, bool grad_f32) { return numel * ((grad_f32 ? 4u : 2u) * (uint64_t)R + 12u + 14u); }
-constexpr uint64_t kAdamStoreBytes = 14;                           // per element: w', m', v', w16
-inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored, bool list)
-{
-    if (footprint < kResidentMinBytes) return CC_CACHE_STREAMING;
-    if (footprint < kResidentMaxBytes) return CC_CACHE_RESIDENT;
-    return (list ? footprint < kListWriteThroughMaxBytes : stored < kWriteThroughMaxStoreBytes) ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
-}
-// LAMB's two sweeps want different stores once the shard has outgrown the Infinity Cache: written through in the first,
-// whose m' and v' the second reads again, and in the second, whose output nobody reads before the next step,
-// non-temporal from this many stored bytes per step on.  BERT-Large list in slices, R = 8, us with write-through in both /
-// write-through and non-temporal: 51.1 / 53.7 at 5.3 M elements, 100.7 / 102.7 at 11.2 M, but 127.9 / 124.3 at 14 M,
-// 194 / 180 at 21 M, 379 / 357 at 42 M (non-temporal in both: 372).
-constexpr uint64_t kLambThroughMaxStoreBytes = 176ull << 20;
 
 // Small chunks of a shard that does not fit the Infinity Cache (step's buffers of kResidentMaxBytes and more) are bound
 // by HBM, and what the addresses in flight look like decides: every XCD takes runs of 32 chunks (piece_in_runs), and the
@@ -119,10 +91,7 @@ struct cc_plan {
     bool ordered = false;                   // large shards: persistent workgroups take chunks in table order
     int32_t schedule = CC_SCHEDULE_AUTO;    // what the caller asked for
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
-    int32_t mem = CC_CACHE_STREAMING;       // the policy in use (other than STREAMING: small-chunk layouts only)
-    int32_t mem_lamb = CC_CACHE_STREAMING;  // ... by LAMB's first sweep
-    int32_t mem_lamb2 = CC_CACHE_STREAMING; // ... and by its second
-    int32_t mem_unfused = CC_CACHE_STREAMING; // by the unfused pipelines, which read again what they stored
+    ccf::CachePolicies mem;                 // the policies in use (other than STREAMING: small-chunk layouts only)
     bool spread = false;                    // small chunks of a shard bound by HBM (see kSpreadLds)
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
     int32_t cus = 0;                        // compute units of the device the plan was created on
@@ -157,7 +126,7 @@ inline unsigned ordered_grid(const cc_plan *p)
 
 // Every per-chunk streaming kernel exists for two workgroup sizes, and the small one for every cache policy; the
 // plan's layout and policy pick one.  The statement given sees BLK (int) and MEM (Streaming, Resident or WriteThrough).
-#define BY_BLOCK(p, ...) BY_BLOCK_MEM(p, (p)->mem, __VA_ARGS__)
+#define BY_BLOCK(p, ...) BY_BLOCK_MEM(p, (p)->mem.adam, __VA_ARGS__)
 #define BY_BLOCK_MEM(p, mem_, ...)                                                          \
     do {                                                                                    \
         if ((p)->lay().block == kBigBlock) { constexpr int BLK = kBigBlock; typedef Streaming MEM; __VA_ARGS__; }        \

@@ -1,0 +1,80 @@
+"""Which cache policy each kernel family of a plan uses (csrc/cache_rules.hpp), compiled for the host: the bounds that the
+header states, one element below and at each of them."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2105_05720_amd import binding as cc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+AUTO, STREAM, RESIDENT, THROUGH = cc.CC_CACHE_AUTO, cc.CC_CACHE_STREAMING, cc.CC_CACHE_RESIDENT, cc.CC_CACHE_WRITE_THROUGH
+MIB = 1 << 20
+
+MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "cache_rules.hpp"
+
+int main(int argc, char **argv)
+{
+    for (int i = 1; i + 4 < argc; i += 5) {
+        const ccf::CachePolicies c = ccf::cache_policies(atoi(argv[i]), strtoull(argv[i + 1], nullptr, 10), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]) != 0);
+        printf("%d %d %d %d %d\n", c.adam, c.lamb1, c.lamb2, c.unfused, c.unfused_lamb);
+    }
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def policies(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(MAIN)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
+
+    def ask(asked, numel, R, f32, is_list):
+        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, is_list)], capture_output=True, text=True, timeout=60)
+        return tuple(int(x) for x in out.stdout.split())
+    return ask
+
+
+def below_and_at(nbytes, per_element):
+    n = -(-nbytes // per_element)
+    return n - 1, n
+
+
+@pytest.mark.parametrize("R,f32", [(1, False), (8, False), (16, False), (4, True)])
+@pytest.mark.parametrize("is_list", [False, True])
+def test_automatic_policies_at_their_bounds(policies, R, f32, is_list):
+    per = (4 if f32 else 2) * R + 26
+    below, at = below_and_at(4 * MIB, per)
+    assert policies(AUTO, below, R, f32, is_list) == (STREAM,) * 5
+    assert policies(AUTO, at, R, f32, is_list) == (RESIDENT,) * 5
+    below, at = below_and_at(200 * MIB, per)
+    assert policies(AUTO, below, R, f32, is_list) == (RESIDENT,) * 5
+    assert policies(AUTO, at, R, f32, is_list) == (THROUGH,) * 5
+    below, at = below_and_at(300 * MIB, per) if is_list else below_and_at(288 * MIB, 14)
+    assert [policies(AUTO, n, R, f32, is_list)[0] for n in (below, at)] == [THROUGH, STREAM]
+    # fused LAMB writes its first sweep through from 200 MiB of buffers on, its second until 176 MiB are stored per step
+    below, at = below_and_at(176 * MIB, 14)
+    assert [policies(AUTO, n, R, f32, is_list)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (THROUGH, STREAM)]
+    assert policies(AUTO, 1 << 30, R, f32, is_list)[1:3] == (THROUGH, STREAM)
+
+
+@pytest.mark.parametrize("R,f32", [(1, False), (8, False), (16, False), (4, True)])
+@pytest.mark.parametrize("is_list", [False, True])
+def test_the_unfused_pipelines_go_by_what_one_of_their_launches_stores(policies, R, f32, is_list):
+    """Write-through from 200 MiB of buffers while a launch stores less than 288 MiB: 14 bytes per element in Adam's update,
+    8 in LAMB's first sweep, so the two pipelines change at 20.6 and 36 Mi elements, list or not."""
+    below, at = below_and_at(288 * MIB, 14)
+    assert [policies(AUTO, n, R, f32, is_list)[3:] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, THROUGH)]
+    below, at = below_and_at(288 * MIB, 8)
+    assert [policies(AUTO, n, R, f32, is_list)[3:] for n in (below, at)] == [(STREAM, THROUGH), (STREAM, STREAM)]
+
+
+def test_a_policy_that_was_asked_for_holds_everywhere(policies):
+    for p in (STREAM, RESIDENT, THROUGH):
+        for n in (100, 1 << 22, 1 << 25):
+            assert policies(p, n, 8, False, True) == (p,) * 5
