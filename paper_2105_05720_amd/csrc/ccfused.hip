@@ -805,6 +805,7 @@ constexpr int kEpilogueBlock = 512;             // the unfused pipeline's kernel
 constexpr uint64_t kEpilogueRunsMinBytes = 16ull << 20, kEpilogueCachedBytes = 80ull << 20, kEpilogueNarrowMinBytes = 384ull << 20;
 constexpr int32_t kEpilogueNarrowMinR = 4;
 constexpr unsigned kEpilogueNarrowLds = 16384;   // bytes per workgroup: 160 KiB hold ten
+constexpr uint64_t kEpilogueLaunchElems = 1ull << 34;        // 2^31 threads of 8 elements each
 
 int epilogue_grid(uint64_t numel, uint32_t chunk, unsigned *grid)
 {
@@ -826,19 +827,28 @@ int cc_fused_epilogue(const cc_epilogue *e, void *stream)
     const bool narrow = bytes >= kEpilogueNarrowMinBytes && e->R >= kEpilogueNarrowMinR;
     a.runs = bytes >= kEpilogueRunsMinBytes && !narrow;
     const unsigned lds = narrow ? kEpilogueNarrowLds : 0u;
-    unsigned grid;
-    if ((rc = epilogue_grid(e->numel, kEpiloguePiece, &grid))) return rc;
+    unsigned whole;
+    if ((rc = epilogue_grid(e->numel, kEpiloguePiece, &whole))) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if (bytes < kEpilogueCachedBytes) switch (e->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, Resident>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, a); break;
-        FOR_EACH_R(CASE)
+    in_launches(e->numel, kEpilogueLaunchElems, [&](uint64_t at, uint64_t count) {
+        EpilogueArgs part = a;
+        part.numel = count;
+        part.first += at;
+        for (int r = 0; r < e->R; ++r) part.partial[r] += at;
+        part.residual += at;
+        part.out += at;
+        const unsigned grid = (unsigned)((count + kEpiloguePiece - 1) / kEpiloguePiece);
+        if (bytes < kEpilogueCachedBytes) switch (e->R) {
+#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, Resident>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, part); break;
+            FOR_EACH_R(CASE)
 #undef CASE
-    }
-    else switch (e->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, WriteThrough>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, a); break;
-        FOR_EACH_R(CASE)
+        }
+        else switch (e->R) {
+#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, WriteThrough>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, part); break;
+            FOR_EACH_R(CASE)
 #undef CASE
-    }
+        }
+    });
     return launched("fused_epilogue_kernel");
 }
 

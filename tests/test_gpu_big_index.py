@@ -1,4 +1,4 @@
-"""A tensor of more than 2^31 elements: element indices above 2^31 and byte offsets above 2^33 must not wrap.
+"""Tensors of more than 2^31 elements: element indices above 2^31 and byte offsets above 2^33 must not wrap.
 
 Adam is element-wise, so the oracle can be given slices of the tensor: the start, the places where a 32-bit element
 index or a 32-bit byte offset would wrap (element 2^30 = byte 2^32 of an fp32 array, element 2^31 = byte 2^32 of an
@@ -12,6 +12,7 @@ import oracle
 from paper_2105_05720_amd import binding as cc
 from paper_2105_05720_amd.shard import Shard
 from parity import hyper_pair, to_np_bits, to_np_f32
+from test_gpu_epilogue import check
 from util import half_ulp_distance, state_error
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,27 @@ def test_adam_on_a_tensor_of_more_than_2_to_31_elements(schedule):
     k = a0 + 5003
     assert float(shard.w_of(0)[k]) == float(ots[2].w[5003]) and float(shard.w_of(0)[k + 1]) != float(ots[2].w[5004])
     shard.destroy()
+
+
+def test_epilogue_of_more_elements_than_one_launch_has_threads_for():
+    """2^35 elements and a few: eight elements a thread would be 2^32 threads, more than a launch may have, so the call goes
+    out in several.  One buffer is both the partial output and the residual; windows at the start, across the seams, where
+    element indices and byte offsets pass a power of two, and at the ragged end, each against the oracle; zeros between them."""
+    n, hidden, first, p, seed = (1 << 35) + 3 * 512 + 13, 3072, 3072 * 5 + 8, 0.3, 2 ** 33 + 5
+    free, _ = torch.cuda.mem_get_info()
+    if free < 150 * (1 << 30):
+        pytest.skip("needs 150 GB of free device memory")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(35)
+    bias = torch.empty(hidden, device="cuda").normal_(0, 0.1, generator=gen).half()
+    x = torch.zeros(n, dtype=torch.float16, device="cuda")
+    out = torch.full((n + 64,), 9.0, dtype=torch.float16, device="cuda")
+    windows = [(0, 5000)] + [((1 << k) - 2504, (1 << k) + 2504) for k in (31, 32, 33, 34)] + [((1 << 35) - 2504, n)]
+    for a, b in windows:
+        x[a:b] = torch.empty(b - a, device="cuda").normal_(0, 0.5, generator=gen).half()
+    cc.cc_fused_epilogue([x], bias, x, out, first, hidden, p, seed, numel=n)
+    torch.cuda.synchronize()
+    for a, b in windows + [(k, k + 4096) for k in (1 << 30, 3 << 32, 3 << 33)]:
+        kept = check(to_np_bits(out[a:b]), [x[a:b]], bias, x[a:b], first + a, p, seed)
+        assert 0.65 < kept.mean() < 0.75
+    assert bool((out[n:] == 9.0).all())

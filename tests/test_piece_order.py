@@ -1,5 +1,6 @@
 """The order in which the workgroups of a grid take the pieces of a call (csrc/piece_order.hpp), compiled for the host:
-every piece is taken exactly once, whatever the grid, and a round's XCD takes consecutive pieces."""
+every piece is taken exactly once, whatever the grid, and a round's XCD takes consecutive pieces; and the launches of a call
+that is too large for one cover it without a gap."""
 import os
 import subprocess
 
@@ -31,6 +32,18 @@ int main()
             if (ccf::piece_in_runs(512 + 8 * k + x, 1024) != 512 + 64 * x + k) { printf("XCD %u, %u\n", x, k); return 1; }
     const uint32_t most = 0x7fffffffu;                           // the largest grid a launch may have
     if (ccf::piece_in_runs(most - 1, most) != most - 1 || ccf::piece_in_runs(0, most) != 0) { printf("largest grid\n"); return 1; }
+    for (uint64_t most : {1ull << 34, 512ull, 1024ull})
+        for (uint64_t numel : {0ull, 1ull, 511ull, 512ull, 513ull, 1024ull, 1025ull, (1ull << 34) - 1, 1ull << 34, (1ull << 34) + 8, 1ull << 35, (1ull << 36) + 7}) {
+            if (numel / most > 100000) continue;
+            uint64_t next = 0;
+            bool ok = true;
+            ccf::in_launches(numel, most, [&](uint64_t at, uint64_t count) {
+                const uint64_t threads = (count + 511) / 512 * 64;
+                ok = ok && at == next && at % 512 == 0 && count > 0 && count <= most && threads < 1ull << 32;
+                next = at + count;
+            });
+            if (!ok || next != numel) { printf("launches of %llu elements\n", (unsigned long long)numel); return 1; }
+        }
     return 0;
 }
 """
