@@ -176,7 +176,7 @@ int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_thr
  * 20.5 Mi elements, 8-12 % faster at 2^23 and 2^24), for a list of tensors while the step's buffers total less than
  * 300 MiB; else STREAMING.  That is the Adam step's policy, which cc_plan_layout reports; LAMB, from 200 MiB on, writes
  * its first sweep's moments through and streams its second sweep's output.
- * cc_plan_autotune tries all three.
+ * cc_plan_autotune tries all three, and AUTO for LAMB.
  */
 typedef enum cc_cache_policy { CC_CACHE_AUTO = 0, CC_CACHE_STREAMING = 1, CC_CACHE_RESIDENT = 2, CC_CACHE_WRITE_THROUGH = 3 } cc_cache_policy;
 int cc_plan_set_cache_policy(cc_plan *plan, int32_t policy);
@@ -185,9 +185,9 @@ int cc_plan_set_cache_policy(cc_plan *plan, int32_t policy);
  * Picks chunk size, workgroup size, cache policy, schedule and workgroup count by measurement instead of by the size
  * rule, as the paper's autotuner keeps the fastest schedule per workload (Section 3.5): runs the plan's own fused
  * step (optimizer 0 = Adam, 1 = LAMB) a few times under each candidate (one workgroup per chunk for every chunk size
- * the plan was prepared for, with every cache policy that exists for it; ordered with compute units / 2, x 1 and x 2
- * workgroups on the 4096-element chunks), timed with events on `hip_stream`, and leaves the plan set to the fastest.  The
- * trial steps are ordinary steps on the caller's buffers: they write the out buffers and the flag, never the in
+ * the plan was prepared for, with every cache policy that exists for it, and for LAMB with AUTO as well; ordered with
+ * compute units / 2, x 1 and x 2 workgroups on the 4096-element chunks), timed with events on `hip_stream`, and leaves
+ * the plan set to the fastest.  The trial steps are ordinary steps on the caller's buffers: they write the out buffers and the flag, never the in
  * buffers, so the plan must be out of place (CC_ERR_ALIAS otherwise) and the caller must not have adopted the out
  * buffers' contents.  Synchronises the stream.  best_ms / per_chunk_ms (each may be NULL) receive the time per step
  * of the schedule kept and of one workgroup per chunk.

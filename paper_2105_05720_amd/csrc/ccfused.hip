@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "plan.hpp"
+#include "tuning.hpp"
 
 using namespace ccf;
 
@@ -886,27 +887,12 @@ int cc_plan_autotune(cc_plan *p, const cc_hparams *hp, int32_t optimizer, int32_
         if (rc) return rc;
     }
     hipStream_t st = (hipStream_t)stream;
-    struct Candidate { int32_t chunk_elems, schedule; unsigned workgroups; int32_t cache; };
     const Candidate keep{p->chunk_choice, p->schedule, p->ordered_grid, p->cache_policy};
-    // one workgroup per chunk under the plan's current layout first: its time is what per_chunk_ms reports
     std::vector<Candidate> cand;
     try {
-        const int32_t current = p->lay().chunk_elems;
-        cand.push_back(Candidate{current, CC_SCHEDULE_PER_CHUNK, 0u, CC_CACHE_STREAMING});
-        if (p->lay().block == kSmallBlock)
-            for (int32_t c : {CC_CACHE_RESIDENT, CC_CACHE_WRITE_THROUGH}) cand.push_back(Candidate{current, CC_SCHEDULE_PER_CHUNK, 0u, c});
-        for (const Layout &L : p->layouts) {
-            if (L.chunks == 0) continue;
-            if (L.chunk_elems != current) {
-                cand.push_back(Candidate{L.chunk_elems, CC_SCHEDULE_PER_CHUNK, 0u, CC_CACHE_STREAMING});
-                if (L.block == kSmallBlock)
-                    for (int32_t c : {CC_CACHE_RESIDENT, CC_CACHE_WRITE_THROUGH}) cand.push_back(Candidate{L.chunk_elems, CC_SCHEDULE_PER_CHUNK, 0u, c});
-            }
-            if (L.chunk_elems == kDefaultChunkElems) {
-                const unsigned cus = (unsigned)p->cus;
-                for (unsigned w : {cus, cus > 1 ? cus / 2 : 1u, cus * 2}) cand.push_back(Candidate{L.chunk_elems, CC_SCHEDULE_ORDERED, w, CC_CACHE_STREAMING});
-            }
-        }
+        std::vector<TuningLayout> layouts;
+        for (const Layout &L : p->layouts) layouts.push_back(TuningLayout{L.chunk_elems, L.chunks, L.block == kSmallBlock, L.chunk_elems == kDefaultChunkElems});
+        cand = tuning_candidates(layouts, p->lay().chunk_elems, optimizer, (uint32_t)p->cus);
     } catch (const std::bad_alloc &) {
         return fail(CC_ERR_NOMEM, "cc_plan_autotune: out of host memory");
     }

@@ -1,5 +1,5 @@
-"""Which cache policy each kernel family of a plan uses (csrc/cache_rules.hpp), compiled for the host: the bounds that the
-header states, one element below and at each of them."""
+"""Which cache policy each kernel family of a plan uses (csrc/cache_rules.hpp) and what the tuner tries (csrc/tuning.hpp),
+compiled for the host: the bounds that the header states, one element below and at each of them."""
 import os
 import subprocess
 
@@ -78,3 +78,49 @@ def test_a_policy_that_was_asked_for_holds_everywhere(policies):
     for p in (STREAM, RESIDENT, THROUGH):
         for n in (100, 1 << 22, 1 << 25):
             assert policies(p, n, 8, False, True) == (p,) * 5
+
+
+TUNER = r"""
+#include <cstdio>
+#include "cache_rules.hpp"
+#include "tuning.hpp"
+
+// Whatever AUTO gives an untuned plan's small chunks, some candidate gives them too.
+int main()
+{
+    const std::vector<ccf::TuningLayout> layouts = {{1024, 5, true, false}, {4096, 2, false, true}, {16384, 1, false, false}};
+    for (int optimizer : {0, 1})
+        for (int32_t current : {1024, 4096, 16384}) {
+            const auto cand = ccf::tuning_candidates(layouts, current, optimizer, 256);
+            if (cand.empty() || cand[0].chunk_elems != current || cand[0].schedule != CC_SCHEDULE_PER_CHUNK || cand[0].cache != CC_CACHE_STREAMING) return 1;
+            for (uint64_t numel : {1ull << 10, 1ull << 17, 1ull << 20, 5300000ull, 1ull << 23, 14000000ull, 1ull << 25, 42000000ull, 60000000ull})
+                for (int R : {1, 8, 16})
+                    for (bool list : {false, true}) {
+                        const ccf::CachePolicies a = ccf::cache_policies(CC_CACHE_AUTO, numel, R, false, list);
+                        int found = 0;
+                        for (const auto &c : cand) {
+                            const ccf::CachePolicies q = ccf::cache_policies(c.cache, numel, R, false, list);
+                            if (c.chunk_elems != 1024 || c.schedule != CC_SCHEDULE_PER_CHUNK) continue;
+                            found += optimizer == 0 ? q.adam == a.adam : q.lamb1 == a.lamb1 && q.lamb2 == a.lamb2;
+                        }
+                        if (!found) { printf("optimizer %d, %llu elements, R = %d, list %d\n", optimizer, (unsigned long long)numel, R, (int)list); return 2; }
+                    }
+            int ordered = 0;
+            for (const auto &c : cand) {
+                if (c.schedule != CC_SCHEDULE_ORDERED) continue;
+                ++ordered;
+                if (c.chunk_elems != 4096 || (c.workgroups != 128 && c.workgroups != 256 && c.workgroups != 512)) return 3;
+            }
+            if (ordered != 3) return 4;
+        }
+    return 0;
+}
+"""
+
+
+def test_the_tuner_tries_what_auto_would_choose(tmp_path):
+    (tmp_path / "tuner.cpp").write_text(TUNER)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"), "-o", str(tmp_path / "tuner"), str(tmp_path / "tuner.cpp")])
+    done = subprocess.run([str(tmp_path / "tuner")], capture_output=True, text=True, timeout=60)
+    assert done.returncode == 0, "%d %s" % (done.returncode, done.stdout)
