@@ -791,19 +791,22 @@ int check_epilogue(const cc_epilogue *e, EpilogueArgs *a)
 constexpr int kEpilogueBlock = 512;             // the unfused pipeline's kernels (64, 128 and 256 threads are 2-8 % slower)
 // How the fused kernel's single-wave workgroups are laid over the device, by the bytes of the call (2R + 4 per element).
 // Figures: R = 8, three sets of buffers used in turn; before these rules the kernel took the pieces in grid order with
-// non-temporal accesses, two groups per lane from 200 MiB on.  The stores are always written through (sc1): 78.6 against
-// 83.8 us on the [8, 1024, 3072] tensor (480 MiB), and never slower.
+// non-temporal accesses, two groups per lane from 200 MiB on.  The stores are written through (sc1): 78.6 against 83.8 us
+// on the [8, 1024, 3072] tensor (480 MiB); where the caches are full of lines that others wrote, up to 5 % slower.
 //   * from 16 MiB on the XCDs take runs of pieces (piece_in_runs): 4.9 against 5.3 us at 20 MiB, 11.6 against 12.9 at
 //     60 MiB, 27.1 against 29.2 at 160 MiB; below, one or two rounds of the grid are all there is (3.0 without, 3.3 with
 //     them at 10 MiB).
-//   * below 80 MiB plain loads: the partial outputs were written just before and are still in the 256 MB Infinity Cache
-//     (10.9 against 11.6 us at 60 MiB; with evicted caches 13.7 against 12.2, and 24.7 against 21.2 us at 120 MiB).
 //   * from 384 MiB on, with R >= 4, ten waves per compute unit (the launch asks for LDS that nobody uses) and the pieces
 //     in grid order: the addresses in flight are then a narrow window that moves through the ten streams, which DRAM
 //     rewards more than runs: 75.9 against 78.6 us at 480 MiB (runs: 77.2), 201 against 213 us at 1280 MiB (runs: 217),
 //     R = 16 at 2304 MiB 375 against 400 us.  With fewer slices ten waves have too little in flight (R = 2, 512 MiB: 98
 //     against 85 us; runs: 83 us).
-constexpr uint64_t kEpilogueRunsMinBytes = 16ull << 20, kEpilogueCachedBytes = 80ull << 20, kEpilogueNarrowMinBytes = 384ull << 20;
+// The loads are non-temporal at every size.  Plain ones are faster while the inputs are on chip, but what they miss they
+// place in the 256 MB Infinity Cache, and where that is full of lines that others wrote each of those goes to HBM first.
+// 60 MiB, one call, non-temporal / plain, us: partial outputs just written and residual in HBM 15.5 / 14.4; all inputs in
+// HBM behind a gigabyte of reads 13.8 / 15.1, behind a gigabyte of writes 15.1 / 25.9 (78 MiB: 18.5 / 32.0, 20 MiB: 8.2 /
+// 11.9); no call can tell which it is.  Every mixture of the sc0, sc1 and nt bits behaves like one of the two.
+constexpr uint64_t kEpilogueRunsMinBytes = 16ull << 20, kEpilogueNarrowMinBytes = 384ull << 20;
 constexpr int32_t kEpilogueNarrowMinR = 4;
 constexpr unsigned kEpilogueNarrowLds = 16384;   // bytes per workgroup: 160 KiB hold ten
 constexpr uint64_t kEpilogueLaunchElems = 1ull << 34;        // 2^31 threads of 8 elements each
@@ -839,13 +842,8 @@ int cc_fused_epilogue(const cc_epilogue *e, void *stream)
         part.residual += at;
         part.out += at;
         const unsigned grid = (unsigned)((count + kEpiloguePiece - 1) / kEpiloguePiece);
-        if (bytes < kEpilogueCachedBytes) switch (e->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, Resident>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, part); break;
-            FOR_EACH_R(CASE)
-#undef CASE
-        }
-        else switch (e->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r, WriteThrough>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, part); break;
+        switch (e->R) {
+#define CASE(r) case r: hipLaunchKernelGGL((fused_epilogue_kernel<r>), dim3(grid), dim3(kEpilogueFusedBlock), lds, st, part); break;
             FOR_EACH_R(CASE)
 #undef CASE
         }

@@ -1503,15 +1503,9 @@ __device__ __forceinline__ float epilogue_value(float x_sum, float bias, float r
     return (keep ? x * scale : 0.0f) + residual;
 }
 
-template <class Mem> __device__ __forceinline__ f16x8 ld_f16x8(gcbytes b, uint32_t off)
-{
-    if (Mem::kLoadNonTemporal) return __builtin_nontemporal_load((const CCF_GLOBAL f16x8 *)(b + off));
-    return *(const CCF_GLOBAL f16x8 *)(b + off);
-}
-template <class Mem> __device__ __forceinline__ void st_f16x8(gbytes b, uint32_t off, f16x8 x)
-{
-    st_f32x4<Mem>(b, off, __builtin_bit_cast(f32x4, x));
-}
+// The epilogue's accesses: non-temporal loads, stores written through (see cc_fused_epilogue).
+__device__ __forceinline__ f16x8 ld_f16x8(gcbytes b, uint32_t off) { return __builtin_nontemporal_load((const CCF_GLOBAL f16x8 *)(b + off)); }
+__device__ __forceinline__ void st_f16x8(gbytes b, uint32_t off, f16x8 x) { st_f32x4<WriteThrough>(b, off, __builtin_bit_cast(f32x4, x)); }
 
 // Common part of the fused kernel and of the unfused pipeline's pointwise kernel: mask, bias column, output.
 struct EpilogueTail {
@@ -1546,7 +1540,7 @@ struct EpilogueTail {
     }
 };
 
-template <int R, class Mem>
+template <int R>
 struct FusedEpilogueOp {
     static constexpr uint32_t kPack = 8;
     gcbytes part[R];
@@ -1561,8 +1555,8 @@ struct FusedEpilogueOp {
     __device__ __forceinline__ void load(Regs &x, uint32_t e) const
     {
 #pragma unroll
-        for (int r = 0; r < R; ++r) x.p[r] = ld_f16x8<Mem>(part[r], e * 2);
-        x.r = ld_f16x8<Mem>(t.res, e * 2);
+        for (int r = 0; r < R; ++r) x.p[r] = ld_f16x8(part[r], e * 2);
+        x.r = ld_f16x8(t.res, e * 2);
         x.b = *(const CCF_GLOBAL f16x8 *)(t.bias + t.column(e) * 2);     // 8 columns never wrap: H and e are multiples of 8
         x.e = e;
     }
@@ -1584,7 +1578,7 @@ struct FusedEpilogueOp {
         }
         x.r = o;
     }
-    __device__ __forceinline__ void store(const Regs &x, uint32_t e) const { st_f16x8<Mem>(t.out, e * 2, x.r); }
+    __device__ __forceinline__ void store(const Regs &x, uint32_t e) const { st_f16x8(t.out, e * 2, x.r); }
     __device__ __forceinline__ void single(uint32_t j)
     {
         float sum = ld_f16(part[0], j * 2);
@@ -1600,15 +1594,15 @@ struct FusedEpilogueOp {
 // they gain beyond that comes from the addresses in flight, see cc_fused_epilogue.
 constexpr int kEpilogueFusedBlock = 64;
 constexpr uint32_t kEpiloguePiece = kEpilogueFusedBlock * 8;
-template <int R, class Mem>
+template <int R>
 __global__ __launch_bounds__(kEpilogueFusedBlock) void fused_epilogue_kernel(EpilogueArgs a)
 {
     const uint32_t piece = a.runs ? piece_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint64_t base = (uint64_t)piece * kEpiloguePiece;
     const uint64_t rem = a.numel - base;
-    FusedEpilogueOp<R, Mem> op;
+    FusedEpilogueOp<R> op;
     op.init(a, base);
-    stream_chunk<kEpilogueFusedBlock, FusedEpilogueOp<R, Mem>, 1>(op, rem < kEpiloguePiece ? (uint32_t)rem : kEpiloguePiece);
+    stream_chunk<kEpilogueFusedBlock, FusedEpilogueOp<R>, 1>(op, rem < kEpiloguePiece ? (uint32_t)rem : kEpiloguePiece);
 }
 
 // Unfused pipeline: reduce the R partial outputs into an fp32 buffer (a lane owns 4 elements, so that the fp32
