@@ -126,8 +126,10 @@ void resolve_schedule(cc_plan *p)
     else p->ordered = L.chunks >= kOrderedMinChunksPerCu * (int64_t)p->cus && !(p->grad_f32 && p->R > kOrderedMaxF32Slices);
     if (L.chunk_elems != kDefaultChunkElems || L.chunks == 0) p->ordered = false;
     const bool small = L.block == kSmallBlock && !p->ordered;
-    p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, p->single < 0) : CachePolicies{};
-    p->spread = small && step_footprint(p->numel, p->R, p->grad_f32) >= kResidentMaxBytes;
+    const bool one_sweep = L.chunk_elems == kSmallChunkElems;
+    p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, p->single < 0, one_sweep) : CachePolicies{};
+    p->beyond_cache = small && step_footprint(p->numel, p->R, p->grad_f32) >= kResidentMaxBytes;
+    p->spread = p->beyond_cache && one_sweep;
 }
 
 void free_layout(Layout &L)

@@ -41,7 +41,7 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
     if (p->single >= 0) {                  // one tensor: no table, descriptor in the kernel arguments
         const DevTensor &t = L.host_tensors[(size_t)p->single];
         if constexpr (!std::is_same<MEM, Resident>::value)
-            if (p->spread && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
+            if (p->beyond_cache && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
         switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, 0, st, t, s, p->d_flag_scratch, flag); break;
             FOR_EACH_R(CASE)

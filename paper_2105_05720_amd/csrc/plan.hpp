@@ -24,8 +24,8 @@ constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-
 constexpr int kOrderedMaxF32Slices = 8;           // fp32 slices: the ordered schedule wins up to 8 (config-2 list: 3.18 against 3.41 ms), at 16 two chunks spill
 constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per compute unit a plan keeps one workgroup per chunk
 
-// Small chunks of a shard that does not fit the Infinity Cache (step's buffers of kResidentMaxBytes and more) are bound
-// by HBM, and what the addresses in flight look like decides: every XCD takes runs of 32 chunks (piece_in_runs), and the
+// Chunks of 1024 elements of a shard that does not fit the Infinity Cache (step's buffers of kResidentMaxBytes and more) are
+// bound by HBM, and what the addresses in flight look like decides: every XCD takes runs of 32 chunks (piece_in_runs), and the
 // fused Adam kernel asks for LDS that nobody uses, so that six of its 128-thread workgroups fit a compute unit instead of
 // up to sixteen.  Together, us before / runs only / runs and six workgroups: 36.6 / 36.1 / 35.9 at 5.3 M elements, 82.0 /
 // 81.1 / 80.3 at 11.2 M, 389.2 / 385.7 / 382.9 at 56 M.  LAMB's first sweep adds up its chunk behind a barrier and cannot
@@ -92,7 +92,8 @@ struct cc_plan {
     int32_t schedule = CC_SCHEDULE_AUTO;    // what the caller asked for
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
     ccf::CachePolicies mem;                 // the policies in use (other than STREAMING: small-chunk layouts only)
-    bool spread = false;                    // small chunks of a shard bound by HBM (see kSpreadLds)
+    bool beyond_cache = false;              // small chunks of a shard bound by HBM (one tensor: see kFlatPiece)
+    bool spread = false;                    // ... of 1024 elements (see kSpreadLds)
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
     int32_t cus = 0;                        // compute units of the device the plan was created on
     int32_t single = -1;                    // index of the only tensor with elements, or -1 if there are several (or none)

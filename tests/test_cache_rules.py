@@ -18,8 +18,8 @@ MAIN = r"""
 
 int main(int argc, char **argv)
 {
-    for (int i = 1; i + 4 < argc; i += 5) {
-        const ccf::CachePolicies c = ccf::cache_policies(atoi(argv[i]), strtoull(argv[i + 1], nullptr, 10), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]) != 0);
+    for (int i = 1; i + 5 < argc; i += 6) {
+        const ccf::CachePolicies c = ccf::cache_policies(atoi(argv[i]), strtoull(argv[i + 1], nullptr, 10), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]) != 0, atoi(argv[i + 5]) != 0);
         printf("%d %d %d %d %d\n", c.adam, c.lamb1, c.lamb2, c.unfused, c.unfused_lamb);
     }
     return 0;
@@ -34,8 +34,8 @@ def policies(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
                            "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
 
-    def ask(asked, numel, R, f32, is_list):
-        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, is_list)], capture_output=True, text=True, timeout=60)
+    def ask(asked, numel, R, f32, is_list, one_sweep=True):
+        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, is_list, one_sweep)], capture_output=True, text=True, timeout=60)
         return tuple(int(x) for x in out.stdout.split())
     return ask
 
@@ -74,6 +74,18 @@ def test_the_unfused_pipelines_go_by_what_one_of_their_launches_stores(policies,
     assert [policies(AUTO, n, R, f32, is_list)[3:] for n in (below, at)] == [(STREAM, THROUGH), (STREAM, STREAM)]
 
 
+@pytest.mark.parametrize("R,f32", [(1, False), (8, False), (4, True)])
+@pytest.mark.parametrize("is_list", [False, True])
+def test_chunks_of_several_sweeps_go_by_what_a_launch_stores(policies, R, f32, is_list):
+    """Small chunks above 1024 elements: the same for a list as for one tensor, and both of LAMB's sweeps alike."""
+    below, at = below_and_at(288 * MIB, 14)
+    assert [policies(AUTO, n, R, f32, is_list, False)[0] for n in (below, at)] == [THROUGH, STREAM]
+    below, at = below_and_at(288 * MIB, 8)
+    assert [policies(AUTO, n, R, f32, is_list, False)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, STREAM)]
+    below, at = below_and_at(200 * MIB, (4 if f32 else 2) * R + 26)
+    assert policies(AUTO, below, R, f32, is_list, False) == (RESIDENT,) * 5
+
+
 def test_a_policy_that_was_asked_for_holds_everywhere(policies):
     for p in (STREAM, RESIDENT, THROUGH):
         for n in (100, 1 << 22, 1 << 25):
@@ -96,10 +108,10 @@ int main()
             for (uint64_t numel : {1ull << 10, 1ull << 17, 1ull << 20, 5300000ull, 1ull << 23, 14000000ull, 1ull << 25, 42000000ull, 60000000ull})
                 for (int R : {1, 8, 16})
                     for (bool list : {false, true}) {
-                        const ccf::CachePolicies a = ccf::cache_policies(CC_CACHE_AUTO, numel, R, false, list);
+                        const ccf::CachePolicies a = ccf::cache_policies(CC_CACHE_AUTO, numel, R, false, list, true);
                         int found = 0;
                         for (const auto &c : cand) {
-                            const ccf::CachePolicies q = ccf::cache_policies(c.cache, numel, R, false, list);
+                            const ccf::CachePolicies q = ccf::cache_policies(c.cache, numel, R, false, list, true);
                             if (c.chunk_elems != 1024 || c.schedule != CC_SCHEDULE_PER_CHUNK) continue;
                             found += optimizer == 0 ? q.adam == a.adam : q.lamb1 == a.lamb1 && q.lamb2 == a.lamb2;
                         }
