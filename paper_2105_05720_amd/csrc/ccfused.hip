@@ -798,19 +798,22 @@ constexpr int kEpilogueBlock = 512;             // the unfused pipeline's kernel
 //   * from 16 MiB on the XCDs take runs of pieces (piece_in_runs): 4.9 against 5.3 us at 20 MiB, 11.6 against 12.9 at
 //     60 MiB, 27.1 against 29.2 at 160 MiB; below, one or two rounds of the grid are all there is (3.0 without, 3.3 with
 //     them at 10 MiB).
-//   * from 384 MiB on, with R >= 4, ten waves per compute unit (the launch asks for LDS that nobody uses) and the pieces
-//     in grid order: the addresses in flight are then a narrow window that moves through the ten streams, which DRAM
-//     rewards more than runs: 75.9 against 78.6 us at 480 MiB (runs: 77.2), 201 against 213 us at 1280 MiB (runs: 217),
-//     R = 16 at 2304 MiB 375 against 400 us.  With fewer slices ten waves have too little in flight (R = 2, 512 MiB: 98
-//     against 85 us; runs: 83 us).
+//   * from 384 MiB on few waves per compute unit (the launch asks for LDS that nobody uses) and the pieces in grid order:
+//     the addresses in flight are then a narrow window that moves through the streams, which DRAM rewards more than runs.
+//     Ten waves with R >= 8: 75.9 against 78.6 us at 480 MiB (runs: 77.2), 201 against 213 at 1280 MiB (runs: 217), R = 16
+//     at 2304 MiB 375 against 400.  R = 4 to 7 have too little in flight with ten and take a reservation of 12544 bytes
+//     instead; before / ten waves / runs / that, us: R = 4 at 560 MiB 92.9 / 95.6 / 94.5 / 90.5, at 800 MiB 131 / 134 / 137 /
+//     127; R = 7 at 560 MiB 96.4 / 89.8 / 90.3 / 86.8, where R = 8 takes 96.7 / 86.7 / 90.4 / 87.8.  R = 3 is
+//     as well off with the runs (at 560 MiB 88.9 / runs 95.0, behind a gigabyte of other reads 89.5 / 87.6) and R = 1 and 2
+//     are better off (R = 2 at 560 MiB 100 / 90.5 and 99.6 / 84.4).
 // The loads are non-temporal at every size.  Plain ones are faster while the inputs are on chip, but what they miss they
 // place in the 256 MB Infinity Cache, and where that is full of lines that others wrote each of those goes to HBM first.
 // 60 MiB, one call, non-temporal / plain, us: partial outputs just written and residual in HBM 15.5 / 14.4; all inputs in
 // HBM behind a gigabyte of reads 13.8 / 15.1, behind a gigabyte of writes 15.1 / 25.9 (78 MiB: 18.5 / 32.0, 20 MiB: 8.2 /
 // 11.9); no call can tell which it is.  Every mixture of the sc0, sc1 and nt bits behaves like one of the two.
 constexpr uint64_t kEpilogueRunsMinBytes = 16ull << 20, kEpilogueNarrowMinBytes = 384ull << 20;
-constexpr int32_t kEpilogueNarrowMinR = 4;
-constexpr unsigned kEpilogueNarrowLds = 16384;   // bytes per workgroup: 160 KiB hold ten
+constexpr int32_t kEpilogueNarrowMinR = 4, kEpilogueTenWavesMinR = 8;
+constexpr unsigned kEpilogueNarrowLds = 12544, kEpilogueTenWavesLds = 16384;   // bytes per workgroup, of 160 KiB
 constexpr uint64_t kEpilogueLaunchElems = 1ull << 34;        // 2^31 threads of 8 elements each
 
 int epilogue_grid(uint64_t numel, uint32_t chunk, unsigned *grid)
@@ -832,7 +835,7 @@ int cc_fused_epilogue(const cc_epilogue *e, void *stream)
     const uint64_t bytes = e->numel * (2u * (uint64_t)e->R + 4u);
     const bool narrow = bytes >= kEpilogueNarrowMinBytes && e->R >= kEpilogueNarrowMinR;
     a.runs = bytes >= kEpilogueRunsMinBytes && !narrow;
-    const unsigned lds = narrow ? kEpilogueNarrowLds : 0u;
+    const unsigned lds = !narrow ? 0u : e->R >= kEpilogueTenWavesMinR ? kEpilogueTenWavesLds : kEpilogueNarrowLds;
     unsigned whole;
     if ((rc = epilogue_grid(e->numel, kEpiloguePiece, &whole))) return rc;
     hipStream_t st = (hipStream_t)stream;

@@ -81,8 +81,9 @@ def test_fused_equals_unfused_epilogue_bit_for_bit(n):
 
 @pytest.mark.parametrize("R,n", [
     (8, (16 << 20) // 20 - 5), (8, 512 * 2048 + 512 * 511 + 8),      # around 16 MiB: grid order, and runs with all but one piece of a round left over
-    (8, (80 << 20) // 20 - 3), (16, 512 * 512 * 12 + 1),             # around 80 MiB: plain loads below, non-temporal from there on; a last piece of one element
+    (8, (80 << 20) // 20 - 3), (16, 512 * 512 * 12 + 1),             # between those bounds; a last piece of one element
     (4, (384 << 20) // 12 + 3), (3, (384 << 20) // 10 + 7),          # from 384 MiB: few waves with four slices and more, runs with fewer
+    (8, (384 << 20) // 20 + 9),                                      # and ten waves per compute unit with eight and more
 ])
 def test_every_launch_shape_equals_unfused_bit_for_bit(R, n):
     partials, bias, residual = make(n, R, 96, 5)
