@@ -58,6 +58,16 @@ def test_static_entry_point_grid_sizes_back_and_forth_and_overflow():
     run_pair(2048, 2, 32, cc.Hyper(step=1))                          # and the next call is clean again
 
 
+def test_static_entry_point_beyond_the_infinity_cache():
+    """From 200 MiB of buffers on the call runs in single-wave workgroups of 256 elements, on the same counting words: one
+    element below, at and ragged above that bound (58 bytes per element at R = 16), and at R = 1 where it stores 288 MiB and
+    more, with the overflow in the last element in turn; a small call behind them is clean."""
+    at = -(-(200 << 20) // 58)
+    for n, R, inject in ((at - 1, 16, None), (at, 16, (15, at - 1)), (at + 255, 16, None), (-(-(288 << 20) // 14) + 3, 1, None)):
+        run_pair(n, R, 41, cc.Hyper(step=2), inject)
+    run_pair(3000, 2, 42, cc.Hyper(step=1))
+
+
 def test_static_entry_point_rejects_what_it_cannot_do():
     sh = Shard([4096], [0.0], 2, chunk_elems=1024, align_elems=8)
     t = one_tensor_of(sh, 0)
