@@ -15,20 +15,20 @@ namespace ccf {
 constexpr uint64_t kResidentMinBytes = 4ull << 20, kResidentMaxBytes = 200ull << 20;
 // ... and from there on non-temporal loads with write-through stores while one Adam launch stores less than this (see
 // WriteThrough): what it writes then about fits the Infinity Cache.  One tensor at R = 8: 141 against 147 us at 20 Mi
-// elements, 160 against 157 us at 22 Mi.
+// elements, 160 against 157 us at 22 Mi.  It holds for a list as well.  BERT-Large list cut into slices, written through /
+// non-temporal, us, for 8.4 M, 14 M and 18.7 M elements at R = 8: back to back 54.1 / 60.1, 87.0 / 96.7, 114.6 / 129; behind
+// sixteen matrix products and pointwise passes, as a backward pass is, 59.0 / 63.5, 93.0 / 101, 120 / 132; with the
+// gradient slices written after those 57.9 / 59.7, 90.3 / 94.8, 119 / 130; behind a 2 GiB copy 60.0 / 63.6, 94.8 / 101, 124 / 132.
+// Only a program that steps several such shards right behind each other has it the other way (three in turn: 63.3 / 61.7, 104 /
+// 98.9, 136 / 130).
 constexpr uint64_t kWriteThroughMaxStoreBytes = 288ull << 20;
-// A list of tensors goes back to non-temporal stores earlier, once the step's buffers exceed this.  BERT-Large list cut
-// into slices, three shards in turn, written through / non-temporal, us: 35.9 / 39.6 at 5.3 M elements (R = 8: 231 MB),
-// but 67.7 / 61.6 at 8.4 M (370 MB), 88.1 / 80.3 at 11.2 M, 151 / 145 at 21 M; R = 16 at 11.2 M (673 MB) 120.7 / 111.4;
-// eight fp32 slices at 8.4 M (504 MB) 92.2 / 83.7.
-constexpr uint64_t kListWriteThroughMaxBytes = 300ull << 20;
 inline uint64_t step_footprint(uint64_t numel, int R, bool grad_f32) { return numel * ((grad_f32 ? 4u : 2u) * (uint64_t)R + 12u + 14u); }
 constexpr uint64_t kAdamStoreBytes = 14, kLambStoreBytes = 8;      // per element: w', m', v', w16 / m', v' (LAMB's first sweep)
-inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored, bool list)
+inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored)
 {
     if (footprint < kResidentMinBytes) return CC_CACHE_STREAMING;
     if (footprint < kResidentMaxBytes) return CC_CACHE_RESIDENT;
-    return (list ? footprint < kListWriteThroughMaxBytes : stored < kWriteThroughMaxStoreBytes) ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
+    return stored < kWriteThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
 }
 // LAMB's two sweeps want different stores once the shard has outgrown the Infinity Cache: written through in the first,
 // whose m' and v' the second reads again, and in the second, whose output nobody reads before the next step,
@@ -39,23 +39,20 @@ constexpr uint64_t kLambThroughMaxStoreBytes = 176ull << 20;
 
 // What a plan's small-chunk kernels use, by kernel family (cc_cache_policy values).
 struct CachePolicies {
-    int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step; what cc_plan_layout reports
+    int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step (what cc_plan_layout reports) and the unfused pipelines: reduce, Adam from the sum, cast
     int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep
     int32_t lamb2 = CC_CACHE_STREAMING;         // ... and its second
-    int32_t unfused = CC_CACHE_STREAMING;       // the unfused pipelines: reduce, Adam from the sum, cast
-    int32_t unfused_lamb = CC_CACHE_STREAMING;  // ... and LAMB's two sweeps in them, by the bytes that its first one stores
+    int32_t unfused_lamb = CC_CACHE_STREAMING;  // LAMB's two sweeps in the unfused pipeline, by the bytes that its first one stores
 };
-// one_sweep: the chunks are one sweep of a workgroup (1024 elements).  The list's bound and LAMB's pair hold for those only:
-// with 2048-element chunks, which a caller has to ask for, they cost Adam on 8.4 M elements in 73 tensors 56.4 -> 67.4 us
-// and LAMB on 25 M elements 210.5 -> 224.9 us (R = 8, one shard step after step).
-inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool grad_f32, bool list, bool one_sweep)
+// one_sweep: the chunks are one sweep of a workgroup (1024 elements).  LAMB's pair holds for those only: with 2048-element
+// chunks, which a caller has to ask for, it costs LAMB on 25 M elements 210.5 -> 224.9 us (R = 8, one shard step after step).
+inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool grad_f32, bool one_sweep)
 {
-    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked, asked, asked};
+    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked, asked};
     const uint64_t footprint = step_footprint(numel, R, grad_f32), stored = numel * kAdamStoreBytes;
     CachePolicies c;
-    c.adam = auto_cache_policy(footprint, stored, list && one_sweep);
-    c.unfused = auto_cache_policy(footprint, stored, false);
-    c.unfused_lamb = auto_cache_policy(footprint, numel * kLambStoreBytes, false);
+    c.adam = auto_cache_policy(footprint, stored);
+    c.unfused_lamb = auto_cache_policy(footprint, numel * kLambStoreBytes);
     if (footprint < kResidentMaxBytes || !one_sweep) c.lamb1 = c.lamb2 = c.unfused_lamb;
     else {
         c.lamb1 = CC_CACHE_WRITE_THROUGH;

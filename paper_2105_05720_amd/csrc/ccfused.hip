@@ -127,7 +127,7 @@ void resolve_schedule(cc_plan *p)
     if (L.chunk_elems != kDefaultChunkElems || L.chunks == 0) p->ordered = false;
     const bool small = L.block == kSmallBlock && !p->ordered;
     const bool one_sweep = L.chunk_elems == kSmallChunkElems;
-    p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, p->single < 0, one_sweep) : CachePolicies{};
+    p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, one_sweep) : CachePolicies{};
     p->beyond_cache = small && step_footprint(p->numel, p->R, p->grad_f32) >= kResidentMaxBytes;
     p->spread = p->beyond_cache && one_sweep;
 }
@@ -670,7 +670,7 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
     d.wd = t->weight_decay;
     const unsigned grid = (unsigned)((t->numel + (uint64_t)kSmallChunkElems - 1) / (uint64_t)kSmallChunkElems);
     const int mode = (hp->skip_mode == 1 ? kModeGuard : 0) | (hp->adam_mode == 0 ? kModeL2 : 0);
-    const int32_t mem = auto_cache_policy(step_footprint(t->numel, R, false), t->numel * kAdamStoreBytes, false);   // the plans' AUTO rule
+    const int32_t mem = auto_cache_policy(step_footprint(t->numel, R, false), t->numel * kAdamStoreBytes);   // the plans' AUTO rule
     launch_fused_adam_flat_f16(d, R, grid, mem, s, fs, flag, st, mode);
     return launched("fused_adam_flat_kernel");
 }

@@ -74,19 +74,19 @@ void launch_adam_from_sum_b(const cc_plan *p, const StepScalars &s, const int32_
 
 void launch_reduce(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    if (p->grad_f32) BY_BLOCK_MEM(p, p->mem.unfused, (launch_reduce_r<BLK, true, MEM>(p, s, flag, st)));
-    else BY_BLOCK_MEM(p, p->mem.unfused, (launch_reduce_r<BLK, false, MEM>(p, s, flag, st)));
+    if (p->grad_f32) BY_BLOCK(p, (launch_reduce_r<BLK, true, MEM>(p, s, flag, st)));
+    else BY_BLOCK(p, (launch_reduce_r<BLK, false, MEM>(p, s, flag, st)));
 }
 
 void launch_reduce_half(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    BY_BLOCK_MEM(p, p->mem.unfused, (launch_reduce_half_b<BLK, MEM>(p, s, flag, st)));
+    BY_BLOCK(p, (launch_reduce_half_b<BLK, MEM>(p, s, flag, st)));
 }
 
 void launch_adam_from_sum(const cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st, int mode, bool sum16)
 {
-    if (sum16) BY_BLOCK_MEM(p, p->mem.unfused, (launch_adam_from_sum_b<BLK, true, MEM>(p, s, flag, st, mode)));
-    else BY_BLOCK_MEM(p, p->mem.unfused, (launch_adam_from_sum_b<BLK, false, MEM>(p, s, flag, st, mode)));
+    if (sum16) BY_BLOCK(p, (launch_adam_from_sum_b<BLK, true, MEM>(p, s, flag, st, mode)));
+    else BY_BLOCK(p, (launch_adam_from_sum_b<BLK, false, MEM>(p, s, flag, st, mode)));
 }
 
 // A plan without chunks launches no streaming kernel, so the flag is cleared by a one-thread kernel (a kernel
@@ -104,7 +104,7 @@ int cast_launch(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream
         return launched("cast_ordered_kernel");
     }
     const dim3 grid((unsigned)p->chunks());
-    BY_BLOCK_MEM(p, p->mem.unfused, hipLaunchKernelGGL((cast_kernel<BLK, MEM>), grid, dim3(BLK), 0, st, p->lay().table_tensors(), p->lay().table_chunks(), s, flag, guarded));
+    BY_BLOCK(p, hipLaunchKernelGGL((cast_kernel<BLK, MEM>), grid, dim3(BLK), 0, st, p->lay().table_tensors(), p->lay().table_chunks(), s, flag, guarded));
     return launched("cast_kernel");
 }
 

@@ -18,9 +18,9 @@ MAIN = r"""
 
 int main(int argc, char **argv)
 {
-    for (int i = 1; i + 5 < argc; i += 6) {
-        const ccf::CachePolicies c = ccf::cache_policies(atoi(argv[i]), strtoull(argv[i + 1], nullptr, 10), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]) != 0, atoi(argv[i + 5]) != 0);
-        printf("%d %d %d %d %d\n", c.adam, c.lamb1, c.lamb2, c.unfused, c.unfused_lamb);
+    for (int i = 1; i + 4 < argc; i += 5) {
+        const ccf::CachePolicies c = ccf::cache_policies(atoi(argv[i]), strtoull(argv[i + 1], nullptr, 10), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]) != 0);
+        printf("%d %d %d %d\n", c.adam, c.lamb1, c.lamb2, c.unfused_lamb);
     }
     return 0;
 }
@@ -34,8 +34,8 @@ def policies(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
                            "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
 
-    def ask(asked, numel, R, f32, is_list, one_sweep=True):
-        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, is_list, one_sweep)], capture_output=True, text=True, timeout=60)
+    def ask(asked, numel, R, f32, one_sweep=True):
+        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, one_sweep)], capture_output=True, text=True, timeout=60)
         return tuple(int(x) for x in out.stdout.split())
     return ask
 
@@ -46,50 +46,47 @@ def below_and_at(nbytes, per_element):
 
 
 @pytest.mark.parametrize("R,f32", [(1, False), (8, False), (16, False), (4, True)])
-@pytest.mark.parametrize("is_list", [False, True])
-def test_automatic_policies_at_their_bounds(policies, R, f32, is_list):
+def test_automatic_policies_at_their_bounds(policies, R, f32):
     per = (4 if f32 else 2) * R + 26
     below, at = below_and_at(4 * MIB, per)
-    assert policies(AUTO, below, R, f32, is_list) == (STREAM,) * 5
-    assert policies(AUTO, at, R, f32, is_list) == (RESIDENT,) * 5
+    assert policies(AUTO, below, R, f32) == (STREAM,) * 4
+    assert policies(AUTO, at, R, f32) == (RESIDENT,) * 4
     below, at = below_and_at(200 * MIB, per)
-    assert policies(AUTO, below, R, f32, is_list) == (RESIDENT,) * 5
-    assert policies(AUTO, at, R, f32, is_list) == (THROUGH,) * 5
-    below, at = below_and_at(300 * MIB, per) if is_list else below_and_at(288 * MIB, 14)
-    assert [policies(AUTO, n, R, f32, is_list)[0] for n in (below, at)] == [THROUGH, STREAM]
+    assert policies(AUTO, below, R, f32) == (RESIDENT,) * 4
+    assert policies(AUTO, at, R, f32) == (THROUGH,) * 4
+    below, at = below_and_at(288 * MIB, 14)                   # the Adam step's own stores, for a list as for one tensor
+    assert [policies(AUTO, n, R, f32)[0] for n in (below, at)] == [THROUGH, STREAM]
     # fused LAMB writes its first sweep through from 200 MiB of buffers on, its second until 176 MiB are stored per step
     below, at = below_and_at(176 * MIB, 14)
-    assert [policies(AUTO, n, R, f32, is_list)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (THROUGH, STREAM)]
-    assert policies(AUTO, 1 << 30, R, f32, is_list)[1:3] == (THROUGH, STREAM)
+    assert [policies(AUTO, n, R, f32)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (THROUGH, STREAM)]
+    assert policies(AUTO, 1 << 30, R, f32)[1:3] == (THROUGH, STREAM)
 
 
 @pytest.mark.parametrize("R,f32", [(1, False), (8, False), (16, False), (4, True)])
-@pytest.mark.parametrize("is_list", [False, True])
-def test_the_unfused_pipelines_go_by_what_one_of_their_launches_stores(policies, R, f32, is_list):
+def test_the_unfused_pipelines_go_by_what_one_of_their_launches_stores(policies, R, f32):
     """Write-through from 200 MiB of buffers while a launch stores less than 288 MiB: 14 bytes per element in Adam's update,
-    8 in LAMB's first sweep, so the two pipelines change at 20.6 and 36 Mi elements, list or not."""
+    8 in LAMB's first sweep, so the two pipelines change at 20.6 and 36 Mi elements."""
     below, at = below_and_at(288 * MIB, 14)
-    assert [policies(AUTO, n, R, f32, is_list)[3:] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, THROUGH)]
+    assert [policies(AUTO, n, R, f32)[::3] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, THROUGH)]
     below, at = below_and_at(288 * MIB, 8)
-    assert [policies(AUTO, n, R, f32, is_list)[3:] for n in (below, at)] == [(STREAM, THROUGH), (STREAM, STREAM)]
+    assert [policies(AUTO, n, R, f32)[::3] for n in (below, at)] == [(STREAM, THROUGH), (STREAM, STREAM)]
 
 
 @pytest.mark.parametrize("R,f32", [(1, False), (8, False), (4, True)])
-@pytest.mark.parametrize("is_list", [False, True])
-def test_chunks_of_several_sweeps_go_by_what_a_launch_stores(policies, R, f32, is_list):
-    """Small chunks above 1024 elements: the same for a list as for one tensor, and both of LAMB's sweeps alike."""
+def test_chunks_of_several_sweeps_go_by_what_a_launch_stores(policies, R, f32):
+    """Small chunks above 1024 elements: both of LAMB's sweeps alike."""
     below, at = below_and_at(288 * MIB, 14)
-    assert [policies(AUTO, n, R, f32, is_list, False)[0] for n in (below, at)] == [THROUGH, STREAM]
+    assert [policies(AUTO, n, R, f32, False)[0] for n in (below, at)] == [THROUGH, STREAM]
     below, at = below_and_at(288 * MIB, 8)
-    assert [policies(AUTO, n, R, f32, is_list, False)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, STREAM)]
+    assert [policies(AUTO, n, R, f32, False)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, STREAM)]
     below, at = below_and_at(200 * MIB, (4 if f32 else 2) * R + 26)
-    assert policies(AUTO, below, R, f32, is_list, False) == (RESIDENT,) * 5
+    assert policies(AUTO, below, R, f32, False) == (RESIDENT,) * 4
 
 
 def test_a_policy_that_was_asked_for_holds_everywhere(policies):
     for p in (STREAM, RESIDENT, THROUGH):
         for n in (100, 1 << 22, 1 << 25):
-            assert policies(p, n, 8, False, True) == (p,) * 5
+            assert policies(p, n, 8, False) == (p,) * 4
 
 
 TUNER = r"""
@@ -106,17 +103,16 @@ int main()
             const auto cand = ccf::tuning_candidates(layouts, current, optimizer, 256);
             if (cand.empty() || cand[0].chunk_elems != current || cand[0].schedule != CC_SCHEDULE_PER_CHUNK || cand[0].cache != CC_CACHE_STREAMING) return 1;
             for (uint64_t numel : {1ull << 10, 1ull << 17, 1ull << 20, 5300000ull, 1ull << 23, 14000000ull, 1ull << 25, 42000000ull, 60000000ull})
-                for (int R : {1, 8, 16})
-                    for (bool list : {false, true}) {
-                        const ccf::CachePolicies a = ccf::cache_policies(CC_CACHE_AUTO, numel, R, false, list, true);
-                        int found = 0;
-                        for (const auto &c : cand) {
-                            const ccf::CachePolicies q = ccf::cache_policies(c.cache, numel, R, false, list, true);
-                            if (c.chunk_elems != 1024 || c.schedule != CC_SCHEDULE_PER_CHUNK) continue;
-                            found += optimizer == 0 ? q.adam == a.adam : q.lamb1 == a.lamb1 && q.lamb2 == a.lamb2;
-                        }
-                        if (!found) { printf("optimizer %d, %llu elements, R = %d, list %d\n", optimizer, (unsigned long long)numel, R, (int)list); return 2; }
+                for (int R : {1, 8, 16}) {
+                    const ccf::CachePolicies a = ccf::cache_policies(CC_CACHE_AUTO, numel, R, false, true);
+                    int found = 0;
+                    for (const auto &c : cand) {
+                        const ccf::CachePolicies q = ccf::cache_policies(c.cache, numel, R, false, true);
+                        if (c.chunk_elems != 1024 || c.schedule != CC_SCHEDULE_PER_CHUNK) continue;
+                        found += optimizer == 0 ? q.adam == a.adam : q.lamb1 == a.lamb1 && q.lamb2 == a.lamb2;
                     }
+                    if (!found) { printf("optimizer %d, %llu elements, R = %d\n", optimizer, (unsigned long long)numel, R); return 2; }
+                }
             int ordered = 0;
             for (const auto &c : cand) {
                 if (c.schedule != CC_SCHEDULE_ORDERED) continue;

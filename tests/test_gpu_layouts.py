@@ -171,11 +171,11 @@ def test_unfused_steps_need_the_reserved_buffer_and_never_allocate():
     sh.destroy(); ref.destroy()
 
 
-@pytest.mark.parametrize("log2n,R,policy", [(21, 8, cc.CC_CACHE_RESIDENT), (23, 2, cc.CC_CACHE_WRITE_THROUGH)])
+@pytest.mark.parametrize("log2n,R,policy", [(21, 8, cc.CC_CACHE_RESIDENT), (23, 2, cc.CC_CACHE_WRITE_THROUGH), (23, 8, cc.CC_CACHE_WRITE_THROUGH)])
 @pytest.mark.parametrize("fn,ofn", [(cc.cc_fused_adam_step, oracle.adam_step), (cc.cc_fused_lamb_step, oracle.lamb_step)])
 def test_mid_size_shard_under_the_automatic_cache_policy(fn, ofn, log2n, R, policy):
-    """2^21 elements with R = 8 (88 MB of buffers: AUTO keeps the shard on chip) and 2^23 elements with R = 2 (252 MB, of
-    which a launch stores 117 MB: AUTO writes through); two steps, every element against the oracle."""
+    """2^21 elements with R = 8 (88 MB of buffers: AUTO keeps the shard on chip) and 2^23 elements with R = 2 and 8 (252 and
+    352 MB, of which a launch stores 117 MB: AUTO writes through); two steps, every element against the oracle."""
     n = 1 << log2n
     sh = Shard([n - 4096 * 100 - 3, 4096 * 100 + 3], [0.01, 0.0], R, unfused=False)
     assert cc.cc_plan_layout(sh.plans[0]) == (1024, 128, policy)
@@ -188,7 +188,8 @@ def test_mid_size_shard_under_the_automatic_cache_policy(fn, ofn, log2n, R, poli
 
 @pytest.mark.parametrize("fn,ofn,numels,R,why", [
     (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 3584 - 7, 3, 9], 16, "just over 200 MiB: written through, 14 rounds of runs and two workgroups behind them"),
-    (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 5000 + 1, 17, 1024 * 503], 16, "over 300 MiB: a list goes back to non-temporal stores"),
+    (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 5000 + 1, 17, 1024 * 503], 16, "over 300 MiB: still written through"),
+    (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 21070 - 7, 5], 1, "288 MiB stored and more: non-temporal stores"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 7900 + 5, 11], 1, "176 MiB stored per step, just below: both sweeps write through"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 7907 + 5, 11], 1, "and just over: the second sweep stores non-temporally"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 512, 1024 * 511 + 3, 1024 * 512, 17, 1024 * 512, 1024 * 500 + 1, 1024 * 512, 1024 * 509 + 1023, 1024 * 20], 16,
