@@ -30,34 +30,31 @@ inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored)
     if (footprint < kResidentMaxBytes) return CC_CACHE_RESIDENT;
     return stored < kWriteThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
 }
-// LAMB's two sweeps want different stores once the shard has outgrown the Infinity Cache: written through in the first,
-// whose m' and v' the second reads again, and in the second, whose output nobody reads before the next step,
-// non-temporal from this many stored bytes per step on.  BERT-Large list in slices, R = 8, us with write-through in both /
-// write-through and non-temporal: 51.1 / 53.7 at 5.3 M elements, 100.7 / 102.7 at 11.2 M, but 127.9 / 124.3 at 14 M,
-// 194 / 180 at 21 M, 379 / 357 at 42 M (non-temporal in both: 372).
-constexpr uint64_t kLambThroughMaxStoreBytes = 176ull << 20;
+// LAMB goes by the 8 bytes per element that its first sweep stores, up to 36 Mi elements.  Beyond that its two sweeps want
+// different stores: written through in the first, whose m' and v' the second reads again, non-temporal in the second, whose
+// output nobody reads before the next step.  BERT-Large list in slices, R = 8, 42 M elements, non-temporal in both / write-through and
+// non-temporal / write-through in both, us: back to back 370 / 349 / 353, behind matrix products and pointwise passes 375 / 360 /
+// 353, three shards in turn 372 / 350 / 376.  Below, write-through in both is the better one wherever a program steps one shard
+// (write-through and non-temporal / write-through in both, back to back, behind products, with the gradient slices written after
+// those, behind a copy: 121.6 / 117.4, 127.1 / 126.7, 119.7 / 120.1, 132.5 / 129.7 at 14 M, 231.0 / 225.4, 238.8 / 237.3, 241.2 /
+// 231.5, 251.6 / 246.2 at 28 M), if not with three in turn (122.3 / 124.6 and 234.5 / 250.0).
 
 // What a plan's small-chunk kernels use, by kernel family (cc_cache_policy values).
 struct CachePolicies {
     int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step (what cc_plan_layout reports) and the unfused pipelines: reduce, Adam from the sum, cast
     int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep
-    int32_t lamb2 = CC_CACHE_STREAMING;         // ... and its second
-    int32_t unfused_lamb = CC_CACHE_STREAMING;  // LAMB's two sweeps in the unfused pipeline, by the bytes that its first one stores
+    int32_t lamb = CC_CACHE_STREAMING;          // ... and its second, and both in the unfused pipeline
 };
 // one_sweep: the chunks are one sweep of a workgroup (1024 elements).  LAMB's pair holds for those only: with 2048-element
-// chunks, which a caller has to ask for, it costs LAMB on 25 M elements 210.5 -> 224.9 us (R = 8, one shard step after step).
+// chunks, which a caller has to ask for, both sweeps keep the same.
 inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool grad_f32, bool one_sweep)
 {
-    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked, asked};
-    const uint64_t footprint = step_footprint(numel, R, grad_f32), stored = numel * kAdamStoreBytes;
+    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked};
+    const uint64_t footprint = step_footprint(numel, R, grad_f32);
     CachePolicies c;
-    c.adam = auto_cache_policy(footprint, stored);
-    c.unfused_lamb = auto_cache_policy(footprint, numel * kLambStoreBytes);
-    if (footprint < kResidentMaxBytes || !one_sweep) c.lamb1 = c.lamb2 = c.unfused_lamb;
-    else {
-        c.lamb1 = CC_CACHE_WRITE_THROUGH;
-        c.lamb2 = stored < kLambThroughMaxStoreBytes ? CC_CACHE_WRITE_THROUGH : CC_CACHE_STREAMING;
-    }
+    c.adam = auto_cache_policy(footprint, numel * kAdamStoreBytes);
+    c.lamb = auto_cache_policy(footprint, numel * kLambStoreBytes);
+    c.lamb1 = footprint < kResidentMaxBytes || !one_sweep ? c.lamb : CC_CACHE_WRITE_THROUGH;
     return c;
 }
 

@@ -20,7 +20,7 @@ int main(int argc, char **argv)
 {
     for (int i = 1; i + 4 < argc; i += 5) {
         const ccf::CachePolicies c = ccf::cache_policies(atoi(argv[i]), strtoull(argv[i + 1], nullptr, 10), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]) != 0);
-        printf("%d %d %d %d\n", c.adam, c.lamb1, c.lamb2, c.unfused_lamb);
+        printf("%d %d %d\n", c.adam, c.lamb1, c.lamb);
     }
     return 0;
 }
@@ -49,17 +49,17 @@ def below_and_at(nbytes, per_element):
 def test_automatic_policies_at_their_bounds(policies, R, f32):
     per = (4 if f32 else 2) * R + 26
     below, at = below_and_at(4 * MIB, per)
-    assert policies(AUTO, below, R, f32) == (STREAM,) * 4
-    assert policies(AUTO, at, R, f32) == (RESIDENT,) * 4
+    assert policies(AUTO, below, R, f32) == (STREAM,) * 3
+    assert policies(AUTO, at, R, f32) == (RESIDENT,) * 3
     below, at = below_and_at(200 * MIB, per)
-    assert policies(AUTO, below, R, f32) == (RESIDENT,) * 4
-    assert policies(AUTO, at, R, f32) == (THROUGH,) * 4
+    assert policies(AUTO, below, R, f32) == (RESIDENT,) * 3
+    assert policies(AUTO, at, R, f32) == (THROUGH,) * 3
     below, at = below_and_at(288 * MIB, 14)                   # the Adam step's own stores, for a list as for one tensor
     assert [policies(AUTO, n, R, f32)[0] for n in (below, at)] == [THROUGH, STREAM]
-    # fused LAMB writes its first sweep through from 200 MiB of buffers on, its second until 176 MiB are stored per step
-    below, at = below_and_at(176 * MIB, 14)
-    assert [policies(AUTO, n, R, f32)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (THROUGH, STREAM)]
-    assert policies(AUTO, 1 << 30, R, f32)[1:3] == (THROUGH, STREAM)
+    # LAMB writes both sweeps through until its first one stores 288 MiB, then the first only
+    below, at = below_and_at(288 * MIB, 8)
+    assert [policies(AUTO, n, R, f32)[1:] for n in (below, at)] == [(THROUGH, THROUGH), (THROUGH, STREAM)]
+    assert policies(AUTO, 1 << 30, R, f32)[1:] == (THROUGH, STREAM)
 
 
 @pytest.mark.parametrize("R,f32", [(1, False), (8, False), (16, False), (4, True)])
@@ -67,9 +67,9 @@ def test_the_unfused_pipelines_go_by_what_one_of_their_launches_stores(policies,
     """Write-through from 200 MiB of buffers while a launch stores less than 288 MiB: 14 bytes per element in Adam's update,
     8 in LAMB's first sweep, so the two pipelines change at 20.6 and 36 Mi elements."""
     below, at = below_and_at(288 * MIB, 14)
-    assert [policies(AUTO, n, R, f32)[::3] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, THROUGH)]
+    assert [policies(AUTO, n, R, f32)[::2] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, THROUGH)]
     below, at = below_and_at(288 * MIB, 8)
-    assert [policies(AUTO, n, R, f32)[::3] for n in (below, at)] == [(STREAM, THROUGH), (STREAM, STREAM)]
+    assert [policies(AUTO, n, R, f32)[::2] for n in (below, at)] == [(STREAM, THROUGH), (STREAM, STREAM)]
 
 
 @pytest.mark.parametrize("R,f32", [(1, False), (8, False), (4, True)])
@@ -78,15 +78,15 @@ def test_chunks_of_several_sweeps_go_by_what_a_launch_stores(policies, R, f32):
     below, at = below_and_at(288 * MIB, 14)
     assert [policies(AUTO, n, R, f32, False)[0] for n in (below, at)] == [THROUGH, STREAM]
     below, at = below_and_at(288 * MIB, 8)
-    assert [policies(AUTO, n, R, f32, False)[1:3] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, STREAM)]
+    assert [policies(AUTO, n, R, f32, False)[1:] for n in (below, at)] == [(THROUGH, THROUGH), (STREAM, STREAM)]
     below, at = below_and_at(200 * MIB, (4 if f32 else 2) * R + 26)
-    assert policies(AUTO, below, R, f32, False) == (RESIDENT,) * 4
+    assert policies(AUTO, below, R, f32, False) == (RESIDENT,) * 3
 
 
 def test_a_policy_that_was_asked_for_holds_everywhere(policies):
     for p in (STREAM, RESIDENT, THROUGH):
         for n in (100, 1 << 22, 1 << 25):
-            assert policies(p, n, 8, False) == (p,) * 4
+            assert policies(p, n, 8, False) == (p,) * 3
 
 
 TUNER = r"""
@@ -109,7 +109,7 @@ int main()
                     for (const auto &c : cand) {
                         const ccf::CachePolicies q = ccf::cache_policies(c.cache, numel, R, false, true);
                         if (c.chunk_elems != 1024 || c.schedule != CC_SCHEDULE_PER_CHUNK) continue;
-                        found += optimizer == 0 ? q.adam == a.adam : q.lamb1 == a.lamb1 && q.lamb2 == a.lamb2;
+                        found += optimizer == 0 ? q.adam == a.adam : q.lamb1 == a.lamb1 && q.lamb == a.lamb;
                     }
                     if (!found) { printf("optimizer %d, %llu elements, R = %d\n", optimizer, (unsigned long long)numel, R); return 2; }
                 }
