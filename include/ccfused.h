@@ -147,7 +147,8 @@ int cc_plan_destroy(cc_plan *plan);
  *                          order from a counter and keep the next chunk's loads in flight; needs the default
  *                          chunk size of large shards (cc_default_chunk_elems()).
  *   CC_SCHEDULE_AUTO       (default) ordered for large shards, per chunk for small ones.
- * cc_plan_schedule reports what the plan will use (schedule: ORDERED or PER_CHUNK; workgroups per launch).
+ * cc_plan_schedule reports what the plan will use (schedule: ORDERED or PER_CHUNK; workgroups per launch, which is the
+ * number of chunks for PER_CHUNK, but see cc_plan_layout for the one kernel that launches more).
  */
 typedef enum cc_schedule { CC_SCHEDULE_AUTO = 0, CC_SCHEDULE_PER_CHUNK = 1, CC_SCHEDULE_ORDERED = 2 } cc_schedule;
 int cc_plan_set_schedule(cc_plan *plan, int32_t schedule, int32_t workgroups);
@@ -159,7 +160,7 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  * cc_plan_layout reports what the plan will use (each pointer may be NULL): chunk size, threads per workgroup,
  * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).  (One tensor in chunks below 4096
  * elements whose step's buffers total 200 MiB and more is the exception: there the fused Adam step runs single-wave
- * workgroups of 256 elements.)
+ * workgroups of 256 elements, unless the caller has asked for CC_CACHE_RESIDENT.)
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);
@@ -186,9 +187,9 @@ int cc_plan_set_cache_policy(cc_plan *plan, int32_t policy);
  * step (optimizer 0 = Adam, 1 = LAMB) a few times under each candidate (one workgroup per chunk for every chunk size
  * the plan was prepared for, with every cache policy that exists for it, and for LAMB with AUTO as well; ordered with
  * compute units / 2, x 1 and x 2 workgroups on the 4096-element chunks), timed with events on `hip_stream`, and leaves
- * the plan set to the fastest.  The trial steps are ordinary steps on the caller's buffers: they write the out buffers and the flag, never the in
- * buffers, so the plan must be out of place (CC_ERR_ALIAS otherwise) and the caller must not have adopted the out
- * buffers' contents.  Synchronises the stream.  best_ms / per_chunk_ms (each may be NULL) receive the time per step
+ * the plan set to the fastest.  The trial steps are ordinary steps on the caller's buffers: they write the out buffers and
+ * the flag, never the in buffers, so the plan must be out of place (CC_ERR_ALIAS otherwise) and the caller must not have
+ * adopted the out buffers' contents.  Synchronises the stream.  best_ms / per_chunk_ms (each may be NULL) receive the time per step
  * of the schedule kept and of one workgroup per chunk.
  */
 int cc_plan_autotune(cc_plan *plan, const cc_hparams *hp, int32_t optimizer, int32_t *d_overflow_flag,

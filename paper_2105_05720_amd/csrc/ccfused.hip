@@ -586,7 +586,7 @@ static __device__ __align__(256) unsigned char scratch[sizeof(ccf::FlagScratch)]
 
 namespace {
 
-constexpr uint64_t kStaticMaxElems = 64ull << 20;        // 65536 workgroups of 1024 elements
+constexpr uint64_t kStaticMaxElems = 64ull << 20;        // 65536 workgroups of 1024 elements, or 262144 of 256 (see kFlatPiece)
 constexpr int kMaxDevices = 64;
 std::mutex g_static_mutex;
 ccf::FlagScratch *g_static_scratch[kMaxDevices] = {};

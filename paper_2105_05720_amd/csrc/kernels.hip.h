@@ -187,8 +187,10 @@ template <class Mem> __device__ __forceinline__ void st_f16x4(gbytes b, uint32_t
 
 // ---- where a workgroup works -----------------------------------------------------------------------------------
 // Descriptors and table entries are constant while a kernel runs, and are read through pointers that say so: behind the
-// flag's atomic and the stores written in assembly the compiler otherwise takes them for memory that may change, fetches
-// them with vector loads and keeps every buffer's address in vector registers (R = 8 fused Adam: 118 registers, 104 with them).
+// flag's atomic and the stores written in assembly the compiler otherwise takes them for memory that may change, and may
+// fetch them with vector loads and keep every buffer's address in vector registers.  Vector registers of the list's fused
+// Adam kernel with addresses there / in scalar registers (-Rpass-analysis=kernel-resource-usage): R = 8 written through
+// 118 / 104, non-temporal 118 / 114; R = 16 219 / 140 and 219 / 149.
 #define CCF_CONSTANT __attribute__((address_space(4)))
 typedef const CCF_CONSTANT DevTensor *Descriptor;
 typedef const CCF_CONSTANT struct Chunk *ChunkEntry;
@@ -230,7 +232,7 @@ __device__ __forceinline__ Where locate_at(const DevTensor *__restrict__ tensors
 // step (same machine, with / without: 4.70 / 4.90 us on 398 tensors in 571 chunks, 9.60 / 9.90 us on 10 tensors in
 // 1280 chunks).
 constexpr uint32_t kChunkRunLog2 = 5;
-constexpr int kLineOfGrads = 7;        // grad[7] ends the descriptor's second cache line
+constexpr int kLineOfGrads = 7;
 // LAST_FIRST: a second sweep over a shard bound by HBM takes the chunks from the other end, and so finds on chip what the
 // first sweep touched last.  LAMB, R = 8, from the same end / from the other: 353 / 350.5 us at 42 M elements of the BERT-Large
 // list, 482 / 475.5 at 56 M, R = 1 one tensor of 40 M elements 249.5 / 245.5; up to 21 M elements within 1 %.  The ordered
@@ -249,7 +251,9 @@ __device__ __forceinline__ Where locate(const DevTensor *__restrict__ tensors, c
     Where wh;
     wh.t = (Descriptor)tensors + tensor;
     // Fields from all over the descriptor before the first is looked at, so that its cache lines arrive together.  Left
-    // alone the compiler asks for the length, waits, and then asks for the rest.
+    // alone the compiler asks for the length, waits, and then asks for the rest.  Descriptors are 224 bytes apart, so every
+    // other one starts in the middle of a 64-byte line; the length, grad[0], grad[7] and the index lie in all of the lines
+    // that up to eight slices need.  With more, an entry that starts on a line gets the line of grad[8] to grad[15] later.
     uint32_t own_index = wh.t->chunk_index, own_tensor = wh.t->tensor;
     asm volatile("" : "+s"(own_index), "+s"(own_tensor) : "s"(wh.t->numel), "s"(wh.t->grad[0]), "s"(wh.t->grad[kLineOfGrads]));
     wh.tensor = own_tensor;
@@ -397,8 +401,11 @@ struct FlagCount {
 //   void compute(Regs&);                           arithmetic on the group
 //   void store(const Regs&, uint32_t e) const;     vector stores
 //   void single(uint32_t j);                       one element, scalar accesses (ragged end of a tensor)
-// A sweep is two groups BLOCK*kPack elements apart.  A full sweep issues the loads of both groups, then computes
-// and stores; the ragged end of a chunk (only a tensor's last chunk has one) falls back group by group.
+// and, where its chunks go through a Sweep, compute() in two parts:
+//   void reduce(Regs&);                            what the overflow flag needs (sweep_and_publish only)
+//   void update(Regs&);                            the rest; called for lanes whose pack is inside the chunk only
+// A sweep is GROUPS groups, BLOCK*kPack elements apart: it issues the loads of all of them, then computes and stores.
+
 // The last len % kPack elements of a chunk: one lane each, so that they cost one trip to memory together (one lane going
 // through three of them cost three).
 template <class Op>
@@ -408,6 +415,7 @@ __device__ __forceinline__ void ragged_end(Op &op, uint32_t len)
     if (threadIdx.x < (len & kMask)) op.single((len & ~kMask) + threadIdx.x);
 }
 
+// A chunk of any length: full sweeps, then group by group.
 template <int BLOCK, class Op, int GROUPS = 2>
 __device__ __forceinline__ void stream_chunk(Op &op, uint32_t len)
 {

@@ -35,9 +35,11 @@ constexpr unsigned kSpreadLds = 24000;
 // One tensor that does not fit the Infinity Cache and stays below the ordered schedule: single-wave workgroups of one
 // group per lane, in grid order, and so few of them per compute unit (LDS that nobody uses again) that the addresses in
 // flight are a narrow window that moves through all streams.  Without a table a workgroup starts its loads at once, so a
-// small one costs nothing.  How few depends on what a wave has in flight, 4 (bytes of a slice element x R + 12) per lane:
-// the reservation that measured best was 10000 bytes at R = 1, 11600 at 2, 13312 at 4, 16000 at 8 and for four fp32
-// slices; short launches want more waves (5 M elements, R = 8: 32.3 us with 10000, 33.7 with 16000).  us, 128-thread
+// small one costs nothing.  How few depends on what a wave has in flight, 4 (bytes of a slice element x R + 12) per lane.
+// The reservation is a straight line in that, close to what measured best (in parentheses): 10000 bytes at R = 1 (10000),
+// 10800 at 2 (11600), 12400 at 4 (13312), 15600 at 8 and for four fp32 slices (16000), i.e. 16, 15, 13 and 10 workgroups per
+// compute unit, one more than the best at R = 2 and 4; short launches want more waves (5 M elements, R = 8: 32.3 us with
+// 10000, 33.7 with 16000).  us, 128-thread
 // workgroups per 1024 elements / this: R = 8 33.1 / 32.3 at 5 M elements, 60.4 / 57.3 at 8.4 M, 172 / 165 at 25 M, 419 /
 // 393 at 60 M; R = 1 139 / 133 at 30 M; R = 2 80.8 / 75.4 at 16 M; R = 16 101 / 97 at 10 M, 377 / 378 at 40 M; four fp32
 // slices in place 90.8 / 82.5 at 12.3 M, 283 / 255 at 40 M.
