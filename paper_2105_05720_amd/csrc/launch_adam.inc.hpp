@@ -49,8 +49,9 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
         }
         return;
     }
+    const unsigned lds = p->spread ? list_lds(p->numel, p->R, GF32, std::is_same<MEM, Streaming>::value) : 0u;
     switch (p->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((fused_adam_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, p->spread ? kSpreadLds : 0u, st, L.table_tensors(), L.table_chunks(), s, p->d_flag_scratch, flag); break;
+#define CASE(r) case r: hipLaunchKernelGGL((fused_adam_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, lds, st, L.table_tensors(), L.table_chunks(), s, p->d_flag_scratch, flag); break;
         FOR_EACH_R(CASE)
 #undef CASE
     }

@@ -1,0 +1,54 @@
+// How many workgroups of the fused Adam kernels share a compute unit on shards bound by HBM, set through LDS that the launch
+// asks for and nobody uses.  No HIP in here: the host can run it as well.
+#pragma once
+
+#include <stdint.h>
+
+#include "cache_rules.hpp"
+
+namespace ccf {
+
+// Chunks of 1024 elements of a shard that does not fit the Infinity Cache (step's buffers of kResidentMaxBytes and more) are
+// bound by HBM, and what the addresses in flight look like decides: every XCD takes runs of 32 chunks (piece_in_runs), and the
+// fused Adam kernel asks for LDS that nobody uses, so that six of its 128-thread workgroups fit a compute unit instead of
+// up to sixteen.  Together, us before / runs only / runs and six workgroups: 36.6 / 36.1 / 35.9 at 5.3 M elements, 82.0 /
+// 81.1 / 80.3 at 11.2 M, 389.2 / 385.7 / 382.9 at 56 M.  LAMB's first sweep adds up its chunk behind a barrier and cannot
+// spare the waves (42 M elements: 357 us for both phases, 382 us with ten waves per compute unit).
+//
+// Once a step stores too much to write through (kWriteThroughMaxStoreBytes), a list with more than 16 bytes of slices per element is left four workgroups per compute
+// unit, and three with more than eight fp32 slices: with the addresses in scalar registers (see Descriptor) six of them hold
+// more streams in flight than DRAM likes, where registers used to keep them at four.  BERT-Large list in slices, back to back and
+// behind a 2 GiB copy, us before / six / four / three: 56 M elements, R = 12 455 / 469 / 456 / 490 and 458 / 473 / 458 / 510, R = 16 532 /
+// 547 / 537 / 564 and 527 / 552 / 538 / 586, R = 9 401 / 409 / 403 / 444; 28 M, R = 16 266 / 272 / 266 / 283 and 265 / 276 / 269 / 299;
+// twelve fp32 slices, 28 M 353 / 359 / 358 / 344 and 357 / 364 / 360 / 349, 56 M 720 / 723 / 716 / 689; eight, 28 M 285 / 273 / 269 /
+// 268, 42 M with the slices written just before 431 / 414 / 403 / 408.  While the stores are written through, six is right or
+// within 1 % (R = 12, 9.3 M elements 70.7 / 69.3 / 71.4 / 84.5).
+constexpr unsigned kSpreadLds = 24000, kFourWorkgroupsLds = 40000, kThreeWorkgroupsLds = 54000;   // of 160 KiB
+constexpr int kSixWorkgroupsMaxSliceBytes = 16, kFourWorkgroupsMaxF32Slices = 8;
+inline unsigned list_lds(uint64_t numel, int R, bool grad_f32, bool non_temporal_stores)
+{
+    const bool large = non_temporal_stores && numel * kAdamStoreBytes >= kWriteThroughMaxStoreBytes;
+    if (!large || (grad_f32 ? 4 : 2) * R <= kSixWorkgroupsMaxSliceBytes) return kSpreadLds;
+    return grad_f32 && R > kFourWorkgroupsMaxF32Slices ? kThreeWorkgroupsLds : kFourWorkgroupsLds;
+}
+
+// One tensor that does not fit the Infinity Cache and stays below the ordered schedule: single-wave workgroups of one
+// group per lane, in grid order, and so few of them per compute unit (LDS that nobody uses again) that the addresses in
+// flight are a narrow window that moves through all streams.  Without a table a workgroup starts its loads at once, so a
+// small one costs nothing.  How few depends on what a wave has in flight, 4 (bytes of a slice element x R + 12) per lane.
+// The reservation is a straight line in that, close to what measured best (in parentheses): 10000 bytes at R = 1 (10000),
+// 10800 at 2 (11600), 12400 at 4 (13312), 15600 at 8 and for four fp32 slices (16000), i.e. 16, 15, 13 and 10 workgroups per
+// compute unit, one more than the best at R = 2 and 4; short launches want more waves (5 M elements, R = 8: 32.3 us with
+// 10000, 33.7 with 16000).  us, one shard back to back, 128-thread workgroups per 1024 elements / this: R = 8 33 / 32 at 5 M
+// elements, 176 / 166 at 25 M, 432 / 397 at 60 M; R = 1 141 / 133 at 30 M; R = 2 199 / 189 at 40 M; R = 16 88 / 82 at 10 M, 403 / 377 at
+// 40 M, 577 / 566 at 60 M; four fp32 slices 74 / 74 at 12 M (behind a 2 GiB copy 83 / 78), 298 / 256 at 40 M.
+constexpr int kFlatBlock = 64;
+constexpr uint32_t kFlatPiece = kFlatBlock * 4;
+constexpr uint64_t kFlatShortBytes = 300ull << 20, kFlatMaxElems = 1ull << 33;      // 2^31 threads: a launch has less than 2^32
+inline unsigned flat_lds(uint64_t footprint, uint32_t slice_bytes)        // slice_bytes: of all slices, per element
+{
+    const unsigned lds = 4400u + 400u * (slice_bytes + 12u);
+    return footprint < kFlatShortBytes ? 10000u : lds < 16000u ? lds : 16000u;
+}
+
+}  // namespace ccf

@@ -11,6 +11,7 @@
 #include "cache_rules.hpp"
 #include "ccfused.h"
 #include "kernels.hip.h"
+#include "occupancy.hpp"
 
 namespace ccf {
 
@@ -23,35 +24,6 @@ constexpr int kBigBlock = 512, kSmallBlock = 128;
 constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-chunk layout keeps a descriptor per chunk (224 B each)
 constexpr int kOrderedMaxF32Slices = 8;           // fp32 slices: the ordered schedule wins up to 8 (config-2 list: 3.18 against 3.41 ms), at 16 two chunks spill
 constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per compute unit a plan keeps one workgroup per chunk
-
-// Chunks of 1024 elements of a shard that does not fit the Infinity Cache (step's buffers of kResidentMaxBytes and more) are
-// bound by HBM, and what the addresses in flight look like decides: every XCD takes runs of 32 chunks (piece_in_runs), and the
-// fused Adam kernel asks for LDS that nobody uses, so that six of its 128-thread workgroups fit a compute unit instead of
-// up to sixteen.  Together, us before / runs only / runs and six workgroups: 36.6 / 36.1 / 35.9 at 5.3 M elements, 82.0 /
-// 81.1 / 80.3 at 11.2 M, 389.2 / 385.7 / 382.9 at 56 M.  LAMB's first sweep adds up its chunk behind a barrier and cannot
-// spare the waves (42 M elements: 357 us for both phases, 382 us with ten waves per compute unit).
-constexpr unsigned kSpreadLds = 24000;
-
-// One tensor that does not fit the Infinity Cache and stays below the ordered schedule: single-wave workgroups of one
-// group per lane, in grid order, and so few of them per compute unit (LDS that nobody uses again) that the addresses in
-// flight are a narrow window that moves through all streams.  Without a table a workgroup starts its loads at once, so a
-// small one costs nothing.  How few depends on what a wave has in flight, 4 (bytes of a slice element x R + 12) per lane.
-// The reservation is a straight line in that, close to what measured best (in parentheses): 10000 bytes at R = 1 (10000),
-// 10800 at 2 (11600), 12400 at 4 (13312), 15600 at 8 and for four fp32 slices (16000), i.e. 16, 15, 13 and 10 workgroups per
-// compute unit, one more than the best at R = 2 and 4; short launches want more waves (5 M elements, R = 8: 32.3 us with
-// 10000, 33.7 with 16000).  us, 128-thread
-// workgroups per 1024 elements / this: R = 8 33.1 / 32.3 at 5 M elements, 60.4 / 57.3 at 8.4 M, 172 / 165 at 25 M, 419 /
-// 393 at 60 M; R = 1 139 / 133 at 30 M; R = 2 80.8 / 75.4 at 16 M; R = 16 101 / 97 at 10 M, 377 / 378 at 40 M; four fp32
-// slices in place 90.8 / 82.5 at 12.3 M, 283 / 255 at 40 M.
-constexpr int kFlatBlock = 64;
-constexpr uint32_t kFlatPiece = kFlatBlock * 4;
-constexpr uint64_t kFlatShortBytes = 300ull << 20, kFlatMaxElems = 1ull << 33;      // 2^31 threads: a launch has less than 2^32
-inline unsigned flat_lds(uint64_t footprint, uint32_t slice_bytes)        // slice_bytes: of all slices, per element
-{
-    const unsigned lds = 4400u + 400u * (slice_bytes + 12u);
-    return footprint < kFlatShortBytes ? 10000u : lds < 16000u ? lds : 16000u;
-}
-
 
 // Records the message for cc_last_error() on this thread and returns the code.
 int fail(cc_status code, const char *fmt, ...);

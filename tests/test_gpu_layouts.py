@@ -190,6 +190,7 @@ def test_mid_size_shard_under_the_automatic_cache_policy(fn, ofn, log2n, R, poli
     (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 3584 - 7, 3, 9], 16, "just over 200 MiB: written through, 14 rounds of runs and two workgroups behind them"),
     (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 5000 + 1, 17, 1024 * 503], 16, "over 300 MiB: still written through"),
     (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 21070 - 7, 5], 1, "288 MiB stored and more: non-temporal stores"),
+    (cc.cc_fused_adam_step, oracle.adam_step, [1024 * 21070 - 5, 3], 9, "... and four workgroups per compute unit"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 7900 + 5, 11], 1, "both sweeps write through"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 31870 + 5, 11], 1, "288 MiB of moments and more: the second sweep stores non-temporally"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 512, 1024 * 511 + 3, 1024 * 512, 17, 1024 * 512, 1024 * 500 + 1, 1024 * 512, 1024 * 509 + 1023, 1024 * 20], 16,

@@ -1,0 +1,43 @@
+"""How many workgroups of the fused Adam kernels a compute unit holds on shards bound by HBM (csrc/occupancy.hpp), compiled for
+the host: the bounds that the header states, at and beside each of them."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MIB = 1 << 20
+
+MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "occupancy.hpp"
+
+int main(int, char **argv)
+{
+    printf("%u\n", ccf::list_lds(strtoull(argv[1], nullptr, 10), atoi(argv[2]), atoi(argv[3]) != 0, atoi(argv[4]) != 0));
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def per_cu(tmp_path_factory):
+    """Workgroups per compute unit of 160 KiB LDS."""
+    d = tmp_path_factory.mktemp("occupancy")
+    (d / "rules.cpp").write_text(MAIN)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
+
+    def ask(*args):
+        lds = int(subprocess.run([str(d / "rules")] + [str(int(x)) for x in args], capture_output=True, text=True, timeout=60, check=True).stdout)
+        assert 0 < lds < 64 * 1024                                       # what a launch may ask for without an attribute
+        return 160 * 1024 // lds
+    return ask
+
+
+def test_lists(per_cu):
+    large = -(-288 * MIB // 14)                                          # from here on the stores are non-temporal
+    for R, f32, n in [(1, 0, 6), (8, 0, 6), (9, 0, 4), (16, 0, 4), (4, 1, 6), (5, 1, 4), (8, 1, 4), (9, 1, 3), (16, 1, 3)]:
+        assert [per_cu(k, R, f32, nt) for k, nt in ((large - 1, 1), (large, 1), (1 << 26, 1))] == [6, n, n], (R, f32)
+        assert per_cu(large, R, f32, 0) == 6                             # written through because the caller asked for it
