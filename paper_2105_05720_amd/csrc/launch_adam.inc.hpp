@@ -13,9 +13,8 @@ namespace {
 template <int MODE, bool GF32, class MEM>
 void launch_flat_pieces(const DevTensor &t, int R, StepScalars s, FlagScratch *fs, int32_t *flag, hipStream_t st)
 {
-    constexpr uint32_t kSliceBytes = GF32 ? 4 : 2;
     const dim3 grid((unsigned)((t.numel + kFlatPiece - 1) / kFlatPiece)), block(kFlatBlock);
-    const unsigned lds = flat_lds(step_footprint(t.numel, R, GF32), kSliceBytes * (uint32_t)R);
+    const unsigned lds = flat_lds(t.numel, R, GF32, std::is_same<MEM, Streaming>::value);
     s.chunk_elems = kFlatPiece;
     switch (R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, kFlatBlock, GF32, 1, MEM>), grid, block, lds, st, t, s, fs, flag); break;

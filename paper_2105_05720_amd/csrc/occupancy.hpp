@@ -39,16 +39,25 @@ inline unsigned list_lds(uint64_t numel, int R, bool grad_f32, bool non_temporal
 // The reservation is a straight line in that, close to what measured best (in parentheses): 10000 bytes at R = 1 (10000),
 // 10800 at 2 (11600), 12400 at 4 (13312), 15600 at 8 and for four fp32 slices (16000), i.e. 16, 15, 13 and 10 workgroups per
 // compute unit, one more than the best at R = 2 and 4; short launches want more waves (5 M elements, R = 8: 32.3 us with
-// 10000, 33.7 with 16000).  us, one shard back to back, 128-thread workgroups per 1024 elements / this: R = 8 33 / 32 at 5 M
+// 10000, 33.7 with 16000).  So does a step on fp16 slices that writes through, where one shard is stepped by itself: at R = 8
+// and 12 the line ends at 13600 bytes (12 workgroups).  us before / with 15600 / 13600, back to back, with the slices written just
+// before, behind a 2 GiB copy: 7.6 M elements, R = 8 50.2 / 49.9 / 47.5, 51.7 / 52.8 / 50.3, 58.0 / 52.9 / 52.2; 11 M 70.8 / 70.6 / 67.2, 72.1 /
+// 72.7 / 69.7, 79.9 / 72.2 / 71.7; 14 M 86.5 / 88.1 / 85.6, 88.8 / 90.1 / 87.7, 97.6 / 90.6 / 91.0; three shards in turn 81.6 / 73.8 / 74.4
+// at 11 M; 12 M, R = 12 86.8 / 85.7 / 84.6.  R = 16 and fp32 slices are 0 to 2 % better off with 16000 (18 M, R = 16 behind a copy 178 /
+// 172 / 174; four fp32 slices, 12 M 84.0 / 77.8 / 78.6).  us, one shard back to back, 128-thread workgroups per 1024 elements / this: R = 8 33 / 32 at 5 M
 // elements, 176 / 166 at 25 M, 432 / 397 at 60 M; R = 1 141 / 133 at 30 M; R = 2 199 / 189 at 40 M; R = 16 88 / 82 at 10 M, 403 / 377 at
 // 40 M, 577 / 566 at 60 M; four fp32 slices 74 / 74 at 12 M (behind a 2 GiB copy 83 / 78), 298 / 256 at 40 M.
 constexpr int kFlatBlock = 64;
 constexpr uint32_t kFlatPiece = kFlatBlock * 4;
 constexpr uint64_t kFlatShortBytes = 300ull << 20, kFlatMaxElems = 1ull << 33;      // 2^31 threads: a launch has less than 2^32
-inline unsigned flat_lds(uint64_t footprint, uint32_t slice_bytes)        // slice_bytes: of all slices, per element
+constexpr unsigned kFlatMostLds = 16000, kFlatThroughMostLds = 13600;
+constexpr int kFlatThroughMaxR = 12;
+inline unsigned flat_lds(uint64_t numel, int R, bool grad_f32, bool non_temporal_stores)
 {
-    const unsigned lds = 4400u + 400u * (slice_bytes + 12u);
-    return footprint < kFlatShortBytes ? 10000u : lds < 16000u ? lds : 16000u;
+    if (step_footprint(numel, R, grad_f32) < kFlatShortBytes) return 10000u;
+    const unsigned lds = 4400u + 400u * ((grad_f32 ? 4u : 2u) * (unsigned)R + 12u);
+    const unsigned most = !non_temporal_stores && !grad_f32 && R <= kFlatThroughMaxR ? kFlatThroughMostLds : kFlatMostLds;
+    return lds < most ? lds : most;
 }
 
 }  // namespace ccf

@@ -15,7 +15,8 @@ MAIN = r"""
 
 int main(int, char **argv)
 {
-    printf("%u\n", ccf::list_lds(strtoull(argv[1], nullptr, 10), atoi(argv[2]), atoi(argv[3]) != 0, atoi(argv[4]) != 0));
+    const auto rule = argv[5][0] == 'l' ? ccf::list_lds : ccf::flat_lds;
+    printf("%u\n", rule(strtoull(argv[1], nullptr, 10), atoi(argv[2]), atoi(argv[3]) != 0, atoi(argv[4]) != 0));
     return 0;
 }
 """
@@ -29,8 +30,8 @@ def per_cu(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
                            "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
 
-    def ask(*args):
-        lds = int(subprocess.run([str(d / "rules")] + [str(int(x)) for x in args], capture_output=True, text=True, timeout=60, check=True).stdout)
+    def ask(*args, rule="list"):
+        lds = int(subprocess.run([str(d / "rules")] + [str(int(x)) for x in args] + [rule], capture_output=True, text=True, timeout=60, check=True).stdout)
         assert 0 < lds < 64 * 1024                                       # what a launch may ask for without an attribute
         return 160 * 1024 // lds
     return ask
@@ -41,3 +42,10 @@ def test_lists(per_cu):
     for R, f32, n in [(1, 0, 6), (8, 0, 6), (9, 0, 4), (16, 0, 4), (4, 1, 6), (5, 1, 4), (8, 1, 4), (9, 1, 3), (16, 1, 3)]:
         assert [per_cu(k, R, f32, nt) for k, nt in ((large - 1, 1), (large, 1), (1 << 26, 1))] == [6, n, n], (R, f32)
         assert per_cu(large, R, f32, 0) == 6                             # written through because the caller asked for it
+
+
+@pytest.mark.parametrize("R,f32,through,streamed", [(1, 0, 16, 16), (2, 0, 15, 15), (4, 0, 13, 13), (6, 0, 12, 11), (8, 0, 12, 10), (12, 0, 12, 10),
+                                                    (13, 0, 10, 10), (16, 0, 10, 10), (4, 1, 10, 10), (16, 1, 10, 10)])
+def test_one_tensor(per_cu, R, f32, through, streamed):
+    at = -(-300 * MIB // ((4 if f32 else 2) * R + 26))
+    assert [per_cu(n, R, f32, nt, rule="flat") for nt in (0, 1) for n in (at - 1, at, 1 << 26)] == [16, through, through, 16, streamed, streamed]
