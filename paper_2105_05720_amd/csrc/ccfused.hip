@@ -547,7 +547,7 @@ int check_hparams(const cc_hparams *hp, const void *flag, Opt opt, int32_t R, bo
 int check_step(const cc_plan *p, const cc_hparams *hp, const void *flag, Opt opt, StepScalars *s)
 {
     if (!p) return fail(CC_ERR_NULL, "plan is NULL");
-    s->runs = p->spread && chunks_in_runs(step_footprint(p->numel, p->R, p->grad_f32), opt == Opt::Lamb) ? 1u : 0u;
+    s->runs = p->spread ? 1u : 0u;
     return check_hparams(hp, flag, opt, p->R, p->in_place, p->lay().chunk_elems, s);
 }
 

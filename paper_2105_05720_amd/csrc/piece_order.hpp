@@ -26,16 +26,6 @@ CCF_ANYWHERE uint32_t piece_in_runs(uint32_t b, uint32_t grid)
     return (round << kRoundLog2) + ((in & 7u) << RUN_LOG2) + (in >> 3);
 }
 
-// Whether the small chunks of a plan's step are taken in runs, by the bytes of the step's buffers: from 200 MiB on, where
-// they do not stay in the Infinity Cache, in an Adam step; in a LAMB step from 240 MiB on, because both its sweeps are faster in
-// table order while most of the state they share is still on chip.  LAMB, us before there were runs / with runs / in table order
-// now: 5.3 M elements of the BERT-Large list, R = 8 (220 MiB) back to back 50.0 / 50.5 / 48.6, behind a 2 GiB copy 58.5 / 58.9 /
-// 57.0; one tensor of 4 M elements, R = 16 (221 MiB) 53.2 / 51.7 / 50.0 and 62.2 / 59.8 / 59.2, eight fp32 slices (221 MiB) with
-// the slices written just before 50.5 / 52.0 / 49.0; but 6 M elements of the list, R = 8 (252 MiB) 57.3 / 54.6 / 55.5 and 66.8 /
-// 63.8 / 64.6.
-constexpr uint64_t kAdamRunsMinBytes = 200ull << 20, kLambRunsMinBytes = 240ull << 20;
-inline bool chunks_in_runs(uint64_t step_bytes, bool lamb) { return step_bytes >= (lamb ? kLambRunsMinBytes : kAdamRunsMinBytes); }
-
 // A launch has less than 2^32 threads.  A call whose pieces would need more goes out as several launches of `most` elements
 // and what is left: launch(first element, elements) for each, in order.
 template <class Launch>

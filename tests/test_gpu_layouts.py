@@ -194,9 +194,7 @@ def test_mid_size_shard_under_the_automatic_cache_policy(fn, ofn, log2n, R, poli
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 7900 + 5, 11], 1, "both sweeps write through"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 5001, 1024 * 31870 + 5, 11], 1, "288 MiB of moments and more: the second sweep stores non-temporally"),
     (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 512, 1024 * 511 + 3, 1024 * 512, 17, 1024 * 512, 1024 * 500 + 1, 1024 * 512, 1024 * 509 + 1023, 1024 * 20], 16,
-     "no tensor above 512 chunks: the second sweep adds up the norms itself; 203 MiB, still in table order"),
-    (cc.cc_fused_lamb_step, oracle.lamb_step, [1024 * 512, 1024 * 511 + 3, 1024 * 512, 17, 1024 * 512, 1024 * 500 + 1, 1024 * 512, 1024 * 509 + 1023, 1024 * 512, 1024 * 260 + 2], 16,
-     "... 245 MiB: in runs from the end of the table"),
+     "no tensor above 512 chunks: the second sweep adds up the norms itself, in runs from the end of the table"),
 ])
 def test_chunks_in_runs(fn, ofn, numels, R, why):
     """Shards that do not fit the Infinity Cache: each XCD takes runs of 32 chunks and what is left behind the last full

@@ -30,10 +30,6 @@ int main()
     for (uint32_t x = 0; x < 8; ++x)                             // one XCD's workgroups b = x, x + 8, ... of the second round
         for (uint32_t k = 0; k < 64; ++k)
             if (ccf::piece_in_runs(512 + 8 * k + x, 1024) != 512 + 64 * x + k) { printf("XCD %u, %u\n", x, k); return 1; }
-    for (bool lamb : {false, true}) {                            // which steps take their chunks so
-        const uint64_t from = (lamb ? 240ull : 200ull) << 20;
-        if (ccf::chunks_in_runs(from - 1, lamb) || !ccf::chunks_in_runs(from, lamb) || ccf::chunks_in_runs(0, lamb) || !ccf::chunks_in_runs(~0ull, lamb)) { printf("steps in runs\n"); return 1; }
-    }
     const uint32_t most = 0x7fffffffu;                           // the largest grid a launch may have
     if (ccf::piece_in_runs(most - 1, most) != most - 1 || ccf::piece_in_runs(0, most) != 0) { printf("largest grid\n"); return 1; }
     for (uint64_t most : {1ull << 34, 512ull, 1024ull})
