@@ -175,7 +175,8 @@ int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_thr
  * RESIDENT while they total less than 200 MiB (4-24 % faster than STREAMING between 2^18 and 2^22 elements in the size
  * sweep); else WRITE_THROUGH while the Adam step stores less than 288 MiB (14 bytes per element: up to 20.5 Mi elements,
  * 8-12 % faster at 2^23 and 2^24); else STREAMING.  That is the Adam step's policy, which cc_plan_layout reports; LAMB stores
- * 8 bytes per element in its first sweep and goes by those, and from 288 MiB on still writes that sweep through.
+ * 8 bytes per element in its first sweep and goes by those, and from 288 MiB on still writes that sweep through; the unfused LAMB
+ * pipeline writes both its sweeps through from 200 MiB on.
  * cc_plan_autotune tries all three, and AUTO for LAMB.
  */
 typedef enum cc_cache_policy { CC_CACHE_AUTO = 0, CC_CACHE_STREAMING = 1, CC_CACHE_RESIDENT = 2, CC_CACHE_WRITE_THROUGH = 3 } cc_cache_policy;

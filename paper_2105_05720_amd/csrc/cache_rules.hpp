@@ -37,13 +37,17 @@ inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored)
 // 353, three shards in turn 372 / 350 / 376.  Below, write-through in both is the better one wherever a program steps one shard
 // (write-through and non-temporal / write-through in both, back to back, behind products, with the gradient slices written after
 // those, behind a copy: 121.6 / 117.4, 127.1 / 126.7, 119.7 / 120.1, 132.5 / 129.7 at 14 M, 231.0 / 225.4, 238.8 / 237.3, 241.2 /
-// 231.5, 251.6 / 246.2 at 28 M), if not with three in turn (122.3 / 124.6 and 234.5 / 250.0).
+// 231.5, 251.6 / 246.2 at 28 M), if not with three in turn (122.3 / 124.6 and 234.5 / 250.0).  At 56 to 60 M elements the pair is 3 to
+// 5 % ahead back to back and, with eight and more slices that were written just before, 0 to 3 % behind non-temporal in both.
+// The unfused pipeline's update reads in its second sweep what the first one wrote and hands its own output to the cast, so both
+// are written through: non-temporal in both / this, 42 M elements, R = 8 back to back 453 / 423, behind a copy 457 / 439; R = 1 363 / 337
+// and 370 / 352; 56 M, R = 8 606 / 569 and 611 / 591; one tensor of 60 M, R = 4 581 / 535 and 578 / 548.
 
 // What a plan's small-chunk kernels use, by kernel family (cc_cache_policy values).
 struct CachePolicies {
     int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step (what cc_plan_layout reports) and the unfused pipelines: reduce, Adam from the sum, cast
-    int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep
-    int32_t lamb = CC_CACHE_STREAMING;          // ... and its second, and both in the unfused pipeline
+    int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep, and both behind the unfused pipeline's reduce
+    int32_t lamb = CC_CACHE_STREAMING;          // fused LAMB's second sweep
 };
 // one_sweep: the chunks are one sweep of a workgroup (1024 elements).  LAMB's pair holds for those only: with 2048-element
 // chunks, which a caller has to ask for, both sweeps keep the same.

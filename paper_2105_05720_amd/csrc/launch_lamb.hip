@@ -39,7 +39,7 @@ void launch_lamb_phase1_from_sum(const cc_plan *p, const StepScalars &s, hipStre
     const Layout &L = p->lay();
     const dim3 grid((unsigned)L.chunks);
     if (p->ordered) hipLaunchKernelGGL((lamb_phase1_from_sum_ordered_kernel<kBigBlock>), dim3(ordered_grid(p)), dim3(kBigBlock), 0, st, ORDERED_ARGS(p, kSpanFromSum), s, p->d_partials, p->d_queue);
-    else BY_BLOCK_MEM(p, p->mem.lamb, hipLaunchKernelGGL((lamb_phase1_from_sum_kernel<BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials));
+    else BY_BLOCK_MEM(p, p->mem.lamb1, hipLaunchKernelGGL((lamb_phase1_from_sum_kernel<BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials));
 }
 
 int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st, bool emit16)
@@ -54,7 +54,7 @@ int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipS
     }
     const dim3 grid((unsigned)L.chunks);
     if (emit16) BY_BLOCK_MEM(p, p->mem.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
-    else BY_BLOCK_MEM(p, p->mem.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<false, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
+    else BY_BLOCK_MEM(p, p->mem.lamb1, hipLaunchKernelGGL((lamb_phase2_kernel<false, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
     return launched("lamb_phase2_kernel");
 }
 
