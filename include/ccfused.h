@@ -239,7 +239,8 @@ int cc_fused_adam_step_static(const cc_tensor *tensor, int32_t R, const cc_hpara
  * cc_fused_lamb_step = phase 1 then phase 2.  The two phases are exported separately so that a
  * cross-rank sum of the per-tensor norms can be placed between them.  The single call gives the same bits in two
  * launches instead of three when no tensor has more than 512 chunks: the workgroups of phase 2 then add up their own
- * tensor's partial sums (same additions, same order) instead of a per-tensor launch between the phases.
+ * tensor's partial sums (same additions, same order) instead of a per-tensor launch between the phases; and in one launch
+ * when the shard has at most 64 chunks of 1024 elements: the workgroups then wait for each other's sums.
  */
 int cc_fused_lamb_step(cc_plan *plan, const cc_hparams *hp, int32_t *d_overflow_flag, void *hip_stream);
 int cc_fused_lamb_phase1(cc_plan *plan, const cc_hparams *hp, int32_t *d_overflow_flag, void *hip_stream);
@@ -323,6 +324,11 @@ int cc_pattern_probe(const cc_tensor *tensor, int32_t R, int32_t what, int32_t c
 /* Waits for `hip_stream`, then reads the ordered schedule's ticket counter and finished-workgroup word of the plan
  * (both are zero between launches; a test aid). */
 int cc_plan_queue_state(cc_plan *plan, uint32_t *next_ticket, uint64_t *done_word, void *hip_stream);
+
+/* In a LAMB step of one launch (see cc_fused_lamb_step) a wave that has looked for the other workgroups' sums `polls` times in
+ * vain leaves its part of w to the last one that started, so that no wait depends on how many workgroups the device holds
+ * at a time.  Results do not depend on the limit (a test aid; polls >= 0). */
+int cc_plan_set_meeting_limit(cc_plan *plan, int32_t polls);
 
 /* What the current device reports about itself (any output pointer may be NULL): compute units, memory clock in
  * kHz and memory bus width in bits as hipDeviceGetAttribute gives them, total device memory in bytes. */

@@ -66,6 +66,7 @@ EXPORTS = {
     "cc_plan_layout": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "cc_plan_set_cache_policy": (C.c_int, [C.c_void_p, C.c_int32]),
     "cc_plan_reserve_unfused": (C.c_int, [C.c_void_p]),
+    "cc_plan_set_meeting_limit": (C.c_int, [C.c_void_p, C.c_int32]),
     "cc_plan_queue_state": (C.c_int, [C.c_void_p, C.POINTER(C.c_uint32), C.POINTER(C.c_uint64), C.c_void_p]),
     "cc_plan_autotune": (C.c_int, [C.c_void_p, C.POINTER(cc_hparams), C.c_int32, C.c_void_p, C.c_void_p,
                                    C.POINTER(C.c_float), C.POINTER(C.c_float)]),
@@ -279,6 +280,10 @@ def cc_plan_set_cache_policy(plan: Plan, policy: int = CC_CACHE_AUTO) -> None:
 
 def cc_plan_reserve_unfused(plan: Plan) -> None:
     _check(load().cc_plan_reserve_unfused(plan.handle))
+
+
+def cc_plan_set_meeting_limit(plan: Plan, polls: int) -> None:
+    _check(load().cc_plan_set_meeting_limit(plan.handle, polls))
 
 
 def cc_plan_queue_state(plan: Plan, stream=None):

@@ -362,8 +362,9 @@ int cc_plan_create_ex(const cc_tensor *tensors, int32_t T, int32_t R, int32_t ch
     PLAN_TRY(hipMalloc((void **)&p->d_partials, sizeof(double) * 2 * (size_t)(most_chunks + 1)));
     PLAN_TRY(hipMalloc((void **)&p->d_sums, sizeof(double) * 2 * (size_t)T));
     PLAN_TRY(hipMemset(p->d_sums, 0, sizeof(double) * 2 * (size_t)T));
-    PLAN_TRY(hipMalloc((void **)&p->d_flag_scratch, sizeof(FlagScratch)));
-    PLAN_TRY(hipMemset(p->d_flag_scratch, 0, sizeof(FlagScratch)));
+    PLAN_TRY(hipMalloc((void **)&p->d_meeting, sizeof(LambMeeting)));
+    PLAN_TRY(hipMemset(p->d_meeting, 0, sizeof(LambMeeting)));
+    p->d_flag_scratch = &p->d_meeting->flag;
     PLAN_TRY(hipMalloc((void **)&p->d_queue, sizeof(WorkQueue)));
     PLAN_TRY(hipMemset(p->d_queue, 0, sizeof(WorkQueue)));
     {
@@ -459,6 +460,14 @@ int cc_plan_queue_state(cc_plan *p, uint32_t *next_ticket, uint64_t *done_word, 
     return CC_OK;
 }
 
+int cc_plan_set_meeting_limit(cc_plan *p, int32_t polls)
+{
+    if (!p) return fail(CC_ERR_NULL, "cc_plan_set_meeting_limit: plan is NULL");
+    if (polls < 0) return fail(CC_ERR_ARG, "cc_plan_set_meeting_limit: polls = %d", polls);
+    p->meeting_limit = (uint32_t)polls;
+    return CC_OK;
+}
+
 int cc_plan_schedule(const cc_plan *p, int32_t *schedule, int32_t *workgroups)
 {
     if (!p) return fail(CC_ERR_NULL, "cc_plan_schedule: plan is NULL");
@@ -474,7 +483,7 @@ int cc_plan_destroy(cc_plan *p)
     if (p->d_partials) (void)hipFree(p->d_partials);
     if (p->d_sums) (void)hipFree(p->d_sums);
     if (p->d_gsum) (void)hipFree(p->d_gsum);
-    if (p->d_flag_scratch) (void)hipFree(p->d_flag_scratch);
+    if (p->d_meeting) (void)hipFree(p->d_meeting);
     if (p->d_queue) (void)hipFree(p->d_queue);
     delete p;
     return CC_OK;
@@ -703,6 +712,7 @@ int cc_fused_lamb_step(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *st
     StepScalars s;
     int rc = check_step(p, hp, flag, Opt::Lamb, &s);
     if (rc) return rc;
+    if (lamb_in_one_launch(p)) return lamb_one_launch(p, s, flag, (hipStream_t)stream);
     if (norms_fold_into_phase2(p)) {
         // two launches instead of three: nobody reads the sums between the phases here
         hipStream_t st = (hipStream_t)stream;

@@ -684,12 +684,25 @@ struct GradSlices<R, false, MemT> {
         }
         S[0] = (float)a; S[1] = (float)b; S[2] = (float)c; S[3] = (float)d;
     }
+    // One element: loads, and their sum.
+    struct One { _Float16 g[R]; };
+    __device__ __forceinline__ void load1(One &x, uint32_t j) const
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) x.g[r] = *(const CCF_GLOBAL _Float16 *)(g[r] + j * 2);
+    }
+    __device__ __forceinline__ static float sum1(const One &x)
+    {
+        double S = (double)(float)x.g[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) S += (double)(float)x.g[r];
+        return (float)S;
+    }
     __device__ __forceinline__ float sum1(uint32_t j) const
     {
-        double S = (double)ld_f16(g[0], j * 2);
-#pragma unroll
-        for (int r = 1; r < R; ++r) S += (double)ld_f16(g[r], j * 2);
-        return (float)S;
+        One x;
+        load1(x, j);
+        return sum1(x);
     }
 };
 
@@ -719,12 +732,24 @@ struct GradSlices<R, true, MemT> {
         for (int r = 1; r < R; ++r) { a += (double)x.g[r].x; b += (double)x.g[r].y; c += (double)x.g[r].z; d += (double)x.g[r].w; }
         S[0] = (float)a; S[1] = (float)b; S[2] = (float)c; S[3] = (float)d;
     }
+    struct One { float g[R]; };
+    __device__ __forceinline__ void load1(One &x, uint32_t j) const
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) x.g[r] = ld_f32(g[r], j * 4);
+    }
+    __device__ __forceinline__ static float sum1(const One &x)
+    {
+        double S = x.g[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) S += (double)x.g[r];
+        return (float)S;
+    }
     __device__ __forceinline__ float sum1(uint32_t j) const
     {
-        double S = ld_f32(g[0], j * 4);
-#pragma unroll
-        for (int r = 1; r < R; ++r) S += (double)ld_f32(g[r], j * 4);
-        return (float)S;
+        One x;
+        load1(x, j);
+        return sum1(x);
     }
 };
 
@@ -1256,6 +1281,191 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
         op.scale(sw, su);
         return true;
     });
+}
+
+// LAMB in one launch, for shards of at most kMeetingChunks chunks (of 1024 elements).  Such a step is nothing but latency:
+// as two launches it pays for the end of a kernel, the start of the next and a second trip to memory between the partial
+// sums and their use.  Here every workgroup keeps its chunk in registers, publishes its sums and waits for those of the
+// others.  Same sums in the same order and the same update from the same values, so the same bits as in two launches.
+// Two launches / one, us per step, one tensor, R = 8, graph replay: 6.8 / 5.4 at 1024 elements, 7.6 / 5.7 at 10007, 8.0 / 6.5
+// at 30000, 8.7 / 7.5 at 65000; eager calls, which also save the host a launch, 7.5-9.2 / 5.1-5.9 up to 10007 elements.
+// Every wave polls every chunk's sums, so the gain shrinks with the number of chunks: with up to 256, four words per
+// lane, 8.5-9.4 / 8.5-8.6 at 128 chunks, 9.0-9.6 / 9.2-9.6 at 196, 9.0-9.6 / 9.8-10.0 at 254.
+//
+//   * A workgroup publishes its two sums as four words of 32 bits, each with the launch's tag next to it in one 64-bit
+//     word, so that a reader needs no order between the words and nothing has to be reset: words of other launches carry
+//     other tags (31 bits of the phase that FlagCount counts, which wrap).  The tag's lowest bit tells whether the workgroup
+//     saw an inf/NaN: with the sums a wave learns whether the step is to be skipped, before it writes w.  Lane i of every wave
+//     polls chunk i of its tensor, and the first word of chunk i of the shard.  (One chunk's words lie together: by word, 64
+//     chunks in four lines, a wave looks at fewer lines but the chunks' stores meet in them: 5.7 -> 6.4 us at 10007 elements.)
+//   * Every wait ends, however few of the workgroups the device holds at a time (a stream that may use one compute unit,
+//     other kernels in the way).  A workgroup publishes before it waits.  The wave that FlagCount finds to be the last
+//     arrival of the launch knows that all workgroups have started, so all of them will publish, and waits without a
+//     limit.  Any other wave gives up after `limit` polls: it moves the word `outcome` to (tag, ABANDONED) and leaves,
+//     its part of w unwritten.  The last arrival, once it has all sums, exchanges the word to (tag, CLOSED), and if
+//     that returns ABANDONED it computes the whole shard's w again from the step's inputs, which a LAMB step never
+//     overwrites.  A wave that finds CLOSED instead knows that every sum has been published and polls on.
+constexpr uint32_t kMeetingChunks = 64;
+struct LambMeeting {
+    FlagScratch flag;                                                // what the other kernels use
+    FlagScratch::Line outcome;
+    struct alignas(32) Sums { unsigned long long word[4]; } sums[kMeetingChunks];      // by chunk
+};
+constexpr unsigned long long kAbandoned = 1ull, kClosed = 2ull;
+
+__device__ __forceinline__ unsigned long long ld_word(const unsigned long long *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One look at the sums of a tensor's n chunks from `first` on and at the overflow marks of all `total` chunks of the shard.
+// True (for the whole wave) if all are there.
+__device__ __forceinline__ bool meet(const LambMeeting *mt, uint32_t first, uint32_t n, uint32_t total, uint32_t tag, double &sw, double &su,
+                                     bool &overflowed)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const bool others = n != total && lane < total, own = lane < n;
+    unsigned long long x[4] = {}, y = 0ull;
+    if (own) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = ld_word(&mt->sums[first + lane].word[k]);
+    }
+    if (others) y = ld_word(mt->sums[lane].word);
+    bool here = !others || (uint32_t)(y >> 33) == tag;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) here = here && (!own || (uint32_t)(x[k] >> 33) == tag);
+    if (__builtin_amdgcn_ballot_w64(!here) != 0ull) return false;
+    overflowed = __builtin_amdgcn_ballot_w64((((x[0] | y) >> 32) & 1ull) != 0ull) != 0ull;
+    sw = wave_sum(__hiloint2double((int)(uint32_t)x[1], (int)(uint32_t)x[0]));      // as tensor_sums adds up to 64 chunks;
+    su = wave_sum(__hiloint2double((int)(uint32_t)x[3], (int)(uint32_t)x[2]));      // lanes without one hold zeros
+    return true;
+}
+
+template <class Grad, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void lamb_one_launch_kernel(const DevTensor *__restrict__ per_chunk, StepScalars s,
+                                                                double *__restrict__ sums, LambMeeting *__restrict__ mt,
+                                                                int32_t *__restrict__ flag, uint32_t limit)
+{
+    typedef typename Grad::Mem Mem;
+    typedef LambPhase1Op<Grad> Op;
+    typedef Sweep<BLOCK, 2, Op> S;
+    FlagCount<BLOCK> fc;
+    fc.arrive(&mt->flag);
+    const Where wh = locate(per_chunk, nullptr, s);
+    Op op;
+    op.init(wh.t, wh.base, s);
+    // The whole packs and the ragged end's elements, all loads together.  (Lanes without one load the chunk's first.)
+    S sw;
+    const bool packs = wh.len >= Op::kPack, rest = threadIdx.x < (wh.len & (Op::kPack - 1));
+    const uint32_t j = (wh.len & ~(Op::kPack - 1u)) + threadIdx.x;
+    const uint32_t j1 = rest ? j : 0u;
+    typename Grad::One g1;
+    op.grad.load1(g1, j1);
+    float w1 = ld_f32(op.w_in, j1 * 4), m1 = ld_f32(op.m_in, j1 * 4), v1 = ld_f32(op.v_in, j1 * 4);
+    if (packs) sw.load(op, wh.len);
+    __builtin_amdgcn_sched_barrier(0);
+    fc.slot_level(&mt->flag);
+    __builtin_amdgcn_sched_barrier(0);
+    if (packs) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) op.reduce(sw.x[g]);
+    }
+    fc.top_level(&mt->flag, flag);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+        if (S::mine(g, wh.len)) op.update(sw.x[g]);
+    if (rest) op.one(Grad::sum1(g1), w1, m1, v1);
+    double dw = op.sw, du = op.su;
+    block_sum2<BLOCK>(dw, du);
+    const bool block_bad = __syncthreads_or(op.bad ? 1 : 0) != 0;
+    const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)fc.tag()) & 0x7fffffffu;
+    if (threadIdx.x < 4) {
+        const double x = threadIdx.x < 2 ? dw : du;
+        const uint32_t half = (uint32_t)((threadIdx.x & 1u) ? __double2hiint(x) : __double2loint(x));
+        const uint32_t mark = tag << 1 | (block_bad ? 1u : 0u);
+        __hip_atomic_store(&mt->sums[wh.slot].word[threadIdx.x], (unsigned long long)mark << 32 | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+        if (S::mine(g, wh.len)) op.store(sw.x[g], S::first(g));
+    if (rest) { st_f32(op.m_out, j * 4, m1); st_f32(op.v_out, j * 4, v1); }
+
+    const bool last = __builtin_amdgcn_ballot_w64(fc.launch_last) != 0ull;        // uniform: this wave is the last arrival
+    const unsigned long long abandoned = (unsigned long long)tag << 2 | kAbandoned, closed = (unsigned long long)tag << 2 | kClosed;
+    double tw = 0.0, tu = 0.0;
+    bool overflowed = false, patient = last, left = false;
+    for (uint32_t polls = 0; !meet(mt, wh.t->first_chunk, wh.t->num_chunks, gridDim.x, tag, tw, tu, overflowed); ++polls) {
+        __builtin_amdgcn_s_sleep(1);
+        if (patient || polls < limit) continue;
+        unsigned long long cur = 0ull;
+        if ((threadIdx.x & 63u) == 0u) {
+            cur = ld_word(&mt->outcome.word);
+            while (cur != abandoned && cur != closed)
+                if (__hip_atomic_compare_exchange_strong(&mt->outcome.word, &cur, abandoned, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) cur = abandoned;
+        }
+        if (__builtin_amdgcn_ballot_w64(cur == closed) == 0ull) { left = true; break; }
+        patient = true;
+    }
+    LambPhase2Op<true, Mem> p2;
+    const auto finish_pack = [&](const typename Op::Regs &x, uint32_t e) {
+        typename LambPhase2Op<true, Mem>::Regs y;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { y.w[k] = x.w[k]; y.m[k] = x.m[k]; y.v[k] = x.v[k]; }
+        p2.update(y);
+        p2.store(y, e);
+    };
+    if (!left) {
+        p2.init(wh.t, wh.base, s);
+        p2.scale(tw, tu);
+        if (wh.index == 0 && threadIdx.x == 0) { sums[2 * (uint64_t)wh.t->tensor] = tw; sums[2 * (uint64_t)wh.t->tensor + 1] = tu; }
+        if (!overflowed) {               // whole-step skip: w and w16 stay as they were
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+                if (S::mine(g, wh.len)) finish_pack(sw.x[g], S::first(g));
+            if (rest) {
+                const float wn = p2.one(w1, m1, v1);
+                st_f32(p2.w_out, j * 4, wn);
+                st_f16(p2.w16, j * 2, wn);
+            }
+        }
+    }
+    fc.finish(op.bad, &mt->flag, flag);
+    if (last) {
+        unsigned long long prev = 0ull;
+        if ((threadIdx.x & 63u) == 0u) prev = __hip_atomic_exchange(&mt->outcome.word, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_ballot_w64(prev == abandoned) != 0ull) {
+            // Some waves have left: everybody's w once more, by this wave alone.  Other waves write the same values.
+            for (uint32_t c = 0; c < gridDim.x; ++c) {
+                Where at;
+                at.t = (Descriptor)per_chunk + c;
+                at.index = at.t->chunk_index;
+                finish_where(at, s.chunk_elems);
+                while (!meet(mt, at.t->first_chunk, at.t->num_chunks, gridDim.x, tag, tw, tu, overflowed)) {}    // all are there
+                if (at.index == 0 && (threadIdx.x & 63u) == 0u) { sums[2 * (uint64_t)at.t->tensor] = tw; sums[2 * (uint64_t)at.t->tensor + 1] = tu; }
+                if (overflowed) continue;
+                Op again;
+                again.init(at.t, at.base, s);
+                p2.init(at.t, at.base, s);
+                p2.scale(tw, tu);
+                const auto finish_one = [&](float S, uint32_t e) {
+                    float w = ld_f32(again.w_in, e * 4), m = ld_f32(again.m_in, e * 4), v = ld_f32(again.v_in, e * 4);
+                    again.one(S, w, m, v);
+                    const float wn = p2.one(w, m, v);
+                    st_f32(p2.w_out, e * 4, wn);
+                    st_f16(p2.w16, e * 2, wn);
+                };
+                uint32_t e = (threadIdx.x & 63u) * Op::kPack;
+                for (; e + Op::kPack <= at.len; e += 64u * Op::kPack) {
+                    typename Op::Regs x;
+                    again.load(x, e);
+                    again.compute(x);
+                    finish_pack(x, e);
+                }
+                for (uint32_t r = (at.len & ~(Op::kPack - 1u)) + (threadIdx.x & 63u); r < at.len; r += 64u) finish_one(again.grad.sum1(r), r);
+            }
+        }
+    }
 }
 
 template <bool EMIT16, int BLOCK>

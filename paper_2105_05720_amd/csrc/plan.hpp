@@ -22,6 +22,9 @@ constexpr uint64_t kSmallShardElems = 64u << 20; // below this many elements the
 constexpr int32_t kMaxChunkElems = 1 << 24;      // lane offsets inside a chunk are 32-bit byte offsets
 constexpr int kBigBlock = 512, kSmallBlock = 128;
 constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-chunk layout keeps a descriptor per chunk (224 B each)
+// Looks of a wave at the other workgroups' sums before it gives up (see LambMeeting), a millisecond or two: longer than other
+// kernels commonly keep a small grid's last workgroups waiting, and about what the last arrival then takes for 64 chunks.
+constexpr uint32_t kMeetingPolls = 2048;
 constexpr int kOrderedMaxF32Slices = 8;           // fp32 slices: the ordered schedule wins up to 8 (config-2 list: 3.18 against 3.41 ms), at 16 two chunks spill
 constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per compute unit a plan keeps one workgroup per chunk
 
@@ -61,7 +64,9 @@ struct cc_plan {
     std::vector<ccf::Layout> layouts;       // one per chunk size the plan was prepared for
     int active = 0;                         // the layout the step calls use
     int32_t chunk_choice = 0;               // what the caller asked for (0 = the size rule)
-    ccf::FlagScratch *d_flag_scratch = nullptr;  // zero between launches
+    ccf::LambMeeting *d_meeting = nullptr;  // zero when the plan is created
+    ccf::FlagScratch *d_flag_scratch = nullptr;  // d_meeting->flag
+    uint32_t meeting_limit = ccf::kMeetingPolls;
     bool ordered = false;                   // large shards: persistent workgroups take chunks in table order
     int32_t schedule = CC_SCHEDULE_AUTO;    // what the caller asked for
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
@@ -136,6 +141,13 @@ int lamb_norms(cc_plan *p, hipStream_t st);
 // R = 8, us per step folded / three launches: 7.1 / 8.9 at one chunk, 9.2 / 10.7 at 128, 9.6 / 10.9 at 256, 11.4 / 11.6
 // at 512, but 16.5 / 14.3 at 1024.
 constexpr uint32_t kFoldNormsMaxChunks = 512;
+// Whether cc_fused_lamb_step is a single launch (see LambMeeting): one workgroup per 1024-element chunk, at most kMeetingChunks.
+inline bool lamb_in_one_launch(const cc_plan *p)
+{
+    const Layout &L = p->lay();
+    return !p->ordered && L.chunk_elems == kSmallChunkElems && L.chunks > 0 && L.chunks <= (int64_t)kMeetingChunks && L.d_per_chunk;
+}
+int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
 inline bool norms_fold_into_phase2(const cc_plan *p)
 {
     const Layout &L = p->lay();

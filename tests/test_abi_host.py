@@ -259,6 +259,7 @@ def test_step_calls_reject_null_plan_and_bad_copy_arguments():
     assert lib.cc_plan_set_cache_policy(None, 0) == cc.CC_ERR_NULL
     assert lib.cc_plan_reserve_unfused(None) == cc.CC_ERR_NULL
     assert lib.cc_plan_queue_state(None, None, None, None) == cc.CC_ERR_NULL
+    assert lib.cc_plan_set_meeting_limit(None, 0) == cc.CC_ERR_NULL
     assert lib.cc_pattern_probe(None, 4, 0, cc.CC_CACHE_STREAMING, 0x1000, None) == cc.CC_ERR_NULL
     t = cc._c_tensor(_tensor())
     assert lib.cc_pattern_probe(C.byref(t), 5, 0, cc.CC_CACHE_STREAMING, 0x1000, None) == cc.CC_ERR_ARG
