@@ -13,7 +13,7 @@ from concurrent.futures import ThreadPoolExecutor
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
-SOURCES = [os.path.join(CSRC, n) for n in ("ccfused.hip", "launch_adam_f16.hip", "launch_adam_f32.hip", "launch_lamb.hip",
+SOURCES = [os.path.join(CSRC, n) for n in ("ccfused.hip", "launch_adam_f16.hip", "launch_adam_f32.hip", "launch_lamb.hip", "launch_lamb_one.hip",
                                            "launch_unfused.hip")]
 EXPORTS_MAP = os.path.join(CSRC, "exports.map")
 DEPS = SOURCES + [os.path.join(CSRC, "kernels.hip.h"), os.path.join(CSRC, "plan.hpp"), os.path.join(CSRC, "piece_order.hpp"),

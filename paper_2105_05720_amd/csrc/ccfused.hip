@@ -321,6 +321,8 @@ int cc_plan_create_ex(const cc_tensor *tensors, int32_t T, int32_t R, int32_t ch
             d.num_chunks = (uint32_t)((x.numel + (uint64_t)ce - 1) / (uint64_t)ce);
             if (d.num_chunks > L.most_tensor_chunks) L.most_tensor_chunks = d.num_chunks;
             first += d.num_chunks;
+            d.first_group = L.groups;
+            L.groups += (d.num_chunks + 63u) / 64u;
         }
         std::vector<uint32_t> table;
         try {

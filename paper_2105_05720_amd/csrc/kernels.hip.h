@@ -53,7 +53,7 @@ struct DevTensor {
     uint32_t num_chunks;
     uint32_t tensor;          // index of this tensor in the plan's list
     uint32_t chunk_index;     // per-chunk copies of the descriptor only (see locate_at): which chunk of the tensor
-    uint32_t pad_;
+    uint32_t first_group;     // which group of 64 chunks its first one starts, counted over the shard (see LambMeeting)
 };
 
 // Chunk table entry: which tensor, and which chunk_elems-sized piece of it.
@@ -1283,33 +1283,39 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
     });
 }
 
-// LAMB in one launch, for shards of at most kMeetingChunks chunks (of 1024 elements).  Such a step is nothing but latency:
-// as two launches it pays for the end of a kernel, the start of the next and a second trip to memory between the partial
-// sums and their use.  Here every workgroup keeps its chunk in registers, publishes its sums and waits for those of the
-// others.  Same sums in the same order and the same update from the same values, so the same bits as in two launches.
+// LAMB in one launch, for shards of at most kMeetingMostChunks chunks (of 1024 elements).  Such a step is mostly latency: as
+// two launches it pays for the end of a kernel, the start of the next and a second trip to memory between the partial sums
+// and their use.  Here every workgroup keeps its chunk in registers, publishes its sums and waits for those of the others.
+// Same sums in the same order and the same update from the same values, so the same bits as in two launches.
 // Two launches / one, us per step, one tensor, R = 8, graph replay: 6.8 / 5.4 at 1024 elements, 7.6 / 5.7 at 10007, 8.0 / 6.5
 // at 30000, 8.7 / 7.5 at 65000; eager calls, which also save the host a launch, 7.5-9.2 / 5.1-5.9 up to 10007 elements.
-// Every wave polls every chunk's sums, so the gain shrinks with the number of chunks: with up to 256, four words per
-// lane, 8.5-9.4 / 8.5-8.6 at 128 chunks, 9.0-9.6 / 9.2-9.6 at 196, 9.0-9.6 / 9.8-10.0 at 254.
 //
 //   * A workgroup publishes its two sums as four words of 32 bits, each with the launch's tag next to it in one 64-bit
 //     word, so that a reader needs no order between the words and nothing has to be reset: words of other launches carry
 //     other tags (31 bits of the phase that FlagCount counts, which wrap).  The tag's lowest bit tells whether the workgroup
-//     saw an inf/NaN: with the sums a wave learns whether the step is to be skipped, before it writes w.  Lane i of every wave
-//     polls chunk i of its tensor, and the first word of chunk i of the shard.  (One chunk's words lie together: by word, 64
-//     chunks in four lines, a wave looks at fewer lines but the chunks' stores meet in them: 5.7 -> 6.4 us at 10007 elements.)
+//     saw an inf/NaN: with the sums a wave learns whether the step is to be skipped, before it writes w.  (One chunk's words
+//     lie together: by word, 64 chunks in four lines, a wave looks at fewer lines but the chunks' stores meet in them: 5.7 ->
+//     6.4 us at 10007 elements.)
+//   * Up to kMeetingChunks chunks lane i of every wave polls chunk i of its tensor, and the first word of chunk i of the shard.
+//     Beyond that (GROUPED) too many waves would look at too many lines (8.5 us at 128 chunks, 10.0 at 254, where two launches
+//     take 9.0 to 9.6): the second wave of every 64th workgroup of a tensor adds up 64 chunks and publishes the group's sums,
+//     and every wave polls groups.  They are published in kGroupCopies copies, one for the workgroups of each XCD, so that not
+//     all of them read the same lines, and polls are 0.4 us apart (at 1024 chunks 16.8 us with none between them, 16.1 with
+//     0.4, 15.5 with 1.3, which costs 0.6 at 100).
 //   * Every wait ends, however few of the workgroups the device holds at a time (a stream that may use one compute unit,
 //     other kernels in the way).  A workgroup publishes before it waits.  The wave that FlagCount finds to be the last
-//     arrival of the launch knows that all workgroups have started, so all of them will publish, and waits without a
-//     limit.  Any other wave gives up after `limit` polls: it moves the word `outcome` to (tag, ABANDONED) and leaves,
-//     its part of w unwritten.  The last arrival, once it has all sums, exchanges the word to (tag, CLOSED), and if
-//     that returns ABANDONED it computes the whole shard's w again from the step's inputs, which a LAMB step never
-//     overwrites.  A wave that finds CLOSED instead knows that every sum has been published and polls on.
-constexpr uint32_t kMeetingChunks = 64;
+//     arrival of the launch knows that all workgroups have started, so all of them will publish.  Any other wave, the one
+//     that adds up a group included, gives up after `limit` polls: it moves the word `outcome` to (tag, ABANDONED) and
+//     leaves, its part of w unwritten.  The last arrival waits until it has all it needs, and then exchanges the word to
+//     (tag, CLOSED), or, while groups are missing, until it finds ABANDONED there.  If it finds ABANDONED either way it
+//     computes the whole shard's w again, from the chunks' sums and the step's inputs, which a LAMB step never overwrites.
+//     A wave that finds CLOSED when it would give up knows that everything has been published and polls on.
+constexpr uint32_t kMeetingChunks = 64, kMeetingMostChunks = 512, kMeetingGroups = 64, kGroupCopies = 8;
 struct LambMeeting {
     FlagScratch flag;                                                // what the other kernels use
     FlagScratch::Line outcome;
-    struct alignas(32) Sums { unsigned long long word[4]; } sums[kMeetingChunks];      // by chunk
+    struct alignas(32) Sums { unsigned long long word[4]; };
+    Sums chunk[kMeetingMostChunks], group[kGroupCopies][kMeetingGroups];
 };
 constexpr unsigned long long kAbandoned = 1ull, kClosed = 2ull;
 
@@ -1318,37 +1324,57 @@ __device__ __forceinline__ unsigned long long ld_word(const unsigned long long *
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One look at the sums of a tensor's n chunks from `first` on and at the overflow marks of all `total` chunks of the shard.
-// True (for the whole wave) if all are there.
-__device__ __forceinline__ bool meet(const LambMeeting *mt, uint32_t first, uint32_t n, uint32_t total, uint32_t tag, double &sw, double &su,
-                                     bool &overflowed)
+// Word k of the sums (sw, su), with the launch's tag and the overflow mark.
+__device__ __forceinline__ void publish(LambMeeting::Sums *p, uint32_t k, uint32_t tag, bool bad, double sw, double su)
+{
+    const double x = k < 2 ? sw : su;
+    const uint32_t half = (uint32_t)((k & 1u) ? __double2hiint(x) : __double2loint(x));
+    __hip_atomic_store(&p->word[k], (unsigned long long)(tag << 1 | (bad ? 1u : 0u)) << 32 | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One look of a wave at n <= 64 sums from `p` on (lane i gets the i-th, the others zeros) and at the overflow marks of those
+// and of the m <= 64 from `q` on.  True (for the whole wave) if all of them are this launch's.
+__device__ __forceinline__ bool look(const LambMeeting::Sums *p, uint32_t n, const LambMeeting::Sums *q, uint32_t m, uint32_t tag, double &sw,
+                                     double &su, bool &overflowed)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const bool others = n != total && lane < total, own = lane < n;
     unsigned long long x[4] = {}, y = 0ull;
-    if (own) {
+    if (lane < n) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = ld_word(&mt->sums[first + lane].word[k]);
+        for (int k = 0; k < 4; ++k) x[k] = ld_word(&p[lane].word[k]);
     }
-    if (others) y = ld_word(mt->sums[lane].word);
-    bool here = !others || (uint32_t)(y >> 33) == tag;
+    if (lane < m) y = ld_word(q[lane].word);
+    bool here = lane >= m || (uint32_t)(y >> 33) == tag;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) here = here && (!own || (uint32_t)(x[k] >> 33) == tag);
+    for (int k = 0; k < 4; ++k) here = here && (lane >= n || (uint32_t)(x[k] >> 33) == tag);
     if (__builtin_amdgcn_ballot_w64(!here) != 0ull) return false;
     overflowed = __builtin_amdgcn_ballot_w64((((x[0] | y) >> 32) & 1ull) != 0ull) != 0ull;
-    sw = wave_sum(__hiloint2double((int)(uint32_t)x[1], (int)(uint32_t)x[0]));      // as tensor_sums adds up to 64 chunks;
-    su = wave_sum(__hiloint2double((int)(uint32_t)x[3], (int)(uint32_t)x[2]));      // lanes without one hold zeros
+    sw = __hiloint2double((int)(uint32_t)x[1], (int)(uint32_t)x[0]);
+    su = __hiloint2double((int)(uint32_t)x[3], (int)(uint32_t)x[2]);
     return true;
 }
 
-template <class Grad, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void lamb_one_launch_kernel(const DevTensor *__restrict__ per_chunk, StepScalars s,
+// A wave has waited long enough.  True: it has to leave its part of w to the last arrival.
+__device__ __forceinline__ bool give_up(LambMeeting *mt, unsigned long long abandoned, unsigned long long closed)
+{
+    unsigned long long cur = 0ull;
+    if ((threadIdx.x & 63u) == 0u) {
+        cur = ld_word(&mt->outcome.word);
+        while (cur != abandoned && cur != closed)
+            if (__hip_atomic_compare_exchange_strong(&mt->outcome.word, &cur, abandoned, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) cur = abandoned;
+    }
+    return __builtin_amdgcn_ballot_w64(cur == closed) == 0ull;
+}
+
+template <class Grad, bool GROUPED, int BLOCK>
+__global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTensor *__restrict__ per_chunk, StepScalars s,
                                                                 double *__restrict__ sums, LambMeeting *__restrict__ mt,
-                                                                int32_t *__restrict__ flag, uint32_t limit)
+                                                                int32_t *__restrict__ flag, uint32_t limit, uint32_t total_groups)
 {
     typedef typename Grad::Mem Mem;
     typedef LambPhase1Op<Grad> Op;
     typedef Sweep<BLOCK, 2, Op> S;
+    static_assert(BLOCK == 128, "the second wave leads a group while the first one publishes");
     FlagCount<BLOCK> fc;
     fc.arrive(&mt->flag);
     const Where wh = locate(per_chunk, nullptr, s);
@@ -1379,32 +1405,45 @@ __global__ __launch_bounds__(BLOCK) void lamb_one_launch_kernel(const DevTensor 
     block_sum2<BLOCK>(dw, du);
     const bool block_bad = __syncthreads_or(op.bad ? 1 : 0) != 0;
     const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)fc.tag()) & 0x7fffffffu;
-    if (threadIdx.x < 4) {
-        const double x = threadIdx.x < 2 ? dw : du;
-        const uint32_t half = (uint32_t)((threadIdx.x & 1u) ? __double2hiint(x) : __double2loint(x));
-        const uint32_t mark = tag << 1 | (block_bad ? 1u : 0u);
-        __hip_atomic_store(&mt->sums[wh.slot].word[threadIdx.x], (unsigned long long)mark << 32 | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (threadIdx.x < 4) publish(&mt->chunk[wh.slot], threadIdx.x, tag, block_bad, dw, du);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 2; ++g)
         if (S::mine(g, wh.len)) op.store(sw.x[g], S::first(g));
     if (rest) { st_f32(op.m_out, j * 4, m1); st_f32(op.v_out, j * 4, v1); }
 
+    const uint32_t lane = threadIdx.x & 63u, total = gridDim.x, n = wh.t->num_chunks;
     const bool last = __builtin_amdgcn_ballot_w64(fc.launch_last) != 0ull;        // uniform: this wave is the last arrival
     const unsigned long long abandoned = (unsigned long long)tag << 2 | kAbandoned, closed = (unsigned long long)tag << 2 | kClosed;
     double tw = 0.0, tu = 0.0;
     bool overflowed = false, patient = last, left = false;
-    for (uint32_t polls = 0; !meet(mt, wh.t->first_chunk, wh.t->num_chunks, gridDim.x, tag, tw, tu, overflowed); ++polls) {
-        __builtin_amdgcn_s_sleep(1);
-        if (patient || polls < limit) continue;
-        unsigned long long cur = 0ull;
-        if ((threadIdx.x & 63u) == 0u) {
-            cur = ld_word(&mt->outcome.word);
-            while (cur != abandoned && cur != closed)
-                if (__hip_atomic_compare_exchange_strong(&mt->outcome.word, &cur, abandoned, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) cur = abandoned;
+    uint32_t polls = 0;
+    if (GROUPED && (wh.index & 63u) == 0u && threadIdx.x >= 64u) {                // this wave adds up a group of chunks
+        const uint32_t members = n - wh.index < 64u ? n - wh.index : 64u;
+        while (!look(&mt->chunk[wh.slot], members, nullptr, 0u, tag, tw, tu, overflowed)) {
+            __builtin_amdgcn_s_sleep(1);
+            if (patient || polls++ < limit) continue;
+            if ((left = give_up(mt, abandoned, closed))) break;
+            patient = true;
         }
-        if (__builtin_amdgcn_ballot_w64(cur == closed) == 0ull) { left = true; break; }
+        if (!left) {
+            tw = wave_sum(tw);
+            tu = wave_sum(tu);
+            if (lane < 4u * kGroupCopies) publish(&mt->group[lane >> 2][wh.t->first_group + (wh.index >> 6)], lane & 3u, tag, overflowed, tw, tu);
+        }
+    }
+    // What this wave waits for: its tensor's sums, by chunk or by group, and everybody's marks.
+    const LambMeeting::Sums *all = GROUPED ? mt->group[blockIdx.x % kGroupCopies] : mt->chunk;
+    const uint32_t first = GROUPED ? wh.t->first_group : wh.t->first_chunk, count = GROUPED ? (n + 63u) >> 6 : n;
+    const uint32_t everybody = GROUPED ? total_groups : total, others = count == everybody ? 0u : everybody;
+    while (!left && !look(all + first, count, all, others, tag, tw, tu, overflowed)) {
+        __builtin_amdgcn_s_sleep(GROUPED ? 16 : 1);
+        if (last) {                      // a group whose leader has left is never published: the redo below needs none
+            if (GROUPED && __builtin_amdgcn_ballot_w64(lane == 0u && ld_word(&mt->outcome.word) == abandoned) != 0ull) left = true;
+            continue;
+        }
+        if (patient || polls++ < limit) continue;
+        if ((left = give_up(mt, abandoned, closed))) break;
         patient = true;
     }
     LambPhase2Op<true, Mem> p2;
@@ -1415,55 +1454,83 @@ __global__ __launch_bounds__(BLOCK) void lamb_one_launch_kernel(const DevTensor 
         p2.update(y);
         p2.store(y, e);
     };
+    const auto finish_one = [&](float w, float m, float v, uint32_t e) {
+        const float wn = p2.one(w, m, v);
+        st_f32(p2.w_out, e * 4, wn);
+        st_f16(p2.w16, e * 2, wn);
+    };
     if (!left) {
+        // as tensor_sums adds up to 1024 chunks: 64 at a time by a butterfly, and those one after the other
+        if (GROUPED) {
+            const double gw = tw, gu = tu;
+            tw = tu = 0.0;
+            for (uint32_t g = 0; g < count; ++g) { tw += __shfl(gw, (int)g, 64); tu += __shfl(gu, (int)g, 64); }
+        } else {
+            tw = wave_sum(tw);
+            tu = wave_sum(tu);
+        }
         p2.init(wh.t, wh.base, s);
         p2.scale(tw, tu);
-        if (wh.index == 0 && threadIdx.x == 0) { sums[2 * (uint64_t)wh.t->tensor] = tw; sums[2 * (uint64_t)wh.t->tensor + 1] = tu; }
+        if (wh.index == 0 && threadIdx.x == 0) { sums[2 * (uint64_t)wh.tensor] = tw; sums[2 * (uint64_t)wh.tensor + 1] = tu; }
         if (!overflowed) {               // whole-step skip: w and w16 stay as they were
 #pragma unroll
             for (int g = 0; g < 2; ++g)
                 if (S::mine(g, wh.len)) finish_pack(sw.x[g], S::first(g));
-            if (rest) {
-                const float wn = p2.one(w1, m1, v1);
-                st_f32(p2.w_out, j * 4, wn);
-                st_f16(p2.w16, j * 2, wn);
-            }
+            if (rest) finish_one(w1, m1, v1, j);
         }
     }
     fc.finish(op.bad, &mt->flag, flag);
-    if (last) {
+    if (!last) return;
+    if (!left) {                         // all sums have been published, those of the groups too
         unsigned long long prev = 0ull;
-        if ((threadIdx.x & 63u) == 0u) prev = __hip_atomic_exchange(&mt->outcome.word, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__builtin_amdgcn_ballot_w64(prev == abandoned) != 0ull) {
-            // Some waves have left: everybody's w once more, by this wave alone.  Other waves write the same values.
-            for (uint32_t c = 0; c < gridDim.x; ++c) {
-                Where at;
-                at.t = (Descriptor)per_chunk + c;
-                at.index = at.t->chunk_index;
-                finish_where(at, s.chunk_elems);
-                while (!meet(mt, at.t->first_chunk, at.t->num_chunks, gridDim.x, tag, tw, tu, overflowed)) {}    // all are there
-                if (at.index == 0 && (threadIdx.x & 63u) == 0u) { sums[2 * (uint64_t)at.t->tensor] = tw; sums[2 * (uint64_t)at.t->tensor + 1] = tu; }
-                if (overflowed) continue;
-                Op again;
-                again.init(at.t, at.base, s);
-                p2.init(at.t, at.base, s);
-                p2.scale(tw, tu);
-                const auto finish_one = [&](float S, uint32_t e) {
-                    float w = ld_f32(again.w_in, e * 4), m = ld_f32(again.m_in, e * 4), v = ld_f32(again.v_in, e * 4);
-                    again.one(S, w, m, v);
-                    const float wn = p2.one(w, m, v);
-                    st_f32(p2.w_out, e * 4, wn);
-                    st_f16(p2.w16, e * 2, wn);
-                };
-                uint32_t e = (threadIdx.x & 63u) * Op::kPack;
-                for (; e + Op::kPack <= at.len; e += 64u * Op::kPack) {
-                    typename Op::Regs x;
-                    again.load(x, e);
-                    again.compute(x);
-                    finish_pack(x, e);
-                }
-                for (uint32_t r = (at.len & ~(Op::kPack - 1u)) + (threadIdx.x & 63u); r < at.len; r += 64u) finish_one(again.grad.sum1(r), r);
+        if (lane == 0u) prev = __hip_atomic_exchange(&mt->outcome.word, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_ballot_w64(prev == abandoned) == 0ull) return;
+    }
+    // Some waves have left: everybody's w once more, by this wave alone, from the chunks' sums, which everybody has published
+    // or will.  Waves that have not left write the same values.
+    bool skip = false;
+    for (uint32_t c = 0; c < total; c += 64u) {
+        while (!look(&mt->chunk[c], total - c < 64u ? total - c : 64u, nullptr, 0u, tag, tw, tu, overflowed)) __builtin_amdgcn_s_sleep(1);
+        skip = skip || overflowed;
+    }
+    for (uint32_t c = 0; c < total; ++c) {
+        Where at;
+        at.t = (Descriptor)per_chunk + c;
+        at.index = at.t->chunk_index;
+        finish_where(at, s.chunk_elems);
+        if (at.index == 0) {             // the first chunk of a tensor: chunks come in tensor order
+            double cw = 0.0, cu = 0.0;
+            for (uint32_t g = 0; g < at.t->num_chunks; g += 64u) {
+                const uint32_t members = at.t->num_chunks - g < 64u ? at.t->num_chunks - g : 64u;
+                double aw = 0.0, au = 0.0;
+                while (!look(&mt->chunk[c + g], members, nullptr, 0u, tag, aw, au, overflowed)) __builtin_amdgcn_s_sleep(1);
+                cw += wave_sum(aw);
+                cu += wave_sum(au);
             }
+            tw = cw;
+            tu = cu;
+            if (lane == 0u) { sums[2 * (uint64_t)at.t->tensor] = tw; sums[2 * (uint64_t)at.t->tensor + 1] = tu; }
+        }
+        if (skip) continue;
+        Op again;
+        again.init(at.t, at.base, s);
+        p2.init(at.t, at.base, s);
+        p2.scale(tw, tu);
+        for (uint32_t e = lane * Op::kPack; e + Op::kPack <= at.len; e += 2u * 64u * Op::kPack) {
+            const uint32_t e2 = e + 64u * Op::kPack;
+            const bool two = e2 + Op::kPack <= at.len;
+            again.load(sw.x[0], e);
+            again.load(sw.x[1], two ? e2 : e);
+            __builtin_amdgcn_sched_barrier(0);
+            again.compute(sw.x[0]);
+            finish_pack(sw.x[0], e);
+            if (two) { again.compute(sw.x[1]); finish_pack(sw.x[1], e2); }
+        }
+        const uint32_t r = (at.len & ~(Op::kPack - 1u)) + lane;
+        if (r < at.len) {
+            float w = ld_f32(again.w_in, r * 4), m = ld_f32(again.m_in, r * 4), v = ld_f32(again.v_in, r * 4);
+            again.one(again.grad.sum1(r), w, m, v);
+            finish_one(w, m, v, r);
         }
     }
 }

@@ -1,5 +1,4 @@
-// Launches of the LAMB kernels: the step in one launch, phase 1 (fused and from the stored sum), the per-tensor second level,
-// phase 2.
+// Launches of the LAMB kernels: phase 1 (fused and from the stored sum), the per-tensor second level, phase 2.
 #include "plan.hpp"
 
 namespace ccf {
@@ -27,28 +26,7 @@ void launch_lamb_phase1_r(const cc_plan *p, const StepScalars &s, int32_t *flag,
     }
 }
 
-template <bool GF32, class MEM>
-void launch_lamb_one_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
-{
-    const Layout &L = p->lay();
-    const dim3 grid((unsigned)L.chunks), block(kSmallBlock);
-    switch (p->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((lamb_one_launch_kernel<GradSlices<r, GF32, MEM>, kSmallBlock>), grid, block, 0, st, L.d_per_chunk, s, p->d_sums, p->d_meeting, flag, p->meeting_limit); break;
-        FOR_EACH_R(CASE)
-#undef CASE
-    }
-}
-
 }  // namespace
-
-int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
-{
-    // Up to 65536 elements: written through or not is all the same to a launch that has to wait anyway.
-    const bool streaming = p->mem.lamb1 == CC_CACHE_STREAMING;
-    if (p->grad_f32) streaming ? launch_lamb_one_r<true, Streaming>(p, s, flag, st) : launch_lamb_one_r<true, Resident>(p, s, flag, st);
-    else streaming ? launch_lamb_one_r<false, Streaming>(p, s, flag, st) : launch_lamb_one_r<false, Resident>(p, s, flag, st);
-    return launched("lamb_one_launch_kernel");
-}
 
 void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {

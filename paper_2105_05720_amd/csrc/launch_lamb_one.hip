@@ -1,0 +1,39 @@
+// The small LAMB step in one launch (see LambMeeting).
+#include "plan.hpp"
+
+namespace ccf {
+
+namespace {
+
+template <bool GF32, bool GROUPED, class MEM>
+void launch_lamb_one_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+{
+    const Layout &L = p->lay();
+    const dim3 grid((unsigned)L.chunks), block(kSmallBlock);
+    switch (p->R) {
+#define CASE(r) case r: hipLaunchKernelGGL((lamb_one_launch_kernel<GradSlices<r, GF32, MEM>, GROUPED, kSmallBlock>), grid, block, 0, st, L.d_per_chunk, s, p->d_sums, p->d_meeting, flag, p->meeting_limit, L.groups); break;
+        FOR_EACH_R(CASE)
+#undef CASE
+    }
+}
+
+// Up to 65536 elements every wave looks at every chunk's sums, beyond that at every group's.  A plan that was asked to keep its
+// loads non-temporal and write through gets plain loads: the shard fits the Infinity Cache many times.
+template <bool GF32>
+void launch_lamb_one(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+{
+    const bool grouped = p->lay().chunks > (int64_t)kMeetingChunks;
+    if (p->mem.lamb1 == CC_CACHE_STREAMING) grouped ? launch_lamb_one_r<GF32, true, Streaming>(p, s, flag, st) : launch_lamb_one_r<GF32, false, Streaming>(p, s, flag, st);
+    else grouped ? launch_lamb_one_r<GF32, true, Resident>(p, s, flag, st) : launch_lamb_one_r<GF32, false, Resident>(p, s, flag, st);
+}
+
+}  // namespace
+
+int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+{
+    if (p->grad_f32) launch_lamb_one<true>(p, s, flag, st);
+    else launch_lamb_one<false>(p, s, flag, st);
+    return launched("lamb_one_launch_kernel");
+}
+
+}  // namespace ccf

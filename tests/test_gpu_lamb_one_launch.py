@@ -1,10 +1,10 @@
-"""LAMB steps of at most 64 chunks run as one launch in which the workgroups wait for each other's norms.
+"""LAMB steps of at most 512 chunks run as one launch in which the workgroups wait for each other's norms.
 
 Against the two phase calls (separate launches, same additions in the same order): sums, state and flag bit for bit, with
 every wave patient and with none (a limit of 0 polls: whoever does not find all norms at once leaves its part of w to the last
 workgroup that started), with and without an overflow, and against the oracle.  Sizes at the edges: one element, less than a
-pack, around a chunk, 64 chunks (the most) and 65
-(two launches), lists with empty, tiny and ragged tensors."""
+pack, around a chunk, 64 and 65 chunks (sums by
+chunk and by group of 64), 512 (the most) and 513 (three launches), lists with empty, tiny and ragged tensors, 64 groups (the most) and 65."""
 import numpy as np
 import pytest
 import torch
@@ -17,7 +17,8 @@ from parity import OracleState, compare_committed, hyper_pair, seeded_grads, see
 pytestmark = pytest.mark.gpu
 
 LISTS = [[1], [3], [1023], [1024], [1027], [10007], [64 * 1024], [64 * 1024 + 1],
-         [5, 0, 1024, 4099, 1, 2048, 7], [1] * 64, [20 * 1024 + 2, 42 * 1024 + 1, 1]]
+         [5, 0, 1024, 4099, 1, 2048, 7], [1] * 64, [20 * 1024 + 2, 42 * 1024 + 1, 1],
+         [129 * 1024 - 3], [1 << 19], [(1 << 19) + 1], [5, 0, 100 * 1024 + 3, 1, 64 * 1024, 300001], [1] * 61 + [192 * 1024], [1] * 62 + [192 * 1024]]
 
 
 def _phases(plan, hp, flag, stream=None):
