@@ -125,6 +125,8 @@ void resolve_schedule(cc_plan *p)
     else if (p->schedule == CC_SCHEDULE_PER_CHUNK) p->ordered = false;
     else p->ordered = L.chunks >= kOrderedMinChunksPerCu * (int64_t)p->cus && !(p->grad_f32 && p->R > kOrderedMaxF32Slices);
     if (L.chunk_elems != kDefaultChunkElems || L.chunks == 0) p->ordered = false;
+    const bool nothing_asked = p->chunk_choice == 0 && p->schedule == CC_SCHEDULE_AUTO && p->ordered_grid == 0 && p->cache_policy == CC_CACHE_AUTO;
+    p->flat_adam = nothing_asked && p->single >= 0 && flat_beyond_small(p->numel, p->R, p->grad_f32);
     const bool small = L.block == kSmallBlock && !p->ordered;
     const bool one_sweep = L.chunk_elems == kSmallChunkElems;
     p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, one_sweep) : CachePolicies{};

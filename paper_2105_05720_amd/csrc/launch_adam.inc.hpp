@@ -27,6 +27,8 @@ template <int MODE, int BLK, bool GF32, class MEM>
 void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
     const Layout &L = p->lay();
+    if constexpr (BLK == kBigBlock)
+        if (p->flat_adam) return launch_flat_pieces<MODE, GF32, Streaming>(L.host_tensors[(size_t)p->single], p->R, s, p->d_flag_scratch, flag, st);
     if (p->ordered) {
         const dim3 grid(ordered_grid(p)), block(kBigBlock);
         switch (p->R) {

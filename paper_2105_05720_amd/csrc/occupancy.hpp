@@ -60,4 +60,21 @@ inline unsigned flat_lds(uint64_t numel, int R, bool grad_f32, bool non_temporal
     return lds < most ? lds : most;
 }
 
+// From kSmallShardElems elements on a plan's chunks are large and the ordered schedule takes over, but the fused Adam step on
+// one tensor for which nothing else was asked stays with single-wave pieces while they are the faster ones (where the arrays lie
+// moves either side by 1 to 2 %).  Two shards in turn,
+// us, large chunks (ordered up to eight fp32 slices) / pieces: fp16 slices, 64 Mi elements R = 8 470 / 444, 128 Mi 914 / 875;
+// 70 M elements R = 1 324 / 308, R = 2 347 / 338, R = 4 384 / 372, R = 16 667 / 651; 200 M R = 1 897 / 879, R = 2 957 / 953, R = 4 1092 /
+// 1051, R = 8 1340 / 1327, R = 16 1891 / 1886 (150 M 1410 / 1417); but 260 M R = 1 1133 / 1181, R = 16 2474 / 2521 and 500 M R = 1 2146 /
+// 2244, R = 4 2661 / 2676, R = 8 3285 / 3314.  With four and more fp32 slices, of which a compute unit's two chunks in flight are
+// as much as it holds, at every size: R = 4 485 / 458 at 70 M, 1388 / 1318 at 200 M, 3467 / 3280 at 500 M; R = 8 694 / 665, 2018 / 1854,
+// 4968 / 4557; R = 12 906 / 865 at 70 M; R = 16 1108 / 1070 and 3229 / 3117 at 200 M.
+constexpr uint64_t kSmallShardElems = 64u << 20, kFlatF16MaxElems = 192u << 20;
+constexpr int kFlatAlwaysF32Slices = 4;
+inline bool flat_beyond_small(uint64_t numel, int R, bool grad_f32)
+{
+    if (numel < kSmallShardElems || numel > kFlatMaxElems) return false;
+    return numel < kFlatF16MaxElems || (grad_f32 && R >= kFlatAlwaysF32Slices);
+}
+
 }  // namespace ccf

@@ -18,7 +18,6 @@ namespace ccf {
 constexpr int32_t kDefaultChunkElems = 4096;     // one sweep of a 512-thread workgroup (2 groups x 512 lanes x 4 elements)
 constexpr int32_t kSmallChunkElems = 1024;       // one sweep of a 128-thread workgroup: more workgroups for small shards
 constexpr int32_t kLargeChunkElems = 16384;      // four sweeps of a 512-thread workgroup: a quarter of the table and of the launches
-constexpr uint64_t kSmallShardElems = 64u << 20; // below this many elements the default chunk is the small one (size sweep)
 constexpr int32_t kMaxChunkElems = 1 << 24;      // lane offsets inside a chunk are 32-bit byte offsets
 constexpr int kBigBlock = 512, kSmallBlock = 128;
 constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-chunk layout keeps a descriptor per chunk (224 B each)
@@ -73,6 +72,7 @@ struct cc_plan {
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
     ccf::CachePolicies mem;                 // the policies in use (other than STREAMING: small-chunk layouts only)
     bool beyond_cache = false;              // small chunks of a shard bound by HBM (one tensor: see kFlatPiece)
+    bool flat_adam = false;                 // large chunks, but the fused Adam step in single-wave pieces (see flat_beyond_small)
     bool spread = false;                    // ... of 1024 elements (see kSpreadLds)
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
     int32_t cus = 0;                        // compute units of the device the plan was created on

@@ -257,3 +257,26 @@ def test_both_forms_of_the_chunk_table(fn, ofn):
         run_steps(sh, ost, fn, ofn, [hyper_pair(step=t) for t in (1, 2)], "%d chunks" % (len(numels) - 5 + 2048),
                   lambda i: seeded_grads(sh, 310 + i, 1e-2), expect_flags=[0, 0])
         sh.destroy()
+
+
+@pytest.mark.parametrize("R,dtype,in_place", [(2, torch.float16, False), (2, torch.float16, True), (5, torch.float32, False)])
+def test_one_large_tensor_in_pieces_gives_the_bits_of_the_ordered_schedule(R, dtype, in_place):
+    """One tensor of 64 Mi elements and more for which nothing was chosen: the fused Adam step runs single-wave pieces of 256
+    elements instead of the ordered schedule.  With a ragged end, an overflow in the last element, and without."""
+    numel = (64 << 20) + 4096 * 3 + 257 + 2
+    outs = []
+    for schedule in (cc.CC_SCHEDULE_AUTO, cc.CC_SCHEDULE_ORDERED):
+        shard = Shard([numel], [0.01], R, schedule=schedule, in_place=in_place, grad_dtype=dtype, unfused=False)
+        seeded_state(shard, 41)
+        flags = []
+        for t in (1, 2):
+            seeded_grads(shard, 410 + t, 1e-2)
+            if t == 2:
+                shard.grad_of(R - 1, 0)[-1] = float("inf")
+            flags.append(shard.step(cc.cc_fused_adam_step, cc.Hyper(step=t, skip_mode=int(in_place), adam_mode=int(in_place))))
+        assert flags == [0, 1]
+        outs.append([x.clone() for a in (shard.w, shard.m, shard.v) for x in a] + [x.view(torch.int16).clone() for x in shard.w16])
+        shard.destroy()
+    for a, b in zip(*outs):
+        a, b = (x if x.dtype == torch.int16 else x.view(torch.int32) for x in (a, b))
+        assert torch.equal(a, b)

@@ -15,6 +15,7 @@ MAIN = r"""
 
 int main(int, char **argv)
 {
+    if (argv[5][0] == 'p') return printf("%d\n", ccf::flat_beyond_small(strtoull(argv[1], nullptr, 10), atoi(argv[2]), atoi(argv[3]) != 0) ? 10000 : 20000) < 0;
     const auto rule = argv[5][0] == 'l' ? ccf::list_lds : ccf::flat_lds;
     printf("%u\n", rule(strtoull(argv[1], nullptr, 10), atoi(argv[2]), atoi(argv[3]) != 0, atoi(argv[4]) != 0));
     return 0;
@@ -49,3 +50,10 @@ def test_lists(per_cu):
 def test_one_tensor(per_cu, R, f32, through, streamed):
     at = -(-300 * MIB // ((4 if f32 else 2) * R + 26))
     assert [per_cu(n, R, f32, nt, rule="flat") for nt in (0, 1) for n in (at - 1, at, 1 << 26)] == [16, through, through, 16, streamed, streamed]
+
+
+@pytest.mark.parametrize("R,f32,sizes", [(1, 0, [0, 1, 1, 0, 0, 0]), (16, 0, [0, 1, 1, 0, 0, 0]), (3, 1, [0, 1, 1, 0, 0, 0]),
+                                         (4, 1, [0, 1, 1, 1, 1, 0]), (16, 1, [0, 1, 1, 1, 1, 0])])
+def test_pieces_on_one_large_tensor(per_cu, R, f32, sizes):
+    at = ((64 << 20) - 1, 64 << 20, (192 << 20) - 1, 192 << 20, 1 << 33, (1 << 33) + 1)
+    assert [per_cu(n, R, f32, 0, rule="pieces") == 16 for n in at] == [bool(k) for k in sizes]
