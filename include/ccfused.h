@@ -241,7 +241,7 @@ int cc_fused_adam_step_static(const cc_tensor *tensor, int32_t R, const cc_hpara
  * cross-rank sum of the per-tensor norms can be placed between them.  The single call gives the same bits in two
  * launches instead of three when no tensor has more than 512 chunks: the workgroups of phase 2 then add up their own
  * tensor's partial sums (same additions, same order) instead of a per-tensor launch between the phases; and in one launch
- * when the shard has at most 512 chunks of 1024 elements in at most 64 groups (a group is up to 64 chunks of one tensor): the
+ * when the shard has at most 512 chunks of 1024 elements (two per compute unit) in at most 64 groups (of up to 64 chunks of one tensor): the
  * workgroups then wait for each other's sums.
  */
 int cc_fused_lamb_step(cc_plan *plan, const cc_hparams *hp, int32_t *d_overflow_flag, void *hip_stream);

@@ -146,13 +146,14 @@ constexpr uint32_t kFoldNormsMaxChunks = 512;
 // device holds at a time with room to spare, and no more groups than a wave can look at together.  Eager us per step, one
 // tensor, R = 8, two or three launches / one: 9.4 / 8.2 at 98 chunks, 9.7 / 8.5 at 196, 11.8 / 10.0 at 391, 12.2 / 10.5 at 489,
 // 14.0 / 13.4 at 768, but 15.3 / 16.1 at 1024, where the waves that wait get in the way of those that load.  The line is drawn
-// at 512 for another reason: a compute unit holds four of these workgroups whatever R is, so up to there two such steps fit the
-// device, or one fits half of it; where some have to wait for others to leave, a step takes milliseconds (see kMeetingPolls).
+// at 512, two per compute unit, for another reason: a compute unit holds four of these workgroups whatever R is, so up to there
+// two such steps fit the device, or one fits half of it; where some have to wait for others to leave, a step takes
+// milliseconds (see kMeetingPolls).  A device with fewer compute units, as a partition is, gets a lower line.
 inline bool lamb_in_one_launch(const cc_plan *p)
 {
     const Layout &L = p->lay();
     return !p->ordered && L.chunk_elems == kSmallChunkElems && L.chunks > 0 && L.chunks <= (int64_t)kMeetingMostChunks
-           && L.groups <= kMeetingGroups && L.d_per_chunk;
+           && L.chunks <= 2 * (int64_t)p->cus && L.groups <= kMeetingGroups && L.d_per_chunk;
 }
 int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
 inline bool norms_fold_into_phase2(const cc_plan *p)
