@@ -241,8 +241,11 @@ int cc_fused_adam_step_static(const cc_tensor *tensor, int32_t R, const cc_hpara
  * cross-rank sum of the per-tensor norms can be placed between them.  The single call gives the same bits in two
  * launches instead of three when no tensor has more than 512 chunks: the workgroups of phase 2 then add up their own
  * tensor's partial sums (same additions, same order) instead of a per-tensor launch between the phases; and in one launch
- * when the shard has at most 512 chunks of 1024 elements (two per compute unit) in at most 64 groups (of up to 64 chunks of one tensor): the
- * workgroups then wait for each other's sums.
+ * when the shard has few chunks of 1024 elements, in at most 64 groups (of up to 64 chunks of one tensor): the workgroups then
+ * wait for each other's sums.  Few is a quarter of what the device holds at a time: 512 up to four fp16 or eight fp32 slices, 384 up to
+ * seven or twelve, else 256 (in proportion fewer on a partition of the device).  So several such steps at a time, and other
+ * work beside them, leave room for all workgroups of each.  Where they do not, those that wait make room after some tens of microseconds and
+ * the others take over their part: the step then takes some 10 to 30 us longer than as two launches.  The two phase calls never wait.
  */
 int cc_fused_lamb_step(cc_plan *plan, const cc_hparams *hp, int32_t *d_overflow_flag, void *hip_stream);
 int cc_fused_lamb_phase1(cc_plan *plan, const cc_hparams *hp, int32_t *d_overflow_flag, void *hip_stream);
@@ -327,9 +330,9 @@ int cc_pattern_probe(const cc_tensor *tensor, int32_t R, int32_t what, int32_t c
  * (both are zero between launches; a test aid). */
 int cc_plan_queue_state(cc_plan *plan, uint32_t *next_ticket, uint64_t *done_word, void *hip_stream);
 
-/* In a LAMB step of one launch (see cc_fused_lamb_step) a wave that has looked for the other workgroups' sums `polls` times in
- * vain leaves its part of w to the last one that started, so that no wait depends on how many workgroups the device holds
- * at a time.  Results do not depend on the limit (a test aid; polls >= 0). */
+/* In a LAMB step of one launch (see cc_fused_lamb_step) half of the workgroups leave their part of w to the others after they have
+ * looked for the others' sums `polls` times in vain, the rest after 64 times as many, so that no wait depends on how many
+ * workgroups the device holds at a time.  Results do not depend on the limit (a test aid; polls >= 0). */
 int cc_plan_set_meeting_limit(cc_plan *plan, int32_t polls);
 
 /* What the current device reports about itself (any output pointer may be NULL): compute units, memory clock in

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "ccfused.h"
+#include "meeting.hpp"
 #include "piece_order.hpp"
 
 namespace ccf {
@@ -1283,7 +1284,7 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
     });
 }
 
-// LAMB in one launch, for shards of at most kMeetingMostChunks chunks (of 1024 elements).  Such a step is mostly latency: as
+// LAMB in one launch, for shards of at most kMeetingMostChunks chunks of 1024 elements (see lamb_meets).  Such a step is mostly latency: as
 // two launches it pays for the end of a kernel, the start of the next and a second trip to memory between the partial sums
 // and their use.  Here every workgroup keeps its chunk in registers, publishes its sums and waits for those of the others.
 // Same sums in the same order and the same update from the same values, so the same bits as in two launches.
@@ -1292,7 +1293,7 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
 //
 //   * A workgroup publishes its two sums as four words of 32 bits, each with the launch's tag next to it in one 64-bit
 //     word, so that a reader needs no order between the words and nothing has to be reset: words of other launches carry
-//     other tags (31 bits of the phase that FlagCount counts, which wrap).  The tag's lowest bit tells whether the workgroup
+//     other tags (30 bits of the phase that FlagCount counts, which wrap).  A bit beside the tag tells whether the workgroup
 //     saw an inf/NaN: with the sums a wave learns whether the step is to be skipped, before it writes w.  (One chunk's words
 //     lie together: by word, 64 chunks in four lines, a wave looks at fewer lines but the chunks' stores meet in them: 5.7 ->
 //     6.4 us at 10007 elements.)
@@ -1302,40 +1303,51 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
 //     and every wave polls groups.  They are published in kGroupCopies copies, one for the workgroups of each XCD, so that not
 //     all of them read the same lines, and polls are 0.4 us apart (at 1024 chunks 16.8 us with none between them, 16.1 with
 //     0.4, 15.5 with 1.3, which costs 0.6 at 100).
-//   * Every wait ends, however few of the workgroups the device holds at a time (a stream that may use one compute unit,
-//     other kernels in the way).  A workgroup publishes before it waits.  The wave that FlagCount finds to be the last
-//     arrival of the launch knows that all workgroups have started, so all of them will publish.  Any other wave, the one
-//     that adds up a group included, gives up after `limit` polls: it moves the word `outcome` to (tag, ABANDONED) and
-//     leaves, its part of w unwritten.  The last arrival waits until it has all it needs, and then exchanges the word to
-//     (tag, CLOSED), or, while groups are missing, until it finds ABANDONED there.  If it finds ABANDONED either way it
-//     computes the whole shard's w again, from the chunks' sums and the step's inputs, which a LAMB step never overwrites.
-//     A wave that finds CLOSED when it would give up knows that everything has been published and polls on.
-constexpr uint32_t kMeetingChunks = 64, kMeetingMostChunks = 512, kMeetingGroups = 64, kGroupCopies = 8;
+//   * No wait depends on how many of the workgroups the device holds at a time (several steps on as many streams, other
+//     kernels in the way, a stream that may use one compute unit).  A workgroup publishes before it waits.  The wave that
+//     FlagCount finds to be the last arrival of the launch knows that all workgroups have started, so all of them will
+//     publish.  Any other wave, the one that adds up a group included, gives up in the end: it moves the word `outcome` to
+//     (tag, ABANDONED) and leaves, its part of w unwritten.  Half of the workgroups do so after `limit` looks, some tens of
+//     microseconds, and so make room for those that have not started; the others stay kMeetingPatience times as long.
+//   * The last arrival, once it has all it needs, exchanges the word for (tag, CLOSED).  If ABANDONED was there it puts that
+//     back, and it and whoever else is there share the work of those that have left: they take the shard's chunks from a counter in the same
+//     word and compute their w again, from all chunks' sums and the step's inputs, which a LAMB step never overwrites.
+//     Whoever wrote its own part meanwhile wrote the same values.  A wave learns that some have left from the word, which it looks
+//     at every kMeetingGlance looks, or from another bit beside the tags (a workgroup that leaves sets its own): one that started late,
+//     and finds everything published at once, helps as well.  One that started late and does not find it stays for a few looks only.
+//     A wave that finds CLOSED when it would give up knows that everything has been published and looks on.
+//   * One tensor, R = 8, us for a step beside a kernel that leaves 4 of the 256 compute units free for another 160 us / 960 us, two
+//     launches / one: 157 / 172 and 957 / 970 at 128 chunks; 158 / 177 and 957 / 976 at 256.
 struct LambMeeting {
     FlagScratch flag;                                                // what the other kernels use
     FlagScratch::Line outcome;
     struct alignas(32) Sums { unsigned long long word[4]; };
     Sums chunk[kMeetingMostChunks], group[kGroupCopies][kMeetingGroups];
 };
-constexpr unsigned long long kAbandoned = 1ull, kClosed = 2ull;
+// `outcome`: two bits of state, the tag, and from kTicket on the next chunk to be computed again.
+constexpr unsigned long long kAbandoned = 1ull, kClosed = 2ull, kTicket = 1ull << 32;
+__device__ __forceinline__ bool marks(unsigned long long word, unsigned long long mark) { return (word & (kTicket - 1ull)) == mark; }
 
 __device__ __forceinline__ unsigned long long ld_word(const unsigned long long *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Word k of the sums (sw, su), with the launch's tag and the overflow mark.
-__device__ __forceinline__ void publish(LambMeeting::Sums *p, uint32_t k, uint32_t tag, bool bad, double sw, double su)
+// Marks beside the tag: a workgroup saw an inf/NaN; one has left.
+constexpr uint32_t kMarkBad = 1u, kMarkGone = 2u;
+
+// Word k of the sums (sw, su), with the launch's tag and the marks.
+__device__ __forceinline__ void publish(LambMeeting::Sums *p, uint32_t k, uint32_t tag, uint32_t mark, double sw, double su)
 {
     const double x = k < 2 ? sw : su;
     const uint32_t half = (uint32_t)((k & 1u) ? __double2hiint(x) : __double2loint(x));
-    __hip_atomic_store(&p->word[k], (unsigned long long)(tag << 1 | (bad ? 1u : 0u)) << 32 | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&p->word[k], (unsigned long long)(tag << 2 | mark) << 32 | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One look of a wave at n <= 64 sums from `p` on (lane i gets the i-th, the others zeros) and at the overflow marks of those
-// and of the m <= 64 from `q` on.  True (for the whole wave) if all of them are this launch's.
+// One look of a wave at n <= 64 sums from `p` on (lane i gets the i-th, the others zeros) and at the marks of those and of
+// the m <= 64 from `q` on (`mark`: all of them together).  True (for the whole wave) if all of them are this launch's.
 __device__ __forceinline__ bool look(const LambMeeting::Sums *p, uint32_t n, const LambMeeting::Sums *q, uint32_t m, uint32_t tag, double &sw,
-                                     double &su, bool &overflowed)
+                                     double &su, uint32_t &mark)
 {
     const uint32_t lane = threadIdx.x & 63u;
     unsigned long long x[4] = {}, y = 0ull;
@@ -1344,30 +1356,66 @@ __device__ __forceinline__ bool look(const LambMeeting::Sums *p, uint32_t n, con
         for (int k = 0; k < 4; ++k) x[k] = ld_word(&p[lane].word[k]);
     }
     if (lane < m) y = ld_word(q[lane].word);
-    bool here = lane >= m || (uint32_t)(y >> 33) == tag;
+    bool here = lane >= m || (uint32_t)(y >> 34) == tag;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) here = here && (lane >= n || (uint32_t)(x[k] >> 33) == tag);
+    for (int k = 0; k < 4; ++k) here = here && (lane >= n || (uint32_t)(x[k] >> 34) == tag);
     if (__builtin_amdgcn_ballot_w64(!here) != 0ull) return false;
-    overflowed = __builtin_amdgcn_ballot_w64((((x[0] | y) >> 32) & 1ull) != 0ull) != 0ull;
+    const uint32_t seen = (uint32_t)((x[0] | y) >> 32);
+    mark = (__builtin_amdgcn_ballot_w64((seen & kMarkBad) != 0u) != 0ull ? kMarkBad : 0u) |
+           (__builtin_amdgcn_ballot_w64((seen & kMarkGone) != 0u) != 0ull ? kMarkGone : 0u);
     sw = __hiloint2double((int)(uint32_t)x[1], (int)(uint32_t)x[0]);
     su = __hiloint2double((int)(uint32_t)x[3], (int)(uint32_t)x[2]);
     return true;
 }
 
-// A wave has waited long enough.  True: it has to leave its part of w to the last arrival.
-__device__ __forceinline__ bool give_up(LambMeeting *mt, unsigned long long abandoned, unsigned long long closed)
+// Whether some wave of this launch has left (for the whole wave).
+__device__ __forceinline__ bool abandoned(const LambMeeting *mt, unsigned long long mark)
+{
+    const bool yes = (threadIdx.x & 63u) == 0u && marks(ld_word(&mt->outcome.word), mark);
+    return __builtin_amdgcn_ballot_w64(yes) != 0ull;
+}
+
+// A wave has waited long enough.  True: `outcome` says that some have left, and it may leave.
+__device__ __forceinline__ bool give_up(LambMeeting *mt, unsigned long long left, unsigned long long closed)
 {
     unsigned long long cur = 0ull;
     if ((threadIdx.x & 63u) == 0u) {
         cur = ld_word(&mt->outcome.word);
-        while (cur != abandoned && cur != closed)
-            if (__hip_atomic_compare_exchange_strong(&mt->outcome.word, &cur, abandoned, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) cur = abandoned;
+        while (!marks(cur, left) && !marks(cur, closed))
+            if (__hip_atomic_compare_exchange_strong(&mt->outcome.word, &cur, left, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) cur = left;
     }
-    return __builtin_amdgcn_ballot_w64(cur == closed) == 0ull;
+    return __builtin_amdgcn_ballot_w64((threadIdx.x & 63u) == 0u && marks(cur, left)) != 0ull;
 }
 
-template <class Grad, bool GROUPED, int BLOCK>
-__global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTensor *__restrict__ per_chunk, StepScalars s,
+// A wave's waiting in one launch.
+struct Wait {
+    enum Next { kLook, kLeave, kHelp };
+    unsigned long long left, closed;     // what `outcome` reads when a wave has left, when none will
+    uint32_t polls = 0, most;            // looks in vain so far, and how many before this wave gives up
+    bool last, stays, sure = false;      // the launch's last arrival; one of those that stay; everything has been published
+    __device__ __forceinline__ Wait(uint32_t tag, uint32_t limit, bool last_) : last(last_)
+    {
+        left = (unsigned long long)tag << 2 | kAbandoned;
+        closed = (unsigned long long)tag << 2 | kClosed;
+        stays = meeting_stays(blockIdx.x);
+        most = !stays ? limit : limit > ~0u / kMeetingPatience ? ~0u : limit * kMeetingPatience;
+    }
+    // A look has been in vain.
+    __device__ __forceinline__ Next again(LambMeeting *mt)
+    {
+        ++polls;
+        if (!last && !sure && polls > most) {
+            if (give_up(mt, left, closed)) return kLeave;
+            sure = true;
+        }
+        if ((polls & (kMeetingGlance - 1u)) != 0u || sure || !abandoned(mt, left)) return kLook;
+        if (!stays || polls == kMeetingGlance) most = polls + kMeetingLinger;
+        return kHelp;
+    }
+};
+
+template <class Grad, bool GROUPED, int BLOCK, int WAVES>
+__global__ __launch_bounds__(BLOCK, WAVES) void lamb_one_launch_kernel(const DevTensor *__restrict__ per_chunk, StepScalars s,
                                                                 double *__restrict__ sums, LambMeeting *__restrict__ mt,
                                                                 int32_t *__restrict__ flag, uint32_t limit, uint32_t total_groups)
 {
@@ -1404,8 +1452,8 @@ __global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTens
     double dw = op.sw, du = op.su;
     block_sum2<BLOCK>(dw, du);
     const bool block_bad = __syncthreads_or(op.bad ? 1 : 0) != 0;
-    const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)fc.tag()) & 0x7fffffffu;
-    if (threadIdx.x < 4) publish(&mt->chunk[wh.slot], threadIdx.x, tag, block_bad, dw, du);
+    const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)fc.tag()) & 0x3fffffffu;
+    if (threadIdx.x < 4) publish(&mt->chunk[wh.slot], threadIdx.x, tag, block_bad ? kMarkBad : 0u, dw, du);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 2; ++g)
@@ -1413,38 +1461,29 @@ __global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTens
     if (rest) { st_f32(op.m_out, j * 4, m1); st_f32(op.v_out, j * 4, v1); }
 
     const uint32_t lane = threadIdx.x & 63u, total = gridDim.x, n = wh.t->num_chunks;
-    const bool last = __builtin_amdgcn_ballot_w64(fc.launch_last) != 0ull;        // uniform: this wave is the last arrival
-    const unsigned long long abandoned = (unsigned long long)tag << 2 | kAbandoned, closed = (unsigned long long)tag << 2 | kClosed;
+    Wait wait(tag, limit, __builtin_amdgcn_ballot_w64(fc.launch_last) != 0ull);   // uniform: this wave is the last arrival
+    Wait::Next next = Wait::kLook;
     double tw = 0.0, tu = 0.0;
-    bool overflowed = false, patient = last, left = false;
-    uint32_t polls = 0;
+    uint32_t mark = 0u;
     if (GROUPED && (wh.index & 63u) == 0u && threadIdx.x >= 64u) {                // this wave adds up a group of chunks
         const uint32_t members = n - wh.index < 64u ? n - wh.index : 64u;
-        while (!look(&mt->chunk[wh.slot], members, nullptr, 0u, tag, tw, tu, overflowed)) {
+        while (!look(&mt->chunk[wh.slot], members, nullptr, 0u, tag, tw, tu, mark)) {
             __builtin_amdgcn_s_sleep(1);
-            if (patient || polls++ < limit) continue;
-            if ((left = give_up(mt, abandoned, closed))) break;
-            patient = true;
+            if ((next = wait.again(mt)) != Wait::kLook) break;
         }
-        if (!left) {
+        if (next == Wait::kLook) {
             tw = wave_sum(tw);
             tu = wave_sum(tu);
-            if (lane < 4u * kGroupCopies) publish(&mt->group[lane >> 2][wh.t->first_group + (wh.index >> 6)], lane & 3u, tag, overflowed, tw, tu);
+            if (lane < 4u * kGroupCopies) publish(&mt->group[lane >> 2][wh.t->first_group + (wh.index >> 6)], lane & 3u, tag, mark, tw, tu);
         }
     }
     // What this wave waits for: its tensor's sums, by chunk or by group, and everybody's marks.
     const LambMeeting::Sums *all = GROUPED ? mt->group[blockIdx.x % kGroupCopies] : mt->chunk;
     const uint32_t first = GROUPED ? wh.t->first_group : wh.t->first_chunk, count = GROUPED ? (n + 63u) >> 6 : n;
     const uint32_t everybody = GROUPED ? total_groups : total, others = count == everybody ? 0u : everybody;
-    while (!left && !look(all + first, count, all, others, tag, tw, tu, overflowed)) {
+    while (next == Wait::kLook && !look(all + first, count, all, others, tag, tw, tu, mark)) {
         __builtin_amdgcn_s_sleep(GROUPED ? 16 : 1);
-        if (last) {                      // a group whose leader has left is never published: the redo below needs none
-            if (GROUPED && __builtin_amdgcn_ballot_w64(lane == 0u && ld_word(&mt->outcome.word) == abandoned) != 0ull) left = true;
-            continue;
-        }
-        if (patient || polls++ < limit) continue;
-        if ((left = give_up(mt, abandoned, closed))) break;
-        patient = true;
+        next = wait.again(mt);
     }
     LambPhase2Op<true, Mem> p2;
     const auto finish_pack = [&](const typename Op::Regs &x, uint32_t e) {
@@ -1459,7 +1498,9 @@ __global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTens
         st_f32(p2.w_out, e * 4, wn);
         st_f16(p2.w16, e * 2, wn);
     };
-    if (!left) {
+    unsigned long long was = 0ull;
+    if (next == Wait::kLook) {
+        if (wait.last && lane == 0u) was = __hip_atomic_exchange(&mt->outcome.word, wait.closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // as tensor_sums adds up to 1024 chunks: 64 at a time by a butterfly, and those one after the other
         if (GROUPED) {
             const double gw = tw, gu = tu;
@@ -1472,7 +1513,7 @@ __global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTens
         p2.init(wh.t, wh.base, s);
         p2.scale(tw, tu);
         if (wh.index == 0 && threadIdx.x == 0) { sums[2 * (uint64_t)wh.tensor] = tw; sums[2 * (uint64_t)wh.tensor + 1] = tu; }
-        if (!overflowed) {               // whole-step skip: w and w16 stay as they were
+        if (!(mark & kMarkBad)) {        // whole-step skip: w and w16 stay as they were
 #pragma unroll
             for (int g = 0; g < 2; ++g)
                 if (S::mine(g, wh.len)) finish_pack(sw.x[g], S::first(g));
@@ -1480,42 +1521,59 @@ __global__ __launch_bounds__(BLOCK, 2) void lamb_one_launch_kernel(const DevTens
         }
     }
     fc.finish(op.bad, &mt->flag, flag);
-    if (!last) return;
-    if (!left) {                         // all sums have been published, those of the groups too
-        unsigned long long prev = 0ull;
-        if (lane == 0u) prev = __hip_atomic_exchange(&mt->outcome.word, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__builtin_amdgcn_ballot_w64(prev == abandoned) == 0ull) return;
+    if (next == Wait::kLeave) {
+        if (lane == 0u) publish(&mt->chunk[wh.slot], 0u, tag, kMarkGone | (block_bad ? kMarkBad : 0u), dw, du);
+        return;
     }
-    // Some waves have left: everybody's w once more, by this wave alone, from the chunks' sums, which everybody has published
-    // or will.  Waves that have not left write the same values.
+    if (next == Wait::kLook) {
+        if (wait.last) {
+            if (__builtin_amdgcn_ballot_w64(lane == 0u && marks(was, wait.left)) == 0ull) return;        // nobody has left, and nobody will
+            if (lane == 0u) __hip_atomic_exchange(&mt->outcome.word, was, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if ((wait.polls < kMeetingGlance && !(mark & kMarkGone)) || !abandoned(mt, wait.left)) {
+            return;
+        }
+    }
+    // Some waves have left: the shard's chunks once more, one after the other from the counter, by the waves that are here.
+    // First all the chunks' marks, which also tell that all their sums are there.
     bool skip = false;
-    for (uint32_t c = 0; c < total; c += 64u) {
-        while (!look(&mt->chunk[c], total - c < 64u ? total - c : 64u, nullptr, 0u, tag, tw, tu, overflowed)) __builtin_amdgcn_s_sleep(1);
-        skip = skip || overflowed;
+    for (uint32_t c = 0; c < total;) {
+        if (look(&mt->chunk[c], total - c < 64u ? total - c : 64u, nullptr, 0u, tag, tw, tu, mark)) {
+            skip = skip || (mark & kMarkBad) != 0u;
+            c += 64u;
+            continue;
+        }
+        __builtin_amdgcn_s_sleep(1);
+        if (++wait.polls > wait.most && !wait.last) return;
     }
-    for (uint32_t c = 0; c < total; ++c) {
+    uint32_t summed = ~0u;               // the tensor whose sums p2's scale is from
+    while (true) {
+        unsigned long long ticket = 0ull;
+        if (lane == 0u) ticket = __hip_atomic_fetch_add(&mt->outcome.word, kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_ballot_w64(lane == 0u && marks(ticket, wait.left)) == 0ull) return;
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ticket >> 32));
+        if (c >= total) return;
         Where at;
         at.t = (Descriptor)per_chunk + c;
         at.index = at.t->chunk_index;
         finish_where(at, s.chunk_elems);
-        if (at.index == 0) {             // the first chunk of a tensor: chunks come in tensor order
+        p2.init(at.t, at.base, s);
+        if (at.t->tensor != summed) {
+            summed = at.t->tensor;
             double cw = 0.0, cu = 0.0;
             for (uint32_t g = 0; g < at.t->num_chunks; g += 64u) {
                 const uint32_t members = at.t->num_chunks - g < 64u ? at.t->num_chunks - g : 64u;
-                double aw = 0.0, au = 0.0;
-                while (!look(&mt->chunk[c + g], members, nullptr, 0u, tag, aw, au, overflowed)) __builtin_amdgcn_s_sleep(1);
-                cw += wave_sum(aw);
-                cu += wave_sum(au);
+                if (!look(&mt->chunk[c - at.index + g], members, nullptr, 0u, tag, tw, tu, mark)) return;
+                cw += wave_sum(tw);
+                cu += wave_sum(tu);
             }
             tw = cw;
             tu = cu;
-            if (lane == 0u) { sums[2 * (uint64_t)at.t->tensor] = tw; sums[2 * (uint64_t)at.t->tensor + 1] = tu; }
         }
+        p2.scale(tw, tu);
+        if (at.index == 0 && lane == 0u) { sums[2 * (uint64_t)at.t->tensor] = tw; sums[2 * (uint64_t)at.t->tensor + 1] = tu; }
         if (skip) continue;
         Op again;
         again.init(at.t, at.base, s);
-        p2.init(at.t, at.base, s);
-        p2.scale(tw, tu);
         for (uint32_t e = lane * Op::kPack; e + Op::kPack <= at.len; e += 2u * 64u * Op::kPack) {
             const uint32_t e2 = e + 64u * Op::kPack;
             const bool two = e2 + Op::kPack <= at.len;

@@ -11,7 +11,7 @@ void launch_lamb_one_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hi
     const Layout &L = p->lay();
     const dim3 grid((unsigned)L.chunks), block(kSmallBlock);
     switch (p->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((lamb_one_launch_kernel<GradSlices<r, GF32, MEM>, GROUPED, kSmallBlock>), grid, block, 0, st, L.d_per_chunk, s, p->d_sums, p->d_meeting, flag, p->meeting_limit, L.groups); break;
+#define CASE(r) case r: hipLaunchKernelGGL((lamb_one_launch_kernel<GradSlices<r, GF32, MEM>, GROUPED, kSmallBlock, lamb_meeting_waves(r, GF32)>), grid, block, 0, st, L.d_per_chunk, s, p->d_sums, p->d_meeting, flag, p->meeting_limit, L.groups); break;
         FOR_EACH_R(CASE)
 #undef CASE
     }

@@ -21,9 +21,6 @@ constexpr int32_t kLargeChunkElems = 16384;      // four sweeps of a 512-thread 
 constexpr int32_t kMaxChunkElems = 1 << 24;      // lane offsets inside a chunk are 32-bit byte offsets
 constexpr int kBigBlock = 512, kSmallBlock = 128;
 constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-chunk layout keeps a descriptor per chunk (224 B each)
-// Looks of a wave at the other workgroups' sums before it gives up (see LambMeeting), one to two milliseconds: longer than other
-// kernels commonly keep a grid's last workgroups waiting, and about what the last arrival takes to step the shard by itself.
-constexpr uint32_t kMeetingPolls = 2048;
 constexpr int kOrderedMaxF32Slices = 8;           // fp32 slices: the ordered schedule wins up to 8 (config-2 list: 3.18 against 3.41 ms), at 16 two chunks spill
 constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per compute unit a plan keeps one workgroup per chunk
 
@@ -142,18 +139,11 @@ int lamb_norms(cc_plan *p, hipStream_t st);
 // R = 8, us per step folded / three launches: 7.1 / 8.9 at one chunk, 9.2 / 10.7 at 128, 9.6 / 10.9 at 256, 11.4 / 11.6
 // at 512, but 16.5 / 14.3 at 1024.
 constexpr uint32_t kFoldNormsMaxChunks = 512;
-// Whether cc_fused_lamb_step is a single launch (see LambMeeting): one workgroup per 1024-element chunk, all of which the
-// device holds at a time with room to spare, and no more groups than a wave can look at together.  Eager us per step, one
-// tensor, R = 8, two or three launches / one: 9.4 / 8.2 at 98 chunks, 9.7 / 8.5 at 196, 11.8 / 10.0 at 391, 12.2 / 10.5 at 489,
-// 14.0 / 13.4 at 768, but 15.3 / 16.1 at 1024, where the waves that wait get in the way of those that load.  The line is drawn
-// at 512, two per compute unit, for another reason: a compute unit holds four of these workgroups whatever R is, so up to there
-// two such steps fit the device, or one fits half of it; where some have to wait for others to leave, a step takes
-// milliseconds (see kMeetingPolls).  A device with fewer compute units, as a partition is, gets a lower line.
+// Whether cc_fused_lamb_step is a single launch: one workgroup per 1024-element chunk, and few enough of them (see lamb_meets).
 inline bool lamb_in_one_launch(const cc_plan *p)
 {
     const Layout &L = p->lay();
-    return !p->ordered && L.chunk_elems == kSmallChunkElems && L.chunks > 0 && L.chunks <= (int64_t)kMeetingMostChunks
-           && L.chunks <= 2 * (int64_t)p->cus && L.groups <= kMeetingGroups && L.d_per_chunk;
+    return !p->ordered && L.chunk_elems == kSmallChunkElems && L.d_per_chunk && lamb_meets(L.chunks, L.groups, p->cus, p->R, p->grad_f32);
 }
 int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
 inline bool norms_fold_into_phase2(const cc_plan *p)

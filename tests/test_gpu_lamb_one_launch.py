@@ -1,10 +1,13 @@
-"""LAMB steps of at most 512 chunks run as one launch in which the workgroups wait for each other's norms.
+"""LAMB steps of few chunks (256 to 512, by what the kernel's registers leave room for) run as one launch in which the workgroups
+wait for each other's norms.
 
 Against the two phase calls (separate launches, same additions in the same order): sums, state and flag bit for bit, with
 every wave patient and with none (a limit of 0 polls: whoever does not find all norms at once leaves its part of w to the last
-workgroup that started), with and without an overflow, and against the oracle.  Sizes at the edges: one element, less than a
+workgroup that started) and with some of both, with and without an overflow, and against the oracle.  Sizes at the edges: one element, less than a
 pack, around a chunk, 64 and 65 chunks (sums by
-chunk and by group of 64), 512 (the most) and 513 (three launches), lists with empty, tiny and ragged tensors, 64 groups (the most) and 65."""
+chunk and by group of 64), 256, 384 and 512 (the most, by the slices) and one more, lists with empty, tiny and ragged tensors, 64 groups (the most) and 65."""
+import statistics
+
 import numpy as np
 import pytest
 import torch
@@ -18,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 LISTS = [[1], [3], [1023], [1024], [1027], [10007], [64 * 1024], [64 * 1024 + 1],
          [5, 0, 1024, 4099, 1, 2048, 7], [1] * 64, [20 * 1024 + 2, 42 * 1024 + 1, 1],
-         [129 * 1024 - 3], [1 << 19], [(1 << 19) + 1], [5, 0, 100 * 1024 + 3, 1, 64 * 1024, 300001], [1] * 61 + [192 * 1024], [1] * 62 + [192 * 1024]]
+         [129 * 1024 - 3], [1 << 18], [(1 << 18) + 1], [1 << 19], [(1 << 19) + 1], [5, 0, 100 * 1024 + 3, 1, 64 * 1024, 300001], [1] * 61 + [192 * 1024], [1] * 62 + [192 * 1024]]
 
 
 def _phases(plan, hp, flag, stream=None):
@@ -26,11 +29,30 @@ def _phases(plan, hp, flag, stream=None):
     cc.cc_fused_lamb_phase2(plan, hp, flag, stream)
 
 
+FORMS = [(8, torch.float16, cc.CC_CACHE_AUTO), (1, torch.float32, cc.CC_CACHE_AUTO),
+         (3, torch.float16, cc.CC_CACHE_WRITE_THROUGH), (16, torch.float32, cc.CC_CACHE_RESIDENT)]
+
+
+def _name(n):
+    return "x".join(map(str, n[:4])) + ("_%d" % len(n))
+
+
 @pytest.mark.parametrize("limit", [None, 0])
-@pytest.mark.parametrize("numels", LISTS, ids=lambda n: "x".join(map(str, n[:4])) + ("_%d" % len(n)))
-@pytest.mark.parametrize("R,dtype,policy", [(8, torch.float16, cc.CC_CACHE_AUTO), (1, torch.float32, cc.CC_CACHE_AUTO),
-                                            (3, torch.float16, cc.CC_CACHE_WRITE_THROUGH), (16, torch.float32, cc.CC_CACHE_RESIDENT)])
+@pytest.mark.parametrize("numels", LISTS, ids=_name)
+@pytest.mark.parametrize("R,dtype,policy", FORMS)
 def test_one_launch_gives_the_bits_of_the_two_phases(numels, R, dtype, policy, limit):
+    _compare_with_phases(numels, R, dtype, policy, limit)
+
+
+@pytest.mark.parametrize("limit", [1, 3, 6, 12])
+@pytest.mark.parametrize("numels", [[10007], [64 * 1024], [20 * 1024 + 2, 42 * 1024 + 1, 1], [1 << 18], [5, 0, 100 * 1024 + 3, 1, 64 * 1024]], ids=_name)
+@pytest.mark.parametrize("R,dtype,policy", [FORMS[0], FORMS[1]])
+def test_some_leave_and_some_stay(numels, R, dtype, policy, limit):
+    """About as many looks as a wave needs anyway: some waves write their own part, some leave, some that stay take those over."""
+    _compare_with_phases(numels, R, dtype, policy, limit)
+
+
+def _compare_with_phases(numels, R, dtype, policy, limit):
     wds = [0.01 * (k % 2) for k in range(len(numels))]
     results = []
     for fn in (cc.cc_fused_lamb_step, _phases):
@@ -67,8 +89,8 @@ def test_one_launch_gives_the_bits_of_the_two_phases(numels, R, dtype, policy, l
             assert x is None or torch.equal(x, y), "step %d, output %d" % (t + 1, k)
 
 
-def test_one_launch_matches_the_oracle():
-    numels = [10007, 3, 20 * 1024 + 2]
+@pytest.mark.parametrize("numels", [[10007, 3, 20 * 1024 + 2], [129 * 1024 - 3, 5, 64 * 1024 + 1]], ids=_name)
+def test_one_launch_matches_the_oracle(numels):
     shard = Shard(numels, [0.01, 0.0, 0.01], 4, align_elems=8)
     seeded_state(shard, 5)
     ost = OracleState(shard, range(3))
@@ -83,14 +105,19 @@ def test_one_launch_matches_the_oracle():
     shard.destroy()
 
 
-def test_one_launch_replayed_from_a_graph():
+@pytest.mark.parametrize("limit", [None, 2])
+@pytest.mark.parametrize("numels", [[10007, 3, 20 * 1024 + 2], [129 * 1024 - 3, 5, 64 * 1024 + 1]], ids=_name)
+def test_one_launch_replayed_from_a_graph(numels, limit):
     """The words of earlier replays stay where they are; every replay has to tell its own from theirs."""
-    numels, R = [10007, 3, 20 * 1024 + 2], 4
+    R = 4
     shards = [Shard(numels, [0.01, 0.0, 0.01], R, align_elems=8) for _ in range(2)]
     for s in shards:
         seeded_state(s, 6)
         seeded_grads(s, 60, 1e-2)
     eager, graphed = shards
+    if limit is not None:
+        for p in graphed.plans:
+            cc.cc_plan_set_meeting_limit(p, limit)
 
     def two_steps(s):                    # ping -> pong -> ping: the committed copy is the same buffer afterwards
         for t in (1, 2):
@@ -106,7 +133,7 @@ def test_one_launch_replayed_from_a_graph():
         for s in shards:
             seeded_grads(s, 61 + rep, 1e-2)
             if rep == 2:                 # an overflow: neither copy of w changes, and the next replays go on from them
-                s.grad_of(1, 2)[20 * 1024 + 1] = float("inf")
+                s.grad_of(1, 2)[-1] = float("inf")
         _ = shards[0].w[0].sum().item()  # eager work and a synchronization in between
         two_steps(eager)
         g.replay()
@@ -117,4 +144,47 @@ def test_one_launch_replayed_from_a_graph():
                 bits = torch.int16 if name == "w16" else torch.int32
                 assert torch.equal(a.view(bits), b.view(bits)), "replay %d, %s" % (rep, name)
     for s in shards:
+        s.destroy()
+
+
+@pytest.mark.parametrize("R,numel", [(8, 1 << 19), (8, 1 << 18), (16, 1 << 18), (4, 1 << 19), (8, 1 << 16)])
+def test_steps_on_several_streams_do_not_keep_each_other_out(R, numel):
+    """Four plans on four streams, released together: same bits as one after the other, and not much more time than as phases.  (Where
+    more workgroups waited than the device holds at a time, two such steps took 3.3 ms where the phases take 24 us.)"""
+    plans = [Shard([numel], [0.01], R, unfused=False) for _ in range(4)]
+    streams, gate = [torch.cuda.Stream() for _ in plans], torch.cuda.Stream()
+    want = []
+    for k, s in enumerate(plans):
+        seeded_state(s, 70 + k)
+        seeded_grads(s, 700 + k, 1e-2)
+        s.run(_phases, cc.Hyper(step=1))
+        want.append([x[1].view(torch.int32).clone() for x in (s.w, s.m, s.v)])
+    torch.cuda.synchronize()
+
+    def together(fn):
+        for s in plans:
+            s.w[1].zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(gate):
+            torch.cuda._sleep(400000)                           # until everything has been enqueued
+            start = torch.cuda.Event(enable_timing=True)
+            start.record()
+        ends = [torch.cuda.Event(enable_timing=True) for _ in plans]
+        for s, st, e in zip(plans, streams, ends):
+            st.wait_event(start)
+            with torch.cuda.stream(st):
+                s.run(fn, cc.Hyper(step=1))
+                e.record()
+        torch.cuda.synchronize()
+        assert all(int(s.flag.item()) == 0 for s in plans)
+        for s, bits in zip(plans, want):
+            for x, y in zip((s.w, s.m, s.v), bits):
+                assert torch.equal(x[1].view(torch.int32), y)
+        return max(start.elapsed_time(e) for e in ends)
+
+    together(_phases)
+    phases = statistics.median(together(_phases) for _ in range(5))
+    one = statistics.median(together(cc.cc_fused_lamb_step) for _ in range(5))
+    assert one < 5 * phases, "%.3f ms against %.3f ms" % (one, phases)
+    for s in plans:
         s.destroy()
