@@ -1318,6 +1318,8 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
 //     A wave that finds CLOSED when it would give up knows that everything has been published and looks on.
 //   * One tensor, R = 8, us for a step beside a kernel that leaves 4 of the 256 compute units free for another 160 us / 960 us, two
 //     launches / one: 157 / 172 and 957 / 970 at 128 chunks; 158 / 177 and 957 / 976 at 256.
+//   * Calls that overlap on one plan, which the interface forbids, mix the arrivals and words of two launches; kMeetingBound
+//     ends the waits that would then have no end, with the overflow flag set.
 struct LambMeeting {
     FlagScratch flag;                                                // what the other kernels use
     FlagScratch::Line outcome;
@@ -1398,12 +1400,12 @@ struct Wait {
         left = (unsigned long long)tag << 2 | kAbandoned;
         closed = (unsigned long long)tag << 2 | kClosed;
         stays = meeting_stays(blockIdx.x);
-        most = !stays ? limit : limit > ~0u / kMeetingPatience ? ~0u : limit * kMeetingPatience;
+        most = !stays ? limit : limit > kMeetingBound / kMeetingPatience ? kMeetingBound : limit * kMeetingPatience;
     }
     // A look has been in vain.
     __device__ __forceinline__ Next again(LambMeeting *mt)
     {
-        ++polls;
+        if (++polls > kMeetingBound) return kLeave;
         if (!last && !sure && polls > most) {
             if (give_up(mt, left, closed)) return kLeave;
             sure = true;
@@ -1521,9 +1523,12 @@ __global__ __launch_bounds__(BLOCK, WAVES) void lamb_one_launch_kernel(const Dev
         }
     }
     fc.finish(op.bad, &mt->flag, flag);
+    const auto lost = [&]() {            // only where calls have overlapped: no w that this wave vouches for
+        if (wait.last && lane == 0u) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     if (next == Wait::kLeave) {
         if (lane == 0u) publish(&mt->chunk[wh.slot], 0u, tag, kMarkGone | (block_bad ? kMarkBad : 0u), dw, du);
-        return;
+        return lost();
     }
     if (next == Wait::kLook) {
         if (wait.last) {
@@ -1543,13 +1548,13 @@ __global__ __launch_bounds__(BLOCK, WAVES) void lamb_one_launch_kernel(const Dev
             continue;
         }
         __builtin_amdgcn_s_sleep(1);
-        if (++wait.polls > wait.most && !wait.last) return;
+        if (++wait.polls > (wait.last ? kMeetingBound : wait.most)) return lost();
     }
     uint32_t summed = ~0u;               // the tensor whose sums p2's scale is from
     while (true) {
         unsigned long long ticket = 0ull;
         if (lane == 0u) ticket = __hip_atomic_fetch_add(&mt->outcome.word, kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__builtin_amdgcn_ballot_w64(lane == 0u && marks(ticket, wait.left)) == 0ull) return;
+        if (__builtin_amdgcn_ballot_w64(lane == 0u && marks(ticket, wait.left)) == 0ull) return lost();
         const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ticket >> 32));
         if (c >= total) return;
         Where at;
@@ -1562,7 +1567,7 @@ __global__ __launch_bounds__(BLOCK, WAVES) void lamb_one_launch_kernel(const Dev
             double cw = 0.0, cu = 0.0;
             for (uint32_t g = 0; g < at.t->num_chunks; g += 64u) {
                 const uint32_t members = at.t->num_chunks - g < 64u ? at.t->num_chunks - g : 64u;
-                if (!look(&mt->chunk[c - at.index + g], members, nullptr, 0u, tag, tw, tu, mark)) return;
+                if (!look(&mt->chunk[c - at.index + g], members, nullptr, 0u, tag, tw, tu, mark)) return lost();
                 cw += wave_sum(tw);
                 cu += wave_sum(tu);
             }

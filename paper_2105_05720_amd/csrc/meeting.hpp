@@ -11,6 +11,9 @@ constexpr uint32_t kMeetingChunks = 64, kMeetingMostChunks = 512, kMeetingGroups
 // Looks of a wave at the other workgroups' sums (0.5 to 1 us each) before it gives up, how many times as long the half of the
 // workgroups wait that stays, how often a wave that waits looks whether some have left, and how long one that came after that stays.
 constexpr uint32_t kMeetingPolls = 64, kMeetingPatience = 64, kMeetingGlance = 16, kMeetingLinger = 8;
+// ... and what ends even the waits of those who know that everybody will publish: some seconds.  Only calls that overlap on one
+// plan, which mix their arrivals and words, get there.
+constexpr uint32_t kMeetingBound = 1u << 22;
 // Half of any eight workgroups in a row, and of any that are 2^k apart: workgroups go to XCDs, shader engines and compute
 // units in turn, and on each some have to make room.
 constexpr bool meeting_stays(uint32_t workgroup)

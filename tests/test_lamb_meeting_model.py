@@ -8,7 +8,12 @@ up or glances at the outcome word, and with any number of workgroups resident at
   * from every state that can be reached the launch can still end (no deadlock; a wave that only looks does not move);
   * nobody writes w before every workgroup has published;
   * when the launch has ended, the w of every chunk was written by its own waves or taken from the counter and computed again,
-    and the chunks on the counter were all done by the wave that drew them."""
+    and the chunks on the counter were all done by the wave that drew them.
+
+The second half runs two launches over the same words, as calls that overlap on one plan would, with counted looks: whatever
+they read, every wave leaves."""
+import random
+
 import pytest
 
 OPEN, ABANDONED, CLOSED = 0, 1, 2
@@ -169,3 +174,85 @@ def test_a_model_without_the_handing_over_is_found_out():
                 yield nxt[:7] + (tuple(w if w is None or w[0] != "help" else ("exit",) + w[1:] for w in nxt[7]),)
     with pytest.raises(AssertionError):
         Broken(2, 1, 1, 0, (False, False)).walk()
+
+
+# ---- two launches over the same words ------------------------------------------------------------------------------------
+
+LIMIT, PATIENCE, BOUND = 2, 4, 60
+
+
+def wave(x, tag, b, n, out):
+    """The kernel's waits with their counters.  `x` is shared: arrivals, each chunk's tag, and (tag, state, ticket)."""
+    x["arrived"] += 1
+    last = x["arrived"] % n == 0
+    yield
+    x["chunk"][b] = tag
+    yield
+    polls, sure, most = 0, False, LIMIT * (PATIENCE if b & 1 else 1)
+
+    def mine(state):
+        return x["outcome"][:2] == (tag, state)
+    help_ = False
+    while any(t != tag for t in x["chunk"]):
+        polls += 1
+        yield
+        if polls > BOUND:
+            return out.append((tag, b, last))
+        if not last and not sure and polls > most:
+            if not mine(CLOSED):
+                x["outcome"] = (tag, ABANDONED, 0)
+                return out.append((tag, b, False))
+            sure = True
+        if mine(ABANDONED) and not sure:
+            if not last and polls <= LIMIT:
+                return out.append((tag, b, False))
+            help_ = True
+            break
+    yield
+    if not help_:
+        if last:
+            was = x["outcome"]
+            x["outcome"] = (tag, CLOSED, 0)
+            yield
+            if was[:2] != (tag, ABANDONED):
+                return out.append((tag, b, False))
+            x["outcome"] = was
+        elif polls <= LIMIT or not mine(ABANDONED):
+            return out.append((tag, b, False))
+    while any(t != tag for t in x["chunk"]):
+        polls += 1
+        yield
+        if polls > (BOUND if last else most):
+            return out.append((tag, b, last))
+    while True:
+        yield
+        t, state, ticket = x["outcome"]
+        x["outcome"] = (t, state, ticket + 1)
+        if (t, state) != (tag, ABANDONED):
+            return out.append((tag, b, last))
+        if ticket >= n:
+            return out.append((tag, b, False))
+        for _ in range(2):                                                 # the chunk
+            yield
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 8])
+def test_overlapping_calls_end(n):
+    lost = 0
+    for seed in range(300):
+        rng = random.Random(seed)
+        x = {"arrived": 0, "chunk": [0] * n, "outcome": (0, OPEN, 0)}
+        out = []
+        alive = [wave(x, tag, b, n, out) for tag in (1, 2) for b in range(n)]
+        for _ in range(2 * n * (3 * BOUND + 3 * n + 10)):
+            if not alive:
+                break
+            # now and then one wave runs alone for a while
+            i = rng.randrange(len(alive)) if seed % 2 else rng.randrange(min(2, len(alive)))
+            try:
+                next(alive[i])
+            except StopIteration:
+                alive.pop(i)
+        assert not alive and len(out) == 2 * n
+        lost += any(gone for _, _, gone in out)
+    assert lost > 0 or n == 1                                              # some last arrival had to end its wait
