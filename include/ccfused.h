@@ -163,7 +163,8 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).  (One tensor in chunks below 4096
  * elements whose step's buffers total 200 MiB and more is the exception: there the fused Adam step runs single-wave
  * workgroups of 256 elements, unless the caller has asked for CC_CACHE_RESIDENT.  So it does on one larger tensor for which
- * the caller has chosen nothing, up to 192 Mi elements, and with four and more fp32 slices beyond.)
+ * the caller has chosen nothing, up to 192 Mi elements with up to ten fp16 slices (144 Mi with one) or with fp32 slices, and with
+ * four and more of those beyond.)
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);

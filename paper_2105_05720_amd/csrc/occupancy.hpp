@@ -60,21 +60,30 @@ inline unsigned flat_lds(uint64_t numel, int R, bool grad_f32, bool non_temporal
     return lds < most ? lds : most;
 }
 
-// From kSmallShardElems elements on a plan's chunks are large and the ordered schedule takes over, but the fused Adam step on
-// one tensor for which nothing else was asked stays with single-wave pieces while they are the faster ones (where the arrays lie
-// moves either side by 1 to 2 %).  Two shards in turn,
-// us, large chunks (ordered up to eight fp32 slices) / pieces: fp16 slices, 64 Mi elements R = 8 470 / 444, 128 Mi 914 / 875;
-// 70 M elements R = 1 324 / 308, R = 2 347 / 338, R = 4 384 / 372, R = 16 667 / 651; 200 M R = 1 897 / 879, R = 2 957 / 953, R = 4 1092 /
-// 1051, R = 8 1340 / 1327, R = 16 1891 / 1886 (150 M 1410 / 1417); but 260 M R = 1 1133 / 1181, R = 16 2474 / 2521 and 500 M R = 1 2146 /
-// 2244, R = 4 2661 / 2676, R = 8 3285 / 3314.  With four and more fp32 slices, of which a compute unit's two chunks in flight are
-// as much as it holds, at every size: R = 4 485 / 458 at 70 M, 1388 / 1318 at 200 M, 3467 / 3280 at 500 M; R = 8 694 / 665, 2018 / 1854,
-// 4968 / 4557; R = 12 906 / 865 at 70 M; R = 16 1108 / 1070 and 3229 / 3117 at 200 M.
-constexpr uint64_t kSmallShardElems = 64u << 20, kFlatF16MaxElems = 192u << 20;
-constexpr int kFlatAlwaysF32Slices = 4;
+// From kSmallShardElems elements on a plan's chunks are large and the ordered schedule takes over (up to eight fp32 slices), but the
+// fused Adam step on one tensor for which nothing else was asked stays with single-wave pieces where they are the faster ones.
+// One plan, the same buffers, large chunks and pieces in turn, us, medians of six (one shard by itself, then two in turn; where the
+// arrays lie moves either side by up to 5 %):
+//   fp16, R = 1       67 M elements 313 / 305, 318 / 295; 130 M 592 / 593, 600 / 577; 150 M 712 / 698, 689 / 667; but 201 M 904 / 931, 908 / 930
+//   R = 2             67 M 330 / 313, 335 / 315; 130 M 644 / 617, 633 / 619; 201 M 981 / 952, 982 / 959
+//   R = 4             67 M 372 / 354, 377 / 361; 130 M 721 / 720, 720 / 692; 201 M 1117 / 1091, 1140 / 1094
+//   R = 8             67 M 451 / 442, 457 / 452; 130 M 871 / 863, 880 / 855; 201 M 1347 / 1325, 1351 / 1348
+//   R = 10            67 M 498 / 483, 496 / 486; 130 M 964 / 952, 962 / 950; 201 M 1457 / 1457, 1466 / 1478
+//   R = 12, 14, 16    level: 101 M 806 / 813, 875 / 889, 928 / 946; 201 M 1587 / 1611, 1736 / 1743, 1824 / 1878
+//   fp32, R = 1 to 3  67 M 338 / 329, 373 / 353, 433 / 396; 130 M 636 / 624, 718 / 704, 850 / 779; 201 M 988 / 992, 1118 / 1074, 1302 / 1198
+//   R = 4             67 M 461 / 430; 201 M 1425 / 1308; 400 M 2716 / 2597; 800 M 5721 / 5163
+//   R = 8             67 M 646 / 627; 201 M 1961 / 1856; 400 M 4071 / 3774; 800 M 7797 / 7663
+//   R = 12, 16        67 M 852 / 829, 1049 / 1030; 201 M 2596 / 2476, 3157 / 3079; 800 M 9726 / 9663, 12246 / 12127
+// With fp16 slices and at least 260 M elements the ordered schedule is ahead (R = 1 1133 / 1181, R = 16 2474 / 2521; 500 M R = 1 2146 / 2244,
+// R = 8 3285 / 3314).  With four and more fp32 slices, of which a compute unit's two chunks in flight are as much as it holds, the pieces
+// were ahead at every size up to the 800 M elements measured, and the rule goes on beyond.
+constexpr uint64_t kSmallShardElems = 64u << 20, kFlatNarrowMaxElems = 144u << 20, kFlatWideMaxElems = 192u << 20;
+constexpr int kFlatMaxF16Slices = 10, kFlatAlwaysF32Slices = 4;
 inline bool flat_beyond_small(uint64_t numel, int R, bool grad_f32)
 {
     if (numel < kSmallShardElems || numel > kFlatMaxElems) return false;
-    return numel < kFlatF16MaxElems || (grad_f32 && R >= kFlatAlwaysF32Slices);
+    if (grad_f32) return numel < kFlatWideMaxElems || R >= kFlatAlwaysF32Slices;
+    return R <= kFlatMaxF16Slices && numel < (R == 1 ? kFlatNarrowMaxElems : kFlatWideMaxElems);
 }
 
 }  // namespace ccf

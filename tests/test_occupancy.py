@@ -52,8 +52,10 @@ def test_one_tensor(per_cu, R, f32, through, streamed):
     assert [per_cu(n, R, f32, nt, rule="flat") for nt in (0, 1) for n in (at - 1, at, 1 << 26)] == [16, through, through, 16, streamed, streamed]
 
 
-@pytest.mark.parametrize("R,f32,sizes", [(1, 0, [0, 1, 1, 0, 0, 0]), (16, 0, [0, 1, 1, 0, 0, 0]), (3, 1, [0, 1, 1, 0, 0, 0]),
-                                         (4, 1, [0, 1, 1, 1, 1, 0]), (16, 1, [0, 1, 1, 1, 1, 0])])
+@pytest.mark.parametrize("R,f32,sizes", [(1, 0, [0, 1, 1, 0, 0, 0, 0, 0]), (2, 0, [0, 1, 1, 1, 1, 0, 0, 0]), (10, 0, [0, 1, 1, 1, 1, 0, 0, 0]),
+                                         (11, 0, [0] * 8), (16, 0, [0] * 8), (1, 1, [0, 1, 1, 1, 1, 0, 0, 0]), (3, 1, [0, 1, 1, 1, 1, 0, 0, 0]),
+                                         (4, 1, [0, 1, 1, 1, 1, 1, 1, 0]), (16, 1, [0, 1, 1, 1, 1, 1, 1, 0])])
 def test_pieces_on_one_large_tensor(per_cu, R, f32, sizes):
-    at = ((64 << 20) - 1, 64 << 20, (192 << 20) - 1, 192 << 20, 1 << 33, (1 << 33) + 1)
+    """Only where the measured pairs show a gain: not from eleven fp16 slices on, and up to 144 Mi elements with one."""
+    at = ((64 << 20) - 1, 64 << 20, (144 << 20) - 1, 144 << 20, (192 << 20) - 1, 192 << 20, 1 << 33, (1 << 33) + 1)
     assert [per_cu(n, R, f32, 0, rule="pieces") == 16 for n in at] == [bool(k) for k in sizes]
