@@ -17,22 +17,29 @@ void launch_lamb_one_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hi
     }
 }
 
-// Up to 65536 elements every wave looks at every chunk's sums, beyond that at every group's.  A plan that was asked to keep its
-// loads non-temporal and write through gets plain loads: the shard fits the Infinity Cache many times.
-template <bool GF32>
+// Up to 65536 elements every wave looks at every chunk's sums, beyond that at every group's.
+template <bool GF32, class MEM>
 void launch_lamb_one(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    const bool grouped = p->lay().chunks > (int64_t)kMeetingChunks;
-    if (p->mem.lamb1 == CC_CACHE_STREAMING) grouped ? launch_lamb_one_r<GF32, true, Streaming>(p, s, flag, st) : launch_lamb_one_r<GF32, false, Streaming>(p, s, flag, st);
-    else grouped ? launch_lamb_one_r<GF32, true, Resident>(p, s, flag, st) : launch_lamb_one_r<GF32, false, Resident>(p, s, flag, st);
+    if (p->lay().chunks > (int64_t)kMeetingChunks) launch_lamb_one_r<GF32, true, MEM>(p, s, flag, st);
+    else launch_lamb_one_r<GF32, false, MEM>(p, s, flag, st);
+}
+
+// A shard this small has the same policy in both sweeps (see cache_policies).
+template <bool GF32>
+void launch_lamb_one_by_policy(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+{
+    if (p->mem.lamb1 == CC_CACHE_RESIDENT) launch_lamb_one<GF32, Resident>(p, s, flag, st);
+    else if (p->mem.lamb1 == CC_CACHE_WRITE_THROUGH) launch_lamb_one<GF32, WriteThrough>(p, s, flag, st);
+    else launch_lamb_one<GF32, Streaming>(p, s, flag, st);
 }
 
 }  // namespace
 
 int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    if (p->grad_f32) launch_lamb_one<true>(p, s, flag, st);
-    else launch_lamb_one<false>(p, s, flag, st);
+    if (p->grad_f32) launch_lamb_one_by_policy<true>(p, s, flag, st);
+    else launch_lamb_one_by_policy<false>(p, s, flag, st);
     return launched("lamb_one_launch_kernel");
 }
 

@@ -14,6 +14,7 @@ import torch
 
 import oracle
 from paper_2105_05720_amd import binding as cc
+from paper_2105_05720_amd.launches import launches
 from paper_2105_05720_amd.shard import Shard
 from parity import OracleState, compare_committed, hyper_pair, seeded_grads, seeded_state
 
@@ -188,3 +189,14 @@ def test_steps_on_several_streams_do_not_keep_each_other_out(R, numel):
     assert one < 5 * phases, "%.3f ms against %.3f ms" % (one, phases)
     for s in plans:
         s.destroy()
+
+
+@pytest.mark.parametrize("policy,mem", [(cc.CC_CACHE_STREAMING, "9Streaming"), (cc.CC_CACHE_RESIDENT, "8Resident"), (cc.CC_CACHE_WRITE_THROUGH, "12WriteThrough")])
+@pytest.mark.parametrize("numel", [10007, 65 * 1024])
+def test_the_policy_asked_for_is_the_one_that_runs(numel, policy, mem):
+    for R, dtype in ((2, torch.float16), (2, torch.float32)):
+        shard = Shard([numel], [0.01], R, grad_dtype=dtype, cache_policy=policy)
+        assert cc.cc_plan_layout(shard.plans[0])[2] == policy
+        what = launches(lambda: shard.run(cc.cc_fused_lamb_step, cc.Hyper(step=1)))
+        assert [x.kernel for x in what] == ["lamb_one_launch_kernel"] and mem in what[0].symbol
+        shard.destroy()
