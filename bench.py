@@ -126,19 +126,21 @@ class Timer:
 
 
 def describe(cc, shard, R, optimizer, gf32):
-    sched, wgs = cc.cc_plan_schedule(shard.plans[0])
+    """What a step of this shard runs; the kernels are read from a captured graph of one step, which executes nothing."""
+    from paper_2105_05720_amd.launches import launches
     chunk, block, policy = cc.cc_plan_layout(shard.plans[0])
     _, chunks, table_bytes = cc.cc_plan_info(shard.plans[0])
-    ordered = sched == cc.CC_SCHEDULE_ORDERED
-    one = len([n for n in shard.numels if n]) == 1
-    if optimizer == "adam":
-        kernel = "fused_adam%s_kernel<R=%d, %d threads>" % ("_ordered" if ordered else ("_flat" if one else ""), R, block)
+    fn = cc.cc_fused_adam_step if optimizer == "adam" else cc.cc_fused_lamb_step
+    what = launches(lambda: shard.run(fn, cc.Hyper(step=1, skip_mode=int(shard.in_place))))
+    kernel = " + ".join("%s<%s%d threads>" % (x.kernel, "R=%d, " % R if x.kernel.startswith(("fused_adam", "lamb_phase1", "lamb_one")) else "", x.block)
+                        for x in what)
+    if "_ordered_kernel" in what[0].kernel:
+        schedule = "ordered: %d persistent workgroups take the chunks in table order" % what[0].grid
+    elif what[0].grid != chunks:
+        schedule = "%d workgroups of %d threads, one per piece of 256 elements" % (what[0].grid, what[0].block)
     else:
-        kernel = "lamb_phase1%s_kernel<R=%d, %d threads> + lamb_norms_kernel + lamb_phase2%s_kernel" % (
-            ("_ordered", R, block, "_ordered") if ordered else ("", R, block, ""))
-    return {"chunk_elems": chunk, "chunks": chunks, "table_bytes": table_bytes, "kernel": kernel,
-            "schedule": ("ordered: %d persistent workgroups take the chunks in table order" % wgs) if ordered
-            else "one workgroup of %d threads per chunk" % block,
+        schedule = "one workgroup of %d threads per chunk" % what[0].block
+    return {"chunk_elems": chunk, "chunks": chunks, "table_bytes": table_bytes, "kernel": kernel, "schedule": schedule,
             "cache_policy": {cc.CC_CACHE_RESIDENT: "plain loads, write-through stores (cache-resident shard)",
                              cc.CC_CACHE_WRITE_THROUGH: "non-temporal loads, write-through stores"}.get(policy, "non-temporal accesses")}
 
