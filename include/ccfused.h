@@ -24,7 +24,7 @@
  *     is enqueued; a rejected call enqueues nothing.
  *   - A plan may be used by one stream at a time: its scratch buffers are shared by all of its calls.
  *     Calls on one plan that overlap in time leave wrong outputs and a wrong flag.  A LAMB step of one launch among them
- *     (see cc_fused_lamb_step) ends all the same, after some seconds of waiting at most, with the flag raised.
+ *     (see cc_fused_lamb_step) ends all the same, after some seconds of waiting at most.
  */
 #ifndef CCFUSED_H
 #define CCFUSED_H

@@ -1319,7 +1319,7 @@ __global__ __launch_bounds__(BLOCK) void lamb_phase2_with_norms_kernel(const Dev
 //   * One tensor, R = 8, us for a step beside a kernel that leaves 4 of the 256 compute units free for another 160 us / 960 us, two
 //     launches / one: 157 / 172 and 957 / 970 at 128 chunks; 158 / 177 and 957 / 976 at 256.
 //   * Calls that overlap on one plan, which the interface forbids, mix the arrivals and words of two launches; kMeetingBound
-//     ends the waits that would then have no end, with the overflow flag set.
+//     ends the waits that would then have no end, and a wave that took itself for the last arrival sets the overflow flag.
 struct LambMeeting {
     FlagScratch flag;                                                // what the other kernels use
     FlagScratch::Line outcome;
