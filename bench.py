@@ -125,10 +125,15 @@ class Timer:
         return times[len(times) // 2]
 
 
+# By the template argument of the first kernel.
+POLICIES = (("8Resident", "plain loads, write-through stores (cache-resident shard)"), ("12WriteThrough", "non-temporal loads, write-through stores"),
+            ("11WeightsKept", "non-temporal loads but for the weights in the first sweep, write-through stores"))
+
+
 def describe(cc, shard, R, optimizer, gf32):
     """What a step of this shard runs; the kernels are read from a captured graph of one step, which executes nothing."""
     from paper_2105_05720_amd.launches import launches
-    chunk, block, policy = cc.cc_plan_layout(shard.plans[0])
+    chunk, block, _ = cc.cc_plan_layout(shard.plans[0])
     _, chunks, table_bytes = cc.cc_plan_info(shard.plans[0])
     fn = cc.cc_fused_adam_step if optimizer == "adam" else cc.cc_fused_lamb_step
     what = launches(lambda: shard.run(fn, cc.Hyper(step=1, skip_mode=int(shard.in_place))))
@@ -141,8 +146,7 @@ def describe(cc, shard, R, optimizer, gf32):
     else:
         schedule = "one workgroup of %d threads per chunk" % what[0].block
     return {"chunk_elems": chunk, "chunks": chunks, "table_bytes": table_bytes, "kernel": kernel, "schedule": schedule,
-            "cache_policy": {cc.CC_CACHE_RESIDENT: "plain loads, write-through stores (cache-resident shard)",
-                             cc.CC_CACHE_WRITE_THROUGH: "non-temporal loads, write-through stores"}.get(policy, "non-temporal accesses")}
+            "cache_policy": next((text for name, text in POLICIES if name in what[0].symbol), "non-temporal accesses")}
 
 
 def main() -> int:

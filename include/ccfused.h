@@ -161,8 +161,8 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  * rule.  Adam results do not depend on it; LAMB's norms are summed chunk by chunk, so they move in the last bits.
  * cc_plan_layout reports what the plan will use (each pointer may be NULL): chunk size, threads per workgroup,
  * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).  (One tensor in chunks below 4096
- * elements whose step's buffers total 200 MiB and more is the exception: there the fused Adam step runs single-wave
- * workgroups of 256 elements, unless the caller has asked for CC_CACHE_RESIDENT.  So it does on one larger tensor for which
+ * elements whose step's buffers total 200 MiB and more, or 80 MiB with 1024-element chunks, is the exception: there the fused Adam
+ * step runs single-wave workgroups of 256 elements, unless the caller has asked for CC_CACHE_RESIDENT.  So it does on one larger tensor for which
  * the caller has chosen nothing, up to 192 Mi elements with up to ten fp16 slices (144 Mi with one) or with fp32 slices, and with
  * four and more of those beyond.)
  */
@@ -177,7 +177,8 @@ int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_thr
  * exist for 128-thread workgroups (chunks below 4096 elements) and are ignored otherwise.  Results do not depend on
  * the policy.  AUTO (default): STREAMING while the step's buffers total less than 4 MiB (1-6 % faster there); else
  * RESIDENT while they total less than 200 MiB (4-24 % faster than STREAMING between 2^18 and 2^22 elements in the size
- * sweep); else WRITE_THROUGH while the Adam step stores less than 288 MiB (14 bytes per element: up to 20.5 Mi elements,
+ * sweep), where from 80 MiB on the fused steps on 1024-element chunks read with non-temporal loads (4-25 % faster where the chip's
+ * caches hold anything else), but for what LAMB reads a second time; else WRITE_THROUGH while the Adam step stores less than 288 MiB (14 bytes per element: up to 20.5 Mi elements,
  * 8-12 % faster at 2^23 and 2^24); else STREAMING.  That is the Adam step's policy, which cc_plan_layout reports; LAMB stores
  * 8 bytes per element in its first sweep and goes by those, and from 288 MiB on still writes that sweep through; the unfused LAMB
  * pipeline writes both its sweeps through from 200 MiB on.

@@ -62,4 +62,38 @@ inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool g
     return c;
 }
 
+// What the fused steps' launches use where AUTO says RESIDENT.  A plain load that misses places its line in the Infinity Cache, and
+// where that is full of lines that others wrote (a backward pass, other shards), one of those goes to HBM first.  With the step's
+// buffers at this size and beyond, a step finds too little of what it reads on chip to make up for that: its loads are
+// non-temporal from there on, but for the weights in LAMB's first sweep, which the second reads again.  That one's loads stay
+// plain as long as the w, m' and v' that it reads still fit the eight L2s.
+// us, plain loads / this (Adam: one tensor, which then runs in single-wave pieces, see kFlatPiece; its 63 and 76 MB are below the line):
+//                              three shards in turn   one by itself   behind a 1 GiB fill   behind a copy, with the slices written
+//   Adam R = 8,   63 MB            11.4 / 11.7         10.6 / 10.9        24.0 / 15.7            14.5 / 14.1
+//                 76 MB            13.2 / 13.9         13.0 / 12.6        28.2 / 17.7            16.8 / 15.7
+//                 84 MB            15.5 / 14.9         14.3 / 13.6        30.9 / 18.8            18.4 / 16.8
+//                126 MB            26.4 / 20.7         19.2 / 19.8        43.1 / 25.7            23.3 / 22.8
+//                176 MB            35.8 / 27.8         27.2 / 27.6        58.0 / 34.2            31.6 / 29.5
+//        R = 1,   84 MB            16.2 / 15.9         14.1 / 16.0        26.8 / 19.1            19.0 / 17.9
+//        R = 16, 174 MB            36.7 / 27.5         28.9 / 27.1        62.4 / 33.8            32.5 / 29.2
+//        list, 110 MB              22.0 / 20.0         18.7 / 18.9        40.6 / 25.7            22.9 / 22.1
+//   LAMB R = 8,   63 MB            18.8 / 19.1         17.4 / 17.5        31.8 / 24.6            22.3 / 21.6
+//                 84 MB            23.2 / 22.4         21.7 / 20.9        39.0 / 29.3            26.3 / 24.9
+//                126 MB            36.3 / 31.3         30.3 / 29.2        53.4 / 38.4            34.7 / 32.4
+//                176 MB            48.9 / 40.7         39.8 / 39.0        69.8 / 48.9            43.9 / 41.9
+//        R = 1,  140 MB            41.4 / 35.5         36.0 / 33.8        55.1 / 44.7            43.0 / 39.0
+// (LAMB with all loads of the first sweep non-temporal: 24.4 at 84 MB, 34.3 at 126.  Second sweep with plain / non-temporal loads, three in
+// turn: 22.4 / 23.0 at 24 MB of w, m' and v', 27.1 / 27.4 at 30, 31.1 / 31.3 at 36, 41.5 / 40.7 at 50, R = 1 38.2 / 35.5 at 60.)
+constexpr uint64_t kPlainLoadsMaxBytes = 80ull << 20, kL2Bytes = 32ull << 20, kLambReadAgainBytes = 12;
+constexpr int32_t kWeightsKept = 16;       // beside the cc_cache_policy values: see WeightsKept in kernels.hip.h
+inline CachePolicies fused_policies(CachePolicies c, int32_t asked, uint64_t numel, int R, bool grad_f32, bool one_sweep)
+{
+    const uint64_t footprint = step_footprint(numel, R, grad_f32);
+    if (asked != CC_CACHE_AUTO || !one_sweep || footprint < kPlainLoadsMaxBytes || footprint >= kResidentMaxBytes) return c;
+    c.adam = CC_CACHE_WRITE_THROUGH;
+    c.lamb1 = kWeightsKept;
+    if (numel * kLambReadAgainBytes >= kL2Bytes) c.lamb = CC_CACHE_WRITE_THROUGH;
+    return c;
+}
+
 }  // namespace ccf

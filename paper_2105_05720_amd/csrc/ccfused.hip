@@ -130,8 +130,11 @@ void resolve_schedule(cc_plan *p)
     const bool small = L.block == kSmallBlock && !p->ordered;
     const bool one_sweep = L.chunk_elems == kSmallChunkElems;
     p->mem = small ? cache_policies(p->cache_policy, p->numel, p->R, p->grad_f32, one_sweep) : CachePolicies{};
-    p->beyond_cache = small && step_footprint(p->numel, p->R, p->grad_f32) >= kResidentMaxBytes;
-    p->spread = p->beyond_cache && one_sweep;
+    p->fused = small ? fused_policies(p->mem, p->cache_policy, p->numel, p->R, p->grad_f32, one_sweep) : CachePolicies{};
+    const uint64_t footprint = step_footprint(p->numel, p->R, p->grad_f32);
+    p->spread = small && one_sweep && footprint >= kResidentMaxBytes;
+    p->spread_adam = p->spread || (small && one_sweep && footprint >= kPlainLoadsMaxBytes && p->fused.adam != CC_CACHE_RESIDENT);
+    p->flat_pieces = p->spread_adam || (small && footprint >= kResidentMaxBytes);
 }
 
 void free_layout(Layout &L)
@@ -582,6 +585,7 @@ int cc_fused_adam_step(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *st
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     if (p->chunks() == 0) return clear_flag(flag, st);
+    s.runs = p->spread_adam ? 1u : 0u;
     const int mode = (hp->skip_mode == 1 ? kModeGuard : 0) | (hp->adam_mode == 0 ? kModeL2 : 0);
     if (p->grad_f32) launch_fused_adam_f32(p, s, flag, st, mode);
     else launch_fused_adam_f16(p, s, flag, st, mode);
@@ -683,8 +687,9 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
     d.wd = t->weight_decay;
     const unsigned grid = (unsigned)((t->numel + (uint64_t)kSmallChunkElems - 1) / (uint64_t)kSmallChunkElems);
     const int mode = (hp->skip_mode == 1 ? kModeGuard : 0) | (hp->adam_mode == 0 ? kModeL2 : 0);
-    const int32_t mem = auto_cache_policy(step_footprint(t->numel, R, false), t->numel * kAdamStoreBytes);   // the plans' AUTO rule
-    launch_fused_adam_flat_f16(d, R, grid, mem, s, fs, flag, st, mode);
+    CachePolicies mem = cache_policies(CC_CACHE_AUTO, t->numel, R, false, true);                             // the plans' AUTO rule
+    mem = fused_policies(mem, CC_CACHE_AUTO, t->numel, R, false, true);
+    launch_fused_adam_flat_f16(d, R, grid, mem.adam, s, fs, flag, st, mode);
     return launched("fused_adam_flat_kernel");
 }
 

@@ -136,6 +136,10 @@ __device__ __forceinline__ gbytes chunk_base(void *p, uint64_t byte_off) { retur
 struct Streaming { static constexpr bool kLoadNonTemporal = true, kStoreThrough = false; };
 struct Resident { static constexpr bool kLoadNonTemporal = false, kStoreThrough = true; };
 struct WriteThrough { static constexpr bool kLoadNonTemporal = true, kStoreThrough = true; };
+// LAMB's first sweep only: WriteThrough, but the weights, which the second sweep reads again, by plain loads (see fused_policies).
+struct WeightsKept : WriteThrough {};
+template <class Mem> struct ReadAgain { typedef Mem Policy; };
+template <> struct ReadAgain<WeightsKept> { typedef Resident Policy; };
 
 template <class Mem> __device__ __forceinline__ f32x4 ld_f32x4(gcbytes b, uint32_t off)
 {
@@ -1018,7 +1022,7 @@ struct LambPhase1Op {
     __device__ __forceinline__ void load(Regs &x, uint32_t e) const
     {
         grad.load(x.g, e);
-        ld_f32x4<Mem>(w_in, e * 4, x.w); ld_f32x4<Mem>(m_in, e * 4, x.m); ld_f32x4<Mem>(v_in, e * 4, x.v);
+        ld_f32x4<typename ReadAgain<Mem>::Policy>(w_in, e * 4, x.w); ld_f32x4<Mem>(m_in, e * 4, x.m); ld_f32x4<Mem>(v_in, e * 4, x.v);
     }
     __device__ __forceinline__ void one(float S, float w, float &m, float &v)
     {

@@ -42,7 +42,7 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
     if (p->single >= 0) {                  // one tensor: no table, descriptor in the kernel arguments
         const DevTensor &t = L.host_tensors[(size_t)p->single];
         if constexpr (!std::is_same<MEM, Resident>::value)
-            if (p->beyond_cache && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
+            if (p->flat_pieces && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
         switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, 0, st, t, s, p->d_flag_scratch, flag); break;
             FOR_EACH_R(CASE)
@@ -50,7 +50,7 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
         }
         return;
     }
-    const unsigned lds = p->spread ? list_lds(p->numel, p->R, GF32, std::is_same<MEM, Streaming>::value) : 0u;
+    const unsigned lds = p->spread_adam ? list_lds(p->numel, p->R, GF32, std::is_same<MEM, Streaming>::value) : 0u;
     switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, lds, st, L.table_tensors(), L.table_chunks(), s, p->d_flag_scratch, flag); break;
         FOR_EACH_R(CASE)
@@ -72,7 +72,7 @@ void launch_mode(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStrea
 template <bool GF32>
 void launch_fused_adam(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, int mode)
 {
-    BY_BLOCK(p, (launch_mode<BLK, GF32, MEM>(p, s, flag, st, mode)));
+    BY_BLOCK_MEM(p, p->fused.adam, (launch_mode<BLK, GF32, MEM>(p, s, flag, st, mode)));
 }
 
 }  // namespace

@@ -14,7 +14,7 @@ template <int MODE, class MEM>
 void launch_flat_r(const DevTensor &t, int R, unsigned grid, const StepScalars &s, FlagScratch *fs, int32_t *flag, hipStream_t st)
 {
     if constexpr (!std::is_same<MEM, Resident>::value)
-        if (step_footprint(t.numel, R, false) >= kResidentMaxBytes) return launch_flat_pieces<MODE, false, MEM>(t, R, s, fs, flag, st);
+        if (step_footprint(t.numel, R, false) >= kPlainLoadsMaxBytes) return launch_flat_pieces<MODE, false, MEM>(t, R, s, fs, flag, st);
     switch (R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, kSmallBlock, false, 2, MEM>), dim3(grid), dim3(kSmallBlock), 0, st, t, s, fs, flag); break;
         FOR_EACH_R(CASE)

@@ -30,8 +30,13 @@ void launch_lamb_phase1_r(const cc_plan *p, const StepScalars &s, int32_t *flag,
 
 void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    if (p->grad_f32) BY_BLOCK_MEM(p, p->mem.lamb1, (launch_lamb_phase1_r<BLK, true, MEM>(p, s, flag, st)));
-    else BY_BLOCK_MEM(p, p->mem.lamb1, (launch_lamb_phase1_r<BLK, false, MEM>(p, s, flag, st)));
+    if (p->fused.lamb1 == kWeightsKept) {
+        if (p->grad_f32) launch_lamb_phase1_r<kSmallBlock, true, WeightsKept>(p, s, flag, st);
+        else launch_lamb_phase1_r<kSmallBlock, false, WeightsKept>(p, s, flag, st);
+        return;
+    }
+    if (p->grad_f32) BY_BLOCK_MEM(p, p->fused.lamb1, (launch_lamb_phase1_r<BLK, true, MEM>(p, s, flag, st)));
+    else BY_BLOCK_MEM(p, p->fused.lamb1, (launch_lamb_phase1_r<BLK, false, MEM>(p, s, flag, st)));
 }
 
 void launch_lamb_phase1_from_sum(const cc_plan *p, const StepScalars &s, hipStream_t st)
@@ -53,7 +58,7 @@ int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipS
         return launched("lamb_phase2_ordered_kernel");
     }
     const dim3 grid((unsigned)L.chunks);
-    if (emit16) BY_BLOCK_MEM(p, p->mem.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
+    if (emit16) BY_BLOCK_MEM(p, p->fused.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
     else BY_BLOCK_MEM(p, p->mem.lamb1, hipLaunchKernelGGL((lamb_phase2_kernel<false, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
     return launched("lamb_phase2_kernel");
 }
@@ -62,7 +67,7 @@ int lamb_phase2_with_norms(cc_plan *p, const StepScalars &s, const int32_t *flag
 {
     const Layout &L = p->lay();
     const dim3 grid((unsigned)L.chunks);
-    BY_BLOCK_MEM(p, p->mem.lamb, hipLaunchKernelGGL((lamb_phase2_with_norms_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials, p->d_sums, flag));
+    BY_BLOCK_MEM(p, p->fused.lamb, hipLaunchKernelGGL((lamb_phase2_with_norms_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials, p->d_sums, flag));
     return launched("lamb_phase2_with_norms_kernel");
 }
 

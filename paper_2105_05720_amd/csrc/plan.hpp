@@ -68,9 +68,11 @@ struct cc_plan {
     int32_t schedule = CC_SCHEDULE_AUTO;    // what the caller asked for
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
     ccf::CachePolicies mem;                 // the policies in use (other than STREAMING: small-chunk layouts only)
-    bool beyond_cache = false;              // small chunks of a shard bound by HBM (one tensor: see kFlatPiece)
+    ccf::CachePolicies fused;               // ... by the fused steps (see fused_policies)
+    bool flat_pieces = false;               // small chunks of one tensor bound by HBM: fused Adam in single-wave pieces (see kFlatPiece)
     bool flat_adam = false;                 // large chunks, but the fused Adam step in single-wave pieces (see flat_beyond_small)
-    bool spread = false;                    // ... of 1024 elements (see kSpreadLds)
+    bool spread = false;                    // chunks of 1024 elements of a shard bound by HBM (see kSpreadLds)
+    bool spread_adam = false;               // ... for the fused Adam step
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
     int32_t cus = 0;                        // compute units of the device the plan was created on
     int32_t single = -1;                    // index of the only tensor with elements, or -1 if there are several (or none)

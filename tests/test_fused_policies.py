@@ -1,0 +1,55 @@
+"""What the fused steps' launches use where AUTO says RESIDENT (fused_policies in csrc/cache_rules.hpp), compiled for the host: one element
+below and at each bound that the header states."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2105_05720_amd import binding as cc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+AUTO, RESIDENT, THROUGH, KEPT = cc.CC_CACHE_AUTO, cc.CC_CACHE_RESIDENT, cc.CC_CACHE_WRITE_THROUGH, 16
+MIB = 1 << 20
+
+MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "cache_rules.hpp"
+
+int main(int, char **argv)
+{
+    const int asked = atoi(argv[1]), R = atoi(argv[3]);
+    const uint64_t numel = strtoull(argv[2], nullptr, 10);
+    const bool f32 = atoi(argv[4]) != 0, one_sweep = atoi(argv[5]) != 0;
+    const ccf::CachePolicies c = ccf::fused_policies(ccf::cache_policies(asked, numel, R, f32, one_sweep), asked, numel, R, f32, one_sweep);
+    return printf("%d %d %d\n", c.adam, c.lamb1, c.lamb) < 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def policies(tmp_path_factory):
+    d = tmp_path_factory.mktemp("fused")
+    (d / "rules.cpp").write_text(MAIN)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
+
+    def ask(asked, numel, R, f32, one_sweep=True):
+        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, one_sweep)], capture_output=True, text=True, timeout=60, check=True)
+        return tuple(int(x) for x in out.stdout.split())
+    return ask
+
+
+@pytest.mark.parametrize("R,f32", [(1, False), (8, False), (16, False), (4, True), (16, True)])
+def test_from_80_to_200_mib(policies, R, f32):
+    per = (4 if f32 else 2) * R + 26
+    at, end = -(-80 * MIB // per), -(-200 * MIB // per)
+    again = -(-32 * MIB // 12)                                   # elements whose w, m' and v' fill the L2s
+    assert policies(AUTO, at - 1, R, f32) == (RESIDENT,) * 3
+    for n in {at, end - 1, again - 1, again}:
+        if at <= n < end:
+            assert policies(AUTO, n, R, f32) == (THROUGH, KEPT, RESIDENT if n < again else THROUGH)
+    assert policies(AUTO, end, R, f32) == (THROUGH,) * 3
+    assert policies(AUTO, end - 1, R, f32, one_sweep=False) == (RESIDENT,) * 3
+    for asked in (cc.CC_CACHE_STREAMING, RESIDENT, THROUGH):
+        assert policies(asked, end - 1, R, f32) == (asked,) * 3
