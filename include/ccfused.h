@@ -244,7 +244,9 @@ int cc_fused_adam_step_static(const cc_tensor *tensor, int32_t R, const cc_hpara
  * cc_fused_lamb_step = phase 1 then phase 2.  The two phases are exported separately so that a
  * cross-rank sum of the per-tensor norms can be placed between them.  The single call gives the same bits in two
  * launches instead of three when no tensor has more than 512 chunks: the workgroups of phase 2 then add up their own
- * tensor's partial sums (same additions, same order) instead of a per-tensor launch between the phases; and in one launch
+ * tensor's partial sums (same additions, same order) instead of a per-tensor launch between the phases; also when one
+ * has, the shard is of 600 to 32768 chunks (smaller than 4096 elements each) and no tensor is empty: the workgroups of phase 1
+ * then add them up in groups, and those of phase 2 the groups; and in one launch
  * when the shard has few chunks of 1024 elements, in at most 64 groups (of up to 64 chunks of one tensor): the workgroups then
  * wait for each other's sums.  Few is a quarter of what the device holds at a time: 512 up to four fp16 or eight fp32 slices, 384 up to
  * seven or twelve, else 256 (in proportion fewer on a partition of the device).  So several such steps at a time, and other

@@ -279,9 +279,9 @@ int cc_plan_create_ex(const cc_tensor *tensors, int32_t T, int32_t R, int32_t ch
         delete p;
         return fail(CC_ERR_NOMEM, "cc_plan_create: out of host memory");
     }
+    int32_t nonempty = 0;
     {
         uint64_t goff = 0, total = 0;
-        int32_t nonempty = 0;
         for (int32_t t = 0; t < T; ++t) {
             p->gsum_offset[(size_t)t] = goff;
             goff += (tensors[t].numel + 7) / 8 * 8;            // every tensor starts 32-byte aligned in the fp32 buffer
@@ -369,8 +369,22 @@ int cc_plan_create_ex(const cc_tensor *tensors, int32_t T, int32_t R, int32_t ch
     PLAN_TRY(hipMalloc((void **)&p->d_partials, sizeof(double) * 2 * (size_t)(most_chunks + 1)));
     PLAN_TRY(hipMalloc((void **)&p->d_sums, sizeof(double) * 2 * (size_t)T));
     PLAN_TRY(hipMemset(p->d_sums, 0, sizeof(double) * 2 * (size_t)T));
-    PLAN_TRY(hipMalloc((void **)&p->d_meeting, sizeof(LambMeeting)));
-    PLAN_TRY(hipMemset(p->d_meeting, 0, sizeof(LambMeeting)));
+    size_t meeting_bytes = sizeof(LambMeeting), counts_at = 0, groups_at = 0, chunks_at = 0;
+    // (Of the chunk sizes a plan is prepared for only one has small workgroups.  A tensor without a chunk has sums too, zeros, which
+    // nobody in the first sweep would write: such plans keep the launch that does.)
+    for (const Layout &L : p->layouts)
+        if (L.block == kSmallBlock && lamb_tallies(L.chunks, L.most_tensor_chunks) && nonempty == T) {
+            counts_at = meeting_bytes;
+            chunks_at = counts_at + sizeof(LambTally::Count) * (size_t)L.groups;
+            groups_at = chunks_at + sizeof(TaggedSums) * (size_t)L.chunks;
+            meeting_bytes = groups_at + sizeof(LambTally::Sums) * (size_t)L.groups;
+        }
+    PLAN_TRY(hipMalloc((void **)&p->d_meeting, meeting_bytes));
+    PLAN_TRY(hipMemset(p->d_meeting, 0, meeting_bytes));
+    if (counts_at) {
+        char *at = (char *)p->d_meeting;
+        p->tally = LambTally{(TaggedSums *)(at + chunks_at), (LambTally::Count *)(at + counts_at), (LambTally::Sums *)(at + groups_at)};
+    }
     p->d_flag_scratch = &p->d_meeting->flag;
     PLAN_TRY(hipMalloc((void **)&p->d_queue, sizeof(WorkQueue)));
     PLAN_TRY(hipMemset(p->d_queue, 0, sizeof(WorkQueue)));
@@ -722,6 +736,11 @@ int cc_fused_lamb_step(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *st
     int rc = check_step(p, hp, flag, Opt::Lamb, &s);
     if (rc) return rc;
     if (lamb_in_one_launch(p)) return lamb_one_launch(p, s, flag, (hipStream_t)stream);
+    if (lamb_tallied(p)) {
+        launch_lamb_phase1(p, s, flag, (hipStream_t)stream, p->tally);
+        if ((rc = launched("lamb_phase1_kernel"))) return rc;
+        return lamb_phase2_tallied(p, s, flag, (hipStream_t)stream);
+    }
     if (norms_fold_into_phase2(p)) {
         // two launches instead of three: nobody reads the sums between the phases here
         hipStream_t st = (hipStream_t)stream;

@@ -6,7 +6,7 @@ namespace ccf {
 namespace {
 
 template <int BLK, bool GF32, class MEM>
-void launch_lamb_phase1_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+void launch_lamb_phase1_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, const LambTally &tally)
 {
     const Layout &L = p->lay();
     if (p->ordered) {
@@ -20,7 +20,7 @@ void launch_lamb_phase1_r(const cc_plan *p, const StepScalars &s, int32_t *flag,
     }
     const dim3 grid((unsigned)L.chunks), block(BLK);
     switch (p->R) {
-#define CASE(r) case r: hipLaunchKernelGGL((lamb_phase1_kernel<r, BLK, GF32, MEM>), grid, block, 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials, p->d_flag_scratch, flag); break;
+#define CASE(r) case r: hipLaunchKernelGGL((lamb_phase1_kernel<r, BLK, GF32, MEM>), grid, block, 0, st, L.table_tensors(), L.table_chunks(), s, p->d_partials, tally, p->d_flag_scratch, flag); break;
         FOR_EACH_R(CASE)
 #undef CASE
     }
@@ -28,15 +28,15 @@ void launch_lamb_phase1_r(const cc_plan *p, const StepScalars &s, int32_t *flag,
 
 }  // namespace
 
-void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, const LambTally &tally)
 {
     if (p->fused.lamb1 == kWeightsKept) {
-        if (p->grad_f32) launch_lamb_phase1_r<kSmallBlock, true, WeightsKept>(p, s, flag, st);
-        else launch_lamb_phase1_r<kSmallBlock, false, WeightsKept>(p, s, flag, st);
+        if (p->grad_f32) launch_lamb_phase1_r<kSmallBlock, true, WeightsKept>(p, s, flag, st, tally);
+        else launch_lamb_phase1_r<kSmallBlock, false, WeightsKept>(p, s, flag, st, tally);
         return;
     }
-    if (p->grad_f32) BY_BLOCK_MEM(p, p->fused.lamb1, (launch_lamb_phase1_r<BLK, true, MEM>(p, s, flag, st)));
-    else BY_BLOCK_MEM(p, p->fused.lamb1, (launch_lamb_phase1_r<BLK, false, MEM>(p, s, flag, st)));
+    if (p->grad_f32) BY_BLOCK_MEM(p, p->fused.lamb1, (launch_lamb_phase1_r<BLK, true, MEM>(p, s, flag, st, tally)));
+    else BY_BLOCK_MEM(p, p->fused.lamb1, (launch_lamb_phase1_r<BLK, false, MEM>(p, s, flag, st, tally)));
 }
 
 void launch_lamb_phase1_from_sum(const cc_plan *p, const StepScalars &s, hipStream_t st)
@@ -58,8 +58,16 @@ int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipS
         return launched("lamb_phase2_ordered_kernel");
     }
     const dim3 grid((unsigned)L.chunks);
-    if (emit16) BY_BLOCK_MEM(p, p->fused.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
-    else BY_BLOCK_MEM(p, p->mem.lamb1, hipLaunchKernelGGL((lamb_phase2_kernel<false, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, flag));
+    if (emit16) BY_BLOCK_MEM(p, p->fused.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, nullptr, flag));
+    else BY_BLOCK_MEM(p, p->mem.lamb1, hipLaunchKernelGGL((lamb_phase2_kernel<false, BLK, MEM>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, nullptr, flag));
+    return launched("lamb_phase2_kernel");
+}
+
+int lamb_phase2_tallied(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st)
+{
+    const Layout &L = p->lay();
+    const dim3 grid((unsigned)L.chunks);
+    BY_BLOCK_MEM(p, p->fused.lamb, hipLaunchKernelGGL((lamb_phase2_kernel<true, BLK, MEM, true>), grid, dim3(BLK), 0, st, L.table_tensors(), L.table_chunks(), s, p->d_sums, p->tally.group, flag));
     return launched("lamb_phase2_kernel");
 }
 

@@ -35,4 +35,16 @@ inline bool lamb_meets(int64_t chunks, uint32_t groups, int32_t cus, int R, bool
            && 2 * chunks <= (int64_t)cus * lamb_meeting_waves(R, grad_f32);
 }
 
+// Whether cc_fused_lamb_step's first sweep adds up the chunks' sums group by group and the second the groups (see LambTally), instead of
+// a launch between the two.  `most`: chunks of the largest tensor.  One tensor and lists, us per step with the launch / without:
+//   chunks       606 R = 2   684 R = 8   879 R = 4   1075 R = 8   1447 R = 1   2442 R = 2   2442 R = 16   3907 R = 8   5470 R = 2   7945 R = 4
+//               11.2 / 10.1 12.8 / 11.7 12.9 / 11.6 14.7 / 13.5  14.8 / 13.1  22.4 / 21.0  34.1 / 33.3   39.5 / 38.2  41.1 / 40.6  63.2 / 61.8
+//   15.6 K, R = 2 110.1 / 107.7; 19.5 K, eight fp32 slices 238 / 235.5; 27.3 K, R = 1 180.2 / 178.2; but 39.1 K, R = 8 336.0 / 338.4 and 58.6 K, R = 2
+//   399 / 400.7.  BERT-Large list in 14 slices, R = 4 181.5 / 181.0, in 40, R = 8 74.3 / 73.5; GPT-2 list in 60, R = 4 198.3 / 196.0.
+// Where no tensor has more than kFoldNormsMaxChunks the second sweep adds up the chunks themselves: BERT-Large list in 203 slices, R = 8, 19.5 us that
+// way, 20.6 with the tally.  Between 512 and 600 chunks the launch stays as well: no shard there was looked at.
+constexpr uint32_t kFoldNormsMaxChunks = 512;
+constexpr int64_t kTallyMinChunks = 600, kTallyMaxChunks = 32768;
+inline bool lamb_tallies(int64_t chunks, uint32_t most) { return chunks >= kTallyMinChunks && chunks <= kTallyMaxChunks && most > kFoldNormsMaxChunks; }
+
 }  // namespace ccf

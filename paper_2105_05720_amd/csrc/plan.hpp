@@ -64,6 +64,7 @@ struct cc_plan {
     ccf::LambMeeting *d_meeting = nullptr;  // zero when the plan is created
     ccf::FlagScratch *d_flag_scratch = nullptr;  // d_meeting->flag
     uint32_t meeting_limit = ccf::kMeetingPolls;
+    ccf::LambTally tally{};                 // behind d_meeting, if the layout of small chunks goes by it (see lamb_tallies)
     bool ordered = false;                   // large shards: persistent workgroups take chunks in table order
     int32_t schedule = CC_SCHEDULE_AUTO;    // what the caller asked for
     unsigned ordered_grid = 0;              // workgroups of the ordered schedule (one per compute unit unless set)
@@ -131,28 +132,34 @@ inline uint32_t span_of(SpanKind k)
 // Launch entry points, one family per source file.  `mode` = kModeGuard | kModeL2 bits.
 void launch_fused_adam_f16(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, int mode);
 void launch_fused_adam_f32(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, int mode);
-void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
+void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, const LambTally &tally = {});
 void launch_lamb_phase1_from_sum(const cc_plan *p, const StepScalars &s, hipStream_t st);
 int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st, bool emit16);
 int lamb_norms(cc_plan *p, hipStream_t st);
-// Whether cc_fused_lamb_step lets every phase-2 workgroup add up its own tensor's partials instead of launching the
-// second level: one workgroup per chunk, and no tensor with more chunks than kFoldNormsMaxChunks.  A workgroup reads 16
-// bytes per chunk of its tensor, so the extra traffic grows with the square of a tensor's chunks.  One flat tensor,
-// R = 8, us per step folded / three launches: 7.1 / 8.9 at one chunk, 9.2 / 10.7 at 128, 9.6 / 10.9 at 256, 11.4 / 11.6
-// at 512, but 16.5 / 14.3 at 1024.
-constexpr uint32_t kFoldNormsMaxChunks = 512;
 // Whether cc_fused_lamb_step is a single launch: one workgroup per 1024-element chunk, and few enough of them (see lamb_meets).
 inline bool lamb_in_one_launch(const cc_plan *p)
 {
     const Layout &L = p->lay();
     return !p->ordered && L.chunk_elems == kSmallChunkElems && L.d_per_chunk && lamb_meets(L.chunks, L.groups, p->cus, p->R, p->grad_f32);
 }
+// Whether cc_fused_lamb_step's first sweep adds up the chunks' sums group by group (see LambTally).
+inline bool lamb_tallied(const cc_plan *p)
+{
+    const Layout &L = p->lay();
+    return p->tally.chunk != nullptr && !p->ordered && L.block == kSmallBlock;
+}
 int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
+// Whether cc_fused_lamb_step lets every phase-2 workgroup add up its own tensor's partials instead of launching the
+// second level: one workgroup per chunk, and no tensor with more chunks than kFoldNormsMaxChunks.  A workgroup reads 16
+// bytes per chunk of its tensor, so the extra traffic grows with the square of a tensor's chunks.  One flat tensor,
+// R = 8, us per step folded / three launches: 7.1 / 8.9 at one chunk, 9.2 / 10.7 at 128, 9.6 / 10.9 at 256, 11.4 / 11.6
+// at 512, but 16.5 / 14.3 at 1024.
 inline bool norms_fold_into_phase2(const cc_plan *p)
 {
     const Layout &L = p->lay();
     return !p->ordered && L.block == kSmallBlock && L.chunks > 0 && L.most_tensor_chunks <= kFoldNormsMaxChunks;
 }
+int lamb_phase2_tallied(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st);
 int lamb_phase2_with_norms(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st);
 void launch_reduce(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
 void launch_reduce_half(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
