@@ -20,6 +20,7 @@ CC_OK, CC_ERR_NULL, CC_ERR_ARG, CC_ERR_ALIGN, CC_ERR_ALIAS, CC_ERR_HIP, CC_ERR_N
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libccfused.so")
 _lib = None
+_at = {}           # the addresses of the calls that a training step makes
 _packed = {}       # the calls that a training step makes, typed to take their argument structs as packed bytes (see _step)
 
 
@@ -104,6 +105,7 @@ def load():
             fn.restype = res
             fn.argtypes = args
             if name.startswith(("cc_fused_", "cc_unfused_")):
+                _at[name] = C.cast(fn, C.c_void_p).value
                 as_bytes = [C.c_char_p if a in (C.POINTER(cc_hparams), C.POINTER(cc_tensor), C.POINTER(cc_epilogue)) else a for a in args]
                 _packed[name] = C.CFUNCTYPE(res, *as_bytes)((name, lib))
         _lib = lib
@@ -135,6 +137,7 @@ def _current_stream() -> Optional[int]:
         import torch
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         _torch = torch
+        _bind_native()
     if _raw_stream is None:
         return _torch.cuda.current_stream().cuda_stream or None
     return _raw_stream(_torch.cuda.current_device()) or None
@@ -310,12 +313,14 @@ def cc_plan_info(plan: Plan):
 
 # ---- steps ----
 
-# A small shard's step costs the host more than the device, so the step calls pack their argument structs into bytes in
-# one go (native sizes and alignment, as in cc_hparams, cc_tensor and cc_epilogue) instead of filling ctypes structures
-# field by field: 0.3 against 0.8 us for the hyper-parameters, 1.3 against 2.5 us for a tensor with two slices, and 0.2 us
-# less in the call itself.  What does not pack (an integer address, a value out of its field's range, a wrong type) goes
-# through the ctypes structures, whose conversions and errors are the definition; so does a hyper-parameter object that is
-# not exactly a Hyper, because its to_c() is what counts.
+# A small shard's step costs the host more than the device, so the step calls go through the extension module (step_calls.cpp),
+# which reads the objects' fields itself, from their second call on (the first one finds torch).  us per eager pass of a training
+# loop that makes a new Hyper each time, packed bytes through ctypes / this: 6.1 / 5.1 for Adam on 4099 elements, R = 4; 6.9 / 5.4 for the
+# static call on 100003, R = 2, and 8.0 / 6.3 on 200001, R = 16; 6.1 / 5.3 for LAMB on 10007; 5.7 / 4.6 for the epilogue on 21744, R = 4.
+# What the module does not take (an integer address among a tensor's buffers, a stream that is given, a value out of its field's
+# range, a wrong type) is packed into bytes in one go (native sizes and alignment, as in cc_hparams, cc_tensor and cc_epilogue).
+# What does not pack goes through the ctypes structures, whose conversions and errors are the definition; so does a
+# hyper-parameter object that is not exactly a Hyper, because its to_c() is what counts.
 _PACK_HP = struct.Struct("5f4i").pack
 _PACK_TENSOR = struct.Struct("Q7Q16Qf4x").pack
 _PACK_EPILOGUE = struct.Struct("QQIi16QQQQf4xQ").pack
@@ -344,44 +349,78 @@ def _tensor_bytes(t: Tensor) -> bytes:
         return bytes(_c_tensor(t))
 
 
-# The step calls look into _packed and at the return code themselves: a Python call less for each, 0.15 us together.
 def _fn(name: str):
     if _lib is None:
         load()
     return _packed[name]
 
 
-def _step(name: str, plan: Plan, hp, flag, stream) -> None:
-    rc = (_packed.get(name) or _fn(name))(plan.handle, _hp_bytes(hp), _ptr(flag), _stream(stream))
-    if rc < 0:
-        _check(rc)
+def _not_taken(*args) -> int:
+    return 1
+
+
+_native_step = _native_static = _native_epilogue = _not_taken
+
+
+def _bind_native() -> None:
+    """Lets the step calls go through the extension module: torch is there, and its device has been looked at."""
+    global _native_step, _native_static, _native_epilogue
+    if _raw_stream is None:
+        return
+    from . import _step_calls as native
+    _torch.cuda.current_device()
+    if native.bind(Plan, Hyper, Tensor, _torch.Tensor, _torch.nn.Parameter, _torch._C._cuda_getDevice, _raw_stream):
+        _native_step, _native_static, _native_epilogue = native.step, native.static_step, native.epilogue
+
+
+def _unbind_native() -> None:
+    """In a forked child torch's own calls say that it may not use the GPU."""
+    global _native_step, _native_static, _native_epilogue
+    _native_step = _native_static = _native_epilogue = _not_taken
+
+
+os.register_at_fork(after_in_child=_unbind_native)
+
+
+def _step(rc: int, name: str, plan: Plan, hp, flag, stream) -> None:
+    """A step call that the extension module has not taken (rc = 1), or that has failed."""
+    _check(rc if rc < 0 else _fn(name)(plan.handle, _hp_bytes(hp), _ptr(flag), _stream(stream)))
 
 
 def cc_fused_adam_step(plan: Plan, hp, flag, stream=None) -> None:
-    _step("cc_fused_adam_step", plan, hp, flag, stream)
+    rc = _native_step(_at.get("cc_fused_adam_step"), plan, hp, flag, stream)
+    if rc:
+        _step(rc, "cc_fused_adam_step", plan, hp, flag, stream)
 
 
 def cc_fused_adam_step_static(tensor: Tensor, R: int, hp, flag, stream=None) -> None:
-    fn = _packed.get("cc_fused_adam_step_static") or _fn("cc_fused_adam_step_static")
-    rc = fn(_tensor_bytes(tensor), R, _hp_bytes(hp), _ptr(flag), _stream(stream))
-    if rc < 0:
-        _check(rc)
+    rc = _native_static(_at.get("cc_fused_adam_step_static"), tensor, R, hp, flag, stream)
+    if rc:
+        _check(rc if rc < 0 else _fn("cc_fused_adam_step_static")(_tensor_bytes(tensor), R, _hp_bytes(hp), _ptr(flag), _stream(stream)))
 
 
 def cc_fused_lamb_step(plan: Plan, hp, flag, stream=None) -> None:
-    _step("cc_fused_lamb_step", plan, hp, flag, stream)
+    rc = _native_step(_at.get("cc_fused_lamb_step"), plan, hp, flag, stream)
+    if rc:
+        _step(rc, "cc_fused_lamb_step", plan, hp, flag, stream)
 
 
 def cc_fused_lamb_phase1(plan: Plan, hp, flag, stream=None) -> None:
-    _step("cc_fused_lamb_phase1", plan, hp, flag, stream)
+    rc = _native_step(_at.get("cc_fused_lamb_phase1"), plan, hp, flag, stream)
+    if rc:
+        _step(rc, "cc_fused_lamb_phase1", plan, hp, flag, stream)
 
 
 def cc_fused_lamb_phase2(plan: Plan, hp, flag, stream=None) -> None:
-    _step("cc_fused_lamb_phase2", plan, hp, flag, stream)
+    rc = _native_step(_at.get("cc_fused_lamb_phase2"), plan, hp, flag, stream)
+    if rc:
+        _step(rc, "cc_fused_lamb_phase2", plan, hp, flag, stream)
 
 
 def cc_unfused_adam_step(plan: Plan, hp, flag, stream=None) -> None:
-    _step("cc_unfused_adam_step", plan, hp, flag, stream)
+    rc = _native_step(_at.get("cc_unfused_adam_step"), plan, hp, flag, stream)
+    if rc:
+        _step(rc, "cc_unfused_adam_step", plan, hp, flag, stream)
 
 
 def cc_unfused_adam_step_ex(plan: Plan, hp, flag, stream=None, sum_dtype: int = CC_GRAD_F32) -> None:
@@ -389,7 +428,9 @@ def cc_unfused_adam_step_ex(plan: Plan, hp, flag, stream=None, sum_dtype: int = 
 
 
 def cc_unfused_lamb_step(plan: Plan, hp, flag, stream=None) -> None:
-    _step("cc_unfused_lamb_step", plan, hp, flag, stream)
+    rc = _native_step(_at.get("cc_unfused_lamb_step"), plan, hp, flag, stream)
+    if rc:
+        _step(rc, "cc_unfused_lamb_step", plan, hp, flag, stream)
 
 
 def cc_lamb_norm_buffer(plan: Plan) -> int:
@@ -426,8 +467,9 @@ def _epilogue_bytes(partials, bias, residual, out, first, hidden, dropout_p, see
 
 def cc_fused_epilogue(partials, bias, residual, out, first: int, hidden: int, dropout_p: float, seed: int, stream=None,
                       numel=None) -> None:
-    e = _epilogue_bytes(partials, bias, residual, out, first, hidden, dropout_p, seed, numel)
-    _check(_fn("cc_fused_epilogue")(e, _stream(stream)))
+    rc = _native_epilogue(_at.get("cc_fused_epilogue"), partials, bias, residual, out, first, hidden, dropout_p, seed, stream, numel)
+    if rc:
+        _check(rc if rc < 0 else _fn("cc_fused_epilogue")(_epilogue_bytes(partials, bias, residual, out, first, hidden, dropout_p, seed, numel), _stream(stream)))
 
 
 def cc_unfused_epilogue(partials, bias, residual, out, sum_scratch, first: int, hidden: int, dropout_p: float, seed: int,

@@ -2,12 +2,13 @@
 
 The library is several translation units (one per kernel family) only so that they compile side by side; each is
 compiled to an object file and the objects are linked into one shared library, whose dynamic symbol table is cut down
-to the C ABI by csrc/exports.map."""
+to the C ABI by csrc/exports.map.  Beside it, with g++, the extension module through which Python's step calls reach it."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -21,6 +22,8 @@ DEPS = SOURCES + [os.path.join(CSRC, "kernels.hip.h"), os.path.join(CSRC, "plan.
                   os.path.join(CSRC, "launch_adam.inc.hpp"),
                   os.path.join(ROOT, "include", "ccfused.h"), EXPORTS_MAP]
 LIB = os.path.join(_HERE, "libccfused.so")
+STEP_CALLS_SOURCE = os.path.join(CSRC, "step_calls.cpp")
+STEP_CALLS = os.path.join(_HERE, "_step_calls.so")      # a module of CPython's; host code only
 OBJ_DIR = os.path.join(_HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -38,16 +41,25 @@ FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(STEP_CALLS):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(d) > t for d in DEPS)
+    return any(os.path.getmtime(d) > t for d in DEPS) or os.path.getmtime(STEP_CALLS_SOURCE) > os.path.getmtime(STEP_CALLS)
+
+
+def build_step_calls() -> str:
+    tmp = STEP_CALLS + ".tmp%d" % os.getpid()
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-Wno-cast-function-type",
+                           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-o", tmp, STEP_CALLS_SOURCE])
+    os.replace(tmp, STEP_CALLS)
+    return STEP_CALLS
 
 
 def build_library(force: bool = True, extra=()) -> str:
     """Compile the HIP library.  force=False skips the compile when the built file is newer than its sources."""
     if not force and not is_stale():
         return LIB
+    build_step_calls()
     os.makedirs(OBJ_DIR, exist_ok=True)
     tag = ".%d" % os.getpid()
     objs = [os.path.join(OBJ_DIR, os.path.basename(src)[:-4] + tag + ".o") for src in SOURCES]
