@@ -41,8 +41,8 @@ def plan(handle):
     return p
 
 
-@pytest.mark.parametrize("flag,where", [(T[0], T[0].data_ptr()), (2**63, 2**63), (torch.nn.Parameter(T[1]), T[1].data_ptr())])
-@pytest.mark.parametrize("hp", [cc.Hyper(), HP, cc.Hyper(lr=float("inf"), beta1=float("nan"), step=-2**31)])
+@pytest.mark.parametrize("flag,where", [(T[0], T[0].data_ptr()), (2**63, 2**63), (torch.nn.Parameter(T[1]), T[1].data_ptr())], ids=["tensor", "address", "parameter"])
+@pytest.mark.parametrize("hp", [cc.Hyper(), HP, cc.Hyper(lr=float("inf"), beta1=float("nan"), step=-2**31)], ids=["defaults", "odd", "not finite"])
 def test_step(hp, flag, where):
     seen = Seen(0, C.sizeof(cc.cc_hparams), 0, 0, rc=-4)
     p = plan(1 << 40)
