@@ -164,7 +164,9 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  * elements whose step's buffers total 200 MiB and more, or 80 MiB with 1024-element chunks, is the exception: there the fused Adam
  * step runs single-wave workgroups of 256 elements, unless the caller has asked for CC_CACHE_RESIDENT.  So it does on one larger tensor for which
  * the caller has chosen nothing, up to 192 Mi elements with up to ten fp16 slices (144 Mi with one) or with fp32 slices, and with
- * four and more of those beyond.)
+ * four and more of those beyond.  A list of tensors runs such workgroups where its step stores 288 MiB and more, with up to ten fp16 or
+ * eight fp32 slices and at most one chunk in eight short, in chunks of 1024 elements below 64 Mi elements, and on larger lists for which
+ * the caller has chosen nothing up to 128 Mi elements with up to eight fp16 slices, 256 Mi with fp32 slices.)
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);

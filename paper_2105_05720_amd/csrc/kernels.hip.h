@@ -31,6 +31,7 @@
 
 #include "ccfused.h"
 #include "meeting.hpp"
+#include "occupancy.hpp"
 #include "piece_order.hpp"
 
 namespace ccf {
@@ -209,6 +210,19 @@ struct Where {
     uint32_t len;             // elements in this chunk (the tensor's last chunk may be short)
 };
 
+constexpr int kLineOfGrads = 7;
+// Fields from all over the descriptor before the first is looked at, so that its cache lines arrive together.  Left
+// alone the compiler asks for the length, waits, and then asks for the rest.  Descriptors are 224 bytes apart, so every
+// other one starts in the middle of a 64-byte line; the length, grad[0], grad[7] and the index lie in all of the lines
+// that up to eight slices need.  With more, an entry that starts on a line gets the line of grad[8] to grad[15] later.
+__device__ __forceinline__ uint32_t all_lines(Where &wh)
+{
+    uint32_t own_index = wh.t->chunk_index, own_tensor = wh.t->tensor;
+    asm volatile("" : "+s"(own_index), "+s"(own_tensor) : "s"(wh.t->numel), "s"(wh.t->grad[0]), "s"(wh.t->grad[kLineOfGrads]));
+    wh.tensor = own_tensor;
+    return own_index;
+}
+
 // What is left to derive once the descriptor and the chunk's index are known.
 __device__ __forceinline__ void finish_where(Where &wh, uint32_t chunk_elems)
 {
@@ -237,7 +251,6 @@ __device__ __forceinline__ Where locate_at(const DevTensor *__restrict__ tensors
 // step (same machine, with / without: 4.70 / 4.90 us on 398 tensors in 571 chunks, 9.60 / 9.90 us on 10 tensors in
 // 1280 chunks).
 constexpr uint32_t kChunkRunLog2 = 5;
-constexpr int kLineOfGrads = 7;
 // LAST_FIRST: a second sweep over a shard bound by HBM takes the chunks from the other end, and so finds on chip what the
 // first sweep touched last.  LAMB, R = 8, from the same end / from the other: 353 / 350.5 us at 42 M elements of the BERT-Large
 // list, 482 / 475.5 at 56 M, R = 1 one tensor of 40 M elements 249.5 / 245.5; up to 21 M elements within 1 %.  The ordered
@@ -255,13 +268,7 @@ __device__ __forceinline__ Where locate(const DevTensor *__restrict__ tensors, c
     }
     Where wh;
     wh.t = (Descriptor)tensors + tensor;
-    // Fields from all over the descriptor before the first is looked at, so that its cache lines arrive together.  Left
-    // alone the compiler asks for the length, waits, and then asks for the rest.  Descriptors are 224 bytes apart, so every
-    // other one starts in the middle of a 64-byte line; the length, grad[0], grad[7] and the index lie in all of the lines
-    // that up to eight slices need.  With more, an entry that starts on a line gets the line of grad[8] to grad[15] later.
-    uint32_t own_index = wh.t->chunk_index, own_tensor = wh.t->tensor;
-    asm volatile("" : "+s"(own_index), "+s"(own_tensor) : "s"(wh.t->numel), "s"(wh.t->grad[0]), "s"(wh.t->grad[kLineOfGrads]));
-    wh.tensor = own_tensor;
+    const uint32_t own_index = all_lines(wh);
     wh.index = chunks != nullptr ? index : own_index;
     finish_where(wh, s.chunk_elems);
     return wh;
@@ -881,6 +888,31 @@ __global__ __launch_bounds__(BLOCK) void fused_adam_flat_kernel(DevTensor t, Ste
     AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
     op.init(&t, base, s);
     sweep_and_publish<BLOCK, GROUPS>(op, rem < s.chunk_elems ? (uint32_t)rem : s.chunk_elems, fc, fs, flag);
+}
+
+// The step on a list bound by HBM in single-wave workgroups, one per piece of 256 elements: kPiecesPerChunk for every entry of the table
+// of 1024-element chunks, the last of a short chunk without elements.  What bounds it is DRAM, as for one tensor (kFlatPiece); the
+// two dependent trips to the table and the descriptor cost less than the narrow window of addresses in flight gives.  Rule and
+// figures at list_in_pieces.
+constexpr uint32_t kPiecesPerChunk = 4, kPieceChunk = kFlatPiece * kPiecesPerChunk;
+template <int R, int MODE, bool GF32, class Mem>
+__global__ __launch_bounds__(kFlatBlock) void fused_adam_piece_kernel(const DevTensor *__restrict__ tensors, const Chunk *__restrict__ chunks,
+                                                                      StepScalars s, FlagScratch *__restrict__ fs, int32_t *__restrict__ flag)
+{
+    uint32_t piece = blockIdx.x;         // taken here: behind the arrival's branch the compiler keeps it in a vector register
+    asm volatile("" : "+s"(piece));
+    FlagCount<kFlatBlock> fc;
+    fc.arrive(fs);
+    const ChunkEntry c = (ChunkEntry)chunks + piece / kPiecesPerChunk;
+    Where wh;
+    wh.index = c->index;
+    wh.t = (Descriptor)tensors + c->tensor;
+    all_lines(wh);
+    finish_where(wh, kPieceChunk);
+    const uint32_t first = piece % kPiecesPerChunk * kFlatPiece, rest = wh.len > first ? wh.len - first : 0u;
+    AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
+    op.init(wh.t, wh.base + first, s);
+    sweep_and_publish<kFlatBlock, 1>(op, rest < kFlatPiece ? rest : kFlatPiece, fc, fs, flag);
 }
 
 // The same step under the ordered persistent schedule (chunk_elems == BLOCK * 4 * GROUPS).

@@ -23,10 +23,26 @@ void launch_flat_pieces(const DevTensor &t, int R, StepScalars s, FlagScratch *f
     }
 }
 
+// A list that stores too much to write through, in the same pieces (see list_in_pieces).
+template <int MODE, bool GF32>
+void launch_list_pieces(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
+{
+    const Layout &L = *p->list_pieces;
+    const dim3 grid((unsigned)L.chunks * kPiecesPerChunk), block(kFlatBlock);
+    const unsigned lds = flat_lds(p->numel, p->R, GF32, true);
+    switch (p->R) {
+#define CASE(r) case r: if constexpr (pieces_take(r, GF32)) hipLaunchKernelGGL((fused_adam_piece_kernel<r, MODE, GF32, Streaming>), grid, block, lds, st, L.d_tensors, L.d_chunks, s, p->d_flag_scratch, flag); break;
+        FOR_EACH_R(CASE)
+#undef CASE
+    }
+}
+
 template <int MODE, int BLK, bool GF32, class MEM>
 void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
     const Layout &L = p->lay();
+    if constexpr (std::is_same<MEM, Streaming>::value)
+        if (p->list_pieces) return launch_list_pieces<MODE, GF32>(p, s, flag, st);
     if constexpr (BLK == kBigBlock)
         if (p->flat_adam) return launch_flat_pieces<MODE, GF32, Streaming>(L.host_tensors[(size_t)p->single], p->R, s, p->d_flag_scratch, flag, st);
     if (p->ordered) {

@@ -86,4 +86,28 @@ inline bool flat_beyond_small(uint64_t numel, int R, bool grad_f32)
     return R <= kFlatMaxF16Slices && numel < (R == 1 ? kFlatNarrowMaxElems : kFlatWideMaxElems);
 }
 
+// A list of tensors goes in such pieces as well, with the same reservations (flat_lds), where its step stores too much to write through:
+// below kSmallShardElems instead of 128-thread workgroups, beyond instead of the ordered schedule, if nothing else was asked.
+// us, without / with pieces, three shards in turn, then one by itself:
+//   BERT-Large list   22 M, R = 1 103.5 / 101.7, 102.7 / 100.5; R = 4 126.4 / 123.9, 124.8 / 122.1; R = 8 157.0 / 155.8, 154.2 / 150.3; R = 12 185.5 / 186.2, 182.5 /
+//                     183.5; 26 M, fp32 R = 1 128.3 / 125.3, 127 / 122.5; R = 4 181 / 174.5, 179 / 172; 34 M, R = 8 232.5 / 226.8, 230.9 / 223.5; R = 16 326.8 / 326.7,
+//                     317.4 / 326.0; 42 M, R = 1 194.3 / 189, 194.8 / 186.5; R = 8 295 / 284.5, 290.8 / 279; R = 10 321 / 312, 312 / 311; 56 M, fp32 R = 8 567 / 521, 561 / 516
+//   GPT-2 list        43 M, R = 2 214.5 / 209, 215 / 207; 56 M, R = 4 313.6 / 302, 313.6 / 299.7; R = 16 540 / 537, 530 / 540; 43 M, fp32 R = 16 674.5 / 674, 659 / 663
+//   beyond, ordered / pieces: BERT-Large list 67 M, R = 1 321 / 300, 311 / 304; R = 8 480 / 456, 464 / 453; 84 M, R = 1 383 / 376, 383 / 374.5; R = 4 476 / 460, 462 /
+//                     448.5; R = 8 576 / 571, 561.5 / 564; R = 10 629 / 629.5, 615 / 631; 111 M, R = 1 508 / 485, 500 / 494; R = 8 760 / 748, 739 / 748; but 168 M,
+//                     R = 4 925 / 908, 908 / 901, 208 M, R = 8 1385 / 1394, 1367 / 1405, and 336 M, R = 8 2228 / 2248
+//   ... fp32          67 M, R = 2 395 / 371, 380 / 367; 111 M, R = 4 772 / 745, 783 / 740; 168 M, R = 4 1219 / 1142, 1169 / 1121; 195 M, R = 8 1980 / 1875, 1908 / 1821;
+//                     208 M, R = 4 1479 / 1385, 1445 / 1411; 336 M, R = 8 3460 / 3304, 3287 / 3368; 111 M, R = 16 1699 / 1699, 1732 / 1736
+// While the stores are written through it depends on who steps: 10.5 M, R = 4 65.7 / 63.8 with three in turn, 54.8 / 57.3 by itself.
+// Short chunks leave pieces without elements, so no more than one chunk in eight may be missing from the table.
+constexpr uint64_t kListPiecesMaxElems = 128u << 20, kListPiecesMaxF32Elems = 256u << 20;
+constexpr int kListPiecesMaxF16Slices = 10, kListBeyondMaxF16Slices = 8, kListPiecesMaxF32Slices = 8;
+constexpr bool pieces_take(int R, bool grad_f32) { return R <= (grad_f32 ? kListPiecesMaxF32Slices : kListPiecesMaxF16Slices); }
+inline bool list_in_pieces(uint64_t numel, uint64_t chunks, int R, bool grad_f32)
+{
+    if (!pieces_take(R, grad_f32) || numel * kAdamStoreBytes < kWriteThroughMaxStoreBytes || chunks * 1024u > numel + numel / 8) return false;
+    if (numel < kSmallShardElems) return true;
+    return grad_f32 ? numel < kListPiecesMaxF32Elems : R <= kListBeyondMaxF16Slices && numel < kListPiecesMaxElems;
+}
+
 }  // namespace ccf

@@ -72,6 +72,7 @@ struct cc_plan {
     ccf::CachePolicies fused;               // ... by the fused steps (see fused_policies)
     bool flat_pieces = false;               // small chunks of one tensor bound by HBM: fused Adam in single-wave pieces (see kFlatPiece)
     bool flat_adam = false;                 // large chunks, but the fused Adam step in single-wave pieces (see flat_beyond_small)
+    const ccf::Layout *list_pieces = nullptr;   // several tensors: the chunks whose pieces the fused Adam step takes (see list_in_pieces)
     bool spread = false;                    // chunks of 1024 elements of a shard bound by HBM (see kSpreadLds)
     bool spread_adam = false;               // ... for the fused Adam step
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
