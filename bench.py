@@ -141,6 +141,8 @@ def describe(cc, shard, R, optimizer, gf32):
                         for x in what)
     if "_ordered_kernel" in what[0].kernel:
         schedule = "ordered: %d persistent workgroups take the chunks in table order" % what[0].grid
+    elif what[0].grid != chunks and what[0].kernel.startswith("lamb"):
+        schedule = "one workgroup of %d threads per chunk of 1024 elements" % what[0].block
     elif what[0].grid != chunks:
         schedule = "%d workgroups of %d threads, one per piece of 256 elements" % (what[0].grid, what[0].block)
     else:

@@ -166,7 +166,8 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  * the caller has chosen nothing, up to 192 Mi elements with up to ten fp16 slices (144 Mi with one) or with fp32 slices, and with
  * four and more of those beyond.  A list of tensors runs such workgroups where its step stores 288 MiB and more, with up to ten fp16 or
  * eight fp32 slices and at most one chunk in eight short, in chunks of 1024 elements below 64 Mi elements, and on larger lists for which
- * the caller has chosen nothing up to 128 Mi elements with up to eight fp16 slices, 256 Mi with fp32 slices.)
+ * the caller has chosen nothing up to 128 Mi elements with up to eight fp16 slices, 256 Mi with fp32 slices.  The fused LAMB step keeps
+ * chunks of 1024 elements, one workgroup each, up to 88 Mi elements where the caller has chosen nothing and the ordered schedule would run.)
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);

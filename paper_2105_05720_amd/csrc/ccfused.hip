@@ -135,6 +135,19 @@ void resolve_schedule(cc_plan *p)
     p->spread = small && one_sweep && footprint >= kResidentMaxBytes;
     p->spread_adam = p->spread || (small && one_sweep && footprint >= kPlainLoadsMaxBytes && p->fused.adam != CC_CACHE_RESIDENT);
     p->flat_pieces = p->spread_adam || (small && footprint >= kResidentMaxBytes);
+    p->lamb_active = p->active;
+    p->lamb_ordered = p->ordered;
+    p->lamb_spread = p->spread;
+    if (nothing_asked && p->ordered && lamb_keeps_small_chunks(p->numel))
+        for (size_t i = 0; i < p->layouts.size(); ++i)
+            if (p->layouts[i].chunk_elems == kSmallChunkElems) {
+                const CachePolicies c = cache_policies(CC_CACHE_AUTO, p->numel, p->R, p->grad_f32, true);
+                p->lamb_active = (int)i;
+                p->lamb_ordered = false;
+                p->lamb_spread = true;
+                p->fused.lamb1 = c.lamb1;
+                p->fused.lamb = c.lamb;
+            }
     p->list_pieces = nullptr;
     if (p->single < 0 && p->fused.adam == CC_CACHE_STREAMING && (nothing_asked ? p->ordered || p->spread_adam : p->spread_adam))
         for (const Layout &S : p->layouts)
@@ -585,6 +598,15 @@ int check_step(const cc_plan *p, const cc_hparams *hp, const void *flag, Opt opt
     return check_hparams(hp, flag, opt, p->R, p->in_place, p->lay().chunk_elems, s);
 }
 
+// ... for the fused LAMB step's layout
+int check_lamb_step(const cc_plan *p, const cc_hparams *hp, const void *flag, StepScalars *s)
+{
+    if (const int rc = check_step(p, hp, flag, Opt::Lamb, s)) return rc;
+    s->runs = p->lamb_spread ? 1u : 0u;
+    s->chunk_elems = (uint32_t)p->lamb_lay().chunk_elems;
+    return CC_OK;
+}
+
 // The unfused pipelines need the plan's fp32 reduced-gradient buffer; a step call does not allocate it.
 int ensure_gsum(const cc_plan *p)
 {
@@ -714,7 +736,7 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
 int cc_fused_lamb_phase1(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *stream)
 {
     StepScalars s;
-    int rc = check_step(p, hp, flag, Opt::Lamb, &s);
+    int rc = check_lamb_step(p, hp, flag, &s);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     if (p->chunks() == 0) {
@@ -723,13 +745,13 @@ int cc_fused_lamb_phase1(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *
         launch_lamb_phase1(p, s, flag, st);
         if ((rc = launched("lamb_phase1_kernel"))) return rc;
     }
-    return lamb_norms(p, st);
+    return lamb_norms(p, p->lamb_lay(), st);
 }
 
 int cc_fused_lamb_phase2(cc_plan *p, const cc_hparams *hp, const int32_t *flag, void *stream)
 {
     StepScalars s;
-    int rc = check_step(p, hp, flag, Opt::Lamb, &s);
+    int rc = check_lamb_step(p, hp, flag, &s);
     if (rc) return rc;
     return lamb_phase2_impl(p, s, flag, (hipStream_t)stream, true);
 }
@@ -737,7 +759,7 @@ int cc_fused_lamb_phase2(cc_plan *p, const cc_hparams *hp, const int32_t *flag, 
 int cc_fused_lamb_step(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *stream)
 {
     StepScalars s;
-    int rc = check_step(p, hp, flag, Opt::Lamb, &s);
+    int rc = check_lamb_step(p, hp, flag, &s);
     if (rc) return rc;
     if (lamb_in_one_launch(p)) return lamb_one_launch(p, s, flag, (hipStream_t)stream);
     if (lamb_tallied(p)) {
@@ -790,13 +812,13 @@ int cc_unfused_lamb_step(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *
     hipStream_t st = (hipStream_t)stream;
     if (p->chunks() == 0) {
         if ((rc = clear_flag(flag, st))) return rc;
-        return lamb_norms(p, st);
+        return lamb_norms(p, p->lay(), st);
     }
     launch_reduce(p, s, flag, st);
     if ((rc = launched("reduce_kernel"))) return rc;
     launch_lamb_phase1_from_sum(p, s, st);
     if ((rc = launched("lamb_phase1_from_sum_kernel"))) return rc;
-    if ((rc = lamb_norms(p, st))) return rc;
+    if ((rc = lamb_norms(p, p->lay(), st))) return rc;
     if ((rc = lamb_phase2_impl(p, s, flag, st, false))) return rc;
     return cast_launch(p, s, flag, st, 1);
 }

@@ -8,7 +8,7 @@ namespace {
 template <bool GF32, bool GROUPED, class MEM>
 void launch_lamb_one_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    const Layout &L = p->lay();
+    const Layout &L = p->lamb_lay();
     const dim3 grid((unsigned)L.chunks), block(kSmallBlock);
     switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((lamb_one_launch_kernel<GradSlices<r, GF32, MEM>, GROUPED, kSmallBlock, lamb_meeting_waves(r, GF32)>), grid, block, 0, st, L.d_per_chunk, s, p->d_sums, p->d_meeting, flag, p->meeting_limit, L.groups); break;
@@ -21,7 +21,7 @@ void launch_lamb_one_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hi
 template <bool GF32, class MEM>
 void launch_lamb_one(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
-    if (p->lay().chunks > (int64_t)kMeetingChunks) launch_lamb_one_r<GF32, true, MEM>(p, s, flag, st);
+    if (p->lamb_lay().chunks > (int64_t)kMeetingChunks) launch_lamb_one_r<GF32, true, MEM>(p, s, flag, st);
     else launch_lamb_one_r<GF32, false, MEM>(p, s, flag, st);
 }
 

@@ -86,6 +86,16 @@ inline bool flat_beyond_small(uint64_t numel, int R, bool grad_f32)
     return R <= kFlatMaxF16Slices && numel < (R == 1 ? kFlatNarrowMaxElems : kFlatWideMaxElems);
 }
 
+// The fused LAMB step keeps its chunks of 1024 elements, one workgroup each, somewhat beyond: its first sweep gives the second m' and v' through
+// the Infinity Cache (see cache_policies), which the ordered schedule's non-temporal stores do not, and the less of them fits the less
+// that is worth.  If nothing was asked; us, ordered / this, three shards in turn, then one by itself:
+//   BERT-Large list 67 M, R = 2 476 / 428, 470 / 437; R = 8 605 / 567, 601 / 580; R = 16 794 / 773, 792 / 769; fp32 R = 8 794 / 779, 802 / 739; 84 M, R = 1 562 / 519,
+//   560 / 519; R = 4 638 / 602, 626 / 609.5; R = 8 742 / 724, 734 / 728; fp32 R = 2 637 / 608, 639 / 618; 8.3B list 74 M, R = 2 519 / 484, 515 / 487; R = 8
+//   658 / 636, 666 / 642; one tensor 70 M, R = 1 471 / 437, 470 / 451; R = 8 621 / 603, 615.5 / 614; 84 M, R = 4 631 / 620, 633 / 624; but 100 M, R = 2 686.5 / 686, 688 /
+//   689.5; R = 8 873.5 / 883, 876.5 / 897; GPT-2 list 97 M, R = 8 855 / 847, 859 / 862; BERT-Large list 112 M, R = 8 971.5 / 966, 990 / 997.
+constexpr uint64_t kLambSmallChunksMaxElems = 88u << 20;
+inline bool lamb_keeps_small_chunks(uint64_t numel) { return numel < kLambSmallChunksMaxElems; }
+
 // A list of tensors goes in such pieces as well, with the same reservations (flat_lds), where its step stores too much to write through:
 // below kSmallShardElems instead of 128-thread workgroups, beyond instead of the ordered schedule, if nothing else was asked.
 // us, without / with pieces, three shards in turn, then one by itself:

@@ -73,6 +73,8 @@ struct cc_plan {
     bool flat_pieces = false;               // small chunks of one tensor bound by HBM: fused Adam in single-wave pieces (see kFlatPiece)
     bool flat_adam = false;                 // large chunks, but the fused Adam step in single-wave pieces (see flat_beyond_small)
     const ccf::Layout *list_pieces = nullptr;   // several tensors: the chunks whose pieces the fused Adam step takes (see list_in_pieces)
+    int lamb_active = 0;                    // the layout and schedule of the fused LAMB step: the same, or see lamb_keeps_small_chunks
+    bool lamb_ordered = false, lamb_spread = false;
     bool spread = false;                    // chunks of 1024 elements of a shard bound by HBM (see kSpreadLds)
     bool spread_adam = false;               // ... for the fused Adam step
     int32_t cache_policy = CC_CACHE_AUTO;   // what the caller asked for
@@ -90,6 +92,7 @@ struct cc_plan {
 
     const ccf::Layout &lay() const { return layouts[(size_t)active]; }
     int64_t chunks() const { return lay().chunks; }
+    const ccf::Layout &lamb_lay() const { return layouts[(size_t)lamb_active]; }
 };
 
 namespace ccf {
@@ -109,9 +112,10 @@ inline unsigned ordered_grid(const cc_plan *p)
 // Every per-chunk streaming kernel exists for two workgroup sizes, and the small one for every cache policy; the
 // plan's layout and policy pick one.  The statement given sees BLK (int) and MEM (Streaming, Resident or WriteThrough).
 #define BY_BLOCK(p, ...) BY_BLOCK_MEM(p, (p)->mem.adam, __VA_ARGS__)
-#define BY_BLOCK_MEM(p, mem_, ...)                                                          \
+#define BY_BLOCK_MEM(p, mem_, ...) BY_LAYOUT_MEM((p)->lay(), mem_, __VA_ARGS__)
+#define BY_LAYOUT_MEM(layout_, mem_, ...)                                                   \
     do {                                                                                    \
-        if ((p)->lay().block == kBigBlock) { constexpr int BLK = kBigBlock; typedef Streaming MEM; __VA_ARGS__; }        \
+        if ((layout_).block == kBigBlock) { constexpr int BLK = kBigBlock; typedef Streaming MEM; __VA_ARGS__; }        \
         else if ((mem_) == CC_CACHE_RESIDENT) { constexpr int BLK = kSmallBlock; typedef Resident MEM; __VA_ARGS__; }    \
         else if ((mem_) == CC_CACHE_WRITE_THROUGH) { constexpr int BLK = kSmallBlock; typedef WriteThrough MEM; __VA_ARGS__; } \
         else { constexpr int BLK = kSmallBlock; typedef Streaming MEM; __VA_ARGS__; }                                    \
@@ -136,18 +140,18 @@ void launch_fused_adam_f32(const cc_plan *p, const StepScalars &s, int32_t *flag
 void launch_lamb_phase1(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st, const LambTally &tally = {});
 void launch_lamb_phase1_from_sum(const cc_plan *p, const StepScalars &s, hipStream_t st);
 int lamb_phase2_impl(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st, bool emit16);
-int lamb_norms(cc_plan *p, hipStream_t st);
+int lamb_norms(cc_plan *p, const Layout &L, hipStream_t st);
 // Whether cc_fused_lamb_step is a single launch: one workgroup per 1024-element chunk, and few enough of them (see lamb_meets).
 inline bool lamb_in_one_launch(const cc_plan *p)
 {
-    const Layout &L = p->lay();
-    return !p->ordered && L.chunk_elems == kSmallChunkElems && L.d_per_chunk && lamb_meets(L.chunks, L.groups, p->cus, p->R, p->grad_f32);
+    const Layout &L = p->lamb_lay();
+    return !p->lamb_ordered && L.chunk_elems == kSmallChunkElems && L.d_per_chunk && lamb_meets(L.chunks, L.groups, p->cus, p->R, p->grad_f32);
 }
 // Whether cc_fused_lamb_step's first sweep adds up the chunks' sums group by group (see LambTally).
 inline bool lamb_tallied(const cc_plan *p)
 {
-    const Layout &L = p->lay();
-    return p->tally.chunk != nullptr && !p->ordered && L.block == kSmallBlock;
+    const Layout &L = p->lamb_lay();
+    return p->tally.chunk != nullptr && !p->lamb_ordered && L.block == kSmallBlock;
 }
 int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
 // Whether cc_fused_lamb_step lets every phase-2 workgroup add up its own tensor's partials instead of launching the
@@ -157,8 +161,8 @@ int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t
 // at 512, but 16.5 / 14.3 at 1024.
 inline bool norms_fold_into_phase2(const cc_plan *p)
 {
-    const Layout &L = p->lay();
-    return !p->ordered && L.block == kSmallBlock && L.chunks > 0 && L.most_tensor_chunks <= kFoldNormsMaxChunks;
+    const Layout &L = p->lamb_lay();
+    return !p->lamb_ordered && L.block == kSmallBlock && L.chunks > 0 && L.most_tensor_chunks <= kFoldNormsMaxChunks;
 }
 int lamb_phase2_tallied(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st);
 int lamb_phase2_with_norms(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st);
