@@ -32,6 +32,7 @@
 #include "ccfused.h"
 #include "meeting.hpp"
 #include "occupancy.hpp"
+#include "packed_args.hpp"
 #include "piece_order.hpp"
 
 namespace ccf {
@@ -323,11 +324,12 @@ struct FlagCount {
     __device__ __forceinline__ uint32_t tag() const { return (uint32_t)(prev >> 32) + 1u; }          // this launch's p + 1
 
     // First act of a kernel: the wave's arrival.  Nothing is waited for here.
-    __device__ __forceinline__ void arrive(FlagScratch *fs)
+    __device__ __forceinline__ void arrive(FlagScratch *fs) { arrive(fs, gridDim.x); }
+    __device__ __forceinline__ void arrive(FlagScratch *fs, uint32_t workgroups)
     {
         if (counting_lane()) {
             constexpr uint32_t kWaves = BLOCK / 64;
-            const uint32_t waves = gridDim.x * kWaves;
+            const uint32_t waves = workgroups * kWaves;
             const uint32_t me = blockIdx.x * kWaves + (threadIdx.x >> 6);
             slot = me % kFlagSlots;
             in_slot = (waves - slot + kFlagSlots - 1) / kFlagSlots;      // waves w with w % kFlagSlots == slot
@@ -888,6 +890,34 @@ __global__ __launch_bounds__(BLOCK) void fused_adam_flat_kernel(DevTensor t, Ste
     AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
     op.init(&t, base, s);
     sweep_and_publish<BLOCK, GROUPS>(op, rem < s.chunk_elems ? (uint32_t)rem : s.chunk_elems, fc, fs, flag);
+}
+
+// ... with its arguments in 96 bytes (see PackedAdam), in chunks of kPackedChunk.  us per eager pass, three tensors in turn,
+// without / with: R = 1 4.80 / 4.22 at 1031 elements, R = 4 4.79 / 4.25 at 4099, R = 8 4.80 / 4.45 and R = 16 4.88 / 4.33 at 14000; static call, R = 2 5.38 / 4.89 at 50003;
+// graph replays and shards that the device takes longer for are the same within 1 %.
+constexpr uint32_t kPackedChunk = 1024;
+template <int R, int MODE, int BLOCK, bool GF32, class Mem>
+__global__ __launch_bounds__(BLOCK) void fused_adam_packed_kernel(PackedAdam a)
+{
+    FlagScratch *fs = (FlagScratch *)a.scratch;
+    FlagCount<BLOCK> fc;
+    fc.arrive(fs, (a.numel + (kPackedChunk - 1)) / kPackedChunk);
+    DevTensor t;
+    const auto at = [&](int k) { return packed_at(a, k); };
+    t.w_in = (const float *)at(0); t.m_in = (const float *)at(1); t.v_in = (const float *)at(2);
+    t.w_out = (float *)at(3); t.m_out = (float *)at(4); t.v_out = (float *)at(5);
+    t.w16 = (uint16_t *)at(6);
+#pragma unroll
+    for (int r = 0; r < R; ++r) t.grad[r] = (const void *)packed_slice(a, r);
+    t.wd = a.wd;
+    StepScalars s;
+    s.inv_div = a.inv_div;
+    s.beta1 = a.beta1; s.beta2 = a.beta2; s.omb1 = 1.0 - s.beta1; s.omb2 = 1.0 - s.beta2;
+    s.rc1 = a.rc1; s.rc2 = a.rc2; s.eps = a.eps; s.lr = a.lr;
+    const uint32_t base = blockIdx.x * kPackedChunk, rem = a.numel - base;
+    AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
+    op.init(&t, base, s);
+    sweep_and_publish<BLOCK, 2>(op, rem < kPackedChunk ? rem : kPackedChunk, fc, fs, (int32_t *)packed_flag(a));
 }
 
 // The step on a list bound by HBM in single-wave workgroups, one per piece of 256 elements: kPiecesPerChunk for every entry of the table
@@ -2157,14 +2187,31 @@ struct FusedEpilogueOp {
 constexpr int kEpilogueFusedBlock = 64;
 constexpr uint32_t kEpiloguePiece = kEpilogueFusedBlock * 8;
 template <int R>
-__global__ __launch_bounds__(kEpilogueFusedBlock) void fused_epilogue_kernel(EpilogueArgs a)
+__device__ __forceinline__ void fused_epilogue_piece(const EpilogueArgs &a, uint32_t piece)
 {
-    const uint32_t piece = a.runs ? piece_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
     const uint64_t base = (uint64_t)piece * kEpiloguePiece;
     const uint64_t rem = a.numel - base;
     FusedEpilogueOp<R> op;
     op.init(a, base);
     stream_chunk<kEpilogueFusedBlock, FusedEpilogueOp<R>, 1>(op, rem < kEpiloguePiece ? (uint32_t)rem : kEpiloguePiece);
+}
+template <int R>
+__global__ __launch_bounds__(kEpilogueFusedBlock) void fused_epilogue_kernel(EpilogueArgs a)
+{
+    fused_epilogue_piece<R>(a, a.runs ? piece_in_runs(blockIdx.x, gridDim.x) : blockIdx.x);
+}
+// ... with its arguments in 96 bytes.  us per eager call, three sets of buffers in turn, without / with:
+// 40304 elements, R = 1 4.08 / 3.52, R = 8 4.25 / 3.89; 1 M, R = 8 5.05 / 4.60.
+template <int R>
+__global__ __launch_bounds__(kEpilogueFusedBlock) void fused_epilogue_packed_kernel(PackedEpilogue<R> p)
+{
+    EpilogueArgs a;
+    a.numel = p.numel; a.first = p.first; a.hidden = p.hidden; a.threshold = p.threshold; a.key0 = p.key0; a.key1 = p.key1; a.scale = p.scale;
+    const auto at = [&](int k) { return unpack_address(p.base, p.at[k]); };
+#pragma unroll
+    for (int r = 0; r < R; ++r) a.partial[r] = (const uint16_t *)at(r);
+    a.bias = (const uint16_t *)at(R); a.residual = (const uint16_t *)at(R + 1); a.out = (uint16_t *)at(R + 2);
+    fused_epilogue_piece<R>(a, blockIdx.x);
 }
 
 // Unfused pipeline: reduce the R partial outputs into an fp32 buffer (a lane owns 4 elements, so that the fp32

@@ -37,6 +37,29 @@ void launch_list_pieces(const cc_plan *p, const StepScalars &s, int32_t *flag, h
     }
 }
 
+// One tensor in chunks of kPackedChunk elements whose arguments fit 96 bytes.  False: they do not.
+template <int MODE, bool GF32, class MEM>
+bool launch_packed(const DevTensor &t, int R, const StepScalars &s, FlagScratch *fs, int32_t *flag, hipStream_t st)
+{
+    const auto word = [](const void *p) { return (uint64_t)reinterpret_cast<uintptr_t>(p); };
+    const uint64_t address[8] = {word(t.w_in), word(t.m_in), word(t.v_in), word(t.w_out), word(t.m_out), word(t.v_out), word(t.w16), word(t.grad[0])};
+    uint64_t grad[CC_MAX_R];
+    for (int r = 0; r < R; ++r) grad[r] = word(t.grad[r]);
+    PackedAdam a;
+    if (!pack_adam(address, grad, R, word(flag), word(fs), t.numel, &a)) return false;
+    a.inv_div = s.inv_div;
+    a.wd = t.wd;
+    a.beta1 = (float)s.beta1; a.beta2 = (float)s.beta2;                  // the interface's fp32 values
+    a.rc1 = s.rc1; a.rc2 = s.rc2; a.eps = s.eps; a.lr = s.lr;
+    const dim3 grid((a.numel + (kPackedChunk - 1)) / kPackedChunk), block(kSmallBlock);
+    switch (R) {
+#define CASE(r) case r: hipLaunchKernelGGL((fused_adam_packed_kernel<r, MODE, kSmallBlock, GF32, MEM>), grid, block, 0, st, a); break;
+        FOR_EACH_R(CASE)
+#undef CASE
+    }
+    return true;
+}
+
 template <int MODE, int BLK, bool GF32, class MEM>
 void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st)
 {
@@ -59,6 +82,8 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
         const DevTensor &t = L.host_tensors[(size_t)p->single];
         if constexpr (!std::is_same<MEM, Resident>::value)
             if (p->flat_pieces && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
+        if constexpr (BLK == kSmallBlock && !std::is_same<MEM, WriteThrough>::value)
+            if (L.chunk_elems == kSmallChunkElems && launch_packed<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st)) return;
         switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, 0, st, t, s, p->d_flag_scratch, flag); break;
             FOR_EACH_R(CASE)

@@ -15,6 +15,8 @@ void launch_flat_r(const DevTensor &t, int R, unsigned grid, const StepScalars &
 {
     if constexpr (!std::is_same<MEM, Resident>::value)
         if (step_footprint(t.numel, R, false) >= kPlainLoadsMaxBytes) return launch_flat_pieces<MODE, false, MEM>(t, R, s, fs, flag, st);
+    if constexpr (!std::is_same<MEM, WriteThrough>::value)
+        if (launch_packed<MODE, false, MEM>(t, R, s, fs, flag, st)) return;
     switch (R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, kSmallBlock, false, 2, MEM>), dim3(grid), dim3(kSmallBlock), 0, st, t, s, fs, flag); break;
         FOR_EACH_R(CASE)
