@@ -390,7 +390,7 @@ int cc_plan_create_ex(const cc_tensor *tensors, int32_t T, int32_t R, int32_t ch
     // (Of the chunk sizes a plan is prepared for only one has small workgroups.  A tensor without a chunk has sums too, zeros, which
     // nobody in the first sweep would write: such plans keep the launch that does.)
     for (const Layout &L : p->layouts)
-        if (L.block == kSmallBlock && lamb_tallies(L.chunks, L.most_tensor_chunks) && nonempty == T) {
+        if (L.block == kSmallBlock && nonempty == T && (lamb_tallies(L.chunks, L.most_tensor_chunks) || lamb_one_group_each(L.chunks, L.most_tensor_chunks))) {
             counts_at = meeting_bytes;
             chunks_at = counts_at + sizeof(LambTally::Count) * (size_t)L.groups;
             groups_at = chunks_at + sizeof(TaggedSums) * (size_t)L.chunks;
@@ -400,7 +400,7 @@ int cc_plan_create_ex(const cc_tensor *tensors, int32_t T, int32_t R, int32_t ch
     PLAN_TRY(hipMemset(p->d_meeting, 0, meeting_bytes));
     if (counts_at) {
         char *at = (char *)p->d_meeting;
-        p->tally = LambTally{(TaggedSums *)(at + chunks_at), (LambTally::Count *)(at + counts_at), (LambTally::Sums *)(at + groups_at)};
+        p->tally = LambTally{(TaggedSums *)(at + chunks_at), (LambTally::Count *)(at + counts_at), (LambTally::Sums *)(at + groups_at), nullptr};
     }
     p->d_flag_scratch = &p->d_meeting->flag;
     PLAN_TRY(hipMalloc((void **)&p->d_queue, sizeof(WorkQueue)));
@@ -759,8 +759,15 @@ int cc_fused_lamb_phase1(cc_plan *p, const cc_hparams *hp, int32_t *flag, void *
     if (p->chunks() == 0) {
         if ((rc = clear_flag(flag, st))) return rc;
     } else {
-        launch_lamb_phase1(p, s, flag, st);
+        LambTally tally{};
+        if (lamb_phase1_sums(p)) {
+            tally = p->tally;
+            tally.group = nullptr;
+            tally.sums = reinterpret_cast<LambTally::Sums *>(p->d_sums);
+        }
+        launch_lamb_phase1(p, s, flag, st, tally);
         if ((rc = launched("lamb_phase1_kernel"))) return rc;
+        if (tally.chunk) return CC_OK;
     }
     return lamb_norms(p, p->lamb_lay(), st);
 }

@@ -1153,7 +1153,8 @@ struct LambPhase1Op {
 // Half of LAMB's second level inside its first sweep (see lamb_tallies): as a launch of its own, one workgroup per tensor, it leaves the
 // device idle for 4.6 us at 5 to 24 M elements.  Here a workgroup publishes its chunk's sums as tagged words and counts itself in
 // its group: the chunks that one wave of that launch adds up, those with the same (index / 64) % 16.  Whoever completes the group
-// adds them up; the second sweep adds up its tensor's 16 groups.  Same additions in the same order as tensor_sums, so the same bits.
+// adds them up; the second sweep adds up its tensor's 16 groups.  Where every tensor is one group, which is all of its sums, so does the
+// first of the two phase calls (lamb_phase1_sums).  Same additions in the same order as tensor_sums, so the same bits.
 //   * The words carry the launch's tag, so that the count needs no order behind them: the last one to count looks until all
 //     the words are there.  All of them have been issued by then; nobody waits for a workgroup that has not run.
 //   * The counts only grow.  Every launch adds a power of two to each, because the group's first chunk adds for those that are
@@ -1167,7 +1168,8 @@ struct LambTally {
     struct alignas(128) Count { uint32_t chunks; };
     TaggedSums *chunk;                   // by slot; nullptr: plain partial sums, which lamb_norms_kernel adds up
     Count *count;                        // by DevTensor::first_group + which group of the tensor
-    Sums *group;                         // as well
+    Sums *group;                         // as well; nullptr: every tensor is one group, and its sums go to `sums`
+    Sums *sums;                          // by tensor
 };
 
 // One look of a wave at n sums, lane by lane and `rows` of them, 1024 apart, per lane: adds them up as tensor_sums does if all are this launch's.
@@ -1221,7 +1223,7 @@ __device__ __forceinline__ void tally_group(const LambTally &ty, const Where &wh
             if ((lost = ++looks > kMeetingBound)) break;
     const double tw = wave_sum((a[0] + a[1]) + (a[2] + a[3])), tu = wave_sum((b[0] + b[1]) + (b[2] + b[3]));
     if (lane == 0u) {
-        ty.group[wh.t->first_group + g] = LambTally::Sums{tw, tu};
+        (ty.group != nullptr ? ty.group[wh.t->first_group + g] : ty.sums[wh.tensor]) = LambTally::Sums{tw, tu};
         if (lost) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }

@@ -47,4 +47,13 @@ constexpr uint32_t kFoldNormsMaxChunks = 512;
 constexpr int64_t kTallyMinChunks = 600, kTallyMaxChunks = 32768;
 inline bool lamb_tallies(int64_t chunks, uint32_t most) { return chunks >= kTallyMinChunks && chunks <= kTallyMaxChunks && most > kFoldNormsMaxChunks; }
 
+// Whether the phase calls do without that launch: every tensor is one group, and few enough of them (the counts and
+// groups take 176 bytes each).  us for the two calls with the launch / without, eager, then graph replay: one tensor of 1031 elements, R = 2
+// 12.4 / 9.1, 7.1 / 6.4; 10007, R = 8 12.4 / 9.1, 8.3 / 7.3; 65000, R = 1 12.4 / 9.2, 8.7 / 8.0; BERT-Large list in 512 slices, R = 8 13.3 / 11.5, 13.0 / 11.5;
+// 8.3B list in 450, R = 4 23.6 / 22.3, 23.0 / 21.5.  With tensors of several groups, which the first sweep would have to add up as well, the
+// two take the same time: the trips to memory at its end cost what the launch did (BERT-Large list in 203 slices, R = 2 16.6 / 16.9).
+constexpr uint32_t kOneGroupChunks = 64;
+constexpr int64_t kOneGroupEachMaxChunks = 8192;
+inline bool lamb_one_group_each(int64_t chunks, uint32_t most) { return chunks > 0 && chunks <= kOneGroupEachMaxChunks && most <= kOneGroupChunks; }
+
 }  // namespace ccf

@@ -151,7 +151,13 @@ inline bool lamb_in_one_launch(const cc_plan *p)
 inline bool lamb_tallied(const cc_plan *p)
 {
     const Layout &L = p->lamb_lay();
-    return p->tally.chunk != nullptr && !p->lamb_ordered && L.block == kSmallBlock;
+    return p->tally.chunk != nullptr && !p->lamb_ordered && L.block == kSmallBlock && lamb_tallies(L.chunks, L.most_tensor_chunks);
+}
+// Whether the first phase call's sweep leaves the tensors' sums itself: tensors of one group each.
+inline bool lamb_phase1_sums(const cc_plan *p)
+{
+    const Layout &L = p->lamb_lay();
+    return p->tally.chunk != nullptr && !p->lamb_ordered && L.block == kSmallBlock && lamb_one_group_each(L.chunks, L.most_tensor_chunks);
 }
 int lamb_one_launch(cc_plan *p, const StepScalars &s, int32_t *flag, hipStream_t st);
 // Whether cc_fused_lamb_step lets every phase-2 workgroup add up its own tensor's partials instead of launching the

@@ -63,3 +63,64 @@ def test_sums_are_those_of_the_launch_of_its_own(numels, tallied, kw):
     cc.cc_fused_lamb_step(plan, hp, shard.flag)             # nothing of w is written when the last element overflows
     assert int(shard.flag.item()) == 1 and bool((shard.w[1] == 7.0).all())
     shard.destroy()
+
+
+@pytest.mark.parametrize("numels,own,kw", [
+    ([1], True, {}),
+    ([64 * K], True, {}),                                         # one whole group
+    ([64 * K + 1], False, {}),                                    # two
+    ([5, 63 * K + 7, K, 64 * K, 1] * 40, True, {}),
+    ([3] * 8192, True, {}),                                       # the most
+    ([3] * 8193, False, {}),
+    ([70 * K, 0, 9], False, {}),
+    ([30 * K, 0, 9], False, {}),                                  # an empty tensor's zeros are written by the launch
+    ([128 * K], True, {"chunk_elems": 2048}),
+    ([4 * K + 3, 50], False, {"chunk_elems": 4096}),              # workgroups of 512 threads
+])
+def test_sums_of_the_first_phase_call(numels, own, kw):
+    shard = _filled(numels, 3, **kw)
+    plan, hp = shard.plans[0], cc.Hyper(step=3)
+
+    def phases():
+        cc.cc_fused_lamb_phase1(plan, hp, shard.flag)
+        cc.cc_fused_lamb_phase2(plan, hp, shard.flag)
+    assert [x.kernel for x in launches(phases)] == ["lamb_phase1_kernel"] + ["lamb_norms_kernel"] * (not own) + ["lamb_phase2_kernel"]
+    cc.cc_unfused_lamb_step(plan, hp, shard.flag)
+    want, w_want = np.asarray(cc.cc_lamb_norms_read(plan, len(numels))), shard.w[1].clone()
+    for _ in range(2):
+        cc.cc_fused_adam_step(plan, hp, shard.flag)
+        cc.cc_fused_lamb_phase1(plan, hp, shard.flag)
+        assert np.array_equal(np.asarray(cc.cc_lamb_norms_read(plan, len(numels))), want)
+        cc.cc_fused_lamb_phase2(plan, hp, shard.flag)
+        assert torch.equal(shard.w[1], w_want) and int(shard.flag.item()) == 0
+    shard.destroy()
+
+
+@pytest.mark.parametrize("numels,phases", [([700 * K + 1], False), ([64 * K, 5, 2 * K], True)])
+def test_replays_of_a_captured_step(numels, phases):
+    """A graph of two steps, replayed with other work and eager steps in between: each replay's result is the eager one."""
+    shard = _filled(numels, 2)
+    plan, hp = shard.plans[0], cc.Hyper(step=3)
+
+    def step():
+        if not phases:
+            return cc.cc_fused_lamb_step(plan, hp, shard.flag)
+        cc.cc_fused_lamb_phase1(plan, hp, shard.flag)
+        cc.cc_fused_lamb_phase2(plan, hp, shard.flag)
+    step()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        step()
+        step()
+    for k in range(5):
+        shard.grads[0].mul_(1.25)
+        shard.w[1].fill_(7.0)
+        step()
+        want = shard.w[1].clone()
+        sums = np.asarray(cc.cc_lamb_norms_read(plan, len(numels)))
+        shard.w[1].fill_(7.0)
+        graph.replay()
+        assert torch.equal(shard.w[1], want) and int(shard.flag.item()) == 0
+        assert np.array_equal(np.asarray(cc.cc_lamb_norms_read(plan, len(numels))), sums)
+    shard.destroy()
