@@ -9,10 +9,21 @@ from paper_2105_05720_amd.launches import launches
 pytestmark = pytest.mark.gpu
 
 
-def _slices(R, n, dtype, even, gen):
+class Arena:
+    """Tensors out of one allocation: separate ones may lie more than 64 GiB apart, which does not fit the packed arguments."""
+
+    def __init__(self, nbytes):
+        self.bytes, self.used = torch.zeros(nbytes, dtype=torch.uint8, device="cuda"), 0
+
+    def __call__(self, n, dtype):
+        first, self.used = self.used, self.used + -(-n * dtype.itemsize // 256) * 256
+        return self.bytes[first:first + n * dtype.itemsize].view(dtype)
+
+
+def _slices(arena, R, n, dtype, even):
     """R slices one after the other from the last to the first, or with one of them further away."""
     pitch = -(-n // 64) * 64
-    arena = torch.empty((R + 1) * pitch, device="cuda").normal_(0, 1e-2, generator=gen).to(dtype)
+    arena = arena((R + 1) * pitch, dtype)
     where = list(range(R))[::-1]
     if not even:
         where[-1] = R
@@ -25,19 +36,20 @@ def _slices(R, n, dtype, even, gen):
 def test_adam(numel, R, dtype, hyper):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(numel + R)
-    w = torch.empty(numel, device="cuda").normal_(0, 0.02, generator=gen)
-    m = torch.empty(numel, device="cuda").normal_(0, 1e-3, generator=gen)
-    v = torch.empty(numel, device="cuda").uniform_(0, 1e-6, generator=gen)
+    arena = Arena(numel * (26 + (2 * R + 2) * dtype.itemsize) + (4 << 10) * (R + 12))
+    w, m, v, *out = [arena(numel, torch.float32) for _ in range(6)] + [arena(numel, torch.float16)]
+    w.normal_(0, 0.02, generator=gen)
+    m.normal_(0, 1e-3, generator=gen)
+    v.uniform_(0, 1e-6, generator=gen)
     values = torch.empty(R, numel, device="cuda").normal_(0, 1e-2, generator=gen).to(dtype)
-    flag, hp, results = torch.zeros(2, dtype=torch.int32, device="cuda"), cc.Hyper(step=3, **hyper), []
+    flag, hp, results = arena(2, torch.int32), cc.Hyper(step=3, **hyper), []
     for even in (True, False):
-        grads = _slices(R, numel, dtype, even, gen)
+        grads = _slices(arena, R, numel, dtype, even)
         for g, x in zip(grads, values):
             g.copy_(x)
         for bad in (False, True):
             if bad:
                 grads[-1][-1] = float("inf")
-            out = [torch.full((numel,), 7.0, device="cuda") for _ in range(3)] + [torch.full((numel,), 7.0, dtype=torch.float16, device="cuda")]
             t = cc.Tensor(numel, w, m, v, *out, grads, 0.01)
             plan = cc.cc_plan_create_ex([t], R, 0, cc.CC_GRAD_F16 if dtype == torch.float16 else cc.CC_GRAD_F32)
             calls = [lambda: cc.cc_fused_adam_step(plan, hp, flag[1:])]             # a flag that is not 16-byte aligned
@@ -63,11 +75,14 @@ def test_adam(numel, R, dtype, hyper):
 def test_epilogue(numel, R):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(numel + R)
-    half = lambda n, std: torch.empty(n, device="cuda").normal_(0, std, generator=gen).half()
+    arena = Arena(2 * numel * (R + 4) + (1 << 16))
+
+    def half(n, std):
+        return arena(n, torch.float16).copy_(torch.empty(n, device="cuda").normal_(0, std, generator=gen))
     values, bias, residual = [half(numel, 0.3) for _ in range(R)], half(3072, 0.1), half(numel, 1.0)
     for first in (1 << 33, 0):
         partials = values
-        out = torch.full((numel,), 7.0, dtype=torch.float16, device="cuda")
+        out = arena(numel, torch.float16).fill_(7.0)
         call = lambda: cc.cc_fused_epilogue(partials, bias, residual, out, first, 3072, 0.1, 12345678901)
         small = numel * (2 * R + 4) < 16 << 20
         assert [x.kernel for x in launches(call)] == ["fused_epilogue_packed_kernel" if small else "fused_epilogue_kernel"]
