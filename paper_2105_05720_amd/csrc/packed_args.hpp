@@ -53,10 +53,11 @@ struct PackedAdam {
 };
 static_assert(sizeof(PackedAdam) == 96, "one more costs half a microsecond");
 
+constexpr uint64_t kPackedMaxElems = 0xffffffffull - 0xffffu;         // rounded up to whole workgroups it still fits 32 bits
 // Everything that is an address; false if it does not fit.
 inline bool pack_adam(const uint64_t (&address)[8], const uint64_t *grad, int R, uint64_t flag, uint64_t scratch, uint64_t numel, PackedAdam *a)
 {
-    if (numel > 0xffffffffull) return false;
+    if (numel > kPackedMaxElems) return false;
     uint64_t all[9];
     for (int k = 0; k < 8; ++k) all[k] = address[k];
     all[8] = flag & ~(uint64_t)15;

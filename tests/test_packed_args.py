@@ -85,12 +85,12 @@ def test_adam_at_the_edges(pack):
         for k, x in kw.items():
             v[int(k[1:])] = x
         return ("a", 3, v)
-    cases = [but(), but(_0=b + FAR), but(_0=b + 16 + FAR, _7=b + FAR + 12), but(_7=b + 4), but(_7=b - 4), but(_9=2**32 - 1),
+    cases = [but(), but(_0=b + FAR), but(_0=b + 16 + FAR, _7=b + FAR + 12), but(_7=b + 4), but(_7=b - 4), but(_9=2**32 - 2**16),
              but(_11=b + 1024, _12=b + 1024), but(_10=b + (1 << 36) - 1024, _11=b + (1 << 35), _12=b + 1024)]
     got = pack(cases)
     assert got[0] == good and [x is not None for x in got] == [True, True, True, True, True, True, True, True]
     assert all(x == c[2] for x, c in zip(got, cases))
-    assert pack([but(_0=b + FAR + 32), but(_7=b + FAR + 16), but(_7=b - 4, _0=b + FAR), but(_9=2**32), but(_12=b + 3088), but(_11=b + 2048 + 16),
+    assert pack([but(_0=b + FAR + 32), but(_7=b + FAR + 16), but(_7=b - 4, _0=b + FAR), but(_9=2**32 - 2**16 + 1), but(_12=b + 3088), but(_11=b + 2048 + 16),
                  but(_11=b + 1024 + 2**31 * 16, _12=b + 1024 + 2**32 * 16)]) == [None] * 7
 
 
