@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import struct
+import warnings
 from dataclasses import dataclass, field
 from typing import List, Optional, Sequence
 
@@ -136,8 +137,8 @@ def _current_stream() -> Optional[int]:
     if _torch is None:
         import torch
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        _torch = torch
-        _bind_native()
+        _bind_native(torch)
+        _torch = torch                    # last: where that raised (no device, say), the next call starts here again
     if _raw_stream is None:
         return _torch.cuda.current_stream().cuda_stream or None
     return _raw_stream(_torch.cuda.current_device()) or None
@@ -362,14 +363,19 @@ def _not_taken(*args) -> int:
 _native_step = _native_static = _native_epilogue = _not_taken
 
 
-def _bind_native() -> None:
+def _bind_native(torch=None) -> None:
     """Lets the step calls go through the extension module: torch is there, and its device has been looked at."""
     global _native_step, _native_static, _native_epilogue
     if _raw_stream is None:
         return
-    from . import _step_calls as native
-    _torch.cuda.current_device()
-    if native.bind(Plan, Hyper, Tensor, _torch.Tensor, _torch.nn.Parameter, _torch._C._cuda_getDevice, _raw_stream):
+    try:
+        from . import _step_calls as native
+    except ImportError as e:              # not built, or for another Python: the packed bytes do as well
+        warnings.warn("step calls go through ctypes, 1 to 2 us slower each: %s (python -m paper_2105_05720_amd.build)" % e, RuntimeWarning, stacklevel=2)
+        return
+    torch = torch or _torch
+    torch.cuda.current_device()
+    if native.bind(Plan, Hyper, Tensor, torch.Tensor, torch.nn.Parameter, torch._C._cuda_getDevice, _raw_stream):
         _native_step, _native_static, _native_epilogue = native.step, native.static_step, native.epilogue
 
 

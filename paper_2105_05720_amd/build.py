@@ -2,7 +2,8 @@
 
 The library is several translation units (one per kernel family) only so that they compile side by side; each is
 compiled to an object file and the objects are linked into one shared library, whose dynamic symbol table is cut down
-to the C ABI by csrc/exports.map.  Beside it, with g++, the extension module through which Python's step calls reach it."""
+to the C ABI by csrc/exports.map.  Beside it, with g++, the extension module through which Python's step calls reach it,
+if this Python's headers are there: nothing but time depends on it."""
 from __future__ import annotations
 
 import os
@@ -23,7 +24,8 @@ DEPS = SOURCES + [os.path.join(CSRC, "kernels.hip.h"), os.path.join(CSRC, "plan.
                   os.path.join(ROOT, "include", "ccfused.h"), EXPORTS_MAP]
 LIB = os.path.join(_HERE, "libccfused.so")
 STEP_CALLS_SOURCE = os.path.join(CSRC, "step_calls.cpp")
-STEP_CALLS = os.path.join(_HERE, "_step_calls.so")      # a module of CPython's; host code only
+# A module of CPython's, for the Python that builds it; host code only.
+STEP_CALLS = os.path.join(_HERE, "_step_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(_HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -40,26 +42,35 @@ FLAGS = [
 ]
 
 
+def _older(built, sources) -> bool:
+    return not os.path.exists(built) or any(os.path.getmtime(d) > os.path.getmtime(built) for d in sources)
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(STEP_CALLS):
-        return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(d) > t for d in DEPS) or os.path.getmtime(STEP_CALLS_SOURCE) > os.path.getmtime(STEP_CALLS)
+    return _older(LIB, DEPS)
 
 
-def build_step_calls() -> str:
+def build_step_calls():
+    """The extension module; without a compiler or Python's headers None, and the step calls go the way through ctypes."""
     tmp = STEP_CALLS + ".tmp%d" % os.getpid()
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-Wno-cast-function-type",
-                           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-o", tmp, STEP_CALLS_SOURCE])
+    try:
+        subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-Wno-cast-function-type",
+                               "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-o", tmp, STEP_CALLS_SOURCE])
+    except (OSError, subprocess.CalledProcessError) as e:
+        print("the step calls' extension module was not built (%s); they take 1 to 2 us longer without it" % e, file=sys.stderr)
+        if os.path.exists(STEP_CALLS):
+            os.remove(STEP_CALLS)             # of other sources
+        return None
     os.replace(tmp, STEP_CALLS)
     return STEP_CALLS
 
 
 def build_library(force: bool = True, extra=()) -> str:
-    """Compile the HIP library.  force=False skips the compile when the built file is newer than its sources."""
+    """Compile the HIP library and the extension module.  force=False skips what is newer than its sources."""
+    if force or _older(STEP_CALLS, [STEP_CALLS_SOURCE, os.path.join(ROOT, "include", "ccfused.h")]):
+        build_step_calls()
     if not force and not is_stale():
         return LIB
-    build_step_calls()
     os.makedirs(OBJ_DIR, exist_ok=True)
     tag = ".%d" % os.getpid()
     objs = [os.path.join(OBJ_DIR, os.path.basename(src)[:-4] + tag + ".o") for src in SOURCES]

@@ -2,12 +2,16 @@
 Callbacks stand for the library's entry points."""
 import ctypes as C
 import dataclasses
+import importlib.machinery
+import os
+import sys
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2105_05720_amd import binding as cc
+from paper_2105_05720_amd import build
 
 from paper_2105_05720_amd import _step_calls as native
 T = [torch.zeros(8, dtype=torch.float16) for _ in range(20)]
@@ -115,3 +119,44 @@ def test_a_torch_function_mode_sees_the_tensors():
     with Mode():
         assert native.step(seen.at, plan(0), cc.Hyper(), T[0], None) == 0
     assert Mode.asked == 1
+
+
+@pytest.fixture
+def first_call(monkeypatch):
+    """As before the process's first step call, on a machine with a device."""
+    for name in ("_torch", "_raw_stream"):
+        monkeypatch.setattr(cc, name, None)
+    for name in ("_native_step", "_native_static", "_native_epilogue"):
+        monkeypatch.setattr(cc, name, cc._not_taken)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 2, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 2)
+
+
+def test_without_the_module_the_calls_say_so_once_and_go_through_ctypes(first_call, monkeypatch, recwarn):
+    import paper_2105_05720_amd as package
+    monkeypatch.setitem(sys.modules, package.__name__ + "._step_calls", None)
+    monkeypatch.delattr(package, "_step_calls", raising=False)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert cc._current_stream() == 72
+    recwarn.clear()
+    assert cc._current_stream() == 72 and not recwarn.list
+    assert cc._native_step is cc._native_static is cc._native_epilogue is cc._not_taken
+
+
+def test_a_first_call_that_finds_no_device_is_not_the_last_to_look(first_call, monkeypatch):
+    with monkeypatch.context() as m:
+        m.setattr(torch.cuda, "current_device", lambda: (_ for _ in ()).throw(RuntimeError("no device")))
+        for _ in range(2):
+            with pytest.raises(RuntimeError, match="no device"):
+                cc._current_stream()
+    assert cc._current_stream() == 72 and cc._native_step is native.step
+
+
+def test_the_module_is_built_for_one_python_and_the_library_without_it(monkeypatch, tmp_path, capsys):
+    assert build.STEP_CALLS.endswith(importlib.machinery.EXTENSION_SUFFIXES[0]) and native.__file__ == build.STEP_CALLS
+    monkeypatch.setattr(build, "STEP_CALLS", str(tmp_path / "module.so"))
+    monkeypatch.setattr(build, "is_stale", lambda: False)
+    monkeypatch.setenv("PATH", str(tmp_path))                    # no compiler
+    assert build.build_library(force=False) == build.LIB
+    assert "not built" in capsys.readouterr().err and not os.path.exists(build.STEP_CALLS)
