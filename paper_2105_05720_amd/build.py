@@ -19,7 +19,7 @@ SOURCES = [os.path.join(CSRC, n) for n in ("ccfused.hip", "launch_adam_f16.hip",
                                            "launch_unfused.hip")]
 EXPORTS_MAP = os.path.join(CSRC, "exports.map")
 DEPS = SOURCES + [os.path.join(CSRC, "kernels.hip.h"), os.path.join(CSRC, "plan.hpp"), os.path.join(CSRC, "piece_order.hpp"),
-                  os.path.join(CSRC, "cache_rules.hpp"), os.path.join(CSRC, "meeting.hpp"), os.path.join(CSRC, "packed_args.hpp"), os.path.join(CSRC, "tuning.hpp"), os.path.join(CSRC, "occupancy.hpp"),
+                  os.path.join(CSRC, "cache_rules.hpp"), os.path.join(CSRC, "meeting.hpp"), os.path.join(CSRC, "flag_word.hpp"), os.path.join(CSRC, "packed_args.hpp"), os.path.join(CSRC, "tuning.hpp"), os.path.join(CSRC, "occupancy.hpp"),
                   os.path.join(CSRC, "launch_adam.inc.hpp"),
                   os.path.join(ROOT, "include", "ccfused.h"), EXPORTS_MAP]
 LIB = os.path.join(_HERE, "libccfused.so")

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "ccfused.h"
+#include "flag_word.hpp"
 #include "meeting.hpp"
 #include "occupancy.hpp"
 #include "packed_args.hpp"
@@ -311,7 +312,17 @@ constexpr uint32_t kFlagSlots = 128;
 struct FlagScratch {
     struct alignas(128) Line { unsigned long long word; } slot[kFlagSlots], top, state;
 };
-constexpr unsigned long long kStateBad = 1ull, kStateCleared = 2ull;
+struct FlagWords {
+    unsigned long long *state;
+    int32_t *flag;
+    __device__ __forceinline__ unsigned long long read() const { return __hip_atomic_load(state, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ unsigned long long exchange(unsigned long long x) const { return __hip_atomic_exchange(state, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ bool replace(unsigned long long &cur, unsigned long long x) const
+    {
+        return __hip_atomic_compare_exchange_strong(state, &cur, x, __ATOMIC_ACQ_REL, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ void raise() const { __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
 
 template <int BLOCK>
 struct FlagCount {
@@ -372,29 +383,16 @@ struct FlagCount {
     {
         const bool any = __builtin_amdgcn_ballot_w64(bad) != 0ull;
         if (counting_lane()) {
-            const unsigned long long mine_bad = ((unsigned long long)tag() << 2) | kStateBad;
-            const unsigned long long cleared = ((unsigned long long)tag() << 2) | kStateCleared;
             if (launch_last) {
-                unsigned long long mark = cleared;
-                asm volatile("" : "+v"(mark) : "v"(flag_before));     // not before the flag's exchange has returned
-                const unsigned long long sprev = __hip_atomic_exchange(&fs->state.word, mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (sprev == mine_bad) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uint32_t mine = tag();
+                asm volatile("" : "+v"(mine) : "v"(flag_before));     // not before the flag's exchange has returned
+                flag_cleared(FlagWords{&fs->state.word, flag}, mine);
             }
-            if (any) {
-                unsigned long long cur = __hip_atomic_load(&fs->state.word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-                while (true) {
-                    if (cur == cleared) {                 // the flag was cleared before: this store comes after the 0
-                        __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        break;
-                    }
-                    if (cur == mine_bad) break;           // another wave has reported for this launch already
-                    if (__hip_atomic_compare_exchange_strong(&fs->state.word, &cur, mine_bad, __ATOMIC_ACQ_REL, __ATOMIC_ACQUIRE,
-                                                             __HIP_MEMORY_SCOPE_AGENT))
-                        break;                            // the last arrival's exchange will return this report
-                }
-            }
+            if (any) report(fs, flag);
         }
     }
+    // What a wave finds later than that, by its counting lane.
+    __device__ __forceinline__ void report(FlagScratch *fs, int32_t *flag) const { flag_report(FlagWords{&fs->state.word, flag}, tag()); }
     // Everything behind the arrival at once, for kernels that do not place the stages themselves.
     __device__ __forceinline__ void settle(bool bad, FlagScratch *fs, int32_t *flag)
     {
@@ -1159,7 +1157,8 @@ struct LambPhase1Op {
 //     the words are there.  All of them have been issued by then; nobody waits for a workgroup that has not run.
 //   * The counts only grow.  Every launch adds a power of two to each, because the group's first chunk adds for those that are
 //     missing, and who gets to a multiple of it is the last one.  Nothing is reset, and calls that overlap on one plan, which the
-//     interface forbids, leave the counts as they should be (the bound ends a look for words that another launch has overwritten).
+//     interface forbids, leave the counts as they should be.  The bound ends a look for words that another launch has overwritten:
+//     the sums are then incomplete, and the wave reports an overflow, through the state word, since the flag may not be cleared yet.
 constexpr int kNormBlock = 1024;         // lanes in whose order a tensor's chunks are added up (see tensor_sums)
 constexpr uint32_t kNormGroups = kNormBlock / 64;
 constexpr int kTallyBlock = 128;         // threads of the workgroups that do this
@@ -1210,8 +1209,8 @@ __device__ __forceinline__ bool tally_chunk(const LambTally &ty, const Where &wh
     return (((uint32_t)__builtin_amdgcn_readfirstlane((int)was) + add) & (most - 1u)) == 0u;
 }
 
-// ... and then this, for all of the group.
-__device__ __forceinline__ void tally_group(const LambTally &ty, const Where &wh, uint32_t tag, int32_t *flag)
+// ... and then this, for all of the group.  False (for the whole wave): words were lost.
+__device__ __forceinline__ bool tally_group(const LambTally &ty, const Where &wh, uint32_t tag)
 {
     const uint32_t lane = threadIdx.x & 63u, n = wh.t->num_chunks, g = wh.index / 64u % kNormGroups;
     const TaggedSums *all = ty.chunk + (wh.slot - wh.index);
@@ -1222,10 +1221,8 @@ __device__ __forceinline__ void tally_group(const LambTally &ty, const Where &wh
         while (!(c + kNormBlock < n ? tally_look<4>(all, c + lane, n, tag, a, b) : tally_look<1>(all, c + lane, n, tag, a, b)))
             if ((lost = ++looks > kMeetingBound)) break;
     const double tw = wave_sum((a[0] + a[1]) + (a[2] + a[3])), tu = wave_sum((b[0] + b[1]) + (b[2] + b[3]));
-    if (lane == 0u) {
-        (ty.group != nullptr ? ty.group[wh.t->first_group + g] : ty.sums[wh.tensor]) = LambTally::Sums{tw, tu};
-        if (lost) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (lane == 0u) (ty.group != nullptr ? ty.group[wh.t->first_group + g] : ty.sums[wh.tensor]) = LambTally::Sums{tw, tu};
+    return !lost;
 }
 
 // The sums of a tensor of n chunks from those of its groups, for the whole wave.
@@ -1279,7 +1276,7 @@ __device__ __forceinline__ void sweep_and_tally(Op &op, const Where &wh, const L
     }
     __builtin_amdgcn_sched_barrier(0);
     fc.finish(op.bad, fs, flag);
-    if (last) tally_group(ty, wh, tag, flag);
+    if (last && !tally_group(ty, wh, tag) && fc.counting_lane()) fc.report(fs, flag);
 }
 
 template <class Grad, bool RAISE, int BLOCK>
