@@ -126,7 +126,7 @@ class Timer:
 
 
 # By the template argument of the first kernel.
-POLICIES = (("8Resident", "plain loads, write-through stores (cache-resident shard)"), ("12WriteThrough", "non-temporal loads, write-through stores"),
+POLICIES = (("12WriteThroughELb1E", "non-temporal loads but for the slices, write-through stores"), ("8Resident", "plain loads, write-through stores (cache-resident shard)"), ("12WriteThrough", "non-temporal loads, write-through stores"),
             ("11WeightsKept", "non-temporal loads but for the weights in the first sweep, write-through stores"))
 
 

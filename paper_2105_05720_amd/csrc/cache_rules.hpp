@@ -48,12 +48,13 @@ struct CachePolicies {
     int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step (what cc_plan_layout reports) and the unfused pipelines: reduce, Adam from the sum, cast
     int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep, and both behind the unfused pipeline's reduce
     int32_t lamb = CC_CACHE_STREAMING;          // fused LAMB's second sweep
+    bool slices_plain = false;                  // fused Adam reads the gradient slices with plain loads whatever `adam` says of the state
 };
 // one_sweep: the chunks are one sweep of a workgroup (1024 elements).  LAMB's pair holds for those only: with 2048-element
 // chunks, which a caller has to ask for, both sweeps keep the same.
 inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool grad_f32, bool one_sweep)
 {
-    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked};
+    if (asked != CC_CACHE_AUTO) return CachePolicies{asked, asked, asked, false};
     const uint64_t footprint = step_footprint(numel, R, grad_f32);
     CachePolicies c;
     c.adam = auto_cache_policy(footprint, numel * kAdamStoreBytes);
@@ -84,13 +85,32 @@ inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool g
 //        R = 1,  140 MB            41.4 / 35.5         36.0 / 33.8        55.1 / 44.7            43.0 / 39.0
 // (LAMB with all loads of the first sweep non-temporal: 24.4 at 84 MB, 34.3 at 126.  Second sweep with plain / non-temporal loads, three in
 // turn: 22.4 / 23.0 at 24 MB of w, m' and v', 27.1 / 27.4 at 30, 31.1 / 31.3 at 36, 41.5 / 40.7 at 50, R = 1 38.2 / 35.5 at 60.)
+// Adam on few slices lost by that where one shard is stepped by itself, whose arrays are on chip from step to step: the loads
+// of the state find them there either way, those of the slices, which nobody writes in between, only if they are plain.  So up to 4 bytes of
+// slices per element are read plainly up to kSlicesPlainMaxBytes.  us, plain loads / all non-temporal / this, in the first four situations and
+// with the slices written just before (behind a copy):
+//                              three in turn            one by itself         behind a fill         behind a copy         slices written
+//   one tensor, R = 1,  86 MB  16.7 / 16.5 / 14.3       14.4 / 15.7 / 13.6    28.2 / 19.4 / 20.0    21.2 / 19.0 / 18.7    20.0 / 18.4 / 18.3
+//                      117 MB  23.1 / 22.2 / 19.0       18.6 / 21.0 / 18.1    36.5 / 24.7 / 25.5    26.3 / 23.2 / 22.9    24.4 / 22.6 / 22.2
+//                      147 MB  28.4 / 25.9 / 23.6       22.5 / 26.0 / 22.4    42.8 / 29.2 / 30.8    30.9 / 26.6 / 27.1    28.8 / 26.2 / 26.3
+//             R = 2,  117 MB   22.9 / 21.5 / 19.1       18.9 / 20.3 / 17.7    36.6 / 25.1 / 26.8    27.1 / 22.7 / 23.4    24.3 / 22.7 / 22.4
+//             fp32 R = 1, 117  23.3 / 20.7 / 19.4       18.6 / 19.7 / 18.1    37.4 / 24.7 / 27.4    27.5 / 22.7 / 23.2    23.5 / 22.4 / 22.2
+//   list, R = 1,      136 MB   28.8 / 25.8 / 24.5       22.4 / 25.9 / 21.8    43.8 / 30.5 / 32.0    30.3 / 26.6 / 27.1    28.3 / 26.0 / 26.0
+//         R = 2,      136 MB   29.4 / 24.5 / 24.1       22.2 / 24.6 / 21.9    44.9 / 30.5 / 34.0    31.6 / 26.8 / 27.5    27.3 / 26.2 / 26.4
+// Beyond that line, and with more slices, what the cold ones cost is more: one tensor, R = 1, 204 MB 38.1 / 33.5 / 35.1, 30.7 / 35.2 / 30.3, 59.1 / 38.4 / 40.2,
+// 40.3 / 34.8 / 34.8; R = 2, 204 MB 38.5 / 32.9 / 35.4, 31.1 / 34.2 / 30.2, 60.0 / 38.2 / 42.6, 41.8 / 34.5 / 34.5; R = 4, 117 MB 23.4 / 20.3 / 19.7, 19.0 / 19.3 /
+// 18.4, 39.0 / 24.5 / 29.6, 28.5 / 22.7 / 24.0.  There one shard by itself stays the slower one (R = 1 up to 16 %, R = 2 10 %, R = 4 6 %, R = 8 4 %), and every other
+// situation the faster.
 constexpr uint64_t kPlainLoadsMaxBytes = 80ull << 20, kL2Bytes = 32ull << 20, kLambReadAgainBytes = 12;
+constexpr uint64_t kSlicesPlainMaxBytes = 144ull << 20;
+constexpr bool slices_plain_for(int R, bool grad_f32) { return (grad_f32 ? 4 : 2) * R <= 4; }
 constexpr int32_t kWeightsKept = 16;       // beside the cc_cache_policy values: see WeightsKept in kernels.hip.h
 inline CachePolicies fused_policies(CachePolicies c, int32_t asked, uint64_t numel, int R, bool grad_f32, bool one_sweep)
 {
     const uint64_t footprint = step_footprint(numel, R, grad_f32);
     if (asked != CC_CACHE_AUTO || !one_sweep || footprint < kPlainLoadsMaxBytes || footprint >= kResidentMaxBytes) return c;
     c.adam = CC_CACHE_WRITE_THROUGH;
+    c.slices_plain = slices_plain_for(R, grad_f32) && footprint < kSlicesPlainMaxBytes;
     c.lamb1 = kWeightsKept;
     if (numel * kLambReadAgainBytes >= kL2Bytes) c.lamb = CC_CACHE_WRITE_THROUGH;
     return c;

@@ -746,7 +746,7 @@ int cc_fused_adam_step_static(const cc_tensor *t, int32_t R, const cc_hparams *h
     const int mode = (hp->skip_mode == 1 ? kModeGuard : 0) | (hp->adam_mode == 0 ? kModeL2 : 0);
     CachePolicies mem = cache_policies(CC_CACHE_AUTO, t->numel, R, false, true);                             // the plans' AUTO rule
     mem = fused_policies(mem, CC_CACHE_AUTO, t->numel, R, false, true);
-    launch_fused_adam_flat_f16(d, R, grid, mem.adam, s, fs, flag, st, mode);
+    launch_fused_adam_flat_f16(d, R, grid, mem, s, fs, flag, st, mode);
     return launched("fused_adam_flat_kernel");
 }
 

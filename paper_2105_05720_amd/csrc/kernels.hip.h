@@ -792,10 +792,9 @@ struct GradSumHalf {
 // Adam: reduce (or read the reduced sum) + moments + weight update (+ fp16 emission when fused).
 // One pass, 2R + 26 bytes per parameter when fused.
 // ---------------------------------------------------------------------------------------------------
-template <class Grad, int MODE, bool EMIT16>
+template <class Grad, int MODE, bool EMIT16, class Mem = typename Grad::Mem>
 struct AdamOp {
     static constexpr uint32_t kPack = kStatePack;
-    typedef typename Grad::Mem Mem;
     Grad grad;
     gcbytes w_in, m_in, v_in;
     gbytes w_out, m_out, v_out, w16;
@@ -860,7 +859,10 @@ struct AdamOp {
     template <int BLOCK> __device__ __forceinline__ void end_chunk(uint32_t) {}
 };
 
-template <int R, int MODE, int BLOCK, bool GF32 = false, int GROUPS = 2, class Mem = Streaming>
+// SLICES_PLAIN: the gradient slices by plain loads, the state as Mem says (see fused_policies).
+template <int R, bool GF32, class Mem, bool SLICES_PLAIN>
+using AdamSlices = GradSlices<R, GF32, typename std::conditional<SLICES_PLAIN, Resident, Mem>::type>;
+template <int R, int MODE, int BLOCK, bool GF32 = false, int GROUPS = 2, class Mem = Streaming, bool SLICES_PLAIN = false>
 __global__ __launch_bounds__(BLOCK) void fused_adam_kernel(const DevTensor *__restrict__ tensors,
                                                            const Chunk *__restrict__ chunks, StepScalars s,
                                                            FlagScratch *__restrict__ fs, int32_t *__restrict__ flag)
@@ -868,7 +870,7 @@ __global__ __launch_bounds__(BLOCK) void fused_adam_kernel(const DevTensor *__re
     FlagCount<BLOCK> fc;
     fc.arrive(fs);
     const Where wh = locate(tensors, chunks, s);
-    AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
+    AdamOp<AdamSlices<R, GF32, Mem, SLICES_PLAIN>, MODE, true, Mem> op;
     op.init(wh.t, wh.base, s);
     sweep_and_publish<BLOCK, GROUPS>(op, wh.len, fc, fs, flag);
 }
@@ -877,7 +879,7 @@ __global__ __launch_bounds__(BLOCK) void fused_adam_kernel(const DevTensor *__re
 // no table: workgroup b takes chunk b, and the descriptor travels in the kernel arguments, so the two dependent
 // scalar loads (table entry, then descriptor) in front of the first vector load fall away.  ~1 us of a launch-bound
 // step.
-template <int R, int MODE, int BLOCK, bool GF32 = false, int GROUPS = 2, class Mem = Streaming>
+template <int R, int MODE, int BLOCK, bool GF32 = false, int GROUPS = 2, class Mem = Streaming, bool SLICES_PLAIN = false>
 __global__ __launch_bounds__(BLOCK) void fused_adam_flat_kernel(DevTensor t, StepScalars s, FlagScratch *__restrict__ fs,
                                                                 int32_t *__restrict__ flag)
 {
@@ -885,7 +887,7 @@ __global__ __launch_bounds__(BLOCK) void fused_adam_flat_kernel(DevTensor t, Ste
     fc.arrive(fs);
     const uint64_t base = (uint64_t)blockIdx.x * s.chunk_elems;
     const uint64_t rem = t.numel - base;
-    AdamOp<GradSlices<R, GF32, Mem>, MODE, true> op;
+    AdamOp<AdamSlices<R, GF32, Mem, SLICES_PLAIN>, MODE, true, Mem> op;
     op.init(&t, base, s);
     sweep_and_publish<BLOCK, GROUPS>(op, rem < s.chunk_elems ? (uint32_t)rem : s.chunk_elems, fc, fs, flag);
 }

@@ -11,11 +11,21 @@ namespace {
 
 // One tensor that does not fit the Infinity Cache, in single-wave pieces (see kFlatPiece).
 template <int MODE, bool GF32, class MEM>
-void launch_flat_pieces(const DevTensor &t, int R, StepScalars s, FlagScratch *fs, int32_t *flag, hipStream_t st)
+void launch_flat_pieces(const DevTensor &t, int R, StepScalars s, FlagScratch *fs, int32_t *flag, hipStream_t st, bool slices_plain = false)
 {
     const dim3 grid((unsigned)((t.numel + kFlatPiece - 1) / kFlatPiece)), block(kFlatBlock);
     const unsigned lds = flat_lds(t.numel, R, GF32, std::is_same<MEM, Streaming>::value);
     s.chunk_elems = kFlatPiece;
+    if constexpr (std::is_same<MEM, WriteThrough>::value) {
+        if (slices_plain) {
+            switch (R) {
+#define CASE(r) case r: if constexpr (slices_plain_for(r, GF32)) hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, kFlatBlock, GF32, 1, MEM, true>), grid, block, lds, st, t, s, fs, flag); break;
+                FOR_EACH_R(CASE)
+#undef CASE
+            }
+            return;
+        }
+    }
     switch (R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_flat_kernel<r, MODE, kFlatBlock, GF32, 1, MEM>), grid, block, lds, st, t, s, fs, flag); break;
         FOR_EACH_R(CASE)
@@ -81,7 +91,7 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
     if (p->single >= 0) {                  // one tensor: no table, descriptor in the kernel arguments
         const DevTensor &t = L.host_tensors[(size_t)p->single];
         if constexpr (!std::is_same<MEM, Resident>::value)
-            if (p->flat_pieces && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st);
+            if (p->flat_pieces && t.numel <= kFlatMaxElems) return launch_flat_pieces<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st, p->fused.slices_plain);
         if constexpr (BLK == kSmallBlock && !std::is_same<MEM, WriteThrough>::value)
             if (L.chunk_elems == kSmallChunkElems && launch_packed<MODE, GF32, MEM>(t, p->R, s, p->d_flag_scratch, flag, st)) return;
         switch (p->R) {
@@ -92,6 +102,16 @@ void launch_fused_adam_r(const cc_plan *p, const StepScalars &s, int32_t *flag, 
         return;
     }
     const unsigned lds = p->spread_adam ? list_lds(p->numel, p->R, GF32, std::is_same<MEM, Streaming>::value) : 0u;
+    if constexpr (std::is_same<MEM, WriteThrough>::value) {
+        if (p->fused.slices_plain) {
+            switch (p->R) {
+#define CASE(r) case r: if constexpr (slices_plain_for(r, GF32)) hipLaunchKernelGGL((fused_adam_kernel<r, MODE, BLK, GF32, 2, MEM, true>), grid, block, lds, st, L.table_tensors(), L.table_chunks(), s, p->d_flag_scratch, flag); break;
+                FOR_EACH_R(CASE)
+#undef CASE
+            }
+            return;
+        }
+    }
     switch (p->R) {
 #define CASE(r) case r: hipLaunchKernelGGL((fused_adam_kernel<r, MODE, BLK, GF32, 2, MEM>), grid, block, lds, st, L.table_tensors(), L.table_chunks(), s, p->d_flag_scratch, flag); break;
         FOR_EACH_R(CASE)

@@ -178,7 +178,7 @@ void launch_adam_from_sum(const cc_plan *p, const StepScalars &s, const int32_t 
 int cast_launch(cc_plan *p, const StepScalars &s, const int32_t *flag, hipStream_t st, int guarded);
 int clear_flag(int32_t *flag, hipStream_t st);
 // One fp16-slice tensor, no plan: one workgroup of kSmallBlock per kSmallChunkElems elements, counted on `fs`.
-void launch_fused_adam_flat_f16(const DevTensor &t, int R, unsigned grid, int32_t mem, const StepScalars &s, FlagScratch *fs,
+void launch_fused_adam_flat_f16(const DevTensor &t, int R, unsigned grid, const CachePolicies &mem, const StepScalars &s, FlagScratch *fs,
                                 int32_t *flag, hipStream_t st, int mode);
 
 }  // namespace ccf

@@ -16,12 +16,13 @@ MAIN = r"""
 #include <cstdlib>
 #include "cache_rules.hpp"
 
-int main(int, char **argv)
+int main(int argc, char **argv)
 {
     const int asked = atoi(argv[1]), R = atoi(argv[3]);
     const uint64_t numel = strtoull(argv[2], nullptr, 10);
     const bool f32 = atoi(argv[4]) != 0, one_sweep = atoi(argv[5]) != 0;
     const ccf::CachePolicies c = ccf::fused_policies(ccf::cache_policies(asked, numel, R, f32, one_sweep), asked, numel, R, f32, one_sweep);
+    if (argc > 6) return printf("%d\n", c.slices_plain) < 0;
     return printf("%d %d %d\n", c.adam, c.lamb1, c.lamb) < 0;
 }
 """
@@ -34,8 +35,8 @@ def policies(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
                            "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
 
-    def ask(asked, numel, R, f32, one_sweep=True):
-        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, one_sweep)], capture_output=True, text=True, timeout=60, check=True)
+    def ask(asked, numel, R, f32, one_sweep=True, more=()):
+        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, one_sweep, *more)], capture_output=True, text=True, timeout=60, check=True)
         return tuple(int(x) for x in out.stdout.split())
     return ask
 
@@ -53,3 +54,12 @@ def test_from_80_to_200_mib(policies, R, f32):
     assert policies(AUTO, end - 1, R, f32, one_sweep=False) == (RESIDENT,) * 3
     for asked in (cc.CC_CACHE_STREAMING, RESIDENT, THROUGH):
         assert policies(asked, end - 1, R, f32) == (asked,) * 3
+
+
+@pytest.mark.parametrize("R,f32,kept", [(1, False, True), (2, False, True), (3, False, False), (8, False, False), (1, True, True), (2, True, False)])
+def test_few_slices_are_read_plainly_up_to_144_mib(policies, R, f32, kept):
+    per = (4 if f32 else 2) * R + 26
+    at, end = -(-80 * MIB // per), -(-144 * MIB // per)
+    ask = lambda asked, n, **kw: bool(policies(asked, n, R, f32, more=(1,), **kw)[0])
+    assert [ask(AUTO, n) for n in (at - 1, at, end - 1, end)] == [False, kept, kept, False]
+    assert not ask(AUTO, at, one_sweep=False) and not any(ask(p, at) for p in (cc.CC_CACHE_STREAMING, RESIDENT, THROUGH))

@@ -65,3 +65,34 @@ def test_the_static_step_takes_the_same_line():
         of_plan = launches(lambda: shard.run(cc.cc_fused_adam_step, cc.Hyper(step=1)))
         assert launches(lambda: cc.cc_fused_adam_step_static(t, 8, cc.Hyper(step=1), shard.flag)) == of_plan
         shard.destroy()
+
+
+@pytest.mark.parametrize("numels,R,dtype,kept", [([3000001], 1, torch.float16, True), ([(144 << 20) // 30 - 7], 2, torch.float16, True), ([(144 << 20) // 30 + 9], 2, torch.float16, False),
+                                                 ([7, 0, 1500003, 1025, 1600000], 1, torch.float16, True), ([2900000, 3], 1, torch.float32, True),
+                                                 ([255, 2000001, 2900000], 2, torch.float16, True), ([255, 2900001, 2900000], 2, torch.float16, False)],
+                         ids=lambda x: "x".join(map(str, x[:3])) if isinstance(x, list) else str(x))
+@pytest.mark.parametrize("mode", [{}, {"adam_mode": 0, "skip_mode": 1}], ids=["default", "l2 guard"])
+def test_few_slices_are_read_plainly(numels, R, dtype, kept, mode):
+    """The slices by plain loads up to 144 MiB, with the bits of the policy that reads everything that way; slices that a step before has seen are not kept."""
+    results = []
+    for policy in (cc.CC_CACHE_AUTO, cc.CC_CACHE_RESIDENT):
+        shard = Shard(numels, [0.01 * (k % 2) for k in range(len(numels))], R, align_elems=8, grad_dtype=dtype, cache_policy=policy, unfused=False)
+        step = lambda t: shard.run(cc.cc_fused_adam_step, cc.Hyper(step=t, **mode))
+        assert ("12WriteThroughELb1E" in launches(lambda: step(1))[0].symbol) == (kept and policy == cc.CC_CACHE_AUTO)
+        seeded_state(shard, 3)
+        for t in (1, 2):
+            seeded_grads(shard, 30 + t, 1e-2)
+            step(t)
+            assert int(shard.flag.item()) == 0
+            shard.commit()
+        shard.grad_of(R - 1, len(numels) - 1)[-1] = float("inf")
+        step(3)
+        results.append(_bits(shard) + [shard.flag.clone()])
+        assert int(shard.flag.item()) == 1
+        if len(numels) == 1 and dtype == torch.float16:
+            shard.flag.zero_()
+            cc.cc_fused_adam_step_static(cc.Tensor(numel=numels[0], w_in=shard.w[0], m_in=shard.m[0], v_in=shard.v[0], w_out=shard.w[1], m_out=shard.m[1], v_out=shard.v[1],
+                                                   w16_out=shard.w16[1], grad=shard.grads, weight_decay=0.0), R, cc.Hyper(step=3, **mode), shard.flag)
+            results[-1] += _bits(shard) + [shard.flag.clone()]
+        shard.destroy()
+    assert all(torch.equal(x, y) for x, y in zip(*results))
