@@ -186,7 +186,7 @@ int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_thr
  * 8-12 % faster at 2^23 and 2^24); else STREAMING.  That is the Adam step's policy, which cc_plan_layout reports; LAMB stores
  * 8 bytes per element in its first sweep and goes by those, and from 288 MiB on still writes that sweep through; the unfused LAMB
  * pipeline writes both its sweeps through from 200 MiB on.
- * cc_plan_autotune tries all three, and AUTO for LAMB.
+ * cc_plan_autotune tries all three, AUTO for LAMB, and AUTO with everything else left to the library.
  */
 typedef enum cc_cache_policy { CC_CACHE_AUTO = 0, CC_CACHE_STREAMING = 1, CC_CACHE_RESIDENT = 2, CC_CACHE_WRITE_THROUGH = 3 } cc_cache_policy;
 int cc_plan_set_cache_policy(cc_plan *plan, int32_t policy);
@@ -196,8 +196,8 @@ int cc_plan_set_cache_policy(cc_plan *plan, int32_t policy);
  * rule, as the paper's autotuner keeps the fastest schedule per workload (Section 3.5): runs the plan's own fused
  * step (optimizer 0 = Adam, 1 = LAMB) a few times under each candidate (one workgroup per chunk for every chunk size
  * the plan was prepared for, with every cache policy that exists for it, and for LAMB with AUTO as well; ordered with
- * compute units / 2, x 1 and x 2 workgroups on the 4096-element chunks), timed with events on `hip_stream`, and leaves
- * the plan set to the fastest.  The trial steps are ordinary steps on the caller's buffers: they write the out buffers and
+ * compute units / 2, x 1 and x 2 workgroups on the 4096-element chunks; and what runs where nothing is chosen), timed with events on
+ * `hip_stream`, and leaves the plan set to the fastest.  The trial steps are ordinary steps on the caller's buffers: they write the out buffers and
  * the flag, never the in buffers, so the plan must be out of place (CC_ERR_ALIAS otherwise) and the caller must not have
  * adopted the out buffers' contents.  Synchronises the stream.  best_ms / per_chunk_ms (each may be NULL) receive the time per step
  * of the schedule kept and of one workgroup per chunk.

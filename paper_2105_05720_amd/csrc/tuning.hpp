@@ -24,7 +24,8 @@ struct TuningLayout {
 
 // One workgroup per chunk under the current chunk size first, non-temporal: its time is what per_chunk_ms reports.  Small
 // chunks are tried under every cache policy, and for LAMB under AUTO as well, which may give its two sweeps different ones
-// (cache_policies), as no policy that is asked for does: without it a tuned plan could be slower than an untuned one.
+// (cache_policies), as no policy that is asked for does.  A plan for which nothing is chosen comes last: some of what it runs goes by
+// that (single-wave pieces of large shards, few slices read plainly up to 144 MiB of buffers).  Without these two a tuned plan could be slower than an untuned one.
 inline std::vector<Candidate> tuning_candidates(const std::vector<TuningLayout> &layouts, int32_t current, int32_t optimizer, uint32_t cus)
 {
     std::vector<Candidate> c;
@@ -42,6 +43,7 @@ inline std::vector<Candidate> tuning_candidates(const std::vector<TuningLayout> 
         if (l.orders)
             for (uint32_t w : {cus, cus > 1 ? cus / 2 : 1u, cus * 2}) c.push_back(Candidate{l.chunk_elems, CC_SCHEDULE_ORDERED, w, CC_CACHE_STREAMING});
     }
+    c.push_back(Candidate{0, CC_SCHEDULE_AUTO, 0u, CC_CACHE_AUTO});
     return c;
 }
 

@@ -15,9 +15,17 @@ MAIN = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "cache_rules.hpp"
+#include "tuning.hpp"
 
 int main(int argc, char **argv)
 {
+    if (argc == 2) {                     // how many candidates choose nothing at all
+        const std::vector<ccf::TuningLayout> layouts = {{1024, 5, true, false}, {4096, 2, false, true}, {16384, 1, false, false}};
+        int n = 0;
+        for (const auto &c : ccf::tuning_candidates(layouts, 4096, atoi(argv[1]), 256))
+            n += c.chunk_elems == 0 && c.schedule == CC_SCHEDULE_AUTO && c.workgroups == 0 && c.cache == CC_CACHE_AUTO;
+        return printf("%d\n", n) < 0;
+    }
     const int asked = atoi(argv[1]), R = atoi(argv[3]);
     const uint64_t numel = strtoull(argv[2], nullptr, 10);
     const bool f32 = atoi(argv[4]) != 0, one_sweep = atoi(argv[5]) != 0;
@@ -35,8 +43,8 @@ def policies(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
                            "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
 
-    def ask(asked, numel, R, f32, one_sweep=True, more=()):
-        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in (asked, numel, R, f32, one_sweep, *more)], capture_output=True, text=True, timeout=60, check=True)
+    def ask(asked, numel=None, R=None, f32=None, one_sweep=True, more=()):
+        out = subprocess.run([str(d / "rules")] + [str(int(x)) for x in ((asked,) if numel is None else (asked, numel, R, f32, one_sweep, *more))], capture_output=True, text=True, timeout=60, check=True)
         return tuple(int(x) for x in out.stdout.split())
     return ask
 
@@ -63,3 +71,9 @@ def test_few_slices_are_read_plainly_up_to_144_mib(policies, R, f32, kept):
     ask = lambda asked, n, **kw: bool(policies(asked, n, R, f32, more=(1,), **kw)[0])
     assert [ask(AUTO, n) for n in (at - 1, at, end - 1, end)] == [False, kept, kept, False]
     assert not ask(AUTO, at, one_sweep=False) and not any(ask(p, at) for p in (cc.CC_CACHE_STREAMING, RESIDENT, THROUGH))
+
+
+@pytest.mark.parametrize("optimizer", [0, 1])
+def test_the_tuner_tries_a_plan_for_which_nothing_is_chosen(policies, optimizer):
+    """No policy that is asked for reads few slices plainly and the state not: of the tuner's candidates only this one does."""
+    assert policies(optimizer) == (1,)
