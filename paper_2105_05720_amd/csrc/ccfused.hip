@@ -151,7 +151,7 @@ void resolve_schedule(cc_plan *p)
     p->list_pieces = nullptr;
     if (p->single < 0 && p->fused.adam == CC_CACHE_STREAMING && (nothing_asked ? p->ordered || p->spread_adam : p->spread_adam))
         for (const Layout &S : p->layouts)
-            if (S.chunk_elems == kSmallChunkElems && list_in_pieces(p->numel, (uint64_t)S.chunks, p->R, p->grad_f32)) p->list_pieces = &S;
+            if (S.chunk_elems == kSmallChunkElems && list_in_pieces(p->numel, (uint64_t)S.chunks, p->R, p->grad_f32, nothing_asked)) p->list_pieces = &S;
 }
 
 void free_layout(Layout &L)

@@ -113,10 +113,12 @@ inline bool lamb_keeps_small_chunks(uint64_t numel) { return numel < kLambSmallC
 constexpr uint64_t kListPiecesMaxElems = 128u << 20, kListPiecesMaxF32Elems = 256u << 20;
 constexpr int kListPiecesMaxF16Slices = 10, kListBeyondMaxF16Slices = 8, kListPiecesMaxF32Slices = 8;
 constexpr bool pieces_take(int R, bool grad_f32) { return R <= (grad_f32 ? kListPiecesMaxF32Slices : kListPiecesMaxF16Slices); }
-inline bool list_in_pieces(uint64_t numel, uint64_t chunks, int R, bool grad_f32)
+// nothing_asked: beyond kSmallShardElems whoever asks for chunks of 1024 elements gets a workgroup for each.
+inline bool list_in_pieces(uint64_t numel, uint64_t chunks, int R, bool grad_f32, bool nothing_asked)
 {
     if (!pieces_take(R, grad_f32) || numel * kAdamStoreBytes < kWriteThroughMaxStoreBytes || chunks * 1024u > numel + numel / 8) return false;
     if (numel < kSmallShardElems) return true;
+    if (!nothing_asked) return false;
     return grad_f32 ? numel < kListPiecesMaxF32Elems : R <= kListBeyondMaxF16Slices && numel < kListPiecesMaxElems;
 }
 

@@ -64,3 +64,22 @@ def test_pieces_give_the_bits_of_chunks(numels, R, dtype, pieces, hyper):
             for a, b in zip(*results):
                 assert torch.equal(a, b)
     shard.destroy()
+
+
+@pytest.mark.parametrize("numels,chunk,policy,pieces", [
+    ([LINE, 5], 1024, cc.CC_CACHE_AUTO, True),
+    ([64 * M - 9, 8], 1024, cc.CC_CACHE_STREAMING, True),
+    ([64 * M, 1027], 1024, cc.CC_CACHE_AUTO, False),                              # chunks of 1024 elements get a workgroup each
+    ([64 * M, 1027], 1024, cc.CC_CACHE_STREAMING, False),
+    ([64 * M, 1027], 0, cc.CC_CACHE_STREAMING, False),                            # the ordered schedule
+])
+def test_what_is_asked_for_beyond_64_mi_elements_runs(numels, chunk, policy, pieces):
+    shard = Shard(numels, [0.01, 0.0], 1, align_elems=8, unfused=False)
+    plan = shard.plans[0]
+    cc.cc_plan_set_chunk_elems(plan, chunk)
+    cc.cc_plan_set_cache_policy(plan, policy)
+    ran = launches(lambda: cc.cc_fused_adam_step(plan, cc.Hyper(step=2), shard.flag))
+    assert [x.kernel for x in ran] == ["fused_adam_piece_kernel" if pieces else "fused_adam_kernel" if chunk else "fused_adam_ordered_kernel"]
+    if chunk and not pieces:
+        assert (ran[0].grid, ran[0].block) == (sum(-(-n // 1024) for n in numels), 128)
+    shard.destroy()

@@ -1,0 +1,42 @@
+"""Which lists' Adam steps run single-wave pieces (csrc/occupancy.hpp), compiled for the host: one element below and at each bound that
+the header states."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+M = 1 << 20
+LINE = -(-(288 << 20) // 14)                    # elements from which a step stores too much to write through
+
+MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "occupancy.hpp"
+
+int main(int, char **argv)
+{
+    const auto n = [&](int k) { return strtoull(argv[k], nullptr, 10); };
+    printf("%d\n", ccf::list_in_pieces(n(1), n(2), (int)n(3), n(4) != 0, n(5) != 0));
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(MAIN)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "paper_2105_05720_amd", "csrc"),
+                           "-I", os.path.join(ROOT, "include"), "-o", str(d / "rules"), str(d / "rules.cpp")])
+    return lambda *a: bool(int(subprocess.run([str(d / "rules")] + [str(int(x)) for x in a], capture_output=True, text=True, timeout=60, check=True).stdout))
+
+
+@pytest.mark.parametrize("R,f32,small,beyond", [(1, 0, True, 128 * M), (8, 0, True, 128 * M), (9, 0, True, 0), (10, 0, True, 0), (11, 0, False, 0),
+                                                (1, 1, True, 256 * M), (8, 1, True, 256 * M), (9, 1, False, 0)])
+def test_lists_in_pieces(rule, R, f32, small, beyond):
+    ask = lambda numel, missing=0, nothing_asked=True: rule(numel, -(-(numel + missing) // 1024), R, f32, nothing_asked)
+    assert [ask(LINE - 1), ask(LINE), ask(64 * M - 1), ask(64 * M - 1, nothing_asked=False)] == [False, small, small, small]
+    assert [ask(64 * M), ask((beyond or 65 * M) - 1), ask(beyond or 128 * M)] == [bool(beyond), bool(beyond), False]
+    assert not ask(64 * M, nothing_asked=False) and not ask(100 * M, nothing_asked=False)
+    assert [ask(32 * M, 4 * M), ask(32 * M, 4 * M + 1)] == [small, False]           # one chunk in eight short
