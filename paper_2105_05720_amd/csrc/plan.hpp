@@ -20,6 +20,8 @@ constexpr int32_t kSmallChunkElems = 1024;       // one sweep of a 128-thread wo
 constexpr int32_t kLargeChunkElems = 16384;      // four sweeps of a 512-thread workgroup: a quarter of the table and of the launches
 constexpr int32_t kMaxChunkElems = 1 << 24;      // lane offsets inside a chunk are 32-bit byte offsets
 constexpr int kBigBlock = 512, kSmallBlock = 128;
+// What the kernels say of the small chunks themselves (a tally in other workgroups would leave the sums unwritten, without an error).
+static_assert(kTallyBlock == kSmallBlock && kPackedChunk == kSmallChunkElems && kPieceChunk == kSmallChunkElems, "one set of sizes");
 constexpr int64_t kPerChunkDescriptorsMax = 2048; // chunks up to which a small-chunk layout keeps a descriptor per chunk (224 B each)
 constexpr int kOrderedMaxF32Slices = 8;           // fp32 slices: the ordered schedule wins up to 8 (config-2 list: 3.18 against 3.41 ms), at 16 two chunks spill
 constexpr int64_t kOrderedMinChunksPerCu = 8;    // below this many chunks per compute unit a plan keeps one workgroup per chunk

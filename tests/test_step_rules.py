@@ -1,5 +1,5 @@
-"""Which lists' Adam steps run single-wave pieces (csrc/occupancy.hpp), compiled for the host: one element below and at each bound that
-the header states."""
+"""Which lists' Adam steps run single-wave pieces, which LAMB steps keep small chunks (csrc/occupancy.hpp) and where LAMB's sums are added
+up (csrc/meeting.hpp), compiled for the host: one element or chunk below and at each bound that the headers state."""
 import os
 import subprocess
 
@@ -12,11 +12,14 @@ LINE = -(-(288 << 20) // 14)                    # elements from which a step sto
 MAIN = r"""
 #include <cstdio>
 #include <cstdlib>
+#include "meeting.hpp"
 #include "occupancy.hpp"
 
-int main(int, char **argv)
+int main(int argc, char **argv)
 {
     const auto n = [&](int k) { return strtoull(argv[k], nullptr, 10); };
+    if (argc == 2) return printf("%d\n", ccf::lamb_keeps_small_chunks(n(1))) < 0;
+    if (argc == 4) return printf("%d\n", n(1) ? ccf::lamb_one_group_each((int64_t)n(2), (uint32_t)n(3)) : ccf::lamb_tallies((int64_t)n(2), (uint32_t)n(3))) < 0;
     printf("%d\n", ccf::list_in_pieces(n(1), n(2), (int)n(3), n(4) != 0, n(5) != 0));
     return 0;
 }
@@ -40,3 +43,13 @@ def test_lists_in_pieces(rule, R, f32, small, beyond):
     assert [ask(64 * M), ask((beyond or 65 * M) - 1), ask(beyond or 128 * M)] == [bool(beyond), bool(beyond), False]
     assert not ask(64 * M, nothing_asked=False) and not ask(100 * M, nothing_asked=False)
     assert [ask(32 * M, 4 * M), ask(32 * M, 4 * M + 1)] == [small, False]           # one chunk in eight short
+
+
+def test_lamb_keeps_small_chunks(rule):
+    assert [rule(n) for n in (64 * M, 88 * M - 1, 88 * M)] == [True, True, False]
+
+
+def test_where_lamb_adds_up(rule):
+    tallies, one_group = (lambda chunks, most: rule(0, chunks, most)), (lambda chunks, most: rule(1, chunks, most))
+    assert [tallies(*x) for x in ((599, 599), (600, 600), (600, 513), (600, 512), (32768, 32768), (32769, 32769))] == [False, True, True, False, True, False]
+    assert [one_group(*x) for x in ((0, 0), (1, 1), (64, 64), (65, 65), (65, 64), (8192, 64), (8193, 64))] == [False, True, True, False, True, True, False]
