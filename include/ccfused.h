@@ -149,8 +149,8 @@ int cc_plan_destroy(cc_plan *plan);
  *                          order from a counter and keep the next chunk's loads in flight; needs the default
  *                          chunk size of large shards (cc_default_chunk_elems()).
  *   CC_SCHEDULE_AUTO       (default) ordered for large shards, per chunk for small ones.
- * cc_plan_schedule reports what the plan will use (schedule: ORDERED or PER_CHUNK; workgroups per launch, which is the
- * number of chunks for PER_CHUNK, but see cc_plan_layout for the one kernel that launches more).
+ * cc_plan_schedule reports what the size rule, or the caller, has settled (schedule: ORDERED or PER_CHUNK; workgroups per launch, which is
+ * the number of chunks for PER_CHUNK).  The unfused pipelines run just that; the fused steps have exceptions, listed at cc_plan_layout.
  */
 typedef enum cc_schedule { CC_SCHEDULE_AUTO = 0, CC_SCHEDULE_PER_CHUNK = 1, CC_SCHEDULE_ORDERED = 2 } cc_schedule;
 int cc_plan_set_schedule(cc_plan *plan, int32_t schedule, int32_t workgroups);
@@ -159,15 +159,19 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
 /*
  * Chunk size of the step calls: one of the sizes the plan was prepared for (see cc_plan_create), or 0 for the size
  * rule.  Adam results do not depend on it; LAMB's norms are summed chunk by chunk, so they move in the last bits.
- * cc_plan_layout reports what the plan will use (each pointer may be NULL): chunk size, threads per workgroup,
- * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).  (One tensor in chunks below 4096
- * elements whose step's buffers total 200 MiB and more, or 80 MiB with 1024-element chunks, is the exception: there the fused Adam
- * step runs single-wave workgroups of 256 elements, unless the caller has asked for CC_CACHE_RESIDENT.  So it does on one larger tensor for which
- * the caller has chosen nothing, up to 192 Mi elements with up to ten fp16 slices (144 Mi with one) or with fp32 slices, and with
- * four and more of those beyond.  A list of tensors runs such workgroups where its step stores 288 MiB and more, with up to ten fp16 or
- * eight fp32 slices and at most one chunk in eight short, in chunks of 1024 elements below 64 Mi elements, and on larger lists for which
- * the caller has chosen nothing up to 128 Mi elements with up to eight fp16 slices, 256 Mi with fp32 slices.  The fused LAMB step keeps
- * chunks of 1024 elements, one workgroup each, up to 88 Mi elements where the caller has chosen nothing and the ordered schedule would run.)
+ * cc_plan_layout reports what the size rule, or the caller, has settled (each pointer may be NULL): chunk size, threads per workgroup,
+ * cache policy (CC_CACHE_STREAMING, CC_CACHE_RESIDENT or CC_CACHE_WRITE_THROUGH).  The unfused pipelines run that (LAMB's with the policies stated at cc_plan_set_cache_policy); the fused steps run
+ * something else, which neither call reports, in these cases:
+ *   - Adam, between 80 and 200 MiB of step buffers, 1024-element chunks, policy AUTO (reported as RESIDENT): non-temporal loads, see
+ *     cc_plan_set_cache_policy; so do LAMB's sweeps.
+ *   - Adam, one tensor in chunks below 4096 elements: single-wave workgroups of 256 elements from 200 MiB of step buffers on, from 80 MiB with
+ *     1024-element chunks, unless the caller has asked for CC_CACHE_RESIDENT.
+ *   - Adam, one tensor of 64 Mi elements and more for which the caller has chosen nothing (reported as 4096-element chunks, mostly ORDERED): such
+ *     workgroups, up to 192 Mi elements with up to ten fp16 slices (144 Mi with one) or with fp32 slices, and with four and more of those beyond.
+ *   - Adam, a list whose step stores 288 MiB and more, with up to ten fp16 or eight fp32 slices and at most one chunk in eight short: such
+ *     workgroups, in chunks of 1024 elements below 64 Mi elements, and on larger lists for which the caller has chosen nothing (reported as
+ *     4096-element chunks, ORDERED) up to 128 Mi elements with up to eight fp16 slices, 256 Mi with fp32 slices.
+ *   - LAMB, up to 88 Mi elements where the caller has chosen nothing and ORDERED is reported: one workgroup for each chunk of 1024 elements.
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);
@@ -183,7 +187,7 @@ int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_thr
  * sweep), where from 80 MiB on the fused steps on 1024-element chunks read with non-temporal loads, but for what LAMB reads a second time
  * and, up to 144 MiB, up to 4 bytes of slices per element in the Adam step (2-42 % faster than plain loads where the chip's caches hold anything else; one
  * shard stepped over and over with nothing in between is up to 16 % slower beyond 144 MiB with one or two slices, up to 6 % with four and more); else WRITE_THROUGH while the Adam step stores less than 288 MiB (14 bytes per element: up to 20.5 Mi elements,
- * 8-12 % faster at 2^23 and 2^24); else STREAMING.  That is the Adam step's policy, which cc_plan_layout reports; LAMB stores
+ * 8-12 % faster at 2^23 and 2^24); else STREAMING.  LAMB stores
  * 8 bytes per element in its first sweep and goes by those, and from 288 MiB on still writes that sweep through; the unfused LAMB
  * pipeline writes both its sweeps through from 200 MiB on.
  * cc_plan_autotune tries all three, AUTO for LAMB, and AUTO with everything else left to the library.
@@ -200,7 +204,7 @@ int cc_plan_set_cache_policy(cc_plan *plan, int32_t policy);
  * `hip_stream`, and leaves the plan set to the fastest.  The trial steps are ordinary steps on the caller's buffers: they write the out buffers and
  * the flag, never the in buffers, so the plan must be out of place (CC_ERR_ALIAS otherwise) and the caller must not have
  * adopted the out buffers' contents.  Synchronises the stream.  best_ms / per_chunk_ms (each may be NULL) receive the time per step
- * of the schedule kept and of one workgroup per chunk.
+ * of the schedule kept and of CC_SCHEDULE_PER_CHUNK with the current chunk size and CC_CACHE_STREAMING.
  */
 int cc_plan_autotune(cc_plan *plan, const cc_hparams *hp, int32_t optimizer, int32_t *d_overflow_flag,
                      void *hip_stream, float *best_ms, float *per_chunk_ms);

@@ -45,7 +45,7 @@ inline int32_t auto_cache_policy(uint64_t footprint, uint64_t stored)
 
 // What a plan's small-chunk kernels use, by kernel family (cc_cache_policy values).
 struct CachePolicies {
-    int32_t adam = CC_CACHE_STREAMING;          // the fused Adam step (what cc_plan_layout reports) and the unfused pipelines: reduce, Adam from the sum, cast
+    int32_t adam = CC_CACHE_STREAMING;          // what cc_plan_layout reports: the unfused pipelines (reduce, Adam from the sum, cast) and the fused Adam step, but see fused_policies
     int32_t lamb1 = CC_CACHE_STREAMING;         // fused LAMB's first sweep, and both behind the unfused pipeline's reduce
     int32_t lamb = CC_CACHE_STREAMING;          // fused LAMB's second sweep
     bool slices_plain = false;                  // fused Adam reads the gradient slices with plain loads whatever `adam` says of the state

@@ -22,7 +22,8 @@ struct TuningLayout {
     bool orders;        // the ordered schedule exists
 };
 
-// One workgroup per chunk under the current chunk size first, non-temporal: its time is what per_chunk_ms reports.  Small
+// CC_SCHEDULE_PER_CHUNK with the current chunk size first, non-temporal (in single-wave pieces where those are the rule for such chunks): its
+// time is what per_chunk_ms reports.  Small
 // chunks are tried under every cache policy, and for LAMB under AUTO as well, which may give its two sweeps different ones
 // (cache_policies), as no policy that is asked for does.  A plan for which nothing is chosen comes last: some of what it runs goes by
 // that (single-wave pieces of large shards, few slices read plainly up to 144 MiB of buffers).  Without these two a tuned plan could be slower than an untuned one.
