@@ -171,7 +171,8 @@ int cc_plan_schedule(const cc_plan *plan, int32_t *schedule, int32_t *workgroups
  *   - Adam, a list whose step stores 288 MiB and more, with up to ten fp16 or eight fp32 slices and at most one chunk in eight short: such
  *     workgroups, in chunks of 1024 elements below 64 Mi elements, and on larger lists for which the caller has chosen nothing (reported as
  *     4096-element chunks, ORDERED) up to 128 Mi elements with up to eight fp16 slices, 256 Mi with fp32 slices.
- *   - LAMB, up to 88 Mi elements where the caller has chosen nothing and ORDERED is reported: one workgroup for each chunk of 1024 elements.
+ *   - LAMB, where the caller has chosen nothing and ORDERED is reported: one workgroup for each chunk of 1024 elements, with up to 4 bytes of
+ *     slices per element up to 88 Mi elements (one tensor 72 Mi), and on a list with up to 14 bytes up to 80 Mi.
  */
 int cc_plan_set_chunk_elems(cc_plan *plan, int32_t chunk_elems);
 int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_threads, int32_t *cache_policy);

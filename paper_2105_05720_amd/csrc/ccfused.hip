@@ -138,7 +138,7 @@ void resolve_schedule(cc_plan *p)
     p->lamb_active = p->active;
     p->lamb_ordered = p->ordered;
     p->lamb_spread = p->spread;
-    if (nothing_asked && p->ordered && lamb_keeps_small_chunks(p->numel))
+    if (nothing_asked && p->ordered && lamb_keeps_small_chunks(p->numel, p->R, p->grad_f32, p->single >= 0))
         for (size_t i = 0; i < p->layouts.size(); ++i)
             if (p->layouts[i].chunk_elems == kSmallChunkElems) {
                 const CachePolicies c = cache_policies(CC_CACHE_AUTO, p->numel, p->R, p->grad_f32, true);

@@ -88,13 +88,26 @@ inline bool flat_beyond_small(uint64_t numel, int R, bool grad_f32)
 
 // The fused LAMB step keeps its chunks of 1024 elements, one workgroup each, somewhat beyond: its first sweep gives the second m' and v' through
 // the Infinity Cache (see cache_policies), which the ordered schedule's non-temporal stores do not, and the less of them fits the less
-// that is worth.  If nothing was asked; us, ordered / this, three shards in turn, then one by itself:
-//   BERT-Large list 67 M, R = 2 476 / 428, 470 / 437; R = 8 605 / 567, 601 / 580; R = 16 794 / 773, 792 / 769; fp32 R = 8 794 / 779, 802 / 739; 84 M, R = 1 562 / 519,
-//   560 / 519; R = 4 638 / 602, 626 / 609.5; R = 8 742 / 724, 734 / 728; fp32 R = 2 637 / 608, 639 / 618; 8.3B list 74 M, R = 2 519 / 484, 515 / 487; R = 8
-//   658 / 636, 666 / 642; one tensor 70 M, R = 1 471 / 437, 470 / 451; R = 8 621 / 603, 615.5 / 614; 84 M, R = 4 631 / 620, 633 / 624; but 100 M, R = 2 686.5 / 686, 688 /
-//   689.5; R = 8 873.5 / 883, 876.5 / 897; GPT-2 list 97 M, R = 8 855 / 847, 859 / 862; BERT-Large list 112 M, R = 8 971.5 / 966, 990 / 997.
-constexpr uint64_t kLambSmallChunksMaxElems = 88u << 20;
-inline bool lamb_keeps_small_chunks(uint64_t numel) { return numel < kLambSmallChunksMaxElems; }
+// that is worth.  More slices leave less room for them, and what a copy or a backward pass has left there takes its share.  If nothing was
+// asked; us, ordered / this: one shard by itself, behind a 2 GiB copy, with the slices written just before, three shards in turn:
+//   list, R = 1      67 M 454.9 / 414.3, 467.3 / 434.4, 462.5 / 427.7, 458.4 / 414.1   92 M 609.6 / 583.2, 621.9 / 603.0, 617.0 / 597.1, 616.3 / 580.2
+//         R = 2      67 M 475.6 / 442.5, 487.1 / 462.5, 485.9 / 458.3, 474.9 / 437.1   92 M 632.7 / 614.2, 645.3 / 631.4, 645.7 / 634.3, 638.6 / 609.3
+//         R = 4      74 M 570.7 / 537.3, 576.9 / 561.8, 575.4 / 558.9, 562.1 / 524.0   84 M 633.7 / 612.0, 642.4 / 634.2, 642.5 / 631.2, 634.5 / 609.8
+//                    but 87 M 642.6 / 631.5, 652.9 / 662.1, 649.8 / 651.2, 643.4 / 622.8
+//         R = 7      74 M 635.7 / 612.9, 645.2 / 635.5, 644.7 / 643.6, 632.1 / 601.4   84 M 720.0 / 698.1, 729.2 / 726.9, 728.3 / 727.2, 717.2 / 692.6
+//         R = 8, 16  67 M 599.9 / 580.9, 609.8 / 613.7, 604.4 / 608.9, 600.9 / 575.7   67 M 787.7 / 782.0, 783.3 / 817.1, 778.0 / 820.0, 774.7 / 774.5
+//         fp32 R = 3 74 M 624.5 / 591.2, 631.9 / 611.8, 632.3 / 628.4, 620.8 / 583.8; R = 4 74 M 665.7 / 637.7, 668.2 / 669.0, 663.2 / 681.6, 662.5 / 631.4
+//   tensor, R = 1    75 M 506.2 / 483.8, 512.8 / 507.8, 509.0 / 491.3, 503.9 / 480.1   83 M 557.5 / 547.1, 564.1 / 568.8, 558.7 / 556.6, 558.2 / 547.5
+//         R = 2      75 M 521.0 / 507.6, 529.7 / 529.4, 525.4 / 522.3, 520.4 / 503.7   91 M 630.6 / 627.2, 637.4 / 646.8, 636.6 / 640.3, 627.4 / 618.4
+//         R = 4      71 M 538.7 / 529.1, 544.6 / 562.0, 541.0 / 545.6, 540.9 / 522.8
+constexpr uint64_t kLambFewSlicesMaxElems = 88u << 20, kLambSomeSlicesMaxElems = 80u << 20, kLambOneTensorMaxElems = 72u << 20;
+constexpr int kLambFewSliceBytes = 4, kLambSomeSliceBytes = 14;
+inline bool lamb_keeps_small_chunks(uint64_t numel, int R, bool grad_f32, bool one_tensor)
+{
+    const int bytes = (grad_f32 ? 4 : 2) * R;
+    if (bytes <= kLambFewSliceBytes) return numel < (one_tensor ? kLambOneTensorMaxElems : kLambFewSlicesMaxElems);
+    return !one_tensor && bytes <= kLambSomeSliceBytes && numel < kLambSomeSlicesMaxElems;
+}
 
 // A list of tensors goes in such pieces as well, with the same reservations (flat_lds), where its step stores too much to write through:
 // below kSmallShardElems instead of 128-thread workgroups, beyond instead of the ordered schedule, if nothing else was asked.
@@ -108,6 +121,12 @@ inline bool lamb_keeps_small_chunks(uint64_t numel) { return numel < kLambSmallC
 //                     R = 4 925 / 908, 908 / 901, 208 M, R = 8 1385 / 1394, 1367 / 1405, and 336 M, R = 8 2228 / 2248
 //   ... fp32          67 M, R = 2 395 / 371, 380 / 367; 111 M, R = 4 772 / 745, 783 / 740; 168 M, R = 4 1219 / 1142, 1169 / 1121; 195 M, R = 8 1980 / 1875, 1908 / 1821;
 //                     208 M, R = 4 1479 / 1385, 1445 / 1411; 336 M, R = 8 3460 / 3304, 3287 / 3368; 111 M, R = 16 1699 / 1699, 1732 / 1736
+// It holds behind other work as well; one shard by itself, behind a 2 GiB copy, with the slices written just before, three in turn, without / with:
+//   BERT-Large list   22 M, R = 8 154.6 / 150.7, 156.8 / 153.0, 152.5 / 151.6, 154.9 / 153.3; R = 10 168.9 / 170.4, 170.8 / 168.5, 168.3 / 163.9, 167.5 / 169.5; 42 M, R = 1
+//                     193.0 / 188.5, 195.4 / 190.5, 192.5 / 190.0, 191.4 / 187.1; R = 8 292.1 / 278.6, 293.7 / 282.1, 288.9 / 281.6, 290.7 / 278.6; fp32 R = 8 418.3 /
+//                     394.2, 416.8 / 397.8, 406.1 / 385.5, 410.6 / 391.7; 67 M, R = 1 320.3 / 309.2, 318.7 / 308.9, 314.9 / 302.8, 315.9 / 301.1; R = 8 470.9 / 459.8,
+//                     472.6 / 455.4, 471.7 / 456.4, 468.1 / 450.8; 84 M, R = 1 383.1 / 387.0, 386.5 / 389.4, 381.7 / 385.9, 389.0 / 378.5; 112 M, R = 8 748.9 / 750.7,
+//                     752.2 / 748.5, 748.9 / 745.7, 759.0 / 745.0; fp32 R = 4 778.5 / 778.8, 779.0 / 752.8, 775.9 / 750.7, 774.1 / 754.5
 // While the stores are written through it depends on who steps: 10.5 M, R = 4 65.7 / 63.8 with three in turn, 54.8 / 57.3 by itself.
 // Short chunks leave pieces without elements, so no more than one chunk in eight may be missing from the table.
 constexpr uint64_t kListPiecesMaxElems = 128u << 20, kListPiecesMaxF32Elems = 256u << 20;

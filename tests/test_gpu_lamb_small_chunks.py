@@ -18,6 +18,9 @@ M = 1 << 20
     ([88 * M], 1, torch.float16, False),
     ([130001] * 600, 1, torch.float16, True),              # no tensor of more than 512 chunks: the second sweep adds up the norms
     ([65 * M + 7], 1, torch.float32, True),
+    ([66 * M, 4099], 7, torch.float16, True),
+    ([66 * M, 4099], 8, torch.float16, False),             # more slices
+    ([66 * M + 5], 3, torch.float16, False),
 ])
 def test_beyond_64_mi_elements(numels, R, dtype, small):
     shard = Shard(numels, [0.01] * len(numels), R, align_elems=8, grad_dtype=dtype, unfused=True)

@@ -18,7 +18,7 @@ MAIN = r"""
 int main(int argc, char **argv)
 {
     const auto n = [&](int k) { return strtoull(argv[k], nullptr, 10); };
-    if (argc == 2) return printf("%d\n", ccf::lamb_keeps_small_chunks(n(1))) < 0;
+    if (argc == 5) return printf("%d\n", ccf::lamb_keeps_small_chunks(n(1), (int)n(2), n(3) != 0, n(4) != 0)) < 0;
     if (argc == 4) return printf("%d\n", n(1) ? ccf::lamb_one_group_each((int64_t)n(2), (uint32_t)n(3)) : ccf::lamb_tallies((int64_t)n(2), (uint32_t)n(3))) < 0;
     printf("%d\n", ccf::list_in_pieces(n(1), n(2), (int)n(3), n(4) != 0, n(5) != 0));
     return 0;
@@ -45,8 +45,11 @@ def test_lists_in_pieces(rule, R, f32, small, beyond):
     assert [ask(32 * M, 4 * M), ask(32 * M, 4 * M + 1)] == [small, False]           # one chunk in eight short
 
 
-def test_lamb_keeps_small_chunks(rule):
-    assert [rule(n) for n in (64 * M, 88 * M - 1, 88 * M)] == [True, True, False]
+@pytest.mark.parametrize("R,f32,list_to,tensor_to", [(1, 0, 88, 72), (2, 0, 88, 72), (3, 0, 80, 0), (7, 0, 80, 0), (8, 0, 0, 0), (16, 0, 0, 0),
+                                                     (1, 1, 88, 72), (2, 1, 80, 0), (3, 1, 80, 0), (4, 1, 0, 0)])
+def test_lamb_keeps_small_chunks(rule, R, f32, list_to, tensor_to):
+    for one_tensor, to in ((0, list_to), (1, tensor_to)):
+        assert [rule(n, R, f32, one_tensor) for n in (64 * M, (to or 65) * M - 1, (to or 65) * M)] == [to > 0, to > 0, False]
 
 
 def test_where_lamb_adds_up(rule):
