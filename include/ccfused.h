@@ -187,8 +187,8 @@ int cc_plan_layout(const cc_plan *plan, int32_t *chunk_elems, int32_t *block_thr
  * RESIDENT while they total less than 200 MiB (4-24 % faster than STREAMING between 2^18 and 2^22 elements in the size
  * sweep), where from 80 MiB on the fused steps on 1024-element chunks read with non-temporal loads, but for what LAMB reads a second time
  * and, up to 144 MiB, up to 4 bytes of slices per element in the Adam step (2-42 % faster than plain loads where the chip's caches hold anything else; one
- * shard stepped over and over with nothing in between is up to 16 % slower beyond 144 MiB with one or two slices, up to 6 % with four and more); else WRITE_THROUGH while the Adam step stores less than 288 MiB (14 bytes per element: up to 20.5 Mi elements,
- * 8-12 % faster at 2^23 and 2^24); else STREAMING.  LAMB stores
+ * shard stepped over and over with nothing in between is up to 16 % slower beyond 144 MiB with one or two slices, up to 7 % with four and more); else WRITE_THROUGH while the Adam step
+ * stores less than 288 MiB (14 bytes per element: up to 20.5 Mi elements, 8-12 % faster at 2^23 and 2^24); else STREAMING.  LAMB stores
  * 8 bytes per element in its first sweep and goes by those, and from 288 MiB on still writes that sweep through; the unfused LAMB
  * pipeline writes both its sweeps through from 200 MiB on.
  * cc_plan_autotune tries all three, AUTO for LAMB, and AUTO with everything else left to the library.

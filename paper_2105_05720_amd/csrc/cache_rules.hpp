@@ -99,8 +99,9 @@ inline CachePolicies cache_policies(int32_t asked, uint64_t numel, int R, bool g
 //         R = 2,      136 MB   29.4 / 24.5 / 24.1       22.2 / 24.6 / 21.9    44.9 / 30.5 / 34.0    31.6 / 26.8 / 27.5    27.3 / 26.2 / 26.4
 // Beyond that line, and with more slices, what the cold ones cost is more: one tensor, R = 1, 204 MB 38.1 / 33.5 / 35.1, 30.7 / 35.2 / 30.3, 59.1 / 38.4 / 40.2,
 // 40.3 / 34.8 / 34.8; R = 2, 204 MB 38.5 / 32.9 / 35.4, 31.1 / 34.2 / 30.2, 60.0 / 38.2 / 42.6, 41.8 / 34.5 / 34.5; R = 4, 117 MB 23.4 / 20.3 / 19.7, 19.0 / 19.3 /
-// 18.4, 39.0 / 24.5 / 29.6, 28.5 / 22.7 / 24.0.  There one shard by itself stays the slower one (R = 1 up to 16 %, R = 2 10 %, R = 4 6 %, R = 8 4 %), and every other
-// situation the faster.
+// 18.4, 39.0 / 24.5 / 29.6, 28.5 / 22.7 / 24.0.  There one shard by itself stays the slower one (R = 1 up to 16 %, R = 2 10 %, R = 4 6 %, R = 8 4 %; lists of several hundred tensors, plain / all non-temporal
+// by itself, three in turn, behind a copy, slices written: R = 4, 133 MB 21.6 / 22.9, 28.6 / 23.3, 32.6 / 26.3, 26.0 / 25.3; R = 16, 152 MB 24.3 / 25.8, 34.4 / 27.2, 42.3 / 32.5, 29.0 /
+// 28.8), and every other situation the faster.
 constexpr uint64_t kPlainLoadsMaxBytes = 80ull << 20, kL2Bytes = 32ull << 20, kLambReadAgainBytes = 12;
 constexpr uint64_t kSlicesPlainMaxBytes = 144ull << 20;
 constexpr bool slices_plain_for(int R, bool grad_f32) { return (grad_f32 ? 4 : 2) * R <= 4; }

@@ -42,7 +42,8 @@ inline bool lamb_meets(int64_t chunks, uint32_t groups, int32_t cus, int R, bool
 //   15.6 K, R = 2 110.1 / 107.7; 19.5 K, eight fp32 slices 238 / 235.5; 27.3 K, R = 1 180.2 / 178.2; but 39.1 K, R = 8 336.0 / 338.4 and 58.6 K, R = 2
 //   399 / 400.7.  BERT-Large list in 14 slices, R = 4 181.5 / 181.0, in 40, R = 8 74.3 / 73.5; GPT-2 list in 60, R = 4 198.3 / 196.0.
 // Where no tensor has more than kFoldNormsMaxChunks the second sweep adds up the chunks themselves: BERT-Large list in 203 slices, R = 8, 19.5 us that
-// way, 20.6 with the tally.  Between 512 and 600 chunks the launch stays as well: no shard there was looked at.
+// way, 20.6 with the tally.  Between 512 and 600 chunks the launch stays as well, though the tally would be ahead there too: one tensor of 514, 538, 567 and 598 chunks,
+// R = 1 10.6 / 9.3, 11.4 / 9.5, 11.8 / 9.6 and 11.4 / 9.5, R = 8 11.0 / 9.9, 11.5 / 10.2, 11.8 / 10.3 and 11.6 / 10.3, R = 16 11.9 / 10.9, 12.4 / 11.3, 12.5 / 11.3 and 12.7 / 11.6.
 constexpr uint32_t kFoldNormsMaxChunks = 512;
 constexpr int64_t kTallyMinChunks = 600, kTallyMaxChunks = 32768;
 inline bool lamb_tallies(int64_t chunks, uint32_t most) { return chunks >= kTallyMinChunks && chunks <= kTallyMaxChunks && most > kFoldNormsMaxChunks; }
