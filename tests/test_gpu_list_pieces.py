@@ -26,6 +26,8 @@ RAGGED = [1, 3, 4, 255, 256, 257, 511, 767, 769, 1023, 1024, 1025, 4099]
     ([64 * M, 1027], 1, torch.float16, True, {}),                                 # instead of the ordered schedule
     ([64 * M, 1027], 9, torch.float16, False, {}),
     ([128 * M - 4, 4], 1, torch.float16, False, {}),
+    ([128 * M, 1027], 2, torch.float32, True, {}),                                # fp32 slices: further up
+    ([64 * M, 1027], 9, torch.float32, False, {}),
 ])
 def test_pieces_give_the_bits_of_chunks(numels, R, dtype, pieces, hyper):
     guard = hyper.get("skip_mode") == 1
